@@ -12,6 +12,7 @@
 #include <string>
 #include <vector>
 
+#include "ckm_events.h"
 #include "ckm_internal.h"
 
 namespace {
@@ -262,32 +263,13 @@ Plan plan_auto(int32_t n, int32_t K, int32_t max_items, int32_t waves_per_cu) {
   return p;
 }
 
-Plan plan_stages(int32_t n, int32_t max_items) {
-  // One stage per item from T0 = n/16 up, the longest first, then the first
-  // T0 stages in T0 items: the mask and seen kernels read each stage's rows
-  // from the row array, so an item costs no more than its stages, and the
-  // finest items balance best (n = 4001, K = 4096: 89 ms per evaluate
-  // against 93 with the 24-stage items of plan_auto).
-  if (n < 8) return plan_splits(n, max_items);
-  Plan p;
-  p.kind = 1;
-  p.T0 = std::max(1, n / 16);
-  p.P = 1;
-  p.R1 = n - p.T0;
-  p.R2 = std::max(1, std::min(p.T0, p.R1));
-  p.items = p.R1 + p.R2;
-  if (p.items > max_items) return plan_splits(n, max_items);
-  return p;
+// What tile i of one group takes of a chunk's room.
+static size_t ev_tile_bytes(const ckm_graph& g, int32_t i) {
+  return (g.ev.tile_row[i + 1] - g.ev.tile_row[i]) * kEvRecBytes + (size_t)g.ev.nf * kEvSlotBytes;
 }
 
-// The automatic plan of a graph's evaluate: one stage per item on the mask
-// and seen kernels (they need the row arrays), plan_auto otherwise.
-static Plan plan_for(const ckm_graph* g, const Layout& L, int32_t K) {
-  if (L.rows_on && (g->d_mrecs || g->d_snodes)) return plan_stages(g->n, L.max_splits);
-  return plan_auto(g->n, K, L.max_splits, g->eval_waves);
-}
-
-Layout make_layout(int32_t n, int32_t K) {
+Layout make_layout(const ckm_graph& g, int32_t K) {
+  const int32_t n = g.n;
   Layout L;
   L.n = n;
   L.K = K;
@@ -320,21 +302,66 @@ Layout make_layout(int32_t n, int32_t K) {
   L.bbest_off = off;      off = align256(off + (size_t)L.reduce_blocks * 32);
 
   L.total = off;
-  // S rows, then R rows, of every candidate, word w of row t at
-  // (base(t) + w) * kpad + k: last, and optional (without them the evaluate
-  // stage makes its S rows itself and select recomputes the best R)
+  // The row arrays: last, and optional (without them the evaluate stage
+  // makes its S rows itself and select recomputes the best R).
   const size_t kpad = (size_t)((K + kWave - 1) / kWave) * kWave;
-  const size_t full = (size_t)(n >> 5), rem = (size_t)(n & 31);
-  const size_t rrows_bytes = kpad * (32 * full * (full + 1) / 2 + rem * (full + 1)) * sizeof(uint32_t);
-  // the S rows are in this layout, or (the mask path) as one 64-bit word per
-  // group of 64 candidates and node: room for the larger of the two
-  const size_t mask_bytes = (kpad / kWave) * ckm::mask_rows_words(n) * sizeof(uint64_t);
-  const size_t rows_bytes = std::max(rrows_bytes, mask_bytes);
-  L.rows_on = rows_bytes <= ckm::kRowsMaxBytes;
   L.rows_off = off;
+  if (g.ev.on) {
+    // mask rows of every group, then room for the event records and far
+    // accumulators: of everything, or of kEvMaxBytes; one tile at least
+    const size_t groups = kpad / kWave;
+    const size_t s_bytes = groups * ckm::mask_rows_words(n) * sizeof(uint64_t);
+    size_t all = 0, tile = 0;
+    for (int32_t i = 0; i < g.ev.tiles; ++i) {
+      const size_t b = ev_tile_bytes(g, i);
+      all += b;
+      tile = std::max(tile, b);
+    }
+    L.rows_on = s_bytes <= ckm::kRowsMaxBytes;
+    L.events_off = align256(off + s_bytes);
+    L.ev_bytes = std::max(tile, groups * all <= ckm::kEvMaxBytes ? groups * all : (size_t)ckm::kEvMaxBytes);
+    L.min_rows = L.rows_on ? L.events_off + tile : off;
+    L.total_rows = L.rows_on ? L.events_off + L.ev_bytes : off;
+    return L;
+  }
+  // S rows, then R rows, of every candidate, word w of row t at
+  // (base(t) + w) * kpad + k
+  const size_t full = (size_t)(n >> 5), rem = (size_t)(n & 31);
+  const size_t rows_bytes = kpad * (32 * full * (full + 1) / 2 + rem * (full + 1)) * sizeof(uint32_t);
+  L.rows_on = rows_bytes <= ckm::kRowsMaxBytes;
   L.rrows_off = align256(off + rows_bytes);
-  L.total_rows = L.rows_on ? align256(L.rrows_off + rrows_bytes) : off;
+  L.min_rows = L.total_rows = L.rows_on ? align256(L.rrows_off + rows_bytes) : off;
   return L;
+}
+
+void fit_layout(const ckm_graph& g, Layout& L, size_t work_bytes) {
+  L.rows_on = L.rows_on && work_bytes >= L.min_rows;
+  if (L.rows_on && g.ev.on) L.ev_bytes = std::min(L.ev_bytes, work_bytes - L.events_off);
+}
+
+std::vector<EvChunk> event_chunks(const ckm_graph& g, const Layout& L, int32_t K) {
+  const int32_t groups = (K + kWave - 1) / kWave, tiles = g.ev.tiles;
+  const size_t rec = kEvRecBytes;
+  size_t all = 0;
+  for (int32_t i = 0; i < tiles; ++i) all += ev_tile_bytes(g, i);
+  std::vector<EvChunk> out;
+  if (all <= L.ev_bytes && g.ev.tile_row[tiles] * rec <= kEvGroupMaxBytes) {
+    const int32_t per = (int32_t)std::min<size_t>(groups, L.ev_bytes / all);
+    for (int32_t g0 = 0; g0 < groups; g0 += per) out.push_back({g0, std::min(per, groups - g0), 0, tiles});
+    return out;
+  }
+  // not even one group's: a group at a time, its tiles from the top
+  for (int32_t g0 = 0; g0 < groups; ++g0)
+    for (int32_t hi = tiles; hi > 0;) {
+      int32_t lo = hi - 1;
+      size_t b = ev_tile_bytes(g, lo);
+      while (lo > 0 && b + ev_tile_bytes(g, lo - 1) <= L.ev_bytes &&
+             (g.ev.tile_row[hi] - g.ev.tile_row[lo - 1]) * rec <= kEvGroupMaxBytes)
+        b += ev_tile_bytes(g, --lo);
+      out.push_back({g0, 1, lo, hi});
+      hi = lo;
+    }
+  return out;
 }
 
 }  // namespace ckm
@@ -466,28 +493,33 @@ static ckm_status graph_create(int32_t n, const int32_t* dep_ptr, const int32_t*
   const size_t off_uo = align256(off_di + Ea * sizeof(int32_t));
   const size_t off_rec = align256(off_uo + Ea * sizeof(int32_t));
   const size_t off_mrec = align256(off_rec + (size_t)n * ckm::kNodeRecBytes);
-  // the mask path's records, when the graph fits their format
-  std::vector<char> mrecs;
-  if (!wide && n <= ckm::kMaskPathMaxNodes) {
-    mrecs.resize((size_t)ckm::mask_records_bytes(n));
-    if (!ckm::build_mask_records(n, bytes, cost, dp.data(), di.data(), up.data(), ui.data(), mrecs.data()))
-      mrecs.clear();
-  }
-  // else the seen path's node data, when the graph fits it
-  std::vector<char> snodes;
-  std::vector<uint32_t> sover;
-  int32_t seen_words = 0, seen_tiers = 0, seen_tier_t[2] = {0, 0}, seen_tier_w[2] = {0, 0};
-  if (mrecs.empty() && !wide &&
-      !ckm::build_seen_records(n, bytes, cost, dp.data(), di.data(), up.data(), ui.data(), snodes, sover,
-                               seen_words, seen_tier_t, seen_tier_w, seen_tiers))
-    snodes.clear();
-  const size_t off_snode = align256(off_mrec + mrecs.size());
-  const size_t off_sover = align256(off_snode + snodes.size());
-  const size_t total = align256(off_sover + sover.size() * sizeof(uint32_t));
+  // the event path's tables, when the graph takes it
+  ckm::EventTables ev;
+  const bool events = !wide && ckm::build_events(n, bytes, cost, dp.data(), di.data(), up.data(), ui.data(),
+                                                 ckm::kEvGroupMaxBytes, ev);
+  if (!events) ev = ckm::EventTables();
+  size_t ev_end = off_mrec;
+  const auto place = [&](size_t b) {
+    const size_t at = ev_end;
+    ev_end = align256(ev_end + b);
+    return at;
+  };
+  const size_t off_desc = place(ev.desc.size() * 4), off_extra = place(ev.extra.size() * 4),
+               off_ops = place(ev.ops.size() * 8), off_row = place(ev.row_off.size() * 4),
+               off_main = place(ev.main_rec.size() * 4), off_tile = place(ev.tile_chunk.size() * 4),
+               off_pins = place(ev.pins.size() * 4);
+  const size_t total = ev_end;
   std::vector<char> host(total, 0);
-  if (!mrecs.empty()) memcpy(host.data() + off_mrec, mrecs.data(), mrecs.size());
-  if (!snodes.empty()) memcpy(host.data() + off_snode, snodes.data(), snodes.size());
-  if (!sover.empty()) memcpy(host.data() + off_sover, sover.data(), sover.size() * sizeof(uint32_t));
+  const auto copy = [&](size_t off, const auto& v) {
+    if (!v.empty()) memcpy(host.data() + off, v.data(), v.size() * sizeof(v[0]));
+  };
+  copy(off_desc, ev.desc);
+  copy(off_extra, ev.extra);
+  copy(off_ops, ev.ops);
+  copy(off_row, ev.row_off);
+  copy(off_main, ev.main_rec);
+  copy(off_tile, ev.tile_chunk);
+  copy(off_pins, ev.pins);
   memcpy(host.data() + off_M, bytes, n * sizeof(int64_t));
   memcpy(host.data() + off_C, cost, n * sizeof(int64_t));
   memcpy(host.data() + off_up, up.data(), (n + 1) * sizeof(int32_t));
@@ -509,9 +541,7 @@ static ckm_status graph_create(int32_t n, const int32_t* dep_ptr, const int32_t*
     delete g;
     return fail_hip(e, "hipGetDevice");
   }
-  g->eval_waves = !mrecs.empty()    ? ckm::mask_waves_per_cu()
-                  : !snodes.empty() ? ckm::seen_waves_per_cu(seen_words)
-                                    : ckm::eval_waves_per_cu(n, wide);
+  g->eval_waves = ckm::eval_waves_per_cu(n, wide);
   // the work area of ckm_round_eval_noalloc on this device, resolved once
   e = ckm::noalloc_setup(g->device);
   if (e != hipSuccess) {
@@ -539,34 +569,27 @@ static ckm_status graph_create(int32_t n, const int32_t* dep_ptr, const int32_t*
   g->d_dep_idx = reinterpret_cast<const int32_t*>(base + off_di);
   g->d_dep_upos = reinterpret_cast<const int32_t*>(base + off_uo);
   g->d_recs = base + off_rec;
-  g->d_mrecs = mrecs.empty() ? nullptr : base + off_mrec;
-  g->d_snodes = snodes.empty() ? nullptr : base + off_snode;
-  g->d_sover = snodes.empty() || sover.empty() ? nullptr : base + off_sover;
-  g->seen_words = seen_words;
-  g->seen_tiers = seen_tiers;
-  for (int i = 0; i < 2; ++i) {
-    g->seen_tier_t[i] = seen_tier_t[i];
-    g->seen_tier_w[i] = seen_tier_w[i];
+  if (events) {
+    g->ev.on = true;
+    g->ev.pairs = ev.pairs;
+    g->ev.tiles = ev.tiles;
+    g->ev.nf = ev.nf;
+    g->ev.npins = (int32_t)ev.pins.size();
+    for (int32_t i = 0; i < ev.tiles; ++i) g->ev.tile_row.push_back(ev.row_off[64 * i]);
+    g->ev.tile_row.push_back(ev.row_off[2 * ev.pairs]);
+    g->ev.d_desc = reinterpret_cast<const uint32_t*>(base + off_desc);
+    g->ev.d_extra = reinterpret_cast<const uint32_t*>(base + off_extra);
+    g->ev.d_ops = reinterpret_cast<const double*>(base + off_ops);
+    g->ev.d_row_off = reinterpret_cast<const uint32_t*>(base + off_row);
+    g->ev.d_main_rec = reinterpret_cast<const int32_t*>(base + off_main);
+    g->ev.d_tile_chunk = reinterpret_cast<const int32_t*>(base + off_tile);
+    g->ev.d_pins = reinterpret_cast<const int32_t*>(base + off_pins);
   }
   g->sync = new (std::nothrow) ckm::SyncCache;
   if (!g->sync) {
     (void)hipFree(g->d_mem);
     delete g;
     return fail(CKM_E_NOMEM, "out of host memory");
-  }
-  // the side stream of the overlapped launches (seen-path graphs whose
-  // evaluate LDS holds to a few waves per SIMD)
-  if (g->d_snodes && g->eval_waves <= ckm::kForkMaxWaves) {
-    g->fork = new (std::nothrow) ckm::Fork;
-    e = g->fork ? ckm::fork_create(*g->fork) : hipErrorOutOfMemory;
-    if (e != hipSuccess) {
-      delete g->fork;
-      g->sync->release();
-      delete g->sync;
-      (void)hipFree(g->d_mem);
-      delete g;
-      return fail_hip(e, "side stream");
-    }
   }
   *out = g;
   return CKM_OK;
@@ -575,10 +598,6 @@ static ckm_status graph_create(int32_t n, const int32_t* dep_ptr, const int32_t*
 void ckm_graph_destroy(ckm_graph* g) {
   if (!g) return;
   DeviceGuard dg(g->device);
-  if (g->fork) {
-    ckm::fork_destroy(*g->fork);
-    delete g->fork;
-  }
   if (g->sync) {
     g->sync->release();
     delete g->sync;
@@ -591,7 +610,7 @@ ckm_status ckm_workspace_size(const ckm_graph* g, int32_t K, size_t* bytes) {
   if (!g || !bytes) return fail(CKM_E_INVALID_ARG, "NULL graph or bytes");
   if (K < 1) return fail(CKM_E_INVALID_ARG, "K = %d < 1", K);
   if (K > CKM_MAX_CANDIDATES) return fail(CKM_E_UNSUPPORTED, "K = %d > %d", K, CKM_MAX_CANDIDATES);
-  *bytes = ckm::make_layout(g->n, K).total_rows;
+  *bytes = ckm::make_layout(*g, K).total_rows;
   return CKM_OK;
 }
 
@@ -599,7 +618,7 @@ ckm_status ckm_workspace_size_min(const ckm_graph* g, int32_t K, size_t* bytes) 
   if (!g || !bytes) return fail(CKM_E_INVALID_ARG, "NULL graph or bytes");
   if (K < 1) return fail(CKM_E_INVALID_ARG, "K = %d < 1", K);
   if (K > CKM_MAX_CANDIDATES) return fail(CKM_E_UNSUPPORTED, "K = %d > %d", K, CKM_MAX_CANDIDATES);
-  *bytes = ckm::make_layout(g->n, K).total;
+  *bytes = ckm::make_layout(*g, K).total;
   return CKM_OK;
 }
 
@@ -609,10 +628,10 @@ static ckm_status check_work(const ckm_graph* g, int32_t K, void* d_work, size_t
   if (K < 1) return fail(CKM_E_INVALID_ARG, "K = %d < 1", K);
   if (K > CKM_MAX_CANDIDATES) return fail(CKM_E_UNSUPPORTED, "K = %d > %d", K, CKM_MAX_CANDIDATES);
   if (!d_work) return fail(CKM_E_INVALID_ARG, "work buffer is NULL");
-  *L = ckm::make_layout(g->n, K);
+  *L = ckm::make_layout(*g, K);
   if (work_bytes < L->total)
     return fail(CKM_E_INVALID_ARG, "work buffer of %zu bytes, %zu needed", work_bytes, L->total);
-  L->rows_on = L->rows_on && work_bytes >= L->total_rows;
+  ckm::fit_layout(*g, *L, work_bytes);
   return CKM_OK;
 }
 
@@ -646,7 +665,7 @@ ckm_status ckm_round_async(const ckm_graph* g, int32_t K, uint64_t seed, uint32_
 }
 
 static ckm_status evaluate_impl(const ckm_graph* g, int32_t K, uint64_t seed, uint32_t flags,
-                                int32_t stage_splits, void* d_work, size_t work_bytes, void* stream, bool overlap) {
+                                int32_t stage_splits, void* d_work, size_t work_bytes, void* stream) {
   Layout L;
   ckm_status st = check_work(g, K, d_work, work_bytes, &L);
   if (st != CKM_OK) return st;
@@ -654,17 +673,17 @@ static ckm_status evaluate_impl(const ckm_graph* g, int32_t K, uint64_t seed, ui
     return fail(CKM_E_INVALID_ARG, "unknown flags 0x%x", flags);
   if (stage_splits < 0) return fail(CKM_E_INVALID_ARG, "stage_splits = %d < 0", stage_splits);
   const ckm::Plan plan = stage_splits ? ckm::plan_splits(g->n, std::min(stage_splits, L.max_splits))
-                                      : ckm::plan_for(g, L, K);
+                                      : ckm::plan_auto(g->n, K, L.max_splits, g->eval_waves);
   DeviceGuard dg(g->device);
   if (!dg.ok) return fail(CKM_E_DEVICE, "cannot select the graph's device %d", g->device);
   hipError_t e = ckm::launch_evaluate(*g, L, K, seed, flags, plan, ckm::kSrcRound, nullptr,
-                                      static_cast<char*>(d_work), static_cast<hipStream_t>(stream), overlap);
+                                      static_cast<char*>(d_work), static_cast<hipStream_t>(stream));
   return e == hipSuccess ? CKM_OK : fail_hip(e, "evaluate launch");
 }
 
 ckm_status ckm_evaluate_async(const ckm_graph* g, int32_t K, uint64_t seed, uint32_t flags,
                               int32_t stage_splits, void* d_work, size_t work_bytes, void* stream) {
-  return evaluate_impl(g, K, seed, flags, stage_splits, d_work, work_bytes, stream, true);
+  return evaluate_impl(g, K, seed, flags, stage_splits, d_work, work_bytes, stream);
 }
 
 ckm_status ckm_select_async(const ckm_graph* g, int32_t K, uint64_t seed, int64_t budget,
@@ -693,7 +712,7 @@ ckm_status ckm_round_eval_async(const ckm_graph* g, const double* d_s_frac, int6
                                 uint64_t* d_best_S, uint64_t* d_best_R, int32_t* d_status,
                                 void* d_work, size_t work_bytes, void* stream) {
   return ckm::round_eval(g, d_s_frac, ld, K, seed, budget, flags, d_peak, d_cost, d_feasible, d_best_k, d_best_S,
-                         d_best_R, d_status, d_work, work_bytes, stream, true);
+                         d_best_R, d_status, d_work, work_bytes, stream);
 }
 
 }  // extern "C"
@@ -701,7 +720,7 @@ ckm_status ckm_round_eval_async(const ckm_graph* g, const double* d_s_frac, int6
 ckm_status ckm::round_eval(const ckm_graph* g, const double* d_s_frac, int64_t ld, int32_t K, uint64_t seed,
                            int64_t budget, uint32_t flags, int64_t* d_peak, int64_t* d_cost, uint8_t* d_feasible,
                            int32_t* d_best_k, uint64_t* d_best_S, uint64_t* d_best_R, int32_t* d_status,
-                           void* d_work, size_t work_bytes, void* stream, bool overlap) {
+                           void* d_work, size_t work_bytes, void* stream) {
   Layout L;
   ckm_status st = check_work(g, K, d_work, work_bytes, &L);
   if (st != CKM_OK) return st;
@@ -711,7 +730,7 @@ ckm_status ckm::round_eval(const ckm_graph* g, const double* d_s_frac, int64_t l
     return fail(CKM_E_INVALID_ARG, "NULL peak, cost, feasible or best_k");
   st = ckm_quantize_async(g, d_s_frac, ld, d_work, work_bytes, stream);
   if (st != CKM_OK) return st;
-  st = evaluate_impl(g, K, seed, flags, 0, d_work, work_bytes, stream, overlap);
+  st = evaluate_impl(g, K, seed, flags, 0, d_work, work_bytes, stream);
   if (st != CKM_OK) return st;
   return ckm_select_async(g, K, seed, budget, flags, d_peak, d_cost, d_feasible, d_best_k,
                           d_best_S, d_best_R, d_status, d_work, work_bytes, stream);
@@ -730,7 +749,7 @@ ckm_status ckm_eval_schedules_async(const ckm_graph* g, const uint64_t* d_S, int
   if (budget < 0) return fail(CKM_E_INVALID_ARG, "budget = %lld < 0", (long long)budget);
   if (!d_peak || !d_cost || !d_feasible || !d_best_k)
     return fail(CKM_E_INVALID_ARG, "NULL peak, cost, feasible or best_k");
-  const ckm::Plan plan = ckm::plan_for(g, L, K);
+  const ckm::Plan plan = ckm::plan_auto(g->n, K, L.max_splits, g->eval_waves);
   DeviceGuard dg(g->device);
   if (!dg.ok) return fail(CKM_E_DEVICE, "cannot select the graph's device %d", g->device);
   hipError_t e = ckm::launch_evaluate(*g, L, K, 0, 0, plan, ckm::kSrcUser, d_S, static_cast<char*>(d_work),
@@ -754,7 +773,7 @@ ckm_status ckm_eval_schedules(const ckm_graph* g, const uint64_t* S, int32_t K, 
   const int32_t n = g->n;
   DeviceGuard dg(g->device);
   if (!dg.ok) return fail(CKM_E_DEVICE, "cannot select the graph's device %d", g->device);
-  const Layout L = ckm::make_layout(n, K);
+  const Layout L = ckm::make_layout(*g, K);
   const int32_t W = (n + 63) / 64;
   const size_t rows_bytes = (size_t)n * W * sizeof(uint64_t);
   size_t off = 0;
@@ -798,7 +817,7 @@ ckm_status ckm_threshold_eval_async(const ckm_graph* g, const double* d_s_frac, 
   if (budget < 0) return fail(CKM_E_INVALID_ARG, "budget = %lld < 0", (long long)budget);
   if (!d_peak || !d_cost || !d_feasible || !d_best_k)
     return fail(CKM_E_INVALID_ARG, "NULL peak, cost, feasible or best_k");
-  const ckm::Plan plan = ckm::plan_for(g, L, K);
+  const ckm::Plan plan = ckm::plan_auto(g->n, K, L.max_splits, g->eval_waves);
   DeviceGuard dg(g->device);
   if (!dg.ok) return fail(CKM_E_DEVICE, "cannot select the graph's device %d", g->device);
   hipStream_t s = static_cast<hipStream_t>(stream);
@@ -828,7 +847,7 @@ ckm_status ckm_threshold_eval(const ckm_graph* g, const double* s_frac, int64_t 
 
   DeviceGuard dg(g->device);
   if (!dg.ok) return fail(CKM_E_DEVICE, "cannot select the graph's device %d", g->device);
-  const Layout L = ckm::make_layout(n, K);
+  const Layout L = ckm::make_layout(*g, K);
   const int32_t W = (n + 63) / 64;
   const size_t rows_bytes = (size_t)n * W * sizeof(uint64_t);
   const size_t s_bytes = align256((size_t)n * n * sizeof(double));
@@ -895,7 +914,7 @@ ckm_status ckm_plan(const ckm_graph* g, const uint64_t* S, const uint64_t* R, ui
   const int32_t n = g->n;
   DeviceGuard dg(g->device);
   if (!dg.ok) return fail(CKM_E_DEVICE, "cannot select the graph's device %d", g->device);
-  const Layout L = ckm::make_layout(n, 1);
+  const Layout L = ckm::make_layout(*g, 1);
   const size_t rows_bytes = (size_t)n * ((n + 63) / 64) * sizeof(uint64_t);
   const size_t rows_al = align256(rows_bytes);
   size_t off = 0;
@@ -974,7 +993,7 @@ ckm_status ckm_max_batch(const ckm_graph* g, const double* s_frac, int64_t ld, i
   const int32_t n = g->n;
   DeviceGuard dg(g->device);
   if (!dg.ok) return fail(CKM_E_DEVICE, "cannot select the graph's device %d", g->device);
-  const Layout L = ckm::make_layout(n, K);
+  const Layout L = ckm::make_layout(*g, K);
   const size_t s_bytes = align256((size_t)n * n * sizeof(double));
   size_t off = 0;
   const size_t o_w = off;  off = align256(off + L.total_rows);
@@ -1015,7 +1034,7 @@ ckm_status ckm_round_eval(const ckm_graph* g, const double* s_frac, int64_t ld, 
   const int32_t n = g->n;
   DeviceGuard dg(g->device);
   if (!dg.ok) return fail(CKM_E_DEVICE, "cannot select the graph's device %d", g->device);
-  const Layout L = ckm::make_layout(n, K);
+  const Layout L = ckm::make_layout(*g, K);
   const int32_t W = (n + 63) / 64;
   const size_t s_bytes = align256((size_t)n * n * sizeof(double));
   const size_t rows_bytes = (size_t)n * W * sizeof(uint64_t);

@@ -12,7 +12,21 @@
 
 namespace ckm {
 struct SyncCache;  // buffers and stream of the synchronous entry points (ckm_host.cpp)
-struct Fork;       // second stream of the overlapped producer/evaluate launches
+
+// The event path's tables on the device (EventTables, ckm_events.h); on is
+// false for the graphs that do not take it (wide or very dense).
+struct EventGraph {
+  bool on = false;
+  int32_t pairs = 0, tiles = 0, nf = 0, npins = 0;
+  std::vector<uint64_t> tile_row;   // first event record of each tile's stages, tiles + 1 entries
+  const uint32_t* d_desc = nullptr;
+  const uint32_t* d_extra = nullptr;
+  const double* d_ops = nullptr;
+  const uint32_t* d_row_off = nullptr;
+  const int32_t* d_main_rec = nullptr;
+  const int32_t* d_tile_chunk = nullptr;
+  const int32_t* d_pins = nullptr;
+};
 }
 
 // Graph on the device. Node arrays hold sizes and costs as int64. Users
@@ -37,17 +51,8 @@ struct ckm_graph {
   const int32_t* d_dep_idx = nullptr;
   const int32_t* d_dep_upos = nullptr;
   const void* d_recs = nullptr;  // n node records of ckm::kNodeRecBytes (see ckm_kernels.hip)
-  const void* d_mrecs = nullptr; // mask-path records (mask_records_bytes) when the graph fits them, else NULL
-  const void* d_snodes = nullptr; // else the seen path's node data, when the graph fits it
-  const void* d_sover = nullptr;  // and its overflow entries (NULL when there are none)
-  int32_t seen_words = 0;         // seen bits per lane / 32 on the seen path
-  // seen-path launches by stage: the stages below seen_tier_t[i] touch only
-  // the first seen_tier_w[i] words (seen_tiers of them, split stages falling)
-  int32_t seen_tiers = 0;
-  int32_t seen_tier_t[2] = {0, 0};
-  int32_t seen_tier_w[2] = {0, 0};
+  ckm::EventGraph ev;            // the event path's tables
   ckm::SyncCache* sync = nullptr;  // reused by the synchronous calls; freed with the graph
-  ckm::Fork* fork = nullptr;       // NULL: every launch on the caller's stream
 };
 
 namespace ckm {
@@ -78,30 +83,29 @@ void build_node_records(int32_t n, const int64_t* M, const int64_t* C, bool wide
                         const int32_t* dep_idx, const int32_t* user_ptr, const int32_t* user_idx,
                         void* out);
 
-// Records of the mask path (see ckm_kernels.hip), mask_records_bytes(n)
-// of them; false when some node exceeds their format (more than four
-// dependencies, more than one user more than 32 nodes above it, or a
-// dependency with more than one such later user): the graph then takes the
-// other kernels.
-constexpr int kMaskPathMaxNodes = 1023;   // R row of up to 32 words in registers
-int32_t mask_records_bytes(int32_t n);
-bool build_mask_records(int32_t n, const int64_t* M, const int64_t* C, const int32_t* dep_ptr,
-                        const int32_t* dep_idx, const int32_t* user_ptr, const int32_t* user_idx, void* out);
-// Words of one candidate group's mask rows (rows 0 .. n).
-size_t mask_rows_words(int32_t n);
-// Node data of the seen path (see ckm_kernels.hip) for graphs of up to
-// kSeenMaxNodes nodes: (n + 1) x 128 bytes, the overflow entries (8 dwords
-// each) and the seen words per lane; false when n is too large. tier_t and
-// tier_w (ntiers entries, at most 2): the stages below tier_t[i] touch only
-// the first tier_w[i] seen words (no tiers where they would not pay).
-constexpr int32_t kSeenMaxNodes = 4096;
-bool build_seen_records(int32_t n, const int64_t* M, const int64_t* C, const int32_t* dep_ptr,
-                        const int32_t* dep_idx, const int32_t* user_ptr, const int32_t* user_idx,
-                        std::vector<char>& nodes, std::vector<uint32_t>& over, int32_t& seen_words,
-                        int32_t tier_t[2], int32_t tier_w[2], int32_t& ntiers);
-// Resident waves per CU of the mask and seen evaluate kernels.
-int32_t mask_waves_per_cu();
-int32_t seen_waves_per_cu(int32_t seen_words);
+// Mask rows of one candidate group: the offset of row t, and the words of
+// rows 0 .. n (see ckm_kernels.hip).
+__host__ __device__ __forceinline__ size_t mrow_off(int t) {
+  const size_t q = (size_t)(t >> 3), r = (size_t)(t & 7);
+  return 8 * ((size_t)t + 4 * q * (q ? q - 1 : 0) + q * r);
+}
+inline size_t mask_rows_words(int32_t n) { return mrow_off(n + 1); }
+
+// Event records are made and consumed a chunk at a time: the candidate groups
+// and stage tiles whose records (and far accumulators) fit the room for them,
+// on most calls all. A group's records in a chunk stay under kEvGroupMaxBytes,
+// so that their byte offsets stay clear of the 32-bit buffer offset that marks
+// a lane without a stage; a graph one of whose tiles is larger (hundreds of
+// dependencies per node at 4096 nodes) does not take the event path.
+constexpr uint64_t kEvGroupMaxBytes = (uint64_t)960 << 20;
+constexpr uint64_t kEvMaxBytes = (uint64_t)4 << 30;
+struct EvChunk {
+  int32_t g0 = 0, gn = 0;     // groups
+  int32_t tlo = 0, thi = 0;   // tiles
+};
+struct Layout;
+// The chunks of K candidates, in order.
+std::vector<EvChunk> event_chunks(const ckm_graph& g, const Layout& L, int32_t K);
 
 // Work-buffer layout for (n, K). Offsets are bytes from the buffer start,
 // each 256-byte aligned.
@@ -123,14 +127,19 @@ struct Layout {
          plan_rt_off = 0, plan_rpre_off = 0,
          bbest_off = 0,  // per-block best of the batch multipliers
          total = 0,        // bytes every call needs
-         rows_off = 0,     // S rows of every candidate (kSrcRows), past `total`
-         rrows_off = 0,    // R rows of every candidate, written by the evaluate stage
-         total_rows = 0;   // total plus the two row arrays when they are used
+         rows_off = 0,     // S rows of every candidate (kSrcRows, or mask rows), past `total`
+         rrows_off = 0,    // R rows of every candidate, written by ckm_eval_kernel
+         events_off = 0,   // the event path instead: a chunk's event records and far accumulators,
+         ev_bytes = 0,     // this much room
+         min_rows = 0,     // smallest buffer with the row arrays
+         total_rows = 0;   // total plus the row arrays when they are used
   bool rows_on = false;    // the S rows fit kRowsMaxBytes (and, after
-                           // check_work, the caller's buffer holds both arrays)
+                           // check_work, the caller's buffer holds the arrays)
 };
 
-Layout make_layout(int32_t n, int32_t K);
+Layout make_layout(const ckm_graph& g, int32_t K);
+// The same with the row arrays in a buffer of work_bytes (off when it is too small).
+void fit_layout(const ckm_graph& g, Layout& L, size_t work_bytes);
 
 // Records a thread-local error message (ckm_last_error) and returns st.
 ckm_status set_error(ckm_status st, const char* fmt, ...);
@@ -153,34 +162,17 @@ struct Plan {
   int32_t items = 1, kind = 0, P = 0, T0 = 0, R1 = 0, R2 = 0;
 };
 Plan plan_auto(int32_t n, int32_t K, int32_t max_items, int32_t waves_per_cu);
-Plan plan_stages(int32_t n, int32_t max_items);
 Plan plan_splits(int32_t n, int32_t splits);
 
 // Resident evaluate waves per CU for a graph of n nodes (the runtime's
 // occupancy figure for the kernel variant and LDS size n and wide select).
 int32_t eval_waves_per_cu(int32_t n, bool wide);
 
-// A second stream and two events, made with a seen-path graph on its device,
-// over which launch_evaluate splits its candidate groups in two chunks: the
-// second chunk's producer and evaluate run beside the first chunk's evaluate.
-// The mutex keeps one call's record/wait sequence on the events whole.
-struct Fork {
-  std::mutex mu;
-  hipStream_t side = nullptr;
-  hipEvent_t forked = nullptr, joined = nullptr;
-};
-// Seen-path evaluates resident at no more than this many waves per CU (held
-// there by their LDS) get the overlapped launch and so the second stream.
-constexpr int32_t kForkMaxWaves = 16;
-hipError_t fork_create(Fork& f);
-void fork_destroy(Fork& f);
-
-// ckm_round_eval_async, with the overlapped launch on or off (off for the
-// entry point that creates and allocates nothing).
+// ckm_round_eval_async.
 ckm_status round_eval(const ckm_graph* g, const double* d_s_frac, int64_t ld, int32_t K, uint64_t seed,
                       int64_t budget, uint32_t flags, int64_t* d_peak, int64_t* d_cost, uint8_t* d_feasible,
                       int32_t* d_best_k, uint64_t* d_best_S, uint64_t* d_best_R, int32_t* d_status, void* d_work,
-                      size_t work_bytes, void* stream, bool overlap);
+                      size_t work_bytes, void* stream);
 
 // Kernel launchers (defined in ckm_kernels.hip). They only enqueue work.
 hipError_t launch_quantize(const ckm_graph& g, const Layout& L, const double* d_s, int64_t ld,
@@ -211,12 +203,14 @@ hipError_t launch_max_batch(const ckm_graph& g, const Layout& L, int32_t K, int6
 // array when L.rows_on, rounding it first unless flags has CKM_F_ROUNDED).
 // s_user: for kSrcUser, K
 // caller-supplied S matrices ([K][n][row_words] 32-bit words).
-// With overlap, the candidate groups are split over the caller's stream and
-// g.fork's (when the graph has one and K is large enough); the caller's
-// stream waits for the other before it returns, as after one launch.
 hipError_t launch_evaluate(const ckm_graph& g, const Layout& L, int32_t K, uint64_t seed,
                            uint32_t flags, const Plan& plan, int src, const uint64_t* s_user, char* work,
-                           hipStream_t stream, bool overlap = true);
+                           hipStream_t stream);
+// Event path (ckm_events.hip): the evaluate of all candidates on their mask
+// rows, and the best candidate's R rows.
+hipError_t launch_events(const ckm_graph& g, const Layout& L, int32_t K, char* work, hipStream_t stream);
+hipError_t launch_best_events(const ckm_graph& g, const Layout& L, int32_t K, const int32_t* d_best_k,
+                              uint64_t* d_best_R, char* work, hipStream_t stream);
 hipError_t launch_select(const ckm_graph& g, const Layout& L, int32_t K, uint64_t seed,
                          int64_t budget, uint32_t flags, int64_t* d_peak,
                          int64_t* d_cost, uint8_t* d_feasible, int32_t* d_best_k,

@@ -4,19 +4,15 @@
 // Work decomposition: one wave of 64 lanes owns 64 candidates (lane =
 // candidate) and one work item of stages. All lanes walk the same nodes in
 // the same order, so graph data and loop bounds are wave-uniform and only the
-// candidates' bits and running sums differ per lane. Three evaluate kernels
-// share that shape:
-// - ckm_mask_eval_kernel and ckm_seen_eval_kernel (graphs up to 4096 nodes
-//   with the row arrays in the work buffer): S is rounded beforehand into
-//   mask rows, one 64-bit word per (row, node) whose bit j is candidate j of
-//   the group, so the repair and the FREE tests are 64-bit scalar operations
-//   for the whole group and only the binary64 sums run per lane;
-// - ckm_eval_kernel (the rest: larger or wide graphs, no row arrays): each
-//   lane keeps its own bit rows (32-bit words, bit i%32 of word i/32): S_t,
-//   which becomes R_t as the scan passes, in LDS laid out [word][lane] so that
-//   a wave-uniform word index touches 64 consecutive dwords, and S_{t+1} in
-//   vector registers (in LDS too for the largest graphs). S rows come from a
-//   row array in HBM, [row][word][candidate], or are made in the kernel.
+// candidates' bits and running sums differ per lane. Most graphs take the
+// event path (ckm_events.hip); this file makes its S rows, and evaluates what
+// that path does not: ckm_eval_kernel (wide or very dense graphs, work
+// buffers without the row arrays). Each of its lanes keeps its own bit rows
+// (32-bit words, bit i%32 of word i/32): S_t, which becomes R_t as the scan
+// passes, in LDS laid out [word][lane] so that a wave-uniform word index
+// touches 64 consecutive dwords, and S_{t+1} in vector registers (in LDS too
+// for the largest graphs). S rows come from a row array in HBM,
+// [row][word][candidate], or are made in the kernel.
 //
 // Sums of sizes and costs run in binary64 while the graph's totals stay below
 // 2^53, so every partial sum is an exactly represented integer and the result
@@ -1564,322 +1560,17 @@ __global__ void __launch_bounds__(kWave) ckm_best_closure_kernel(ClosureArgs a) 
 }
 
 // ---------------------------------------------------------------------------
-// Mask path. A group's 64 candidates share one 64-bit word per (stage row,
-// node): bit j is candidate 64g + j. With the rows in that form, the repair
-// of Algorithm 2 and the FREE tests of eq. collectable become scalar-unit
-// operations on whole words (one instruction decides a node for all 64
-// candidates), and the vector unit keeps only the sums, each a masked
-// binary64 update selected by such a word. A node's record and its S words
-// come through the scalar cache; the R bits of the nodes above it stay in
-// each lane's window register and register row, as in the kernel above.
-//
-// Mask rows of a group: row t holds 8 (t/8 + 1) words (nodes 0 .. t rounded
-// up to whole blocks of 8; words for nodes >= t are zero); row n, after the
-// last stage, is all zero.
-__host__ __device__ __forceinline__ size_t mrow_off(int t) {
-  const size_t q = (size_t)(t >> 3), r = (size_t)(t & 7);
-  return 8 * ((size_t)t + 4 * q * (q ? q - 1 : 0) + q * r);
-}
-
-// Node v's data, 128 bytes at 128 v:
-//   [0, 64)   record, 16 dwords (one scalar load)
-//   [64, 96)  slots 2-3 (nodes with three or four dependencies): lm, ref of
-//             slot 2, of slot 3, dependency count, byte offsets in a mask
-//             row of the S_{t+1} words of the slot 2 and 3 dependencies
-//   [96, 112) binary64 M of slots 2 and 3
-// A far reference names a node u more than 32 above v as u << 16 | (u & 31)
-// (none: 0xFFFF << 16). Its R bit matters only when u <= t, i.e. when the
-// field is below (t + 1) << 16: a node above t computes nothing in stage t.
-// Record words:
-//   0: users u of v with u <= v + 32 (bit u - v - 1)
-//   1: ctrl: far reference to the user of v more than 32 above it | slots
-//      2-3 present << 8
-//   slot s (words 2 + 2s, 3 + 2s):
-//      lm: users u of the dependency with v < u <= v + 32 (bit u - v - 1)
-//      ref: far reference to the dependency's later user
-//      An absent slot has lm = 0 and no far reference: it frees nothing, its
-//      size being 0.
-//   6: for node v-1, the byte offset in a mask row of the S_{t+1} word of
-//      its slot 0 dependency (0 for an absent slot), fetched one node ahead
-//   7: high half: the gate, the high half of the least of the node's three
-//      far references (words 1, 3 and 5), or 0 when the node has more than
-//      two dependencies: when the word is at or above the stage's limit
-//      (t + 1) << 16, the node is decided in a form without far lookups or
-//      rare slots (the limit's low half is 0, so the low half of the word
-//      never decides). Low half: for node v-1, the byte offset of its slot 1
-//      dependency's S_{t+1} word, as word 6. (Both offsets in word 6 cost a
-//      shift and a mask per node.)
-//   8-15: binary64 M_v, C_v, M of slots 0 and 1, used from scalar registers
-//      (the vector registers they would take are worth a wave per SIMD)
-// Pairs of nodes are aligned (nodes 2c, 2c+1). A stage's scan starts at the
-// top of its node's pair; a node above t there (or past n - 1, whose data is
-// padded with empty nodes up to np = round_up(n, 4) + 4) computes nothing
-// and holds nothing, so it leaves every sum unchanged.
-constexpr uint32_t kMNoFar = 0xFFFFu << 16, kMRare = 1u << 8;
-constexpr int kMNodeBytes = 128;
-__host__ __device__ __forceinline__ int mask_padded_nodes(int n) { return ((n + 3) & ~3) + 4; }
-
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
-typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
-
-struct MaskArgs {
-  int32_t n, K, items, kind, P, T0, R1, R2;   // work plan (see Plan)
-  int32_t np;                                 // padded node count of the node data
-  double base;                                // M_in + 2 M_param
-  size_t mgroup;                              // words of one group's mask rows
-  cptr<uint64_t> mrows;                       // S masks, group-major
-  cptr<u32x16> mnodes;                        // np x 128 bytes of node data
-  uint32_t* __restrict__ rrows;               // R rows out (row array layout), or NULL
-  int32_t kpad;
-  int64_t* __restrict__ part_peak;
-  int64_t* __restrict__ part_cost;
-  int32_t* __restrict__ hdr;
-  int32_t g0;                                 // group of blockIdx.x = 0
-};
-
-__device__ __forceinline__ bool lane_of(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+// Mask rows (the event path's S rows, see ckm_events.h). A group's 64
+// candidates share one 64-bit word per (stage row, node): bit j is candidate
+// 64g + j. Row t of a group holds 8 (t/8 + 1) words (nodes 0 .. t rounded up
+// to whole blocks of 8; words for nodes >= t are zero); row n, after the last
+// stage, is all zero. The producers below make them from the three sources.
 __device__ __forceinline__ uint64_t mask_of(bool b) { return __builtin_amdgcn_ballot_w64(b); }
-// acc + [lane's bit of m] * x, one masked binary64 update
-__device__ __forceinline__ double madd_m(double acc, uint64_t m, double x) {
-  return fma(lane_of(m) ? 1.0 : 0.0, x, acc);
-}
-// A scalar load at a 32-bit byte offset from a base (one instruction, the
-// offset in a register).
-template <typename T, typename B>
-__device__ __forceinline__ T sload(cptr<B> base, uint32_t off) {
-  return *(const __attribute__((address_space(4))) T*)((const __attribute__((address_space(4))) char*)base + off);
-}
-// 16 bytes at byte offset off + kOff of the node data, in every lane
+// 16 bytes at byte offset off + kOff of a buffer, in every lane
 template <int kOff>
 __device__ __forceinline__ uint4 load_mval(__amdgpu_buffer_rsrc_t rs, uint32_t off) {
   const auto x = __builtin_amdgcn_raw_buffer_load_b128(rs, kOff, (int)off, 0);
   return make_uint4(x[0], x[1], x[2], x[3]);
-}
-
-struct MScan {
-  double U0, Y, maxv, cost;
-  uint32_t Rwin;   // R bits of nodes v+1 .. v+32 (bit d <-> node v + 1 + d)
-};
-
-// The R bit of the far node that field f names (more than 32 above the node
-// being decided: its word of the register row is complete). A shift uses the
-// low five bits of its count by itself. Only for u <= t; the empty asm keeps
-// the compiler from hoisting the indexed register read out of that branch
-// (the word index is clamped to the row all the same).
-__device__ __forceinline__ uint32_t far_bit(const u32x32& Rrow, uint32_t f) {
-  asm volatile("");
-  return (Rrow[(f >> 21) & 31u] >> (f & 31u)) & 1u;
-}
-
-// One dependency slot of node v: the dependency's value is released after
-// v (FREE(t,i,v) = 1) on the candidates that compute v, do not keep the
-// value into stage t+1 and compute none of its later users in stage t.
-template <bool kFar>
-__device__ __forceinline__ double mask_slot(double val, uint64_t R, uint32_t lm, uint32_t ref, double Mi,
-                                            uint64_t s1i, uint32_t Rwin, const u32x32& Rrow, uint32_t tlim) {
-  uint32_t y = Rwin & lm;
-  if (kFar && __builtin_expect(ref < tlim, 0)) y |= far_bit(Rrow, ref);
-  const uint64_t later = mask_of(y != 0u);
-  const uint64_t fr = R & ~(s1i | later);
-  return madd_m(val, fr, Mi);
-}
-
-// What node v needs besides its block: its record, the S_{t+1} words of its
-// slot 0 and 1 dependencies and its binary64 operands (M_v, C_v | M of slots
-// 0, 1), all requested one node ahead.
-struct MNode {
-  u32x16 rec;
-  uint64_t d0, d1;
-};
-
-// Node v of stage t for the 64 candidates of a group: S0, S1 are the words
-// of S_t[v] and S_{t+1}[v]. Algorithm 2: v is computed if it is node t
-// (constraint 4a), or it is not held and is kept into t+1 (1c) or used by a
-// computed node (1b). kTop: v is in the block of node t, and may be t; below
-// that block, v < t and the scan has passed at least one node. Released
-// right after its own compute (eq. collectable with i = v): a computed node
-// that is neither kept nor used, which only node t can be.
-// kSlow: the general form, for a node whose gate (record word 7: the least
-// of its three far references, 0 with more than two dependencies) is below
-// the stage's limit; the fast form has no far lookup and no rare slots.
-template <bool kTop, bool kSlow, bool kSkip>
-__device__ __forceinline__ void mask_node_as(const MaskArgs& a, int t, int v, const MNode& nd, uint64_t S0,
-                                             uint64_t S1, cptr<uint64_t> s1row, MScan& sc, u32x32& Rrow,
-                                             uint32_t tlim) {
-  const u32x16& rec = nd.rec;
-  const uint32_t ctrl = rec[1];
-  const double Mv = dbl(rec[8], rec[9]), Cv = dbl(rec[10], rec[11]);
-  uint32_t x = sc.Rwin & rec[0];
-  if (kSlow && __builtin_expect(ctrl < tlim, 0)) x |= far_bit(Rrow, ctrl);
-  const uint64_t x1 = S1 | mask_of(x != 0u);
-  uint64_t R = x1 & ~S0;
-  sc.U0 = madd_m(sc.U0, S0, Mv);
-  // A lane that does not compute v frees nothing after it, and its val = Y
-  // changes neither maxv (which already covers Y: the running value has only
-  // fallen since the last computed node) nor Y. kSkip: a node that no
-  // candidate of the group computes returns here. Without it such nodes take
-  // the general path, which is faster for randomized rounding (19 % of the
-  // visits on the transformer workload: 0.455 against 0.458 ms; the seen
-  // kernel at n = 4001, K = 4096: 87.2 against 88.0 ms), while the threshold
-  // family, whose groups hold neighbouring thresholds, has many more of them
-  // and gains from the skip on those two graphs (0.557 against 0.570 ms and
-  // 85.2 against 90.3 ms per call).
-  if (kSkip && !kTop && R == 0ull) {
-    sc.Rwin = sc.Rwin + sc.Rwin;
-    return;
-  }
-  double val = sc.Y;
-  if (kTop && v == t) {
-    R = ~0ull;
-    val = madd_m(val, ~x1, Mv);
-  }
-  val = mask_slot<kSlow>(val, R, rec[2], rec[3], dbl(rec[12], rec[13]), nd.d0, sc.Rwin, Rrow, tlim);
-  val = mask_slot<kSlow>(val, R, rec[4], rec[5], dbl(rec[14], rec[15]), nd.d1, sc.Rwin, Rrow, tlim);
-  if (kSlow && __builtin_expect((ctrl & kMRare) != 0u, 0)) {
-    const uint32_t off = (uint32_t)v * kMNodeBytes;
-    const u32x8 r2 = sload<u32x8>(a.mnodes, off + 64);
-    const u32x4 m23 = sload<u32x4>(a.mnodes, off + 96);
-    val = mask_slot<true>(val, R, r2[0], r2[1], dbl(m23[0], m23[1]), sload<uint64_t>(s1row, r2[5]), sc.Rwin, Rrow,
-                          tlim);
-    if (r2[4] >= 4)
-      val = mask_slot<true>(val, R, r2[2], r2[3], dbl(m23[2], m23[3]), sload<uint64_t>(s1row, r2[6]), sc.Rwin,
-                            Rrow, tlim);
-  }
-  // suffix form of the U recurrence (see scan_node): val = Y + freed_v
-  sc.maxv = max_f64(sc.maxv, val);
-  const bool rb = lane_of(R);
-  const double sel = rb ? 1.0 : 0.0;
-  sc.Y = fma(-sel, Mv, val);
-  sc.cost = fma(sel, Cv, sc.cost);
-  sc.Rwin = sc.Rwin + sc.Rwin + (rb ? 1u : 0u);
-}
-
-template <bool kTop, bool kSkip>
-__device__ __forceinline__ void mask_node(const MaskArgs& a, int t, int v, const MNode& nd, uint64_t S0, uint64_t S1,
-                                          cptr<uint64_t> s1row, MScan& sc, u32x32& Rrow) {
-  const uint32_t tlim = (uint32_t)(t + 1) << 16;
-  if (__builtin_expect(nd.rec[7] < tlim, 0))
-    mask_node_as<kTop, true, kSkip>(a, t, v, nd, S0, S1, s1row, sc, Rrow, tlim);
-  else
-    mask_node_as<kTop, false, kSkip>(a, t, v, nd, S0, S1, s1row, sc, Rrow, tlim);
-}
-
-// x, made to depend on a word of a record that a wait delivers, so that the
-// loads it addresses are issued after that wait: scalar loads complete out
-// of order, and a wait for the record would wait for them as well.
-__device__ __forceinline__ uint32_t after_record(uint32_t x, uint32_t word) {
-  asm("" : "+s"(x) : "s"(word));
-  return x;
-}
-
-// The loads node v-1 needs, issued while node v is decided: its record (with
-// its operands) at byte off, and the dependency words node v's record lists
-// for it.
-__device__ __forceinline__ MNode mask_fetch(const MaskArgs& a, const u32x16& rec_v, cptr<uint64_t> s1row,
-                                            uint32_t off) {
-  MNode nx;
-  nx.rec = sload<u32x16>(a.mnodes, off);
-  nx.d0 = sload<uint64_t>(s1row, rec_v[6]);
-  nx.d1 = sload<uint64_t>(s1row, rec_v[7] & 0xFFFFu);
-  return nx;
-}
-
-// Node v at position P of its pair (P = v & 1), with the next node's loads
-// issued first; at P = 0 they include the next pair's words, into Bn0 and
-// Bn1 (the current pair is in B0, B1). The loads alternate between two
-// buffers by position (node v's in buf[P], node v-1's into the other), so
-// nothing moves from one to the other.
-template <int P, bool kTop, bool kSkip>
-__device__ __forceinline__ void mask_step(const MaskArgs& a, int t, int v, MNode (&buf)[2], const u32x4& B0,
-                                          const u32x4& B1, u32x4& Bn0, u32x4& Bn1, cptr<uint64_t> s0row,
-                                          cptr<uint64_t> s1row, MScan& sc, u32x32& Rrow, uint32_t* rrow_t) {
-  constexpr int kCur = P, kNext = P ^ 1;
-  const uint64_t S0 = (uint64_t)B0[2 * P] | (uint64_t)B0[2 * P + 1] << 32;
-  const uint64_t S1 = (uint64_t)B1[2 * P] | (uint64_t)B1[2 * P + 1] << 32;
-  const u32x16& rec = buf[kCur].rec;
-  // node v-1's data (node 0 fetches its own again: nothing is left to load)
-  buf[kNext] = mask_fetch(a, rec, s1row, after_record(v >= 1 ? (uint32_t)(v - 1) * kMNodeBytes : 0u, rec[6]));
-  if (P == 0) {
-    // pair c-1 (v = 2c) starts 16 (c - 1) bytes into a row (0 for c = 0)
-    const uint32_t boff = after_record(v >= 2 ? 8u * (uint32_t)v - 16u : 0u, rec[6]);
-    Bn0 = sload<u32x4>(s0row, boff);
-    Bn1 = sload<u32x4>(s1row, boff);
-  }
-  // The loads stay ahead of the node's gate branch. Placed after it, in a
-  // block that both forms of the node share, they made the compiler route
-  // the fast form through a flag, a test and a taken jump per node pair
-  // (0.456 against 0.452 ms on the transformer workload).
-  asm volatile("" ::: "memory");
-  mask_node<kTop, kSkip>(a, t, v, buf[kCur], S0, S1, s1row, sc, Rrow);
-  if (P == 0 && (v & 31) == 0) {
-    // the R bits of nodes v .. v+31 are complete: one word of R_t, kept in
-    // the register row (and stored for the output)
-    Rrow[v >> 5] = sc.Rwin;
-    if (rrow_t) rrow_t[(size_t)(v >> 5) * a.kpad] = sc.Rwin;
-  }
-}
-
-// Pair c (nodes 2c+1, 2c) from B0, B1; pair c-1 loaded into Bn0, Bn1.
-template <bool kTop, bool kSkip>
-__device__ __forceinline__ void mask_block(const MaskArgs& a, int t, int c, MNode (&buf)[2], const u32x4& B0,
-                                           const u32x4& B1, u32x4& Bn0, u32x4& Bn1, cptr<uint64_t> s0row,
-                                           cptr<uint64_t> s1row, MScan& sc, u32x32& Rrow, uint32_t* rrow_t) {
-  mask_step<1, kTop, kSkip>(a, t, 2 * c + 1, buf, B0, B1, Bn0, Bn1, s0row, s1row, sc, Rrow, rrow_t);
-  mask_step<0, kTop, kSkip>(a, t, 2 * c, buf, B0, B1, Bn0, Bn1, s0row, s1row, sc, Rrow, rrow_t);
-}
-
-// One wave per work item: the 64 candidates of group blockIdx.x over the
-// stages of item blockIdx.y. Graphs up to 1023 nodes (R row in 32 registers),
-// none of whose nodes exceed the record (at most four dependencies, one user
-// more than 32 nodes above the node, one such later user per dependency).
-// Each node's loads are issued one node ahead, in one batch, so that a node
-// waits once, for loads that had a whole node's work to arrive.
-template <bool kSkip>
-__global__ void __launch_bounds__(kWave) ckm_mask_eval_kernel(MaskArgs a) {
-  const int lane = threadIdx.x;
-  const int group = blockIdx.x + a.g0;
-  const int item = blockIdx.y;
-  const uint32_t k = (uint32_t)(group * kWave + lane);
-  int t0, t1;
-  item_range(a, item, t0, t1);
-  const cptr<uint64_t> rows = a.mrows + (size_t)group * a.mgroup;
-  u32x32 Rrow = (u32x32)0u;
-  double seg_peak = -INFINITY;
-  int64_t seg_cost = 0;
-  for (int t = t0; t < t1; ++t) {
-    const cptr<uint64_t> s0row = rows + mrow_off(t);
-    const cptr<uint64_t> s1row = rows + mrow_off(t + 1);
-    uint32_t* rrow_t = a.rrows ? a.rrows + row_base(t) * (size_t)a.kpad + k : nullptr;
-    MScan sc;
-    sc.U0 = (double)a.base;
-    sc.Y = 0.0;
-    sc.maxv = -INFINITY;
-    sc.cost = 0.0;
-    sc.Rwin = 0u;
-    // the scan starts at the top of t's pair: node 2c + 1, whose loads node
-    // 2c + 2's record names
-    const int c = t >> 1;
-    MNode buf[2];
-    const u32x16 top = a.mnodes[(size_t)(2 * c + 2) * (kMNodeBytes / 64)];
-    buf[1] = mask_fetch(a, top, s1row, (uint32_t)(2 * c + 1) * kMNodeBytes);
-    const u32x4 T0 = sload<u32x4>(s0row, 16u * c), T1 = sload<u32x4>(s1row, 16u * c);
-    u32x4 A0, A1, B0, B1;
-    mask_block<true, kSkip>(a, t, c, buf, T0, T1, B0, B1, s0row, s1row, sc, Rrow, rrow_t);
-    int cc = c - 1;
-    for (; cc >= 1; cc -= 2) {
-      mask_block<false, kSkip>(a, t, cc, buf, B0, B1, A0, A1, s0row, s1row, sc, Rrow, rrow_t);
-      mask_block<false, kSkip>(a, t, cc - 1, buf, A0, A1, B0, B1, s0row, s1row, sc, Rrow, rrow_t);
-    }
-    if (cc == 0) mask_block<false, kSkip>(a, t, 0, buf, B0, B1, A0, A1, s0row, s1row, sc, Rrow, rrow_t);
-    seg_peak = fmax(seg_peak, sc.U0 - sc.Y + sc.maxv);
-    seg_cost += (int64_t)sc.cost;
-  }
-  if ((int)k < a.K && t0 < t1) {
-    atomicMax(reinterpret_cast<long long*>(a.part_peak) + k, (long long)seg_peak);
-    atomicAdd(reinterpret_cast<unsigned long long*>(a.part_cost) + k, (unsigned long long)seg_cost);
-  }
-  if (group == 0 && item == 0 && lane == 0) a.hdr[0] = a.items;
 }
 
 }  // namespace
@@ -2052,247 +1743,6 @@ __global__ void __launch_bounds__(kWave) ckm_round_masks_kernel(const uint32_t* 
 }
 
 // ---------------------------------------------------------------------------
-// Seen path: the mask path for graphs of up to 4096 nodes with any number of
-// users and dependencies per node. What a node needs from users more than 32
-// nodes above it goes through a per-lane "seen" bit of the used node: when a
-// far user u of node x (u > x + 32) is decided, it ORs R_t[u] into x's seen
-// bit. When the scan reaches x, the bit holds R_t of x's far users (all above
-// it), and when a user v of x looks for users of x computed after v, the bit
-// holds those of x's far users above v (a far user within 32 above v is also
-// in v's R window). Near users stay in the window, as in the mask path. The
-// seen bits are numbered over the nodes that have a far user, in order of
-// their first far user: W words per lane in LDS (word w of lane j at byte
-// 256 w + 4 j), cleared at each stage. Stage t writes only bits of nodes
-// whose first far user is at most t, a prefix of that order, so the stages
-// below a split point need only the first words: they run in a launch of
-// their own with that much LDS (more waves per CU), where every read past
-// those words lands on one more word that stays zero.
-//
-// Node v's data, 128 bytes at 128 v (v = 0 .. n; node n has only the fetch
-// block for node n-1):
-//   [0, 64)   record, 16 dwords (one scalar load):
-//     0  users u of v with u <= v + 32 (bit u - v - 1)
-//     1  v's seen bit (0 when v has no far user)
-//     2  slots 2-3 present (bit 0) | overflow list present (bit 1) | its
-//        length << 8
-//     3  seen writes of slots 0 (low half) and 1 (high half): the LDS byte
-//        offset of the dependency's seen word | kSWrite when v is a far user
-//        of the dependency
-//     4, 5  slot 0: lm (users u of the dependency with v < u <= v + 32, bit
-//           u - v - 1), the dependency's seen bit (0: it has no far user)
-//     6, 7  slot 1
-//     8  first overflow entry (dependencies beyond the fourth)
-//     fetch block, for node v-1 (all zero for v = 0):
-//     9  byte offsets in a mask row of the S_{t+1} words of v-1's slot 0 and
-//        1 dependencies (low, high half) | kSExtNext: v-1 has slots 2-3
-//     10 the same for slots 2 and 3
-//     11 128 (v - 1)
-//     12 LDS byte offsets of v-1's seen word | of its slot 0 dependency's << 16
-//     13 slot 1 | slot 2 << 16
-//     14 slot 3
-//     15 seen writes of slots 2 and 3 (as word 3)
-//   [64, 112) binary64 M_v, C_v, M of slots 0-3
-//   [112, 128) slots 2 and 3: lm, seen bit each
-// An absent slot has lm = 0, no seen bit and size 0: it frees nothing.
-// Overflow entries, 32 bytes: lm, seen bit, seen write (as word 3), byte
-// offset of the S_{t+1} word, LDS byte offset of the seen word, M (binary64).
-// All loads for node v-1 take their addresses from node v's record, so they
-// are issued after it has arrived, one batch per node.
-constexpr int kSNodeBytes = 128;
-// Graphs with fewer seen words run every stage in one launch.
-constexpr int32_t kSeenSplitMinWords = 16;
-constexpr uint32_t kSExt = 1u, kSOver = 2u, kSWrite = 0x8000u, kSExtNext = 0x8000u;
-
-struct SeenArgs {
-  int32_t n, K, items, kind, P, T0, R1, R2;   // work plan (see Plan)
-  int32_t np;                                 // node data entries: n + 1
-  int32_t seen_words;                         // LDS words per lane of this launch
-  uint32_t seen_lim;                          // byte offset of its last word: reads clamp to it
-  int32_t item0;                              // work item of blockIdx.y = 0
-  double base;                                // M_in + 2 M_param
-  size_t mgroup;                              // words of one group's mask rows
-  cptr<uint64_t> mrows;                       // S masks, group-major
-  cptr<u32x16> snodes;                        // np x 128 bytes of node data
-  cptr<u32x8> over;                           // overflow entries
-  uint32_t* __restrict__ rrows;               // R rows out (row array layout)
-  int32_t kpad;
-  int64_t* __restrict__ part_peak;
-  int64_t* __restrict__ part_cost;
-  int32_t* __restrict__ hdr;
-  int32_t g0;                                 // group of blockIdx.x = 0
-};
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t snode_rsrc(const SeenArgs& a) {
-  return __builtin_amdgcn_make_buffer_rsrc(const_cast<u32x16*>((const u32x16*)a.snodes), 0, a.np * kSNodeBytes,
-                                           kBufWord3);
-}
-// The lane's word at LDS byte offset off (off wave-uniform, a multiple of 256).
-__device__ __forceinline__ uint32_t seen_read(const SeenArgs& a, char* lds_lane, uint32_t off) {
-  return *reinterpret_cast<const uint32_t*>(lds_lane + min(off, a.seen_lim));
-}
-__device__ __forceinline__ void seen_or(char* lds_lane, uint32_t off, uint32_t bits) {
-  atomicOr(reinterpret_cast<uint32_t*>(lds_lane + off), bits);
-}
-
-// What node v needs, all requested while node v+1 is decided.
-struct SNode {
-  u32x16 rec;
-  uint64_t S0, S1;          // S_t[v], S_{t+1}[v]
-  uint64_t d0, d1, d2, d3;  // S_{t+1} words of the slot 0-3 dependencies
-  u32x4 ext;                // slots 2-3
-  uint32_t has_ext;
-  uint4 mc, dm, dm2;        // M_v, C_v | M of slots 0, 1 | M of slots 2, 3
-  uint32_t sv, s0, s1, s2, s3;   // seen words of v and of the slot dependencies
-};
-
-__device__ __forceinline__ SNode seen_fetch(const SeenArgs& a, const u32x16& rec_v, cptr<uint64_t> s0row,
-                                            cptr<uint64_t> s1row, char* lds_lane) {
-  const uint32_t off = rec_v[11], f01 = rec_v[9];
-  SNode nx;
-  nx.rec = sload<u32x16>(a.snodes, off);
-  nx.S0 = sload<uint64_t>(s0row, off >> 4);   // 8 (v - 1)
-  nx.S1 = sload<uint64_t>(s1row, off >> 4);
-  nx.d0 = sload<uint64_t>(s1row, f01 & 0x7FFFu);
-  nx.d1 = sload<uint64_t>(s1row, f01 >> 16);
-  const auto rs = snode_rsrc(a);
-  nx.mc = load_mval<64>(rs, off);
-  nx.dm = load_mval<80>(rs, off);
-  nx.sv = seen_read(a, lds_lane, rec_v[12] & 0xFFFFu);
-  nx.s0 = seen_read(a, lds_lane, rec_v[12] >> 16);
-  nx.s1 = seen_read(a, lds_lane, rec_v[13] & 0xFFFFu);
-  nx.has_ext = f01 & kSExtNext;
-  if (nx.has_ext) {
-    const uint32_t f23 = rec_v[10];
-    nx.d2 = sload<uint64_t>(s1row, f23 & 0xFFFFu);
-    nx.d3 = sload<uint64_t>(s1row, f23 >> 16);
-    nx.ext = sload<u32x4>(a.snodes, off + 112);
-    nx.dm2 = load_mval<96>(rs, off);
-    nx.s2 = seen_read(a, lds_lane, rec_v[13] >> 16);
-    nx.s3 = seen_read(a, lds_lane, rec_v[14]);
-  }
-  return nx;
-}
-
-struct SScan {
-  double U0, Y, maxv, cost;
-  uint32_t Rwin;   // R bits of nodes v+1 .. v+32 (bit d <-> node v + 1 + d)
-};
-
-// One dependency slot of node v (see mask_slot): later users of the
-// dependency are those in v's R window (lm) and those its seen bit holds.
-// Then, when v is a far user of the dependency, R_t[v] goes into its bit.
-__device__ __forceinline__ double seen_slot(double val, uint64_t R, bool rb, uint32_t lm, uint32_t bit, uint32_t sw,
-                                            uint64_t s1i, double Mi, uint32_t Rwin, uint32_t wr, char* lds_lane) {
-  const uint32_t y = (Rwin & lm) | (sw & bit);
-  const uint64_t later = mask_of(y != 0u);
-  const uint64_t fr = R & ~(s1i | later);
-  val = madd_m(val, fr, Mi);
-  if (wr & kSWrite) seen_or(lds_lane, wr & 0x7FFFu, rb ? bit : 0u);
-  return val;
-}
-
-// Node v of stage t (see mask_node and mask_node_as). kTop: v = t.
-template <bool kTop, bool kSkip>
-__device__ __forceinline__ void seen_node(const SeenArgs& a, const SNode& nd, cptr<uint64_t> s1row, SScan& sc,
-                                          char* lds_lane) {
-  const u32x16& r = nd.rec;
-  const double Mv = dbl(nd.mc.x, nd.mc.y), Cv = dbl(nd.mc.z, nd.mc.w);
-  const uint32_t x = (sc.Rwin & r[0]) | (nd.sv & r[1]);
-  const uint64_t x1 = nd.S1 | mask_of(x != 0u);
-  uint64_t R = x1 & ~nd.S0;
-  sc.U0 = madd_m(sc.U0, nd.S0, Mv);
-  if (kSkip && !kTop && R == 0ull) {
-    sc.Rwin = sc.Rwin + sc.Rwin;   // no candidate computes v (see mask_node_as)
-    return;
-  }
-  double val = sc.Y;
-  if (kTop) {
-    R = ~0ull;
-    val = madd_m(val, ~x1, Mv);
-  }
-  const bool rb = lane_of(R);
-  val = seen_slot(val, R, rb, r[4], r[5], nd.s0, nd.d0, dbl(nd.dm.x, nd.dm.y), sc.Rwin, r[3] & 0xFFFFu, lds_lane);
-  val = seen_slot(val, R, rb, r[6], r[7], nd.s1, nd.d1, dbl(nd.dm.z, nd.dm.w), sc.Rwin, r[3] >> 16, lds_lane);
-  if (nd.has_ext) {
-    val = seen_slot(val, R, rb, nd.ext[0], nd.ext[1], nd.s2, nd.d2, dbl(nd.dm2.x, nd.dm2.y), sc.Rwin,
-                    r[15] & 0xFFFFu, lds_lane);
-    val = seen_slot(val, R, rb, nd.ext[2], nd.ext[3], nd.s3, nd.d3, dbl(nd.dm2.z, nd.dm2.w), sc.Rwin, r[15] >> 16,
-                    lds_lane);
-  }
-  if (__builtin_expect((r[2] & kSOver) != 0u, 0)) {
-    // dependencies beyond the fourth, one entry at a time
-    const uint32_t cnt = r[2] >> 8;
-    for (uint32_t c = 0, e = r[8]; c < cnt; ++c, ++e) {
-      const u32x8 en = a.over[e];
-      const uint64_t s1i = sload<uint64_t>(s1row, en[3]);
-      const uint32_t sw = seen_read(a, lds_lane, en[4]);
-      val = seen_slot(val, R, rb, en[0], en[1], sw, s1i, dbl(en[5], en[6]), sc.Rwin, en[2], lds_lane);
-    }
-  }
-  // suffix form of the U recurrence (see scan_node): val = Y + freed_v
-  sc.maxv = max_f64(sc.maxv, val);
-  const double sel = rb ? 1.0 : 0.0;
-  sc.Y = fma(-sel, Mv, val);
-  sc.cost = fma(sel, Cv, sc.cost);
-  sc.Rwin = sc.Rwin + sc.Rwin + (rb ? 1u : 0u);
-}
-
-// Node v from buf[P] (P: its parity in the scan), node v-1's loads into
-// buf[P ^ 1] first.
-template <int P, bool kTop, bool kSkip>
-__device__ __forceinline__ void seen_step(const SeenArgs& a, int v, SNode (&buf)[2], cptr<uint64_t> s0row,
-                                          cptr<uint64_t> s1row, SScan& sc, char* lds_lane, uint32_t* rrow_t) {
-  buf[P ^ 1] = seen_fetch(a, buf[P].rec, s0row, s1row, lds_lane);
-  seen_node<kTop, kSkip>(a, buf[P], s1row, sc, lds_lane);
-  if ((v & 31) == 0) rrow_t[(size_t)(v >> 5) * a.kpad] = sc.Rwin;   // R of nodes v .. v+31
-}
-
-// One wave per work item: the 64 candidates of group blockIdx.x over the
-// stages of item blockIdx.y; the scan of stage t runs from node t down.
-template <bool kSkip>
-__global__ void __launch_bounds__(kWave) ckm_seen_eval_kernel(SeenArgs a) {
-  extern __shared__ uint32_t seen_lds[];
-  const int lane = threadIdx.x;
-  const int group = blockIdx.x + a.g0;
-  const int item = blockIdx.y + a.item0;
-  const uint32_t k = (uint32_t)(group * kWave + lane);
-  char* lds_lane = reinterpret_cast<char*>(seen_lds) + 4 * lane;
-  int t0, t1;
-  item_range(a, item, t0, t1);
-  const cptr<uint64_t> rows = a.mrows + (size_t)group * a.mgroup;
-  double seg_peak = -INFINITY;
-  int64_t seg_cost = 0;
-  for (int t = t0; t < t1; ++t) {
-    for (int w = 0; w < a.seen_words; ++w) *reinterpret_cast<uint32_t*>(lds_lane + 256 * w) = 0u;
-    const cptr<uint64_t> s0row = rows + mrow_off(t);
-    const cptr<uint64_t> s1row = rows + mrow_off(t + 1);
-    uint32_t* rrow_t = a.rrows + row_base(t) * (size_t)a.kpad + k;
-    SScan sc;
-    sc.U0 = (double)a.base;
-    sc.Y = 0.0;
-    sc.maxv = -INFINITY;
-    sc.cost = 0.0;
-    sc.Rwin = 0u;
-    SNode buf[2];
-    const u32x16 top = a.snodes[(size_t)(t + 1) * (kSNodeBytes / 64)];   // its fetch block: node t
-    buf[1] = seen_fetch(a, top, s0row, s1row, lds_lane);
-    seen_step<1, true, kSkip>(a, t, buf, s0row, s1row, sc, lds_lane, rrow_t);
-    int v = t - 1;
-    for (; v >= 1; v -= 2) {
-      seen_step<0, false, kSkip>(a, v, buf, s0row, s1row, sc, lds_lane, rrow_t);
-      seen_step<1, false, kSkip>(a, v - 1, buf, s0row, s1row, sc, lds_lane, rrow_t);
-    }
-    if (v == 0) seen_step<0, false, kSkip>(a, 0, buf, s0row, s1row, sc, lds_lane, rrow_t);
-    seg_peak = fmax(seg_peak, sc.U0 - sc.Y + sc.maxv);
-    seg_cost += (int64_t)sc.cost;
-  }
-  if ((int)k < a.K && t0 < t1) {
-    atomicMax(reinterpret_cast<long long*>(a.part_peak) + k, (long long)seg_peak);
-    atomicAdd(reinterpret_cast<unsigned long long*>(a.part_cost) + k, (unsigned long long)seg_cost);
-  }
-  if (group == 0 && item == 0 && lane == 0) a.hdr[0] = a.items;
-}
-
 // Threshold candidates into mask rows (block (group, y): row n - y):
 // word i of row r is the group's 64 decisions [rank_k < key[r][i]], the
 // threshold test of threshold_word. Keys on and above the diagonal are 0, so
@@ -2465,29 +1915,7 @@ int32_t eval_waves_per_cu(int32_t n, bool wide) {
 
 static unsigned groups_of(int32_t K) { return (unsigned)((K + kWave - 1) / kWave); }
 
-static bool use_mask_path(const ckm_graph& g, const Layout& L) {
-  return L.rows_on && (g.d_mrecs != nullptr || g.d_snodes != nullptr);
-}
-
-int32_t mask_waves_per_cu() {
-  int blocks = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, (const void*)ckm_mask_eval_kernel<false>, kWave, 0) !=
-          hipSuccess ||
-      blocks < 1)
-    blocks = 1;
-  return blocks;
-}
-
-int32_t seen_waves_per_cu(int32_t seen_words) {
-  int blocks = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, (const void*)ckm_seen_eval_kernel<false>, kWave,
-                                                   (size_t)seen_words * 256) != hipSuccess ||
-      blocks < 1)
-    blocks = 1;
-  return blocks;
-}
-
-size_t mask_rows_words(int32_t n) { return mrow_off(n + 1); }
+static bool use_events(const ckm_graph& g, const Layout& L) { return L.rows_on && g.ev.on; }
 
 hipError_t launch_round_rows(const ckm_graph& g, const Layout& L, int32_t K, uint64_t seed, uint32_t flags,
                              char* work, hipStream_t stream) {
@@ -2497,7 +1925,7 @@ hipError_t launch_round_rows(const ckm_graph& g, const Layout& L, int32_t K, uin
 hipError_t launch_round_rows(const ckm_graph& g, const Layout& L, int32_t K, uint64_t seed, uint32_t flags,
                              int32_t g0, int32_t gn, bool clear, char* work, hipStream_t stream) {
   if (!L.rows_on || gn <= 0) return hipSuccess;
-  if (use_mask_path(g, L)) {
+  if (use_events(g, L)) {
     const Totals tot{clear ? at<int64_t>(work, L.part_peak_off) : nullptr, at<int64_t>(work, L.part_cost_off), K};
     hipLaunchKernelGGL(ckm_round_masks_kernel, dim3(gn, g.n + 1), dim3(kWave), 0, stream,
                        at<const uint32_t>(work, L.q_off), at<const uint32_t>(work, L.det_off), g.n, L.ldq,
@@ -2512,38 +1940,6 @@ hipError_t launch_round_rows(const ckm_graph& g, const Layout& L, int32_t K, uin
                      (uint32_t)(seed & 0xFFFFFFFFu), (uint32_t)(seed >> 32), (flags & CKM_F_DET0) ? 1u : 0u, kpad,
                      at<uint32_t>(work, L.rows_off));
   return hipGetLastError();
-}
-
-// Overlapped launches (seen path, when LDS holds its evaluate to at most
-// kForkMaxWaves waves per CU). The first quarter of the candidate groups has
-// its mask rows made alone; the other groups' producer then runs beside the
-// first quarter's evaluate, and their evaluate follows on the side stream.
-// The producers are VALU-bound, and an evaluate that LDS keeps at a few waves
-// per SIMD leaves them registers and VALU slots: at n = 4001, K = 4096 (16 KiB
-// of seen bits per wave, 10 waves per CU) the step drops from 95.3 to
-// 91.7 ms (halves: 93.7, eighths: 91.3). An evaluate that its registers
-// keep at 6 waves per SIMD leaves no room, and the second chunk's longest
-// stages then start behind its producer: n = 1009, K = 1024 on the mask
-// kernel takes 0.68 to 0.73 ms split against 0.611, n = 337, K = 512 on the
-// seen kernel 0.156 against 0.106.
-static int32_t fork_first_groups(int32_t groups) { return groups / 4 > 0 ? groups / 4 : 1; }
-constexpr int32_t kForkMinGroups = 8;
-
-hipError_t fork_create(Fork& f) {
-  hipError_t e = hipStreamCreateWithFlags(&f.side, hipStreamNonBlocking);
-  if (e == hipSuccess) e = hipEventCreateWithFlags(&f.forked, hipEventDisableTiming);
-  if (e == hipSuccess) e = hipEventCreateWithFlags(&f.joined, hipEventDisableTiming);
-  if (e != hipSuccess) fork_destroy(f);
-  return e;
-}
-
-void fork_destroy(Fork& f) {
-  if (f.side) (void)hipStreamSynchronize(f.side);   // nothing of the graph's still running there
-  if (f.forked) (void)hipEventDestroy(f.forked);
-  if (f.joined) (void)hipEventDestroy(f.joined);
-  if (f.side) (void)hipStreamDestroy(f.side);
-  f.forked = f.joined = nullptr;
-  f.side = nullptr;
 }
 
 // The mask rows of groups g0 .. g0 + gn - 1 from source src (kSrcRound,
@@ -2568,133 +1964,23 @@ static hipError_t launch_mask_producer(const ckm_graph& g, const Layout& L, int3
   return hipGetLastError();
 }
 
-// The mask-path evaluate (seen kernel or mask kernel) of groups g0 .. g0 + gn - 1.
-// The evaluate of groups g0 .. g0 + gn - 1 on the mask rows. Rows of the
-// threshold family or of supplied schedules take the kernels that skip a
-// node no candidate of the group computes (see mask_node_as).
-static hipError_t launch_mask_eval(const ckm_graph& g, const Layout& L, int32_t K, const Plan& plan, int src,
-                                   int32_t g0, int32_t gn, char* work, hipStream_t stream) {
-  if (gn <= 0) return hipSuccess;
-  const bool skip = src != kSrcRound;
-  const int32_t kpad = ((K + kWave - 1) / kWave) * kWave;
-  if (g.d_snodes) {
-    SeenArgs m;
-    m.n = g.n;
-    m.K = K;
-    m.items = plan.items;
-    m.kind = plan.kind;
-    m.P = plan.P;
-    m.T0 = plan.T0;
-    m.R1 = plan.R1;
-    m.R2 = plan.R2;
-    m.np = g.n + 1;
-    m.base = (double)g.base;
-    m.mgroup = mask_rows_words(g.n);
-    m.mrows = as_const(at<const uint64_t>(work, L.rows_off));
-    m.snodes = (cptr<u32x16>)(g.d_snodes);
-    m.over = (cptr<u32x8>)(g.d_sover);
-    m.rrows = at<uint32_t>(work, L.rrows_off);
-    m.kpad = kpad;
-    m.part_peak = at<int64_t>(work, L.part_peak_off);
-    m.part_cost = at<int64_t>(work, L.part_cost_off);
-    m.hdr = at<int32_t>(work, L.hdr_off);
-    m.g0 = g0;
-    // items [i0, i0 + ni) with `words` LDS words per lane, reads clamped to
-    // the last of them
-    auto launch = [&](int32_t i0, int32_t ni, int32_t words) {
-      m.item0 = i0;
-      m.seen_words = words;
-      m.seen_lim = (uint32_t)(words - 1) * 256u;
-      if (skip)
-        hipLaunchKernelGGL(ckm_seen_eval_kernel<true>, dim3(gn, ni), dim3(kWave), (size_t)words * 256, stream, m);
-      else
-        hipLaunchKernelGGL(ckm_seen_eval_kernel<false>, dim3(gn, ni), dim3(kWave), (size_t)words * 256, stream, m);
-      return hipGetLastError();
-    };
-    // Items are numbered from stage n-1 down, one stage each above T0: the
-    // stages at or above the first tier's split point take every word; those
-    // below a tier's split point only that tier's words, plus one that stays
-    // zero. A split point among the multi-stage items below T0 ends the tiers.
-    if (g.seen_tiers > 0 && plan.kind == 1 && plan.P == 1) {
-      int32_t i0 = 0, words = g.seen_words;
-      hipError_t e = hipSuccess;
-      for (int i = 0; i < g.seen_tiers && e == hipSuccess; ++i) {
-        const int32_t ts = g.seen_tier_t[i];
-        if (ts < plan.T0 || ts >= g.n) break;
-        const int32_t iend = g.n - ts;
-        if (iend > i0) {
-          e = launch(i0, iend - i0, words);
-          i0 = iend;
-        }
-        words = g.seen_tier_w[i] + 1;
-      }
-      if (e == hipSuccess && i0 < plan.items) e = launch(i0, plan.items - i0, words);
-      return e;
-    }
-    return launch(0, plan.items, g.seen_words);
-  }
-  MaskArgs m;
-  m.n = g.n;
-  m.K = K;
-  m.items = plan.items;
-  m.kind = plan.kind;
-  m.P = plan.P;
-  m.T0 = plan.T0;
-  m.R1 = plan.R1;
-  m.R2 = plan.R2;
-  m.base = (double)g.base;
-  m.mgroup = mask_rows_words(g.n);
-  m.mrows = as_const(at<const uint64_t>(work, L.rows_off));
-  m.np = mask_padded_nodes(g.n);
-  m.mnodes = (cptr<u32x16>)(g.d_mrecs);
-  m.rrows = at<uint32_t>(work, L.rrows_off);
-  m.kpad = kpad;
-  m.part_peak = at<int64_t>(work, L.part_peak_off);
-  m.part_cost = at<int64_t>(work, L.part_cost_off);
-  m.hdr = at<int32_t>(work, L.hdr_off);
-  m.g0 = g0;
-  if (skip)
-    hipLaunchKernelGGL(ckm_mask_eval_kernel<true>, dim3(gn, plan.items), dim3(kWave), 0, stream, m);
-  else
-    hipLaunchKernelGGL(ckm_mask_eval_kernel<false>, dim3(gn, plan.items), dim3(kWave), 0, stream, m);
-  return hipGetLastError();
-}
-
 hipError_t launch_evaluate(const ckm_graph& g, const Layout& L, int32_t K, uint64_t seed,
                            uint32_t flags, const Plan& plan, int src, const uint64_t* s_user, char* work,
-                           hipStream_t stream, bool overlap) {
-  if (use_mask_path(g, L)) {
+                           hipStream_t stream) {
+  if (use_events(g, L)) {
     // mask rows made by a producer (none when the caller rounded them
-    // beforehand), then the evaluate, chunk by chunk
-    const bool produce = !(src == kSrcRound && (flags & CKM_F_ROUNDED));
+    // beforehand), then the event path
     const int32_t G = (int32_t)groups_of(K);
     hipError_t e = hipSuccess;
-    if (!produce) {
+    if (!(src == kSrcRound && (flags & CKM_F_ROUNDED))) {
+      e = launch_mask_producer(g, L, K, seed, flags, src, s_user, 0, G, work, stream);
+    } else {
       // no producer to clear the totals on the way
       hipLaunchKernelGGL(ckm_eval_init_kernel, dim3((K + 255) / 256), dim3(256), 0, stream, K,
                          at<int64_t>(work, L.part_peak_off), at<int64_t>(work, L.part_cost_off));
       e = hipGetLastError();
-      if (e != hipSuccess) return e;
     }
-    if (!(overlap && produce && g.fork && g.d_snodes && g.eval_waves <= kForkMaxWaves && G >= kForkMinGroups)) {
-      if (produce) e = launch_mask_producer(g, L, K, seed, flags, src, s_user, 0, G, work, stream);
-      if (e == hipSuccess) e = launch_mask_eval(g, L, K, plan, src, 0, G, work, stream);
-      return e;
-    }
-    const int32_t ga = fork_first_groups(G);
-    e = launch_mask_producer(g, L, K, seed, flags, src, s_user, 0, ga, work, stream);
-    if (e != hipSuccess) return e;
-    std::lock_guard<std::mutex> lk(g.fork->mu);
-    e = hipEventRecord(g.fork->forked, stream);
-    if (e == hipSuccess) e = hipStreamWaitEvent(g.fork->side, g.fork->forked, 0);
-    if (e == hipSuccess) e = launch_mask_producer(g, L, K, seed, flags, src, s_user, ga, G - ga, work, g.fork->side);
-    if (e == hipSuccess) e = launch_mask_eval(g, L, K, plan, src, ga, G - ga, work, g.fork->side);
-    if (e == hipSuccess) e = hipEventRecord(g.fork->joined, g.fork->side);
-    // the first chunk's evaluate is enqueued whatever happened above, and the
-    // caller's stream always waits for what the side stream was given
-    hipError_t e2 = launch_mask_eval(g, L, K, plan, src, 0, ga, work, stream);
-    hipError_t e3 = hipStreamWaitEvent(stream, g.fork->joined, 0);
-    return e != hipSuccess ? e : e2 != hipSuccess ? e2 : e3;
+    return e == hipSuccess ? launch_events(g, L, K, work, stream) : e;
   }
   EvalArgs a;
   a.n = g.n;
@@ -2820,6 +2106,12 @@ hipError_t launch_select(const ckm_graph& g, const Layout& L, int32_t K, uint64_
   }
   // With the row arrays the evaluate stage kept every candidate's R rows, so
   // the best R is a gather; otherwise Algorithm 2 runs again for it.
+  const bool events = use_events(g, L);
+  if (events && d_best_R) {
+    const hipError_t e = launch_best_events(g, L, K, d_best_k, d_best_R, work, stream);
+    if (e != hipSuccess) return e;
+    d_best_R = nullptr;
+  }
   const bool gather_R = d_best_R && L.rows_on;
   const int32_t kpad = (int32_t)(groups_of(K) * kWave);
   const dim3 rows_grid((L.row_words + 255) / 256, g.n);
@@ -2896,193 +2188,6 @@ static bool build_ext_lists(int32_t v, const int64_t* M, bool wide, const int32_
     dw[b + 3] = (uint32_t)i | (uint32_t)nl << 16;
   }
   dw[kDwExt] = (uint32_t)nfar | (uint32_t)nd << 8 | kExtValid;
-  return true;
-}
-
-int32_t mask_records_bytes(int32_t n) { return mask_padded_nodes(n) * kMNodeBytes; }
-
-bool build_mask_records(int32_t n, const int64_t* M, const int64_t* C, const int32_t* dep_ptr,
-                        const int32_t* dep_idx, const int32_t* user_ptr, const int32_t* user_idx, void* out) {
-  const int32_t np = mask_padded_nodes(n);
-  char* base = static_cast<char*>(out);
-  memset(out, 0, (size_t)mask_records_bytes(n));
-  auto far = [](int u) { return (uint32_t)u << 16 | (uint32_t)(u & 31); };
-  auto put = [](uint32_t* w, double x) { memcpy(w, &x, sizeof(x)); };
-  for (int32_t v = 0; v < np; ++v) {   // no far references, padded nodes included
-    uint32_t* r = reinterpret_cast<uint32_t*>(base + (size_t)v * kMNodeBytes);
-    r[1] = r[3] = r[5] = r[7] = r[16 + 1] = r[16 + 3] = kMNoFar;
-  }
-  for (int32_t v = 0; v < n; ++v) {
-    char* node = base + (size_t)v * kMNodeBytes;
-    uint32_t* r = reinterpret_cast<uint32_t*>(node);
-    uint32_t* r2 = reinterpret_cast<uint32_t*>(node + 64);
-    uint32_t* m23 = reinterpret_cast<uint32_t*>(node + 96);
-    uint32_t ctrl = kMNoFar;   // stays, or names the one far user
-    int nfar = 0;
-    for (int32_t e = user_ptr[v]; e < user_ptr[v + 1]; ++e) {
-      const int u = user_idx[e];
-      if (u - v - 1 < 32) {
-        r[0] |= 1u << (u - v - 1);
-      } else {
-        if (nfar++) return false;
-        ctrl = far(u);
-      }
-    }
-    const int nd = dep_ptr[v + 1] - dep_ptr[v];
-    if (nd > 4) return false;
-    if (nd > 2) {
-      ctrl |= kMRare;
-      r2[4] = (uint32_t)nd;
-    }
-    put(r + 8, (double)M[v]);
-    put(r + 10, (double)C[v]);
-    for (int sl = 0; sl < nd; ++sl) {
-      const int i = dep_idx[dep_ptr[v] + sl];
-      uint32_t* w = sl < 2 ? r + 2 + 2 * sl : r2 + 2 * (sl - 2);
-      if (sl >= 2) r2[5 + (sl - 2)] = (uint32_t)i * 8u;
-      uint32_t ref = kMNoFar;
-      int nlate = 0;
-      for (int32_t e = user_ptr[i]; e < user_ptr[i + 1]; ++e) {
-        const int u = user_idx[e];
-        if (u <= v) continue;
-        if (u - v - 1 < 32) {
-          w[0] |= 1u << (u - v - 1);
-        } else {
-          if (nlate++) return false;
-          ref = far(u);
-        }
-      }
-      w[1] = ref;
-      put(sl < 2 ? r + 12 + 2 * sl : m23 + 2 * (sl - 2), (double)M[i]);
-    }
-    r[1] = ctrl;
-    // the gate: below the stage's limit when a far reference may apply (the
-    // low half takes node v-1's slot 1 offset below)
-    r[7] = (ctrl & kMRare) ? 0u : std::min(ctrl, std::min(r[3], r[5])) & 0xFFFF0000u;
-  }
-  // fetch lists: record v (padded ones included) names the S_{t+1} words of
-  // node v-1's slots 0 (word 6) and 1 (low half of word 7)
-  for (int32_t v = 1; v < np; ++v) {
-    const int32_t u = v - 1;
-    uint32_t f0 = 0, f1 = 0;
-    if (u < n) {
-      const int nd = dep_ptr[u + 1] - dep_ptr[u];
-      if (nd >= 1) f0 = (uint32_t)dep_idx[dep_ptr[u]] * 8u;
-      if (nd >= 2) f1 = (uint32_t)dep_idx[dep_ptr[u] + 1] * 8u;
-    }
-    uint32_t* r = reinterpret_cast<uint32_t*>(base + (size_t)v * kMNodeBytes);
-    r[6] = f0;
-    r[7] = (r[7] & 0xFFFF0000u) | f1;
-  }
-  return true;   // node 0 keeps fetch list 0
-}
-
-bool build_seen_records(int32_t n, const int64_t* M, const int64_t* C, const int32_t* dep_ptr,
-                        const int32_t* dep_idx, const int32_t* user_ptr, const int32_t* user_idx,
-                        std::vector<char>& nodes, std::vector<uint32_t>& over, int32_t& seen_words,
-                        int32_t tier_t[2], int32_t tier_w[2], int32_t& ntiers) {
-  if (n < 1 || n > kSeenMaxNodes) return false;
-  // seen bits: the nodes with a user more than 32 above them, in order of
-  // their first such user (then of the node)
-  std::vector<int32_t> first(n, INT32_MAX);
-  std::vector<int32_t> order;
-  for (int32_t x = 0; x < n; ++x) {
-    for (int32_t e = user_ptr[x]; e < user_ptr[x + 1]; ++e)
-      if (user_idx[e] - x - 1 >= 32) first[x] = std::min(first[x], user_idx[e]);
-    if (first[x] != INT32_MAX) order.push_back(x);
-  }
-  std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) { return first[x] < first[y]; });
-  std::vector<int32_t> slot(n, -1);
-  const int32_t ns = (int32_t)order.size();
-  for (int32_t i = 0; i < ns; ++i) slot[order[i]] = i;
-  seen_words = std::max<int32_t>(1, (ns + 31) / 32);
-  // Stages t < T write only bits of nodes whose first far user is below T:
-  // the first 32 w bits when T is the first far user of bit 32 w. Tiers at
-  // three quarters and half of the words, where that is worth the launches
-  // (at n = 4001, K = 4096: 76.4 ms per step against 79.3 with the half
-  // alone and 90.7 with one launch; more tiers shorten the evaluate alone
-  // but not the step, whose two streams each pay every launch boundary).
-  ntiers = 0;
-  if (seen_words >= kSeenSplitMinWords) {
-    const int32_t ws[2] = {seen_words * 3 / 4, seen_words / 2};
-    for (int i = 0; i < 2; ++i) {
-      tier_t[ntiers] = first[order[32 * ws[i]]];
-      tier_w[ntiers] = ws[i];
-      ++ntiers;
-    }
-  }
-  auto soff = [&](int32_t x) { return slot[x] < 0 ? 0u : (uint32_t)(slot[x] >> 5) * 256u; };
-  auto sbit = [&](int32_t x) { return slot[x] < 0 ? 0u : 1u << (slot[x] & 31); };
-  const int32_t np = n + 1;
-  nodes.assign((size_t)np * kSNodeBytes, 0);
-  over.clear();
-  for (int32_t v = 0; v < n; ++v) {
-    char* node = nodes.data() + (size_t)v * kSNodeBytes;
-    uint32_t* r = reinterpret_cast<uint32_t*>(node);
-    double* val = reinterpret_cast<double*>(node + 64);
-    uint32_t* ext = reinterpret_cast<uint32_t*>(node + 112);
-    for (int32_t e = user_ptr[v]; e < user_ptr[v + 1]; ++e) {
-      const int32_t u = user_idx[e];
-      if (u - v - 1 < 32) r[0] |= 1u << (u - v - 1);
-    }
-    r[1] = sbit(v);
-    val[0] = (double)M[v];
-    val[1] = (double)C[v];
-    const int32_t nd = dep_ptr[v + 1] - dep_ptr[v];
-    uint32_t flags = nd > 2 ? kSExt : 0u;
-    if (nd > 4) {
-      flags |= kSOver | (uint32_t)(nd - 4) << 8;
-      r[8] = (uint32_t)(over.size() / 8);
-    }
-    r[2] = flags;
-    for (int32_t sl = 0; sl < nd; ++sl) {
-      const int32_t i = dep_idx[dep_ptr[v] + sl];
-      uint32_t lm = 0;
-      for (int32_t e = user_ptr[i]; e < user_ptr[i + 1]; ++e) {
-        const int32_t u = user_idx[e];
-        if (u > v && u - v - 1 < 32) lm |= 1u << (u - v - 1);
-      }
-      const uint32_t wr = v - i - 1 >= 32 ? (soff(i) | kSWrite) : 0u;
-      if (sl < 2) {
-        r[4 + 2 * sl] = lm;
-        r[5 + 2 * sl] = sbit(i);
-        r[3] |= wr << (16 * sl);
-        val[2 + sl] = (double)M[i];
-      } else if (sl < 4) {
-        ext[2 * (sl - 2)] = lm;
-        ext[2 * (sl - 2) + 1] = sbit(i);
-        r[15] |= wr << (16 * (sl - 2));
-        val[2 + sl] = (double)M[i];
-      } else {
-        const double mi = (double)M[i];
-        uint32_t mw[2];
-        memcpy(mw, &mi, sizeof(mw));
-        const uint32_t en[8] = {lm, sbit(i), wr, (uint32_t)i * 8u, soff(i), mw[0], mw[1], 0u};
-        over.insert(over.end(), en, en + 8);
-      }
-    }
-  }
-  // fetch blocks: node v's record describes node v-1's loads
-  for (int32_t v = 1; v < np; ++v) {
-    const int32_t u = v - 1;
-    const int32_t nd = dep_ptr[u + 1] - dep_ptr[u];
-    auto dep = [&](int32_t sl) { return dep_idx[dep_ptr[u] + sl]; };
-    uint32_t* r = reinterpret_cast<uint32_t*>(nodes.data() + (size_t)v * kSNodeBytes);
-    uint32_t f01 = 0, f23 = 0;
-    if (nd >= 1) f01 |= (uint32_t)dep(0) * 8u;
-    if (nd >= 2) f01 |= (uint32_t)dep(1) * 8u << 16;
-    if (nd >= 3) {
-      f01 |= kSExtNext;
-      f23 |= (uint32_t)dep(2) * 8u;
-    }
-    if (nd >= 4) f23 |= (uint32_t)dep(3) * 8u << 16;
-    r[9] = f01;
-    r[10] = f23;
-    r[11] = (uint32_t)u * (uint32_t)kSNodeBytes;
-    r[12] = soff(u) | (nd >= 1 ? soff(dep(0)) : 0u) << 16;
-    r[13] = (nd >= 2 ? soff(dep(1)) : 0u) | (nd >= 3 ? soff(dep(2)) : 0u) << 16;
-    r[14] = nd >= 4 ? soff(dep(3)) : 0u;
-  }
   return true;
 }
 

@@ -55,7 +55,7 @@ extern "C" ckm_status ckm_round_eval_noalloc(const ckm_graph* g, const double* d
   if (!g) return ckm::set_error(CKM_E_INVALID_ARG, "graph is NULL");
   if (K < 1) return ckm::set_error(CKM_E_INVALID_ARG, "K = %d < 1", K);
   if (K > CKM_MAX_CANDIDATES) return ckm::set_error(CKM_E_UNSUPPORTED, "K = %d > %d", K, CKM_MAX_CANDIDATES);
-  const ckm::Layout L = ckm::make_layout(g->n, K);
+  const ckm::Layout L = ckm::make_layout(*g, K);
   if (L.total > CKM_NOALLOC_SCRATCH_BYTES)
     return ckm::set_error(CKM_E_UNSUPPORTED, "n = %d, K = %d needs %zu bytes of work area, more than the %zu held",
                           g->n, K, L.total, (size_t)CKM_NOALLOC_SCRATCH_BYTES);
@@ -65,7 +65,6 @@ extern "C" ckm_status ckm_round_eval_noalloc(const ckm_graph* g, const double* d
   // The area is passed as an ordinary work buffer of its full size: the row
   // arrays are used when they fit in it, and every stage initializes what it
   // reads, so nothing carried over from an earlier call is read.
-  // Every launch goes on the caller's stream (no side stream).
   return ckm::round_eval(g, d_s_frac, ld, K, seed, budget, flags, d_peak, d_cost, d_feasible, d_best_k, d_best_S,
-                         d_best_R, d_status, work, CKM_NOALLOC_SCRATCH_BYTES, stream, false);
+                         d_best_R, d_status, work, CKM_NOALLOC_SCRATCH_BYTES, stream);
 }

@@ -15,22 +15,28 @@ bool build_events(int32_t n, const int64_t* M, const int64_t* C, const int32_t* 
                   const int32_t* user_ptr, const int32_t* user_idx, uint64_t max_tile_bytes, EventTables& T) {
   T = EventTables();
   T.n = n;
-  T.np = (n + 3 + kEvChunk - 1) / kEvChunk * kEvChunk;
+  T.np = (n + kEvChunk - 1) / kEvChunk * kEvChunk;
   T.chunks = T.np / kEvChunk;
-  T.pairs = (n + 1) / 2;
-  T.tiles = (2 * T.pairs + 63) / 64;
+  T.tiles = (n + kEvTile - 1) / kEvTile;
   const auto chunk = [](int32_t v) { return v / kEvChunk; };
   const auto is_far = [&](int32_t v, int32_t i) { return chunk(v) - chunk(i) > kEvNear; };
+  // A chunk's far accumulators are stored while the next chunk is decided, far
+  // loads for chunk c issued then in chunk c + kEvAhead + 1, ring entries
+  // loaded kEvAhead chunks before they are written (in the seventh chunk above
+  // theirs): both miss the stores of a far user up to there.
+  const auto too_close = [&](int32_t up, int32_t v) { return chunk(up) <= chunk(v) + kEvAhead + 1; };
+  const auto above_ring = [&](int32_t u, int32_t i) {
+    return is_far(u, i) && chunk(u) - chunk(i) <= kEvNear + 1 + kEvAhead;
+  };
 
-  // Pins: the nodes with the most far users that come within a chunk of each
-  // other, or seven chunks above the node (its ring entry is loaded then).
+  // Pins: the nodes with the most such far users.
   std::vector<int32_t> trouble(n, 0), pin_of(n, -1);
   for (int32_t i = 0; i < n; ++i) {
     for (int32_t e = user_ptr[i]; e < user_ptr[i + 1]; ++e) {
       const int32_t u = user_idx[e];
       if (!is_far(u, i)) continue;
-      if (e + 1 < user_ptr[i + 1] && chunk(user_idx[e + 1]) <= chunk(u) + 1) ++trouble[i];
-      if (chunk(u) == chunk(i) + kEvNear + 1) ++trouble[i];
+      if (e + 1 < user_ptr[i + 1] && too_close(user_idx[e + 1], u)) ++trouble[i];
+      if (above_ring(u, i)) ++trouble[i];
     }
   }
   for (int32_t i = 0; i < n; ++i)
@@ -49,6 +55,7 @@ bool build_events(int32_t n, const int64_t* M, const int64_t* C, const int32_t* 
         if (fslot[i] < 0) fslot[i] = T.nf++;
       }
   }
+  const int32_t spare = T.nf++;
   // The far user of i next above v (0xFFFF: none).
   const auto far_above = [&](int32_t i, int32_t v) {
     const int32_t* b = user_idx + user_ptr[i];
@@ -91,19 +98,25 @@ bool build_events(int32_t n, const int64_t* M, const int64_t* C, const int32_t* 
         off[k] = slot_off(kEvStage + 2 * (v % 8) + k);   // k < 2
         const int32_t up = far_above(i, v);
         flags |= k ? kEvFar1 : kEvFar0;
-        if (up != 0xFFFF && chunk(up) <= chunk(v) + 1) flags |= k ? kEvSync1 : kEvSync0;
-        d[2] |= (uint32_t)fslot[i] << (16 * k);
+        if (up != 0xFFFF && too_close(up, v)) flags |= k ? kEvSync1 : kEvSync0;
+        d[7] |= (uint32_t)fslot[i] << (16 * k);
         d[4 + k] = (uint32_t)i | (uint32_t)up << 16;
       }
     }
-    d[0] = off[0] | off[1] << 16;
+    d[11] = 0;
+    d[12] = (uint32_t)spare * (uint32_t)kEvSlotBytes;
+    if (flags & kEvFar0) {
+      d[11] = (uint32_t)(s.d[0] / 4 * kEvQuadBytes + 4 * (s.d[0] % 4));
+      d[12] = (d[7] & 0xFFFFu) * (uint32_t)kEvSlotBytes;
+    }
+    d[0] = off[0];
+    d[2] = off[1];
+    d[3] = (uint32_t)rec * (uint32_t)kEvRecBytes;
     d[8] = off[2] | off[3] << 16;
     if (s.d[2] >= 0) flags |= kEvSecond;
     const auto op = [&](int32_t a, int32_t b, bool main) {
-      T.ops.push_back(main && v < n ? (double)M[v] : 0.0);
-      T.ops.push_back(main && v < n ? (double)C[v] : 0.0);
-      T.ops.push_back(a >= 0 ? (double)M[a] : 0.0);
-      T.ops.push_back(b >= 0 ? (double)M[b] : 0.0);
+      T.ops.push_back({main && v < n ? (double)M[v] : 0.0, main && v < n ? (uint64_t)C[v] : 0u,
+                       a >= 0 ? (double)M[a] : 0.0, b >= 0 ? (double)M[b] : 0.0});
       ++rec;
     };
     op(s.d[0], s.d[1], true);
@@ -111,7 +124,7 @@ bool build_events(int32_t n, const int64_t* M, const int64_t* C, const int32_t* 
     // records beyond the second
     std::vector<int32_t> rest(far.begin() + fa, far.end());
     rest.insert(rest.end(), near.begin() + na, near.end());
-    d[3] = (uint32_t)(T.extra.size() / kEvExtraDw);
+    d[9] = (uint32_t)(T.extra.size() / kEvExtraDw);
     uint32_t count = 0;
     for (size_t r = 0; r < rest.size(); r += 2, ++count) {
       uint32_t x[kEvExtraDw] = {0, 0, 0, 0, 0xFFFFFFFFu, 0, 0, 0};
@@ -141,23 +154,21 @@ bool build_events(int32_t n, const int64_t* M, const int64_t* C, const int32_t* 
     }
     d[1] = flags | count << 16;
     d[6] = 0xFFFF0000u;
-    d[7] = slot_off(v % kEvRing);
     if (v < n) {
-      if (pin_of[v] >= 0) d[7] = slot_off(kEvPin + pin_of[v]);
+      if (pin_of[v] >= 0) {
+        d[1] |= kEvPinned;
+        d[10] = slot_off(kEvPin + pin_of[v]);
+      }
       if (fslot[v] >= 0) {
         d[6] = (uint32_t)fslot[v] | (uint32_t)farmin[v] << 16;
         for (int32_t e = user_ptr[v]; e < user_ptr[v + 1]; ++e)
-          if (chunk(user_idx[e]) == chunk(v) + kEvNear + 1) d[1] |= kEvEntrySync;
+          if (above_ring(user_idx[e], v)) d[1] |= kEvEntrySync;
       }
       first[v] = s;
     }
-    if ((uint64_t)rec * kEvRecBytes * 64 > max_tile_bytes) return false;
+    if ((uint64_t)rec * kEvRecBytes > max_tile_bytes) return false;
   }
   T.main_rec[T.np] = rec;
-  // node v + 1's first four slots against node v
-  for (int32_t v = 0; v + 1 < n; ++v)
-    for (int k = 0; k < 4; ++k)
-      if (first[v + 1].d[k] == v) T.desc[(size_t)v * kEvDescDw + 1] |= kEvOwnFwd;
   for (int32_t c = 0; c < T.chunks; ++c) {
     uint32_t* d = T.desc.data() + (size_t)c * 64;
     uint32_t fl = 0;
@@ -165,40 +176,20 @@ bool build_events(int32_t n, const int64_t* M, const int64_t* C, const int32_t* 
       const uint32_t f = d[j * kEvDescDw + 1];
       if (((f & kEvFar0) && !(f & kEvSync0)) || ((f & kEvFar1) && !(f & kEvSync1))) fl |= kEvChunkFar;
       if (d[j * kEvDescDw + 6] != 0xFFFF0000u) fl |= kEvChunkEntry;
+      if (f & kEvSecond) fl |= kEvChunkSecond;
+      if (f & kEvEntrySync) fl |= kEvChunkEntrySync;
+      if (f & (0xFFFF0000u | kEvSync0 | kEvSync1 | kEvPinned | kEvFar1)) fl |= kEvChunkRare;
+      if ((f & kEvFar0) && d[j * kEvDescDw + 4] >> 16 != 0xFFFFu) fl |= kEvChunkRare;
     }
+    for (int b = kEvChunkUse, j = 3; j > 0; --j)
+      for (int i = j - 1; i >= 0; --i, ++b)
+        for (int k = 0; k < 4; ++k)
+          if (kEvChunk * c + j < n && first[kEvChunk * c + j].d[k] == kEvChunk * c + i) fl |= 1u << b;
     d[15] = fl;
-    d[kEvDescDw + 15] = (uint32_t)T.main_rec[kEvChunk * (c + 1)];
   }
-  // padded to a multiple of 4 records
   T.nrec = rec;
-  while (T.nrec % 4) {
-    T.ops.insert(T.ops.end(), 4, 0.0);
-    ++T.nrec;
-  }
-
-  // rows of event records
-  T.row_off.assign(2 * T.pairs + 1, 0);
-  uint64_t at = 0;
-  for (int32_t p = 0; p < T.pairs; ++p) {
-    const int32_t last = std::min(2 * p + 1, n - 1);
-    const uint64_t len = ((uint64_t)T.main_rec[last + 1] + 3) / 4 * 4;
-    for (int h = 0; h < 2; ++h) {
-      T.row_off[2 * p + h] = (uint32_t)at;
-      at += len;
-    }
-  }
-  if (at > UINT32_MAX) return false;
-  T.row_off[2 * T.pairs] = (uint32_t)at;
-
-  // the chunk of the node whose record ends the tile's longest row
-  T.tile_chunk.assign(T.tiles, 0);
-  for (int32_t k = 0; k < T.tiles; ++k) {
-    const int32_t p = std::min(32 * k + 31, T.pairs - 1);
-    const int32_t len = (int32_t)(T.row_off[2 * p + 1] - T.row_off[2 * p]);
-    const int32_t v = (int32_t)(std::upper_bound(T.main_rec.begin(), T.main_rec.end() - 1, len - 1) -
-                                T.main_rec.begin()) - 1;
-    T.tile_chunk[k] = chunk(v);
-  }
+  T.ops.insert(T.ops.end(), 8, EvOps{0.0, 0, 0.0, 0.0});
+  for (int32_t k = 0; k < T.tiles; ++k) T.tile_rec.push_back(T.main_rec[kEvChunk * (ev_first_chunk(n, k) + 1)]);
   return true;
 }
 

@@ -10,6 +10,7 @@
 #include <mutex>
 #include <new>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "ckm_events.h"
@@ -263,9 +264,9 @@ Plan plan_auto(int32_t n, int32_t K, int32_t max_items, int32_t waves_per_cu) {
   return p;
 }
 
-// What tile i of one group takes of a chunk's room.
-static size_t ev_tile_bytes(const ckm_graph& g, int32_t i) {
-  return (g.ev.tile_row[i + 1] - g.ev.tile_row[i]) * kEvRecBytes + (size_t)g.ev.nf * kEvSlotBytes;
+// What tiles lo .. hi - 1 of one group take of a chunk's room.
+static size_t ev_room(const ckm_graph& g, int32_t lo, int32_t hi) {
+  return (g.ev.tile_off[hi] - g.ev.tile_off[lo]) + (size_t)(hi - lo) * g.ev.nf * kEvSlotBytes;
 }
 
 Layout make_layout(const ckm_graph& g, int32_t K) {
@@ -307,19 +308,15 @@ Layout make_layout(const ckm_graph& g, int32_t K) {
   const size_t kpad = (size_t)((K + kWave - 1) / kWave) * kWave;
   L.rows_off = off;
   if (g.ev.on) {
-    // mask rows of every group, then room for the event records and far
-    // accumulators: of everything, or of kEvMaxBytes; one tile at least
+    // S tiles of every group, then room for the event records and far
+    // accumulators: of everything, or of kEvMaxBytes; one tile at least (the
+    // last is the largest)
     const size_t groups = kpad / kWave;
-    const size_t s_bytes = groups * ckm::mask_rows_words(n) * sizeof(uint64_t);
-    size_t all = 0, tile = 0;
-    for (int32_t i = 0; i < g.ev.tiles; ++i) {
-      const size_t b = ev_tile_bytes(g, i);
-      all += b;
-      tile = std::max(tile, b);
-    }
+    const size_t s_bytes = groups * ckm::stiles_bytes(n);
+    const size_t all = groups * ev_room(g, 0, g.ev.tiles), tile = ev_room(g, g.ev.tiles - 1, g.ev.tiles);
     L.rows_on = s_bytes <= ckm::kRowsMaxBytes;
     L.events_off = align256(off + s_bytes);
-    L.ev_bytes = std::max(tile, groups * all <= ckm::kEvMaxBytes ? groups * all : (size_t)ckm::kEvMaxBytes);
+    L.ev_bytes = std::max(tile, std::min(all, (size_t)ckm::kEvMaxBytes));
     L.min_rows = L.rows_on ? L.events_off + tile : off;
     L.total_rows = L.rows_on ? L.events_off + L.ev_bytes : off;
     return L;
@@ -339,29 +336,36 @@ void fit_layout(const ckm_graph& g, Layout& L, size_t work_bytes) {
   if (L.rows_on && g.ev.on) L.ev_bytes = std::min(L.ev_bytes, work_bytes - L.events_off);
 }
 
-std::vector<EvChunk> event_chunks(const ckm_graph& g, const Layout& L, int32_t K) {
-  const int32_t groups = (K + kWave - 1) / kWave, tiles = g.ev.tiles;
-  const size_t rec = kEvRecBytes;
-  size_t all = 0;
-  for (int32_t i = 0; i < tiles; ++i) all += ev_tile_bytes(g, i);
-  std::vector<EvChunk> out;
-  if (all <= L.ev_bytes && g.ev.tile_row[tiles] * rec <= kEvGroupMaxBytes) {
-    const int32_t per = (int32_t)std::min<size_t>(groups, L.ev_bytes / all);
-    for (int32_t g0 = 0; g0 < groups; g0 += per) out.push_back({g0, std::min(per, groups - g0), 0, tiles});
-    return out;
+// Whole groups where one fits, else one group's tiles from the top.
+static void fit_chunk(const ckm_graph& g, const Layout& L, int32_t K, EvChunk& c) {
+  const int32_t groups = (K + kWave - 1) / kWave;
+  const size_t all = ev_room(g, 0, g.ev.tiles);
+  if (all <= L.ev_bytes) {
+    c.gn = (int32_t)std::min<size_t>(groups - c.g0, L.ev_bytes / all);
+    c.tlo = 0;
+    return;
   }
-  // not even one group's: a group at a time, its tiles from the top
-  for (int32_t g0 = 0; g0 < groups; ++g0)
-    for (int32_t hi = tiles; hi > 0;) {
-      int32_t lo = hi - 1;
-      size_t b = ev_tile_bytes(g, lo);
-      while (lo > 0 && b + ev_tile_bytes(g, lo - 1) <= L.ev_bytes &&
-             (g.ev.tile_row[hi] - g.ev.tile_row[lo - 1]) * rec <= kEvGroupMaxBytes)
-        b += ev_tile_bytes(g, --lo);
-      out.push_back({g0, 1, lo, hi});
-      hi = lo;
-    }
-  return out;
+  c.gn = 1;
+  c.tlo = c.thi - 1;
+  while (c.tlo > 0 && ev_room(g, c.tlo - 1, c.thi) <= L.ev_bytes) --c.tlo;
+}
+
+bool first_event_chunk(const ckm_graph& g, const Layout& L, int32_t K, EvChunk& c) {
+  c = {0, 0, 0, g.ev.tiles};
+  fit_chunk(g, L, K, c);
+  return true;
+}
+
+bool next_event_chunk(const ckm_graph& g, const Layout& L, int32_t K, EvChunk& c) {
+  if (c.tlo > 0) {
+    c.thi = c.tlo;
+  } else {
+    c.g0 += c.gn;
+    c.thi = g.ev.tiles;
+    if (c.g0 >= (K + kWave - 1) / kWave) return false;
+  }
+  fit_chunk(g, L, K, c);
+  return true;
 }
 
 }  // namespace ckm
@@ -496,7 +500,7 @@ static ckm_status graph_create(int32_t n, const int32_t* dep_ptr, const int32_t*
   // the event path's tables, when the graph takes it
   ckm::EventTables ev;
   const bool events = !wide && ckm::build_events(n, bytes, cost, dp.data(), di.data(), up.data(), ui.data(),
-                                                 ckm::kEvGroupMaxBytes, ev);
+                                                 ckm::kEvTileMaxBytes, ev);
   if (!events) ev = ckm::EventTables();
   size_t ev_end = off_mrec;
   const auto place = [&](size_t b) {
@@ -504,10 +508,11 @@ static ckm_status graph_create(int32_t n, const int32_t* dep_ptr, const int32_t*
     ev_end = align256(ev_end + b);
     return at;
   };
+  std::vector<uint64_t> tile_off(1, 0);
+  for (const int32_t r : ev.tile_rec) tile_off.push_back(tile_off.back() + (uint64_t)r * ckm::kEvRecBytes);
   const size_t off_desc = place(ev.desc.size() * 4), off_extra = place(ev.extra.size() * 4),
-               off_ops = place(ev.ops.size() * 8), off_row = place(ev.row_off.size() * 4),
-               off_main = place(ev.main_rec.size() * 4), off_tile = place(ev.tile_chunk.size() * 4),
-               off_pins = place(ev.pins.size() * 4);
+               off_ops = place(ev.ops.size() * sizeof(ckm::EvOps)), off_tile = place(tile_off.size() * 8),
+               off_main = place(ev.main_rec.size() * 4), off_pins = place(ev.pins.size() * 4);
   const size_t total = ev_end;
   std::vector<char> host(total, 0);
   const auto copy = [&](size_t off, const auto& v) {
@@ -516,9 +521,8 @@ static ckm_status graph_create(int32_t n, const int32_t* dep_ptr, const int32_t*
   copy(off_desc, ev.desc);
   copy(off_extra, ev.extra);
   copy(off_ops, ev.ops);
-  copy(off_row, ev.row_off);
+  copy(off_tile, tile_off);
   copy(off_main, ev.main_rec);
-  copy(off_tile, ev.tile_chunk);
   copy(off_pins, ev.pins);
   memcpy(host.data() + off_M, bytes, n * sizeof(int64_t));
   memcpy(host.data() + off_C, cost, n * sizeof(int64_t));
@@ -571,18 +575,15 @@ static ckm_status graph_create(int32_t n, const int32_t* dep_ptr, const int32_t*
   g->d_recs = base + off_rec;
   if (events) {
     g->ev.on = true;
-    g->ev.pairs = ev.pairs;
     g->ev.tiles = ev.tiles;
     g->ev.nf = ev.nf;
     g->ev.npins = (int32_t)ev.pins.size();
-    for (int32_t i = 0; i < ev.tiles; ++i) g->ev.tile_row.push_back(ev.row_off[64 * i]);
-    g->ev.tile_row.push_back(ev.row_off[2 * ev.pairs]);
+    g->ev.tile_off = std::move(tile_off);
     g->ev.d_desc = reinterpret_cast<const uint32_t*>(base + off_desc);
     g->ev.d_extra = reinterpret_cast<const uint32_t*>(base + off_extra);
-    g->ev.d_ops = reinterpret_cast<const double*>(base + off_ops);
-    g->ev.d_row_off = reinterpret_cast<const uint32_t*>(base + off_row);
+    g->ev.d_ops = base + off_ops;
+    g->ev.d_tile_off = reinterpret_cast<const uint64_t*>(base + off_tile);
     g->ev.d_main_rec = reinterpret_cast<const int32_t*>(base + off_main);
-    g->ev.d_tile_chunk = reinterpret_cast<const int32_t*>(base + off_tile);
     g->ev.d_pins = reinterpret_cast<const int32_t*>(base + off_pins);
   }
   g->sync = new (std::nothrow) ckm::SyncCache;

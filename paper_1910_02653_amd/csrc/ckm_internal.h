@@ -17,14 +17,13 @@ struct SyncCache;  // buffers and stream of the synchronous entry points (ckm_ho
 // false for the graphs that do not take it (wide or very dense).
 struct EventGraph {
   bool on = false;
-  int32_t pairs = 0, tiles = 0, nf = 0, npins = 0;
-  std::vector<uint64_t> tile_row;   // first event record of each tile's stages, tiles + 1 entries
+  int32_t tiles = 0, nf = 0, npins = 0;
+  std::vector<uint64_t> tile_off;   // byte offset of each tile's event records in a group, tiles + 1 entries
   const uint32_t* d_desc = nullptr;
   const uint32_t* d_extra = nullptr;
-  const double* d_ops = nullptr;
-  const uint32_t* d_row_off = nullptr;
+  const void* d_ops = nullptr;
+  const uint64_t* d_tile_off = nullptr;
   const int32_t* d_main_rec = nullptr;
-  const int32_t* d_tile_chunk = nullptr;
   const int32_t* d_pins = nullptr;
 };
 }
@@ -83,29 +82,28 @@ void build_node_records(int32_t n, const int64_t* M, const int64_t* C, bool wide
                         const int32_t* dep_idx, const int32_t* user_ptr, const int32_t* user_idx,
                         void* out);
 
-// Mask rows of one candidate group: the offset of row t, and the words of
-// rows 0 .. n (see ckm_kernels.hip).
-__host__ __device__ __forceinline__ size_t mrow_off(int t) {
-  const size_t q = (size_t)(t >> 3), r = (size_t)(t & 7);
-  return 8 * ((size_t)t + 4 * q * (q ? q - 1 : 0) + q * r);
-}
-inline size_t mask_rows_words(int32_t n) { return mrow_off(n + 1); }
+// S tiles (the event path's S rows, see ckm_kernels.hip): for one candidate
+// group, tile T of 32 stages holds 8 (T + 1) quads of 1024 bytes (nodes 4q ..
+// 4q + 3, 16 bytes per lane), one tile after another.
+__host__ __device__ __forceinline__ uint32_t stile_bytes(int T) { return 8192u * (uint32_t)(T + 1); }
+__host__ __device__ __forceinline__ size_t stile_off(int T) { return (size_t)4096 * T * (T + 1); }
+inline size_t stiles_bytes(int32_t n) { return stile_off((n + 31) / 32); }
 
 // Event records are made and consumed a chunk at a time: the candidate groups
 // and stage tiles whose records (and far accumulators) fit the room for them,
-// on most calls all. A group's records in a chunk stay under kEvGroupMaxBytes,
-// so that their byte offsets stay clear of the 32-bit buffer offset that marks
-// a lane without a stage; a graph one of whose tiles is larger (hundreds of
-// dependencies per node at 4096 nodes) does not take the event path.
-constexpr uint64_t kEvGroupMaxBytes = (uint64_t)960 << 20;
+// on most calls all. A graph one of whose tiles needs more than
+// kEvTileMaxBytes for a group (hundreds of dependencies per node at 4096
+// nodes; buffer offsets are 32 bits) does not take the event path.
+constexpr uint64_t kEvTileMaxBytes = (uint64_t)1 << 30;
 constexpr uint64_t kEvMaxBytes = (uint64_t)4 << 30;
 struct EvChunk {
   int32_t g0 = 0, gn = 0;     // groups
   int32_t tlo = 0, thi = 0;   // tiles
 };
 struct Layout;
-// The chunks of K candidates, in order.
-std::vector<EvChunk> event_chunks(const ckm_graph& g, const Layout& L, int32_t K);
+// The chunks of K candidates, in order (both false when there is none left).
+bool first_event_chunk(const ckm_graph& g, const Layout& L, int32_t K, EvChunk& c);
+bool next_event_chunk(const ckm_graph& g, const Layout& L, int32_t K, EvChunk& c);
 
 // Work-buffer layout for (n, K). Offsets are bytes from the buffer start,
 // each 256-byte aligned.
@@ -127,7 +125,7 @@ struct Layout {
          plan_rt_off = 0, plan_rpre_off = 0,
          bbest_off = 0,  // per-block best of the batch multipliers
          total = 0,        // bytes every call needs
-         rows_off = 0,     // S rows of every candidate (kSrcRows, or mask rows), past `total`
+         rows_off = 0,     // S rows of every candidate (kSrcRows, or S tiles), past `total`
          rrows_off = 0,    // R rows of every candidate, written by ckm_eval_kernel
          events_off = 0,   // the event path instead: a chunk's event records and far accumulators,
          ev_bytes = 0,     // this much room
@@ -181,10 +179,9 @@ hipError_t launch_quantize(const ckm_graph& g, const Layout& L, const double* d_
 // buffer's row array (nothing when L.rows_on is false).
 hipError_t launch_round_rows(const ckm_graph& g, const Layout& L, int32_t K, uint64_t seed, uint32_t flags,
                              char* work, hipStream_t stream);
-// The same for candidate groups g0 .. g0 + gn - 1 (64 candidates each);
-// clear: on the mask path, also reset those candidates' evaluate totals.
+// clear: on the event path, also reset the candidates' evaluate totals.
 hipError_t launch_round_rows(const ckm_graph& g, const Layout& L, int32_t K, uint64_t seed, uint32_t flags,
-                             int32_t g0, int32_t gn, bool clear, char* work, hipStream_t stream);
+                             bool clear, char* work, hipStream_t stream);
 // Threshold family: ranks of the K thresholds, their sorted copy, and the
 // keys of S* in place of the quantized thresholds q.
 hipError_t launch_threshold_keys(const ckm_graph& g, const Layout& L, const double* d_s, int64_t ld,
@@ -206,8 +203,8 @@ hipError_t launch_max_batch(const ckm_graph& g, const Layout& L, int32_t K, int6
 hipError_t launch_evaluate(const ckm_graph& g, const Layout& L, int32_t K, uint64_t seed,
                            uint32_t flags, const Plan& plan, int src, const uint64_t* s_user, char* work,
                            hipStream_t stream);
-// Event path (ckm_events.hip): the evaluate of all candidates on their mask
-// rows, and the best candidate's R rows.
+// Event path (ckm_events.hip): the evaluate of all candidates on their S
+// tiles, and the best candidate's R rows.
 hipError_t launch_events(const ckm_graph& g, const Layout& L, int32_t K, char* work, hipStream_t stream);
 hipError_t launch_best_events(const ckm_graph& g, const Layout& L, int32_t K, const int32_t* d_best_k,
                               uint64_t* d_best_R, char* work, hipStream_t stream);

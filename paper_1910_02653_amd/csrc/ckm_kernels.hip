@@ -1560,66 +1560,59 @@ __global__ void __launch_bounds__(kWave) ckm_best_closure_kernel(ClosureArgs a) 
 }
 
 // ---------------------------------------------------------------------------
-// Mask rows (the event path's S rows, see ckm_events.h). A group's 64
-// candidates share one 64-bit word per (stage row, node): bit j is candidate
-// 64g + j. Row t of a group holds 8 (t/8 + 1) words (nodes 0 .. t rounded up
-// to whole blocks of 8; words for nodes >= t are zero); row n, after the last
-// stage, is all zero. The producers below make them from the three sources.
-__device__ __forceinline__ uint64_t mask_of(bool b) { return __builtin_amdgcn_ballot_w64(b); }
-// 16 bytes at byte offset off + kOff of a buffer, in every lane
-template <int kOff>
-__device__ __forceinline__ uint4 load_mval(__amdgpu_buffer_rsrc_t rs, uint32_t off) {
-  const auto x = __builtin_amdgcn_raw_buffer_load_b128(rs, kOff, (int)off, 0);
-  return make_uint4(x[0], x[1], x[2], x[3]);
+// S tiles (the event path's S rows, see ckm_events.h): per group of 64
+// candidates and tile T of 32 stages, one 32-bit word per node and lane
+// (candidate), bit j being S of stage 32 T + j; quads of four nodes, 16 bytes
+// per lane (stile_off). The producers below make them from the three sources.
+// Block (group, item): 32 nodes of one tile, items numbering the pairs
+// (T, 32-node block nb <= T). Words take their bits from the highest stage
+// down, each shifted in from below; stages at or below a node, and past the
+// last, shift in zeros.
+__device__ __forceinline__ void tile_item(int item, int& T, int& nb) {
+  int t = (int)((sqrtf(8.0f * (float)item + 1.0f) - 1.0f) * 0.5f);
+  while (t * (t + 1) / 2 > item) --t;
+  while ((t + 1) * (t + 2) / 2 <= item) ++t;
+  T = __builtin_amdgcn_readfirstlane(t);
+  nb = __builtin_amdgcn_readfirstlane(item - t * (t + 1) / 2);
+}
+__device__ __forceinline__ void store_tile(char* stiles, size_t group_bytes, int group, int T, int nb, const uint32_t (&w)[32]) {
+  char* dst = stiles + (size_t)group * group_bytes + stile_off(T) + (size_t)nb * 8192 + 16u * threadIdx.x;
+#pragma unroll
+  for (int q = 0; q < 8; ++q)
+    *reinterpret_cast<uint4*>(dst + 1024 * q) = make_uint4(w[4 * q], w[4 * q + 1], w[4 * q + 2], w[4 * q + 3]);
 }
 
-}  // namespace
-// v_writelane_b32 through its compiler intrinsic, so that the compiler sees
-// the instruction and its hazards (this compiler has no builtin for it). The
-// declaration binds a name to the intrinsic, so it stays outside the unnamed
-// namespace: there it would name an internal function that is never defined.
-__device__ int amdgcn_writelane(int x, int lane, int v) __asm("llvm.amdgcn.writelane.i32");
-namespace {
-// Lane L of v takes the wave-uniform x.
-template <int L>
-__device__ __forceinline__ uint32_t write_lane(uint32_t v, uint32_t x) {
-  return (uint32_t)amdgcn_writelane((int)x, L, (int)v);
+// w_i = 2 w_i + [u_i < q_i] for eight nodes: u_i is 16-bit half (i mod 2) of
+// x[i / 2], q_i wave-uniform. Three lane masks rotate, as in append8_uniform.
+__device__ __forceinline__ void shift_in8(uint32_t (&w)[32], int o, const uint32_t x[4], const uint32_t* q) {
+  uint64_t m0, m1, m2;
+  asm("v_cmp_lt_u32_sdwa %[m0], %[x0], %[q0] src0_sel:WORD_0 src1_sel:DWORD\n\t"
+      "v_cmp_lt_u32_sdwa %[m1], %[x0], %[q1] src0_sel:WORD_1 src1_sel:DWORD\n\t"
+      "v_cmp_lt_u32_sdwa %[m2], %[x1], %[q2] src0_sel:WORD_0 src1_sel:DWORD\n\t"
+      "v_addc_co_u32 %[w0], vcc, %[w0], %[w0], %[m0]\n\t"
+      "v_cmp_lt_u32_sdwa %[m0], %[x1], %[q3] src0_sel:WORD_1 src1_sel:DWORD\n\t"
+      "v_addc_co_u32 %[w1], vcc, %[w1], %[w1], %[m1]\n\t"
+      "v_cmp_lt_u32_sdwa %[m1], %[x2], %[q4] src0_sel:WORD_0 src1_sel:DWORD\n\t"
+      "v_addc_co_u32 %[w2], vcc, %[w2], %[w2], %[m2]\n\t"
+      "v_cmp_lt_u32_sdwa %[m2], %[x2], %[q5] src0_sel:WORD_1 src1_sel:DWORD\n\t"
+      "v_addc_co_u32 %[w3], vcc, %[w3], %[w3], %[m0]\n\t"
+      "v_cmp_lt_u32_sdwa %[m0], %[x3], %[q6] src0_sel:WORD_0 src1_sel:DWORD\n\t"
+      "v_addc_co_u32 %[w4], vcc, %[w4], %[w4], %[m1]\n\t"
+      "v_cmp_lt_u32_sdwa %[m1], %[x3], %[q7] src0_sel:WORD_1 src1_sel:DWORD\n\t"
+      "v_addc_co_u32 %[w5], vcc, %[w5], %[w5], %[m2]\n\t"
+      "v_addc_co_u32 %[w6], vcc, %[w6], %[w6], %[m0]\n\t"
+      "v_addc_co_u32 %[w7], vcc, %[w7], %[w7], %[m1]"
+      : [w0] "+v"(w[o]), [w1] "+v"(w[o + 1]), [w2] "+v"(w[o + 2]), [w3] "+v"(w[o + 3]), [w4] "+v"(w[o + 4]),
+        [w5] "+v"(w[o + 5]), [w6] "+v"(w[o + 6]), [w7] "+v"(w[o + 7]), [m0] "=&s"(m0), [m1] "=&s"(m1), [m2] "=&s"(m2)
+      : [x0] "v"(x[0]), [x1] "v"(x[1]), [x2] "v"(x[2]), [x3] "v"(x[3]), [q0] "s"(q[0]), [q1] "s"(q[1]),
+        [q2] "s"(q[2]), [q3] "s"(q[3]), [q4] "s"(q[4]), [q5] "s"(q[5]), [q6] "s"(q[6]), [q7] "s"(q[7])
+      : "vcc");
 }
-// Lanes 2j and 2j+1 take the low and high halves of m[j], j >= J.
-template <int J>
-__device__ __forceinline__ uint32_t put_masks(uint32_t v, const uint64_t (&m)[8]) {
-  v = write_lane<2 * J>(v, (uint32_t)m[J]);
-  v = write_lane<2 * J + 1>(v, (uint32_t)(m[J] >> 32));
-  if constexpr (J + 1 < 8) v = put_masks<J + 1>(v, m);
-  return v;
-}
-
-// The 8 entries of block b of a row of thresholds (q or keys), read into
-// every lane by vector loads: they complete in order, so the next block's
-// can be requested while this one is in use (scalar loads complete out of
-// order, and waiting for one waits for all).
-struct Q8 {
-  uint4 lo, hi;
-  __device__ uint32_t operator[](int j) const {
-    const uint4& h = j < 4 ? lo : hi;
-    const int i = j & 3;
-    return i == 0 ? h.x : i == 1 ? h.y : i == 2 ? h.z : h.w;
-  }
-};
-__device__ __forceinline__ Q8 load_q8(__amdgpu_buffer_rsrc_t rs, uint32_t row_bytes, int b) {
-  // the offset is wave-uniform; stating it keeps it a scalar operand where
-  // the compiler cannot prove it (else it loops over the lanes' values)
-  const uint32_t off = __builtin_amdgcn_readfirstlane(row_bytes + 32u * (uint32_t)b);
-  Q8 x;
-  x.lo = load_mval<0>(rs, off);
-  x.hi = load_mval<16>(rs, off);
-  return x;
+__device__ __forceinline__ void shift8(uint32_t (&w)[32], int o) {
+#pragma unroll
+  for (int i = 0; i < 8; ++i) w[o + i] += w[o + i];
 }
 
-// Randomized rounding into mask row r of a group, lane = candidate. Word i
-// of the row is the group's 64 decisions [u_{k,r,i} < q[r][i]] (the same
-// draws as round_word); candidate 0 takes the deterministic bits under
-// CKM_F_DET0. A block of 8 nodes shares one Philox output per lane.
 // Philox4x32-10 of counter (b, r, k, 0), the counter of block b of row r for
 // candidate k, split by what each part depends on. Round 0 multiplies b
 // (wave-uniform) and k (per lane, the same for every block of the row);
@@ -1671,176 +1664,113 @@ __device__ __forceinline__ void philox_block(const PhiloxRow& pr, uint32_t b, ui
   x[0] = c0; x[1] = c1; x[2] = c2; x[3] = c3;
 }
 
-// Block b of row r (8 nodes) for the 64 candidates of a group, thresholds
-// qb: one Philox output per lane, 8 compares whose lane masks are the words,
-// one 64-byte store.
-__device__ __forceinline__ void round_mask_block(const PhiloxRow& pr, const Q8& qb, int b, int r, uint32_t k,
-                                                 uint32_t key0, uint32_t key1, bool det_here,
-                                                 cptr<uint32_t> drow, uint32_t* dst) {
-  uint64_t m[8];
-  if (8 * b >= r) {
-#pragma unroll
-    for (int j = 0; j < 8; ++j) m[j] = 0ull;
-  } else {
-    uint32_t x[4];
-    philox_block(pr, (uint32_t)b, key0, key1, x);
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-      const uint32_t u = (x[j >> 1] >> (16 * (j & 1))) & 0xFFFFu;
-      m[j] = mask_of(u < qb[j]);
-    }
-    if (det_here) {
-      const uint32_t dw = drow[b >> 2] >> (8 * (b & 3));
-#pragma unroll
-      for (int j = 0; j < 8; ++j) m[j] = (m[j] & ~1ull) | ((dw >> j) & 1u);
-    }
-  }
-  // lanes 16-63 of out are never stored, so out starts from any value
-  const uint32_t out = put_masks<0>(k, m);
-  if (threadIdx.x < 16) dst[16 * b + threadIdx.x] = out;   // words 8b .. 8b+7 of the row
-}
-
-__device__ __forceinline__ void round_mask_row(const uint32_t* __restrict__ q, const uint32_t* __restrict__ det,
-                                               int32_t n, int32_t ldq, int32_t det_words, uint32_t key0,
-                                               uint32_t key1, uint32_t det0, int group, int r, uint64_t* row) {
-  const int lane = threadIdx.x;
-  const uint32_t k = (uint32_t)(group * kWave + lane);
-  uint32_t* dst = reinterpret_cast<uint32_t*>(row);
-  const int nblk = (r >> 3) + 1;
-  const auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(q), 0, n * ldq * 4, kBufWord3);
-  const uint32_t row_bytes = (uint32_t)(r < n ? r : 0) * (uint32_t)ldq * 4u;
-  const cptr<uint32_t> drow = as_const(det + (size_t)(r < n ? r : 0) * det_words);
-  const PhiloxRow pr = philox_row((uint32_t)r, k, key0);
-  const bool det_here = det0 && group == 0;
-  // two threshold buffers by block parity, each block's requested one block
-  // ahead (vector loads complete in order)
-  Q8 qa = load_q8(rs, row_bytes, 0), qb;
-  for (int b = 0; b < nblk; b += 2) {
-    if (b + 1 < nblk) qb = load_q8(rs, row_bytes, b + 1);
-    round_mask_block(pr, qa, b, r, k, key0, key1, det_here, drow, dst);
-    if (b + 1 >= nblk) break;
-    if (b + 2 < nblk) qa = load_q8(rs, row_bytes, b + 2);
-    round_mask_block(pr, qb, b + 1, r, k, key0, key1, det_here, drow, dst);
-  }
-}
-
-// Block (group, y) makes row n - y of the group (rows 0 .. n; row n is
-// zero). Blocks start in order of y, so the longest rows start first and the
-// last to start are the shortest: the launch ends with little left on any
-// SIMD. (Equal pairs of rows y and n - y per block ended with most SIMDs
-// running one wave, the youngest, which the issue order serves last.)
-__global__ void __launch_bounds__(kWave) ckm_round_masks_kernel(const uint32_t* __restrict__ q,
+// Randomized rounding: bit [u_{k,t,i} < q[t][i]] (the draws of round_word);
+// candidate 0 takes the deterministic bits under CKM_F_DET0. Per stage and
+// lane one Philox output serves 8 nodes; the part of it that depends on the
+// stage and candidate alone is made once for the item's four blocks.
+__global__ void __launch_bounds__(kWave) ckm_round_tiles_kernel(const uint32_t* __restrict__ q,
                                                                 const uint32_t* __restrict__ det, int32_t n,
                                                                 int32_t ldq, int32_t det_words, uint32_t key0,
-                                                                uint32_t key1, uint32_t det0, size_t mgroup,
-                                                                uint64_t* __restrict__ mrows, int32_t g0,
-                                                                Totals tot) {
-  const int group = blockIdx.x + g0;
-  const int y = blockIdx.y;
+                                                                uint32_t key1, uint32_t det0, size_t group_bytes,
+                                                                char* __restrict__ stiles, Totals tot) {
+  const int group = blockIdx.x;
   clear_totals(tot, group);
-  uint64_t* rows = mrows + (size_t)group * mgroup;
-  round_mask_row(q, det, n, ldq, det_words, key0, key1, det0, group, n - y, rows + mrow_off(n - y));
-}
-
-// ---------------------------------------------------------------------------
-// Threshold candidates into mask rows (block (group, y): row n - y):
-// word i of row r is the group's 64 decisions [rank_k < key[r][i]], the
-// threshold test of threshold_word. Keys on and above the diagonal are 0, so
-// are their words (row n reads row 0, all of whose keys are 0).
-// Block b (8 nodes) of a threshold row: word i is the lane mask of
-// [rank_k < key_i] (keys at and above the diagonal are 0).
-__device__ __forceinline__ void threshold_mask_block(const Q8& kb, uint32_t rk, uint32_t k, int b, uint32_t* dst) {
-  uint64_t m[8];
+  int T, nb;
+  tile_item(blockIdx.y, T, nb);
+  const uint32_t k = (uint32_t)(group * kWave) + threadIdx.x;
+  const bool det_here = det0 && group == 0;
+  uint32_t w[32];
 #pragma unroll
-  for (int j = 0; j < 8; ++j) m[j] = mask_of(rk < kb[j]);
-  // lanes 16-63 of out are never stored, so out starts from any value
-  const uint32_t out = put_masks<0>(k, m);
-  if (threadIdx.x < 16) dst[16 * b + threadIdx.x] = out;
-}
-
-__global__ void __launch_bounds__(kWave) ckm_threshold_masks_kernel(const uint32_t* __restrict__ key, int32_t ldq,
-                                                                    const uint32_t* __restrict__ rank, int32_t K,
-                                                                    int32_t n, size_t mgroup,
-                                                                    uint64_t* __restrict__ mrows, int32_t g0,
-                                                                    Totals tot) {
-  const int lane = threadIdx.x;
-  const int group = blockIdx.x + g0;
-  clear_totals(tot, group);
-  const uint32_t k = (uint32_t)(group * kWave + lane);
-  const uint32_t rk = rank[k < (uint32_t)K ? k : (uint32_t)K - 1u];
-  uint64_t* rows = mrows + (size_t)group * mgroup;
-  const auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(key), 0, n * ldq * 4, kBufWord3);
-  // row n - y (longest first, as in ckm_round_masks_kernel); the row is
-  // wave-uniform, and stating it keeps the block loop scalar
-  const int r = __builtin_amdgcn_readfirstlane(n - (int)blockIdx.y);
-  uint32_t* dst = reinterpret_cast<uint32_t*>(rows + mrow_off(r));
-  const int lim = r < n ? r : 0;   // row n (after the last stage) is empty
-  const uint32_t rb = (uint32_t)lim * (uint32_t)ldq * 4u;
-  const int nblk = (r >> 3) + 1;
-  // two key buffers by block parity, each block's requested one block ahead
-  Q8 ka = load_q8(rs, rb, 0), kb;
-  for (int b = 0; b < nblk; b += 2) {
-    if (b + 1 < nblk) kb = load_q8(rs, rb, b + 1);
-    threshold_mask_block(ka, rk, k, b, dst);
-    if (b + 1 >= nblk) break;
-    if (b + 2 < nblk) ka = load_q8(rs, rb, b + 2);
-    threshold_mask_block(kb, rk, k, b + 1, dst);
-  }
-}
-
-// Caller-supplied checkpoint matrices into mask rows (block (group, y): row
-// n - y): word i of row r is bit i of row r of each of the group's 64
-// matrices ([K][n][s_words] 32-bit words), for i < r only (bits on and above
-// the diagonal are not part of S). Lanes past K repeat candidate K-1. Each
-// lane reads its matrix row 16 bytes (128 nodes) at a time, the next chunk
-// requested before the current one is turned into masks.
-__device__ __forceinline__ uint4 user_chunk(const uint32_t* row, int c, int lim) {
-  // chunk c: words 4c .. 4c+3; only words with a node below lim are read
-  uint4 x = make_uint4(0u, 0u, 0u, 0u);
-  if (128 * c < lim) x.x = row[4 * c];
-  if (128 * c + 32 < lim) x.y = row[4 * c + 1];
-  if (128 * c + 64 < lim) x.z = row[4 * c + 2];
-  if (128 * c + 96 < lim) x.w = row[4 * c + 3];
-  return x;
-}
-
-__global__ void __launch_bounds__(kWave) ckm_user_masks_kernel(const uint32_t* __restrict__ s_user, int32_t n,
-                                                               int32_t K, int32_t s_words, size_t mgroup,
-                                                               uint64_t* __restrict__ mrows, int32_t g0,
-                                                               Totals tot) {
-  const int lane = threadIdx.x;
-  const int group = blockIdx.x + g0;
-  clear_totals(tot, group);
-  const uint32_t k = (uint32_t)(group * kWave + lane);
-  const uint32_t kk = k < (uint32_t)K ? k : (uint32_t)K - 1u;
-  uint64_t* rows = mrows + (size_t)group * mgroup;
-  // row n - y (longest first, as in ckm_round_masks_kernel); the row is
-  // wave-uniform, and stating it keeps the block loop scalar
-  const int r = __builtin_amdgcn_readfirstlane(n - (int)blockIdx.y);
-  uint32_t* dst = reinterpret_cast<uint32_t*>(rows + mrow_off(r));
-  const int lim = r < n ? r : 0;   // row n (after the last stage) is empty
-  const uint32_t* src = s_user + ((size_t)kk * n + lim) * s_words;
-  const int nblk = (r >> 3) + 1;
-  uint4 cur = user_chunk(src, 0, lim);
-  for (int c = 0; 16 * c < nblk; ++c) {
-    const uint4 nxt = user_chunk(src, c + 1, lim);
-    const uint32_t w4[4] = {cur.x, cur.y, cur.z, cur.w};
+  for (int i = 0; i < 32; ++i) w[i] = 0u;
+  for (int t = 32 * T + 31; t >= 32 * T; --t) {
+    if (t >= n) continue;   // the words are still empty
+    const uint32_t* qrow = (const uint32_t*)q + (size_t)t * ldq + 32 * nb;
+    uint32_t qv[32];
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
-      const int b = 16 * c + q;
-      if (b >= nblk) break;
-      // the block's bits of nodes below lim only
-      const int below = lim - 8 * b;
-      const uint32_t keep = below >= 8 ? 0xFFu : below <= 0 ? 0u : (1u << below) - 1u;
-      const uint32_t byte = (w4[q >> 2] >> (8 * (q & 3))) & keep;
-      uint64_t m[8];
+    for (int i = 0; i < 32; ++i) qv[i] = as_const(qrow)[i];
+    const PhiloxRow pr = philox_row((uint32_t)t, k, key0);
 #pragma unroll
-      for (int j = 0; j < 8; ++j) m[j] = mask_of(((byte >> j) & 1u) != 0u);
-      const uint32_t out = put_masks<0>(k, m);   // lanes 16-63 are not stored
-      if (lane < 16) dst[16 * b + lane] = out;
+    for (int b = 0; b < 4; ++b) {
+      if (32 * nb + 8 * b >= t) {
+        shift8(w, 8 * b);
+      } else {
+        uint32_t x[4];
+        philox_block(pr, (uint32_t)(4 * nb + b), key0, key1, x);
+        shift_in8(w, 8 * b, x, qv + 8 * b);
+      }
     }
-    cur = nxt;
+    if (det_here) {
+      const uint32_t dw = as_const(det)[(size_t)t * det_words + nb];
+      if (threadIdx.x == 0) {
+#pragma unroll
+        for (int i = 0; i < 32; ++i) w[i] = (w[i] & ~1u) | ((dw >> i) & 1u);
+      }
+    }
   }
+  store_tile(stiles, group_bytes, group, T, nb, w);
+}
+
+// Threshold candidates: bit [rank_k < key[t][i]], the threshold test of
+// threshold_word (keys on and above the diagonal are 0).
+__global__ void __launch_bounds__(kWave) ckm_threshold_tiles_kernel(const uint32_t* __restrict__ key, int32_t ldq,
+                                                                    const uint32_t* __restrict__ rank, int32_t K,
+                                                                    int32_t n, size_t group_bytes,
+                                                                    char* __restrict__ stiles, Totals tot) {
+  const int group = blockIdx.x;
+  clear_totals(tot, group);
+  int T, nb;
+  tile_item(blockIdx.y, T, nb);
+  const uint32_t k = (uint32_t)(group * kWave) + threadIdx.x;
+  const uint32_t rk = rank[k < (uint32_t)K ? k : (uint32_t)K - 1u];
+  uint32_t w[32];
+#pragma unroll
+  for (int i = 0; i < 32; ++i) w[i] = 0u;
+  for (int t = 32 * T + 31; t >= 32 * T; --t) {
+    if (t >= n) continue;
+    const cptr<uint32_t> krow = as_const(key) + (size_t)t * ldq + 32 * nb;
+#pragma unroll
+    for (int i = 0; i < 32; ++i) w[i] = w[i] + w[i] + (rk < krow[i] ? 1u : 0u);
+  }
+  store_tile(stiles, group_bytes, group, T, nb, w);
+}
+
+// Caller-supplied checkpoint matrices ([K][n][s_words] 32-bit words): bit i of
+// row t, for i < t only (bits on and above the diagonal are not part of S).
+// Lanes past K repeat candidate K-1. A lane reads its matrix's word nb of the
+// 32 rows and transposes the 32 x 32 bits in its registers, by halves.
+template <int kShift>
+__device__ __forceinline__ void transpose_step(uint32_t (&a)[32], uint32_t m) {
+#pragma unroll
+  for (int i = 0; i < 32; ++i) {
+    if (i & kShift) continue;
+    const uint32_t lo = a[i], hi = a[i + kShift];
+    a[i] = (lo & m) | ((hi & m) << kShift);
+    a[i + kShift] = ((lo >> kShift) & m) | (hi & ~m);
+  }
+}
+__global__ void __launch_bounds__(kWave) ckm_user_tiles_kernel(const uint32_t* __restrict__ s_user, int32_t n,
+                                                               int32_t K, int32_t s_words, size_t group_bytes,
+                                                               char* __restrict__ stiles, Totals tot) {
+  const int group = blockIdx.x;
+  clear_totals(tot, group);
+  int T, nb;
+  tile_item(blockIdx.y, T, nb);
+  const uint32_t k = (uint32_t)(group * kWave) + threadIdx.x;
+  const uint32_t kk = k < (uint32_t)K ? k : (uint32_t)K - 1u;
+  const uint32_t* src = s_user + (size_t)kk * n * s_words + nb;
+  uint32_t w[32];
+#pragma unroll
+  for (int j = 0; j < 32; ++j) {
+    const int t = 32 * T + j, below = t - 32 * nb;   // nodes of the word below the diagonal
+    const uint32_t keep = t >= n || below <= 0 ? 0u : below >= 32 ? ~0u : (1u << below) - 1u;
+    w[j] = src[(size_t)(t < n ? t : n - 1) * s_words] & keep;
+  }
+  transpose_step<16>(w, 0x0000FFFFu);
+  transpose_step<8>(w, 0x00FF00FFu);
+  transpose_step<4>(w, 0x0F0F0F0Fu);
+  transpose_step<2>(w, 0x33333333u);
+  transpose_step<1>(w, 0x55555555u);
+  store_tile(stiles, group_bytes, group, T, nb, w);
 }
 
 template <typename T>
@@ -1915,23 +1845,28 @@ int32_t eval_waves_per_cu(int32_t n, bool wide) {
 
 static unsigned groups_of(int32_t K) { return (unsigned)((K + kWave - 1) / kWave); }
 
+// Work items of the tile producers: (tile, 32-node block) pairs.
+static unsigned tile_items(int32_t n) {
+  const unsigned tiles = (unsigned)(n + 31) / 32;
+  return tiles * (tiles + 1) / 2;
+}
+
 static bool use_events(const ckm_graph& g, const Layout& L) { return L.rows_on && g.ev.on; }
 
 hipError_t launch_round_rows(const ckm_graph& g, const Layout& L, int32_t K, uint64_t seed, uint32_t flags,
                              char* work, hipStream_t stream) {
-  return launch_round_rows(g, L, K, seed, flags, 0, (int32_t)groups_of(K), false, work, stream);
+  return launch_round_rows(g, L, K, seed, flags, false, work, stream);
 }
 
 hipError_t launch_round_rows(const ckm_graph& g, const Layout& L, int32_t K, uint64_t seed, uint32_t flags,
-                             int32_t g0, int32_t gn, bool clear, char* work, hipStream_t stream) {
-  if (!L.rows_on || gn <= 0) return hipSuccess;
+                             bool clear, char* work, hipStream_t stream) {
+  if (!L.rows_on) return hipSuccess;
   if (use_events(g, L)) {
     const Totals tot{clear ? at<int64_t>(work, L.part_peak_off) : nullptr, at<int64_t>(work, L.part_cost_off), K};
-    hipLaunchKernelGGL(ckm_round_masks_kernel, dim3(gn, g.n + 1), dim3(kWave), 0, stream,
+    hipLaunchKernelGGL(ckm_round_tiles_kernel, dim3(groups_of(K), tile_items(g.n)), dim3(kWave), 0, stream,
                        at<const uint32_t>(work, L.q_off), at<const uint32_t>(work, L.det_off), g.n, L.ldq,
                        L.det_words, (uint32_t)(seed & 0xFFFFFFFFu), (uint32_t)(seed >> 32),
-                       (flags & CKM_F_DET0) ? 1u : 0u, mask_rows_words(g.n), at<uint64_t>(work, L.rows_off), g0,
-                       tot);
+                       (flags & CKM_F_DET0) ? 1u : 0u, stiles_bytes(g.n), work + L.rows_off, tot);
     return hipGetLastError();
   }
   const int32_t kpad = ((K + kWave - 1) / kWave) * kWave;
@@ -1942,24 +1877,23 @@ hipError_t launch_round_rows(const ckm_graph& g, const Layout& L, int32_t K, uin
   return hipGetLastError();
 }
 
-// The mask rows of groups g0 .. g0 + gn - 1 from source src (kSrcRound,
-// kSrcThreshold or kSrcUser); their candidates' totals are cleared on the
-// way (the evaluate that follows accumulates into them).
-static hipError_t launch_mask_producer(const ckm_graph& g, const Layout& L, int32_t K, uint64_t seed,
-                                       uint32_t flags, int src, const uint64_t* s_user, int32_t g0, int32_t gn,
-                                       char* work, hipStream_t stream) {
-  if (gn <= 0) return hipSuccess;
+// The S tiles from source src (kSrcRound, kSrcThreshold or kSrcUser); the
+// candidates' totals are cleared on the way (the evaluate that follows
+// accumulates into them).
+static hipError_t launch_tile_producer(const ckm_graph& g, const Layout& L, int32_t K, uint64_t seed, uint32_t flags,
+                                       int src, const uint64_t* s_user, char* work, hipStream_t stream) {
   const Totals tot{at<int64_t>(work, L.part_peak_off), at<int64_t>(work, L.part_cost_off), K};
+  const dim3 grid(groups_of(K), tile_items(g.n));
   if (src == kSrcThreshold) {
-    hipLaunchKernelGGL(ckm_threshold_masks_kernel, dim3(gn, g.n + 1), dim3(kWave), 0, stream,
-                       at<const uint32_t>(work, L.q_off), L.ldq, at<const uint32_t>(work, L.thr_rank_off), K, g.n,
-                       mask_rows_words(g.n), at<uint64_t>(work, L.rows_off), g0, tot);
+    hipLaunchKernelGGL(ckm_threshold_tiles_kernel, grid, dim3(kWave), 0, stream, at<const uint32_t>(work, L.q_off),
+                       L.ldq, at<const uint32_t>(work, L.thr_rank_off), K, g.n, stiles_bytes(g.n), work + L.rows_off,
+                       tot);
   } else if (src == kSrcUser) {
-    hipLaunchKernelGGL(ckm_user_masks_kernel, dim3(gn, g.n + 1), dim3(kWave), 0, stream,
-                       reinterpret_cast<const uint32_t*>(s_user), g.n, K, L.row_words, mask_rows_words(g.n),
-                       at<uint64_t>(work, L.rows_off), g0, tot);
+    hipLaunchKernelGGL(ckm_user_tiles_kernel, grid, dim3(kWave), 0, stream,
+                       reinterpret_cast<const uint32_t*>(s_user), g.n, K, L.row_words, stiles_bytes(g.n),
+                       work + L.rows_off, tot);
   } else {
-    return launch_round_rows(g, L, K, seed, flags, g0, gn, true, work, stream);
+    return launch_round_rows(g, L, K, seed, flags, true, work, stream);
   }
   return hipGetLastError();
 }
@@ -1968,12 +1902,11 @@ hipError_t launch_evaluate(const ckm_graph& g, const Layout& L, int32_t K, uint6
                            uint32_t flags, const Plan& plan, int src, const uint64_t* s_user, char* work,
                            hipStream_t stream) {
   if (use_events(g, L)) {
-    // mask rows made by a producer (none when the caller rounded them
+    // S tiles made by a producer (none when the caller rounded them
     // beforehand), then the event path
-    const int32_t G = (int32_t)groups_of(K);
     hipError_t e = hipSuccess;
     if (!(src == kSrcRound && (flags & CKM_F_ROUNDED))) {
-      e = launch_mask_producer(g, L, K, seed, flags, src, s_user, 0, G, work, stream);
+      e = launch_tile_producer(g, L, K, seed, flags, src, s_user, work, stream);
     } else {
       // no producer to clear the totals on the way
       hipLaunchKernelGGL(ckm_eval_init_kernel, dim3((K + 255) / 256), dim3(256), 0, stream, K,

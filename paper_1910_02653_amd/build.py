@@ -9,8 +9,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 LIB_PATH = os.path.join(HERE, "libckm.so")
 SOURCES = [os.path.join(HERE, "csrc", "ckm_kernels.hip"), os.path.join(HERE, "csrc", "ckm_plan.hip"),
-           os.path.join(HERE, "csrc", "ckm_noalloc.hip"), os.path.join(HERE, "csrc", "ckm_events.hip"),
-           os.path.join(HERE, "csrc", "ckm_events.cpp"),
+           os.path.join(HERE, "csrc", "ckm_noalloc.hip"), os.path.join(HERE, "csrc", "ckm_tiles.hip"),
+           os.path.join(HERE, "csrc", "ckm_tiles.cpp"),
            os.path.join(HERE, "csrc", "ckm_host.cpp")]
 ARCH = "gfx950"
 

@@ -13,8 +13,8 @@
 #include <utility>
 #include <vector>
 
-#include "ckm_events.h"
 #include "ckm_internal.h"
+#include "ckm_tiles.h"
 
 namespace {
 
@@ -264,11 +264,6 @@ Plan plan_auto(int32_t n, int32_t K, int32_t max_items, int32_t waves_per_cu) {
   return p;
 }
 
-// What tiles lo .. hi - 1 of one group take of a chunk's room.
-static size_t ev_room(const ckm_graph& g, int32_t lo, int32_t hi) {
-  return (g.ev.tile_off[hi] - g.ev.tile_off[lo]) + (size_t)(hi - lo) * g.ev.nf * kEvSlotBytes;
-}
-
 Layout make_layout(const ckm_graph& g, int32_t K) {
   const int32_t n = g.n;
   Layout L;
@@ -307,65 +302,20 @@ Layout make_layout(const ckm_graph& g, int32_t K) {
   // makes its S rows itself and select recomputes the best R).
   const size_t kpad = (size_t)((K + kWave - 1) / kWave) * kWave;
   L.rows_off = off;
-  if (g.ev.on) {
-    // S tiles of every group, then room for the event records and far
-    // accumulators: of everything, or of kEvMaxBytes; one tile at least (the
-    // last is the largest)
-    const size_t groups = kpad / kWave;
-    const size_t s_bytes = groups * ckm::stiles_bytes(n);
-    const size_t all = groups * ev_room(g, 0, g.ev.tiles), tile = ev_room(g, g.ev.tiles - 1, g.ev.tiles);
-    L.rows_on = s_bytes <= ckm::kRowsMaxBytes;
-    L.events_off = align256(off + s_bytes);
-    L.ev_bytes = std::max(tile, std::min(all, (size_t)ckm::kEvMaxBytes));
-    L.min_rows = L.rows_on ? L.events_off + tile : off;
-    L.total_rows = L.rows_on ? L.events_off + L.ev_bytes : off;
-    return L;
-  }
-  // S rows, then R rows, of every candidate, word w of row t at
-  // (base(t) + w) * kpad + k
-  const size_t full = (size_t)(n >> 5), rem = (size_t)(n & 31);
-  const size_t rows_bytes = kpad * (32 * full * (full + 1) / 2 + rem * (full + 1)) * sizeof(uint32_t);
-  L.rows_on = rows_bytes <= ckm::kRowsMaxBytes;
-  L.rrows_off = align256(off + rows_bytes);
-  L.min_rows = L.total_rows = L.rows_on ? align256(L.rrows_off + rows_bytes) : off;
-  return L;
-}
-
-void fit_layout(const ckm_graph& g, Layout& L, size_t work_bytes) {
-  L.rows_on = L.rows_on && work_bytes >= L.min_rows;
-  if (L.rows_on && g.ev.on) L.ev_bytes = std::min(L.ev_bytes, work_bytes - L.events_off);
-}
-
-// Whole groups where one fits, else one group's tiles from the top.
-static void fit_chunk(const ckm_graph& g, const Layout& L, int32_t K, EvChunk& c) {
-  const int32_t groups = (K + kWave - 1) / kWave;
-  const size_t all = ev_room(g, 0, g.ev.tiles);
-  if (all <= L.ev_bytes) {
-    c.gn = (int32_t)std::min<size_t>(groups - c.g0, L.ev_bytes / all);
-    c.tlo = 0;
-    return;
-  }
-  c.gn = 1;
-  c.tlo = c.thi - 1;
-  while (c.tlo > 0 && ev_room(g, c.tlo - 1, c.thi) <= L.ev_bytes) --c.tlo;
-}
-
-bool first_event_chunk(const ckm_graph& g, const Layout& L, int32_t K, EvChunk& c) {
-  c = {0, 0, 0, g.ev.tiles};
-  fit_chunk(g, L, K, c);
-  return true;
-}
-
-bool next_event_chunk(const ckm_graph& g, const Layout& L, int32_t K, EvChunk& c) {
-  if (c.tlo > 0) {
-    c.thi = c.tlo;
+  size_t s_bytes, r_bytes;
+  if (g.tile.on) {
+    const int32_t tiles = (n + ckm::kTile - 1) / ckm::kTile;
+    s_bytes = kpad / kWave * stile_off(tiles);
+    r_bytes = kpad / kWave * rtile_off(g.tile.rbase, tiles);
   } else {
-    c.g0 += c.gn;
-    c.thi = g.ev.tiles;
-    if (c.g0 >= (K + kWave - 1) / kWave) return false;
+    // word w of row t at (base(t) + w) * kpad + k
+    const size_t full = (size_t)(n >> 5), rem = (size_t)(n & 31);
+    s_bytes = r_bytes = kpad * (32 * full * (full + 1) / 2 + rem * (full + 1)) * sizeof(uint32_t);
   }
-  fit_chunk(g, L, K, c);
-  return true;
+  L.rows_on = s_bytes <= ckm::kRowsMaxBytes;
+  L.rrows_off = align256(off + s_bytes);
+  L.total_rows = L.rows_on ? align256(L.rrows_off + r_bytes) : off;
+  return L;
 }
 
 }  // namespace ckm
@@ -497,33 +447,37 @@ static ckm_status graph_create(int32_t n, const int32_t* dep_ptr, const int32_t*
   const size_t off_uo = align256(off_di + Ea * sizeof(int32_t));
   const size_t off_rec = align256(off_uo + Ea * sizeof(int32_t));
   const size_t off_mrec = align256(off_rec + (size_t)n * ckm::kNodeRecBytes);
-  // the event path's tables, when the graph takes it
-  ckm::EventTables ev;
-  const bool events = !wide && ckm::build_events(n, bytes, cost, dp.data(), di.data(), up.data(), ui.data(),
-                                                 ckm::kEvTileMaxBytes, ev);
-  if (!events) ev = ckm::EventTables();
-  size_t ev_end = off_mrec;
+  // the tile path's tables (its sums are binary64)
+  ckm::TileTables tt;
+  if (!wide) ckm::build_tiles(n, bytes, cost, dp.data(), di.data(), up.data(), ui.data(), tt);
+  size_t tile_end = off_mrec;
   const auto place = [&](size_t b) {
-    const size_t at = ev_end;
-    ev_end = align256(ev_end + b);
+    const size_t at = tile_end;
+    tile_end = align256(tile_end + b);
     return at;
   };
-  std::vector<uint64_t> tile_off(1, 0);
-  for (const int32_t r : ev.tile_rec) tile_off.push_back(tile_off.back() + (uint64_t)r * ckm::kEvRecBytes);
-  const size_t off_desc = place(ev.desc.size() * 4), off_extra = place(ev.extra.size() * 4),
-               off_ops = place(ev.ops.size() * sizeof(ckm::EvOps)), off_tile = place(tile_off.size() * 8),
-               off_main = place(ev.main_rec.size() * 4), off_pins = place(ev.pins.size() * 4);
-  const size_t total = ev_end;
+  const size_t off_desc = place(tt.desc.size() * 4), off_nmore = place(tt.near_more.size() * 4),
+               off_far = place(tt.far.size() * 4), off_fmore = place(tt.far_more.size() * 4), off_ops = place(tt.ops.size() * sizeof(ckm::SimOps)),
+               off_refs = place(tt.refs.size() * sizeof(ckm::SimRefs)),
+               off_more = place(tt.more.size() * sizeof(ckm::SimMore)), off_moff = place(tt.more_off.size() * 4),
+               off_trec = place(tt.tile_rec.size() * 4), off_hptr = place(tt.hub_ptr.size() * 4),
+               off_hub = place(tt.hub.size() * sizeof(ckm::HubUser));
+  const size_t total = tile_end;
   std::vector<char> host(total, 0);
   const auto copy = [&](size_t off, const auto& v) {
     if (!v.empty()) memcpy(host.data() + off, v.data(), v.size() * sizeof(v[0]));
   };
-  copy(off_desc, ev.desc);
-  copy(off_extra, ev.extra);
-  copy(off_ops, ev.ops);
-  copy(off_tile, tile_off);
-  copy(off_main, ev.main_rec);
-  copy(off_pins, ev.pins);
+  copy(off_desc, tt.desc);
+  copy(off_nmore, tt.near_more);
+  copy(off_far, tt.far);
+  copy(off_fmore, tt.far_more);
+  copy(off_ops, tt.ops);
+  copy(off_refs, tt.refs);
+  copy(off_more, tt.more);
+  copy(off_moff, tt.more_off);
+  copy(off_trec, tt.tile_rec);
+  copy(off_hptr, tt.hub_ptr);
+  copy(off_hub, tt.hub);
   memcpy(host.data() + off_M, bytes, n * sizeof(int64_t));
   memcpy(host.data() + off_C, cost, n * sizeof(int64_t));
   memcpy(host.data() + off_up, up.data(), (n + 1) * sizeof(int32_t));
@@ -573,18 +527,21 @@ static ckm_status graph_create(int32_t n, const int32_t* dep_ptr, const int32_t*
   g->d_dep_idx = reinterpret_cast<const int32_t*>(base + off_di);
   g->d_dep_upos = reinterpret_cast<const int32_t*>(base + off_uo);
   g->d_recs = base + off_rec;
-  if (events) {
-    g->ev.on = true;
-    g->ev.tiles = ev.tiles;
-    g->ev.nf = ev.nf;
-    g->ev.npins = (int32_t)ev.pins.size();
-    g->ev.tile_off = std::move(tile_off);
-    g->ev.d_desc = reinterpret_cast<const uint32_t*>(base + off_desc);
-    g->ev.d_extra = reinterpret_cast<const uint32_t*>(base + off_extra);
-    g->ev.d_ops = base + off_ops;
-    g->ev.d_tile_off = reinterpret_cast<const uint64_t*>(base + off_tile);
-    g->ev.d_main_rec = reinterpret_cast<const int32_t*>(base + off_main);
-    g->ev.d_pins = reinterpret_cast<const int32_t*>(base + off_pins);
+  if (!wide) {
+    g->tile.on = true;
+    g->tile.rbase = tt.rbase;
+    g->tile.nhub = tt.nhub;
+    g->tile.d_desc = reinterpret_cast<const uint32_t*>(base + off_desc);
+    g->tile.d_near_more = reinterpret_cast<const uint32_t*>(base + off_nmore);
+    g->tile.d_far = reinterpret_cast<const uint32_t*>(base + off_far);
+    g->tile.d_far_more = reinterpret_cast<const uint32_t*>(base + off_fmore);
+    g->tile.d_ops = base + off_ops;
+    g->tile.d_refs = base + off_refs;
+    g->tile.d_more = base + off_more;
+    g->tile.d_more_off = reinterpret_cast<const uint32_t*>(base + off_moff);
+    g->tile.d_tile_rec = reinterpret_cast<const int32_t*>(base + off_trec);
+    g->tile.d_hub_ptr = reinterpret_cast<const int32_t*>(base + off_hptr);
+    g->tile.d_hub = base + off_hub;
   }
   g->sync = new (std::nothrow) ckm::SyncCache;
   if (!g->sync) {
@@ -632,7 +589,7 @@ static ckm_status check_work(const ckm_graph* g, int32_t K, void* d_work, size_t
   *L = ckm::make_layout(*g, K);
   if (work_bytes < L->total)
     return fail(CKM_E_INVALID_ARG, "work buffer of %zu bytes, %zu needed", work_bytes, L->total);
-  ckm::fit_layout(*g, *L, work_bytes);
+  L->rows_on = L->rows_on && work_bytes >= L->total_rows;
   return CKM_OK;
 }
 

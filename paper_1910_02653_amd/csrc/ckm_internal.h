@@ -13,18 +13,23 @@
 namespace ckm {
 struct SyncCache;  // buffers and stream of the synchronous entry points (ckm_host.cpp)
 
-// The event path's tables on the device (EventTables, ckm_events.h); on is
-// false for the graphs that do not take it (wide or very dense).
-struct EventGraph {
+// The tile path's tables on the device (TileTables, ckm_tiles.h); on is false
+// for the graphs that do not take it (wide ones).
+struct TileGraph {
   bool on = false;
-  int32_t tiles = 0, nf = 0, npins = 0;
-  std::vector<uint64_t> tile_off;   // byte offset of each tile's event records in a group, tiles + 1 entries
+  uint32_t rbase = 0;
+  int32_t nhub = 0;
   const uint32_t* d_desc = nullptr;
-  const uint32_t* d_extra = nullptr;
+  const uint32_t* d_near_more = nullptr;
+  const uint32_t* d_far = nullptr;
+  const uint32_t* d_far_more = nullptr;
   const void* d_ops = nullptr;
-  const uint64_t* d_tile_off = nullptr;
-  const int32_t* d_main_rec = nullptr;
-  const int32_t* d_pins = nullptr;
+  const void* d_refs = nullptr;
+  const void* d_more = nullptr;
+  const uint32_t* d_more_off = nullptr;
+  const int32_t* d_tile_rec = nullptr;
+  const int32_t* d_hub_ptr = nullptr;
+  const void* d_hub = nullptr;
 };
 }
 
@@ -50,7 +55,7 @@ struct ckm_graph {
   const int32_t* d_dep_idx = nullptr;
   const int32_t* d_dep_upos = nullptr;
   const void* d_recs = nullptr;  // n node records of ckm::kNodeRecBytes (see ckm_kernels.hip)
-  ckm::EventGraph ev;            // the event path's tables
+  ckm::TileGraph tile;           // the tile path's tables
   ckm::SyncCache* sync = nullptr;  // reused by the synchronous calls; freed with the graph
 };
 
@@ -82,28 +87,11 @@ void build_node_records(int32_t n, const int64_t* M, const int64_t* C, bool wide
                         const int32_t* dep_idx, const int32_t* user_ptr, const int32_t* user_idx,
                         void* out);
 
-// S tiles (the event path's S rows, see ckm_kernels.hip): for one candidate
-// group, tile T of 32 stages holds 8 (T + 1) quads of 1024 bytes (nodes 4q ..
-// 4q + 3, 16 bytes per lane), one tile after another.
+// The tile path's S and R words (ckm_tiles.h): for one candidate group, tile T
+// of 32 stages holds a word per lane of 32 (T + 1) nodes, one tile after another. An R tile has rbase bytes before them.
 __host__ __device__ __forceinline__ uint32_t stile_bytes(int T) { return 8192u * (uint32_t)(T + 1); }
 __host__ __device__ __forceinline__ size_t stile_off(int T) { return (size_t)4096 * T * (T + 1); }
-inline size_t stiles_bytes(int32_t n) { return stile_off((n + 31) / 32); }
-
-// Event records are made and consumed a chunk at a time: the candidate groups
-// and stage tiles whose records (and far accumulators) fit the room for them,
-// on most calls all. A graph one of whose tiles needs more than
-// kEvTileMaxBytes for a group (hundreds of dependencies per node at 4096
-// nodes; buffer offsets are 32 bits) does not take the event path.
-constexpr uint64_t kEvTileMaxBytes = (uint64_t)1 << 30;
-constexpr uint64_t kEvMaxBytes = (uint64_t)4 << 30;
-struct EvChunk {
-  int32_t g0 = 0, gn = 0;     // groups
-  int32_t tlo = 0, thi = 0;   // tiles
-};
-struct Layout;
-// The chunks of K candidates, in order (both false when there is none left).
-bool first_event_chunk(const ckm_graph& g, const Layout& L, int32_t K, EvChunk& c);
-bool next_event_chunk(const ckm_graph& g, const Layout& L, int32_t K, EvChunk& c);
+__host__ __device__ __forceinline__ size_t rtile_off(uint32_t rbase, int T) { return stile_off(T) + (size_t)rbase * T; }
 
 // Work-buffer layout for (n, K). Offsets are bytes from the buffer start,
 // each 256-byte aligned.
@@ -126,18 +114,13 @@ struct Layout {
          bbest_off = 0,  // per-block best of the batch multipliers
          total = 0,        // bytes every call needs
          rows_off = 0,     // S rows of every candidate (kSrcRows, or S tiles), past `total`
-         rrows_off = 0,    // R rows of every candidate, written by ckm_eval_kernel
-         events_off = 0,   // the event path instead: a chunk's event records and far accumulators,
-         ev_bytes = 0,     // this much room
-         min_rows = 0,     // smallest buffer with the row arrays
-         total_rows = 0;   // total plus the row arrays when they are used
+         rrows_off = 0,    // R rows (or R tiles) of every candidate, written by the evaluate stage
+         total_rows = 0;   // total plus the two row arrays when they are used
   bool rows_on = false;    // the S rows fit kRowsMaxBytes (and, after
-                           // check_work, the caller's buffer holds the arrays)
+                           // check_work, the caller's buffer holds both)
 };
 
 Layout make_layout(const ckm_graph& g, int32_t K);
-// The same with the row arrays in a buffer of work_bytes (off when it is too small).
-void fit_layout(const ckm_graph& g, Layout& L, size_t work_bytes);
 
 // Records a thread-local error message (ckm_last_error) and returns st.
 ckm_status set_error(ckm_status st, const char* fmt, ...);
@@ -179,7 +162,7 @@ hipError_t launch_quantize(const ckm_graph& g, const Layout& L, const double* d_
 // buffer's row array (nothing when L.rows_on is false).
 hipError_t launch_round_rows(const ckm_graph& g, const Layout& L, int32_t K, uint64_t seed, uint32_t flags,
                              char* work, hipStream_t stream);
-// clear: on the event path, also reset the candidates' evaluate totals.
+// clear: on the tile path, also reset the candidates' evaluate totals.
 hipError_t launch_round_rows(const ckm_graph& g, const Layout& L, int32_t K, uint64_t seed, uint32_t flags,
                              bool clear, char* work, hipStream_t stream);
 // Threshold family: ranks of the K thresholds, their sorted copy, and the
@@ -203,11 +186,11 @@ hipError_t launch_max_batch(const ckm_graph& g, const Layout& L, int32_t K, int6
 hipError_t launch_evaluate(const ckm_graph& g, const Layout& L, int32_t K, uint64_t seed,
                            uint32_t flags, const Plan& plan, int src, const uint64_t* s_user, char* work,
                            hipStream_t stream);
-// Event path (ckm_events.hip): the evaluate of all candidates on their S
-// tiles, and the best candidate's R rows.
-hipError_t launch_events(const ckm_graph& g, const Layout& L, int32_t K, char* work, hipStream_t stream);
-hipError_t launch_best_events(const ckm_graph& g, const Layout& L, int32_t K, const int32_t* d_best_k,
-                              uint64_t* d_best_R, char* work, hipStream_t stream);
+// Tile path (ckm_tiles.hip): the evaluate of all candidates on their S tiles,
+// and the best candidate's R rows.
+hipError_t launch_tiles(const ckm_graph& g, const Layout& L, int32_t K, char* work, hipStream_t stream);
+hipError_t launch_best_tiles(const ckm_graph& g, const Layout& L, const int32_t* d_best_k, uint64_t* d_best_R,
+                             char* work, hipStream_t stream);
 hipError_t launch_select(const ckm_graph& g, const Layout& L, int32_t K, uint64_t seed,
                          int64_t budget, uint32_t flags, int64_t* d_peak,
                          int64_t* d_cost, uint8_t* d_feasible, int32_t* d_best_k,

@@ -5,8 +5,8 @@
 // candidate) and one work item of stages. All lanes walk the same nodes in
 // the same order, so graph data and loop bounds are wave-uniform and only the
 // candidates' bits and running sums differ per lane. Most graphs take the
-// event path (ckm_events.hip); this file makes its S rows, and evaluates what
-// that path does not: ckm_eval_kernel (wide or very dense graphs, work
+// tile path (ckm_tiles.hip); this file makes its S rows, and evaluates what
+// that path does not: ckm_eval_kernel (wide graphs, work
 // buffers without the row arrays). Each of its lanes keeps its own bit rows
 // (32-bit words, bit i%32 of word i/32): S_t, which becomes R_t as the scan
 // passes, in LDS laid out [word][lane] so that a wave-uniform word index
@@ -1086,7 +1086,7 @@ struct Totals {
 };
 __device__ __forceinline__ void clear_totals(const Totals& tot, int group) {
   const int k = group * kWave + (int)threadIdx.x;
-  if (tot.peak && blockIdx.y == 0 && k < tot.K) {
+  if (tot.peak && blockIdx.y == 0 && threadIdx.x < kWave && k < tot.K) {
     tot.peak[k] = INT64_MIN;
     tot.cost[k] = 0;
   }
@@ -1560,14 +1560,13 @@ __global__ void __launch_bounds__(kWave) ckm_best_closure_kernel(ClosureArgs a) 
 }
 
 // ---------------------------------------------------------------------------
-// S tiles (the event path's S rows, see ckm_events.h): per group of 64
+// S tiles (the tile path's S rows, see ckm_tiles.h): per group of 64
 // candidates and tile T of 32 stages, one 32-bit word per node and lane
-// (candidate), bit j being S of stage 32 T + j; quads of four nodes, 16 bytes
-// per lane (stile_off). The producers below make them from the three sources.
-// Block (group, item): 32 nodes of one tile, items numbering the pairs
-// (T, 32-node block nb <= T). Words take their bits from the highest stage
-// down, each shifted in from below; stages at or below a node, and past the
-// last, shift in zeros.
+// (candidate), bit j being S of stage 32 T + j (stile_off). The producers below
+// make them from the three sources. Block (group, item): 32 nodes of one tile,
+// items numbering the pairs (T, 32-node block nb <= T). Words take their bits
+// from the highest stage down, each shifted in from below; stages at or below
+// a node, and past the last, shift in zeros.
 __device__ __forceinline__ void tile_item(int item, int& T, int& nb) {
   int t = (int)((sqrtf(8.0f * (float)item + 1.0f) - 1.0f) * 0.5f);
   while (t * (t + 1) / 2 > item) --t;
@@ -1575,16 +1574,19 @@ __device__ __forceinline__ void tile_item(int item, int& T, int& nb) {
   T = __builtin_amdgcn_readfirstlane(t);
   nb = __builtin_amdgcn_readfirstlane(item - t * (t + 1) / 2);
 }
-__device__ __forceinline__ void store_tile(char* stiles, size_t group_bytes, int group, int T, int nb, const uint32_t (&w)[32]) {
-  char* dst = stiles + (size_t)group * group_bytes + stile_off(T) + (size_t)nb * 8192 + 16u * threadIdx.x;
+// Words of nodes v0 .. v0 + kNodes - 1 of tile T.
+template <int kNodes>
+__device__ __forceinline__ void store_tile(char* stiles, size_t group_bytes, int group, int T, int v0,
+                                           const uint32_t (&w)[kNodes]) {
+  uint32_t* dst = reinterpret_cast<uint32_t*>(stiles + (size_t)group * group_bytes + stile_off(T)) +
+                  (size_t)v0 * kWave + (threadIdx.x & (kWave - 1));
 #pragma unroll
-  for (int q = 0; q < 8; ++q)
-    *reinterpret_cast<uint4*>(dst + 1024 * q) = make_uint4(w[4 * q], w[4 * q + 1], w[4 * q + 2], w[4 * q + 3]);
+  for (int i = 0; i < kNodes; ++i) dst[i * kWave] = w[i];
 }
 
 // w_i = 2 w_i + [u_i < q_i] for eight nodes: u_i is 16-bit half (i mod 2) of
 // x[i / 2], q_i wave-uniform. Three lane masks rotate, as in append8_uniform.
-__device__ __forceinline__ void shift_in8(uint32_t (&w)[32], int o, const uint32_t x[4], const uint32_t* q) {
+__device__ __forceinline__ void shift_in8(uint32_t (&w)[8], const uint32_t x[4], const uint32_t (&q)[8]) {
   uint64_t m0, m1, m2;
   asm("v_cmp_lt_u32_sdwa %[m0], %[x0], %[q0] src0_sel:WORD_0 src1_sel:DWORD\n\t"
       "v_cmp_lt_u32_sdwa %[m1], %[x0], %[q1] src0_sel:WORD_1 src1_sel:DWORD\n\t"
@@ -1602,17 +1604,12 @@ __device__ __forceinline__ void shift_in8(uint32_t (&w)[32], int o, const uint32
       "v_addc_co_u32 %[w5], vcc, %[w5], %[w5], %[m2]\n\t"
       "v_addc_co_u32 %[w6], vcc, %[w6], %[w6], %[m0]\n\t"
       "v_addc_co_u32 %[w7], vcc, %[w7], %[w7], %[m1]"
-      : [w0] "+v"(w[o]), [w1] "+v"(w[o + 1]), [w2] "+v"(w[o + 2]), [w3] "+v"(w[o + 3]), [w4] "+v"(w[o + 4]),
-        [w5] "+v"(w[o + 5]), [w6] "+v"(w[o + 6]), [w7] "+v"(w[o + 7]), [m0] "=&s"(m0), [m1] "=&s"(m1), [m2] "=&s"(m2)
+      : [w0] "+v"(w[0]), [w1] "+v"(w[1]), [w2] "+v"(w[2]), [w3] "+v"(w[3]), [w4] "+v"(w[4]),
+        [w5] "+v"(w[5]), [w6] "+v"(w[6]), [w7] "+v"(w[7]), [m0] "=&s"(m0), [m1] "=&s"(m1), [m2] "=&s"(m2)
       : [x0] "v"(x[0]), [x1] "v"(x[1]), [x2] "v"(x[2]), [x3] "v"(x[3]), [q0] "s"(q[0]), [q1] "s"(q[1]),
         [q2] "s"(q[2]), [q3] "s"(q[3]), [q4] "s"(q[4]), [q5] "s"(q[5]), [q6] "s"(q[6]), [q7] "s"(q[7])
       : "vcc");
 }
-__device__ __forceinline__ void shift8(uint32_t (&w)[32], int o) {
-#pragma unroll
-  for (int i = 0; i < 8; ++i) w[o + i] += w[o + i];
-}
-
 // Philox4x32-10 of counter (b, r, k, 0), the counter of block b of row r for
 // candidate k, split by what each part depends on. Round 0 multiplies b
 // (wave-uniform) and k (per lane, the same for every block of the row);
@@ -1665,73 +1662,72 @@ __device__ __forceinline__ void philox_block(const PhiloxRow& pr, uint32_t b, ui
 }
 
 // Randomized rounding: bit [u_{k,t,i} < q[t][i]] (the draws of round_word);
-// candidate 0 takes the deterministic bits under CKM_F_DET0. Per stage and
-// lane one Philox output serves 8 nodes; the part of it that depends on the
-// stage and candidate alone is made once for the item's four blocks.
-__global__ void __launch_bounds__(kWave) ckm_round_tiles_kernel(const uint32_t* __restrict__ q,
-                                                                const uint32_t* __restrict__ det, int32_t n,
-                                                                int32_t ldq, int32_t det_words, uint32_t key0,
-                                                                uint32_t key1, uint32_t det0, size_t group_bytes,
-                                                                char* __restrict__ stiles, Totals tot) {
+// candidate 0 takes the deterministic bits under CKM_F_DET0. One Philox output
+// serves 8 nodes, which are a wave's; the four waves of a block share the lines
+// of the thresholds.
+constexpr int kItemWaves = 4;
+__global__ void __launch_bounds__(kWave* kItemWaves) ckm_round_tiles_kernel(
+    const uint32_t* __restrict__ q, const uint32_t* __restrict__ det, int32_t n, int32_t ldq, int32_t det_words,
+    uint32_t key0, uint32_t key1, uint32_t det0, size_t group_bytes, char* __restrict__ stiles, Totals tot) {
   const int group = blockIdx.x;
   clear_totals(tot, group);
   int T, nb;
   tile_item(blockIdx.y, T, nb);
-  const uint32_t k = (uint32_t)(group * kWave) + threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave), m = kItemWaves * nb + wave;
+  const uint32_t lane = threadIdx.x & (kWave - 1), k = (uint32_t)(group * kWave) + lane;
   const bool det_here = det0 && group == 0;
-  uint32_t w[32];
+  uint32_t w[8];
 #pragma unroll
-  for (int i = 0; i < 32; ++i) w[i] = 0u;
-  for (int t = 32 * T + 31; t >= 32 * T; --t) {
-    if (t >= n) continue;   // the words are still empty
-    const uint32_t* qrow = (const uint32_t*)q + (size_t)t * ldq + 32 * nb;
-    uint32_t qv[32];
+  for (int i = 0; i < 8; ++i) w[i] = 0u;
+  // stages above the block's first node, from the last one down
+  const int last = (32 * T + 31 < n ? 32 * T + 31 : n - 1), first = 8 * m + 1 > 32 * T ? 8 * m + 1 : 32 * T;
+#pragma unroll 2
+  for (int t = last; t >= first; --t) {
+    const cptr<uint32_t> qrow = as_const(q) + (size_t)t * ldq + 8 * m;
+    uint32_t qv[8], x[4];
 #pragma unroll
-    for (int i = 0; i < 32; ++i) qv[i] = as_const(qrow)[i];
-    const PhiloxRow pr = philox_row((uint32_t)t, k, key0);
-#pragma unroll
-    for (int b = 0; b < 4; ++b) {
-      if (32 * nb + 8 * b >= t) {
-        shift8(w, 8 * b);
-      } else {
-        uint32_t x[4];
-        philox_block(pr, (uint32_t)(4 * nb + b), key0, key1, x);
-        shift_in8(w, 8 * b, x, qv + 8 * b);
-      }
-    }
+    for (int i = 0; i < 8; ++i) qv[i] = qrow[i];
+    philox_block(philox_row((uint32_t)t, k, key0), (uint32_t)m, key0, key1, x);
+    shift_in8(w, x, qv);
     if (det_here) {
-      const uint32_t dw = as_const(det)[(size_t)t * det_words + nb];
-      if (threadIdx.x == 0) {
+      const uint32_t dw = as_const(det)[(size_t)t * det_words + nb] >> (8 * wave);
+      if (lane == 0) {
 #pragma unroll
-        for (int i = 0; i < 32; ++i) w[i] = (w[i] & ~1u) | ((dw >> i) & 1u);
+        for (int i = 0; i < 8; ++i) w[i] = (w[i] & ~1u) | ((dw >> i) & 1u);
       }
     }
   }
-  store_tile(stiles, group_bytes, group, T, nb, w);
+  // bits of the stages below the first (zeros)
+  if (last >= first) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) w[i] <<= first - 32 * T;
+  }
+  store_tile(stiles, group_bytes, group, T, 8 * m, w);
 }
 
 // Threshold candidates: bit [rank_k < key[t][i]], the threshold test of
-// threshold_word (keys on and above the diagonal are 0).
-__global__ void __launch_bounds__(kWave) ckm_threshold_tiles_kernel(const uint32_t* __restrict__ key, int32_t ldq,
-                                                                    const uint32_t* __restrict__ rank, int32_t K,
-                                                                    int32_t n, size_t group_bytes,
-                                                                    char* __restrict__ stiles, Totals tot) {
+// threshold_word (keys on and above the diagonal are 0). A wave has 8 nodes.
+__global__ void __launch_bounds__(kWave* kItemWaves) ckm_threshold_tiles_kernel(
+    const uint32_t* __restrict__ key, int32_t ldq, const uint32_t* __restrict__ rank, int32_t K, int32_t n,
+    size_t group_bytes, char* __restrict__ stiles, Totals tot) {
   const int group = blockIdx.x;
   clear_totals(tot, group);
   int T, nb;
   tile_item(blockIdx.y, T, nb);
-  const uint32_t k = (uint32_t)(group * kWave) + threadIdx.x;
+  const int m = kItemWaves * nb + __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+  const uint32_t k = (uint32_t)(group * kWave) + (threadIdx.x & (kWave - 1));
   const uint32_t rk = rank[k < (uint32_t)K ? k : (uint32_t)K - 1u];
-  uint32_t w[32];
+  uint32_t w[8];
 #pragma unroll
-  for (int i = 0; i < 32; ++i) w[i] = 0u;
-  for (int t = 32 * T + 31; t >= 32 * T; --t) {
-    if (t >= n) continue;
-    const cptr<uint32_t> krow = as_const(key) + (size_t)t * ldq + 32 * nb;
+  for (int i = 0; i < 8; ++i) w[i] = 0u;
+  const int last = 32 * T + 31 < n ? 32 * T + 31 : n - 1;
+#pragma unroll 4
+  for (int t = last; t >= 32 * T; --t) {
+    const cptr<uint32_t> krow = as_const(key) + (size_t)t * ldq + 8 * m;
 #pragma unroll
-    for (int i = 0; i < 32; ++i) w[i] = w[i] + w[i] + (rk < krow[i] ? 1u : 0u);
+    for (int i = 0; i < 8; ++i) w[i] = w[i] + w[i] + (rk < krow[i] ? 1u : 0u);
   }
-  store_tile(stiles, group_bytes, group, T, nb, w);
+  store_tile(stiles, group_bytes, group, T, 8 * m, w);
 }
 
 // Caller-supplied checkpoint matrices ([K][n][s_words] 32-bit words): bit i of
@@ -1770,7 +1766,7 @@ __global__ void __launch_bounds__(kWave) ckm_user_tiles_kernel(const uint32_t* _
   transpose_step<4>(w, 0x0F0F0F0Fu);
   transpose_step<2>(w, 0x33333333u);
   transpose_step<1>(w, 0x55555555u);
-  store_tile(stiles, group_bytes, group, T, nb, w);
+  store_tile(stiles, group_bytes, group, T, 32 * nb, w);
 }
 
 template <typename T>
@@ -1851,7 +1847,7 @@ static unsigned tile_items(int32_t n) {
   return tiles * (tiles + 1) / 2;
 }
 
-static bool use_events(const ckm_graph& g, const Layout& L) { return L.rows_on && g.ev.on; }
+static bool use_tiles(const ckm_graph& g, const Layout& L) { return L.rows_on && g.tile.on; }
 
 hipError_t launch_round_rows(const ckm_graph& g, const Layout& L, int32_t K, uint64_t seed, uint32_t flags,
                              char* work, hipStream_t stream) {
@@ -1861,12 +1857,12 @@ hipError_t launch_round_rows(const ckm_graph& g, const Layout& L, int32_t K, uin
 hipError_t launch_round_rows(const ckm_graph& g, const Layout& L, int32_t K, uint64_t seed, uint32_t flags,
                              bool clear, char* work, hipStream_t stream) {
   if (!L.rows_on) return hipSuccess;
-  if (use_events(g, L)) {
+  if (use_tiles(g, L)) {
     const Totals tot{clear ? at<int64_t>(work, L.part_peak_off) : nullptr, at<int64_t>(work, L.part_cost_off), K};
-    hipLaunchKernelGGL(ckm_round_tiles_kernel, dim3(groups_of(K), tile_items(g.n)), dim3(kWave), 0, stream,
+    hipLaunchKernelGGL(ckm_round_tiles_kernel, dim3(groups_of(K), tile_items(g.n)), dim3(kWave * kItemWaves), 0, stream,
                        at<const uint32_t>(work, L.q_off), at<const uint32_t>(work, L.det_off), g.n, L.ldq,
                        L.det_words, (uint32_t)(seed & 0xFFFFFFFFu), (uint32_t)(seed >> 32),
-                       (flags & CKM_F_DET0) ? 1u : 0u, stiles_bytes(g.n), work + L.rows_off, tot);
+                       (flags & CKM_F_DET0) ? 1u : 0u, stile_off((g.n + 31) / 32), work + L.rows_off, tot);
     return hipGetLastError();
   }
   const int32_t kpad = ((K + kWave - 1) / kWave) * kWave;
@@ -1885,12 +1881,12 @@ static hipError_t launch_tile_producer(const ckm_graph& g, const Layout& L, int3
   const Totals tot{at<int64_t>(work, L.part_peak_off), at<int64_t>(work, L.part_cost_off), K};
   const dim3 grid(groups_of(K), tile_items(g.n));
   if (src == kSrcThreshold) {
-    hipLaunchKernelGGL(ckm_threshold_tiles_kernel, grid, dim3(kWave), 0, stream, at<const uint32_t>(work, L.q_off),
-                       L.ldq, at<const uint32_t>(work, L.thr_rank_off), K, g.n, stiles_bytes(g.n), work + L.rows_off,
+    hipLaunchKernelGGL(ckm_threshold_tiles_kernel, grid, dim3(kWave * kItemWaves), 0, stream, at<const uint32_t>(work, L.q_off),
+                       L.ldq, at<const uint32_t>(work, L.thr_rank_off), K, g.n, stile_off((g.n + 31) / 32), work + L.rows_off,
                        tot);
   } else if (src == kSrcUser) {
     hipLaunchKernelGGL(ckm_user_tiles_kernel, grid, dim3(kWave), 0, stream,
-                       reinterpret_cast<const uint32_t*>(s_user), g.n, K, L.row_words, stiles_bytes(g.n),
+                       reinterpret_cast<const uint32_t*>(s_user), g.n, K, L.row_words, stile_off((g.n + 31) / 32),
                        work + L.rows_off, tot);
   } else {
     return launch_round_rows(g, L, K, seed, flags, true, work, stream);
@@ -1901,9 +1897,9 @@ static hipError_t launch_tile_producer(const ckm_graph& g, const Layout& L, int3
 hipError_t launch_evaluate(const ckm_graph& g, const Layout& L, int32_t K, uint64_t seed,
                            uint32_t flags, const Plan& plan, int src, const uint64_t* s_user, char* work,
                            hipStream_t stream) {
-  if (use_events(g, L)) {
+  if (use_tiles(g, L)) {
     // S tiles made by a producer (none when the caller rounded them
-    // beforehand), then the event path
+    // beforehand), then the tile path
     hipError_t e = hipSuccess;
     if (!(src == kSrcRound && (flags & CKM_F_ROUNDED))) {
       e = launch_tile_producer(g, L, K, seed, flags, src, s_user, work, stream);
@@ -1913,7 +1909,7 @@ hipError_t launch_evaluate(const ckm_graph& g, const Layout& L, int32_t K, uint6
                          at<int64_t>(work, L.part_peak_off), at<int64_t>(work, L.part_cost_off));
       e = hipGetLastError();
     }
-    return e == hipSuccess ? launch_events(g, L, K, work, stream) : e;
+    return e == hipSuccess ? launch_tiles(g, L, K, work, stream) : e;
   }
   EvalArgs a;
   a.n = g.n;
@@ -2039,9 +2035,8 @@ hipError_t launch_select(const ckm_graph& g, const Layout& L, int32_t K, uint64_
   }
   // With the row arrays the evaluate stage kept every candidate's R rows, so
   // the best R is a gather; otherwise Algorithm 2 runs again for it.
-  const bool events = use_events(g, L);
-  if (events && d_best_R) {
-    const hipError_t e = launch_best_events(g, L, K, d_best_k, d_best_R, work, stream);
+  if (use_tiles(g, L) && d_best_R) {
+    const hipError_t e = launch_best_tiles(g, L, d_best_k, d_best_R, work, stream);
     if (e != hipSuccess) return e;
     d_best_R = nullptr;
   }

@@ -1,0 +1,613 @@
+// Tile path (see ckm_tiles.h): the closure kernel, which decides R of every
+// (candidate, stage, node), the hub words, the simulate kernel, which runs the
+// U recurrence, and the gather of the best candidate's R.
+//
+// Decisions are bits: with 32 stages to a word and a candidate to a lane, one
+// instruction decides a node for 32 x 64 (stage, candidate) pairs, and every
+// access to memory or LDS is one word (or four) per lane at a wave-uniform
+// address. The sums are binary64 per (candidate, stage); a word's bit j, taken
+// alone in the low half of a binary64, is 2^(j - 1074), so that one AND and
+// one FMA make a masked update of an accumulator that counts in units of
+// 2^(j - 1074).
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cstdint>
+
+#include "ckm_internal.h"
+#include "ckm_tiles.h"
+
+namespace ckm {
+namespace {
+
+template <typename T>
+using cptr = const __attribute__((address_space(4))) T*;
+typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
+typedef uint64_t u64x8 __attribute__((ext_vector_type(8)));
+typedef __attribute__((address_space(3))) char lds_char;
+typedef __attribute__((address_space(3))) uint32_t lds_u32;
+
+constexpr int kBufWord3 = 0x00020000;          // raw byte-addressed buffer: reads past its end give 0
+constexpr uint32_t kPastEnd = 0xFFFFF000u;     // a lane offset past the end of any tile
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer(const void* p, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, kBufWord3);
+}
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ uint32_t rl(uint32_t w, int lane) { return __builtin_amdgcn_readlane(w, lane); }
+// S_{t+1} of a tile's stages: its own S words shifted, the next tile's first stage on top.
+__device__ __forceinline__ uint32_t s1_of(uint32_t s, uint32_t next) { return __builtin_amdgcn_alignbit(next, s, 1); }
+
+struct TileArgs {
+  int32_t n, tiles;
+  uint32_t rbase;
+  size_t s_bytes, r_bytes;          // S and R tiles of one group
+  const char* stiles;
+  char* rtiles;
+};
+// The buffers of one (group, tile).
+struct TileBufs {
+  __amdgpu_buffer_rsrc_t s, next, r;
+  uint32_t vo, vo_next;             // lane offsets; the next tile's is past the end after the last tile
+  uint32_t r_bytes;
+  __device__ __forceinline__ TileBufs(const TileArgs& a, int group, int tile, int lane) {
+    const char* st = a.stiles + (size_t)group * a.s_bytes + stile_off(tile);
+    const uint32_t bytes = stile_bytes(tile);
+    const bool last = tile + 1 == a.tiles;
+    s = buffer(st, bytes);
+    next = buffer(last ? st : st + bytes, bytes);   // as many nodes of it are read
+    vo = 4u * (uint32_t)lane;
+    vo_next = last ? kPastEnd : vo;
+    r_bytes = a.rbase + bytes;
+    r = buffer(a.rtiles + (size_t)group * a.r_bytes + rtile_off(a.rbase, tile), r_bytes);
+  }
+};
+
+// ---------------------------------------------------------------------------
+// Closure: one block per (group, tile): a wave that decides, and kPrep waves
+// that prepare the block of nodes below.
+constexpr int kPrep = 2;
+constexpr int kPrepNodes = kTile / kPrep;
+
+constexpr int kDescVecs = kTile / kChunk4 * kDescDwords / kWave;   // descriptor dwords per lane and block
+
+struct ClosureArgs {
+  TileArgs t;
+  const uint32_t* desc;
+  const uint32_t* far;
+  cptr<uint32_t> far_more, near_more;
+};
+
+__device__ __forceinline__ uint32_t lds_get(lds_char* p, uint32_t off) { return *(const lds_u32*)(p + off); }
+__device__ __forceinline__ void lds_put(lds_char* p, uint32_t off, uint32_t x) { *(lds_u32*)(p + off) = x; }
+__device__ __forceinline__ uint32_t load_r(const TileBufs& b, uint32_t off) {
+  // a user past the tile's last node computes nothing in its stages
+  return __builtin_amdgcn_raw_buffer_load_b32(b.r, (int)b.vo, (int)(off < b.r_bytes ? off : 0u), 0);
+}
+
+// A prepare wave's S words of one block, requested one block ahead.
+struct PrepIn {
+  uint32_t s[kPrepNodes], next[kPrepNodes];
+};
+__device__ __forceinline__ void prep_load(const TileBufs& b, int v0, PrepIn& in) {
+#pragma unroll
+  for (int i = 0; i < kPrepNodes; ++i) {
+    in.s[i] = __builtin_amdgcn_raw_buffer_load_b32(b.s, (int)b.vo, (int)node_off(v0 + i), 0);
+    in.next[i] = __builtin_amdgcn_raw_buffer_load_b32(b.next, (int)b.vo_next, (int)node_off(v0 + i), 0);
+  }
+}
+// Nodes v0 .. v0 + kPrepNodes - 1 into the prepared words of their block; far:
+// their far users (a dword per lane), x: R of the first of them.
+__device__ __forceinline__ void prep_store(const ClosureArgs& a, const TileBufs& b, lds_char* lds, int v0,
+                                           const PrepIn& in, uint32_t far, uint32_t (&x)[kPrepNodes]) {
+  lds += (uint32_t)(v0 & (kRingNodes - 1)) * kSlotBytes;
+  const uint64_t some = __ballot(far != 0u);
+  if (some & 0xFFFF0000u) {
+    uint32_t y[kPrepNodes];
+#pragma unroll
+    for (int i = 0; i < kPrepNodes; ++i) y[i] = load_r(b, rl(far, 16 + i));
+#pragma unroll
+    for (int i = 0; i < kPrepNodes; ++i) x[i] |= y[i];
+  }
+#pragma unroll
+  for (int i = 0; i < kPrepNodes; ++i) {
+    lds_put(lds, kSlotNeed * kSlotBytes + kSlotBytes * i, s1_of(in.s[i], in.next[i]) | x[i]);
+    lds_put(lds, kSlotS * kSlotBytes + kSlotBytes * i, in.s[i]);
+  }
+  for (uint64_t more = some >> 48; more; more &= more - 1) {
+    const int i = __builtin_ctzll(more);
+    const uint32_t e0 = rl(far, 32 + i), e1 = e0 + rl(far, 48 + i);
+    uint32_t acc = 0;
+    for (uint32_t e = e0; e < e1; e += 8) {
+      uint32_t y[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) y[k] = load_r(b, a.far_more[min(e + k, e1 - 1)]);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) acc |= y[k];
+    }
+    const uint32_t o = (uint32_t)(kSlotNeed + i) * kSlotBytes;
+    lds_put(lds, o, lds_get(lds, o) | acc);
+  }
+}
+
+// R of a chunk's nodes from what each needs (its prepared word and its near
+// users' R) and its S word: uses within the chunk pass through registers. kTop:
+// the tile's own block, nodes 32 T + i, 32 T + i + 1, ...: stages below node v
+// compute nothing at v, stage v computes it.
+template <bool kTop>
+__device__ __forceinline__ void decide(const uint32_t (&need)[4], const uint32_t (&s)[4], uint32_t flags, int i,
+                                       int nodes, uint32_t (&R)[4]) {
+  const auto use = [&](int bit) { return (uint32_t)((int32_t)(flags << (31 - bit)) >> 31); };
+  const auto settle = [&](int j, uint32_t x) {
+    const uint32_t r = x & ~s[j];
+    return kTop ? (r & (~0u << (i + j))) | (i + j < nodes ? 1u << (i + j) : 0u) : r;
+  };
+  R[3] = settle(3, need[3]);
+  R[2] = settle(2, need[2] | (R[3] & use(0)));
+  R[1] = settle(1, need[1] | (R[3] & use(1)) | (R[2] & use(3)));
+  R[0] = settle(0, need[0] | (R[3] & use(2)) | (R[2] & use(4)) | (R[1] & use(5)));
+}
+
+// The block's chunks from the top down. blk: LDS of this lane's column, from
+// the block's ring slots on; r_off: the block's R tile byte offset.
+template <int kNear, bool kTop>
+__device__ __forceinline__ void decide_block(const TileBufs& b, lds_char* lds, lds_char* blk, uint32_t r_off,
+                                             const uint32_t (&d)[kDescVecs], int nodes) {
+  uint32_t need[kTile / 4][4], s[kTile / 4][4];
+#pragma unroll
+  for (int c = kTile / 4 - 1; c >= 0; --c)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      need[c][j] = lds_get(blk, (uint32_t)(kSlotNeed + 4 * c + j) * kSlotBytes);
+      s[c][j] = lds_get(blk, (uint32_t)(kSlotS + 4 * c + j) * kSlotBytes);
+    }
+#pragma unroll
+  for (int c = kTile / 4 - 1; c >= 0; --c) {
+    const uint32_t dc = d[c / 2];
+    const int dl = kDescDwords * (c & 1);
+    uint32_t u[4][kNear], R[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int k = 0; k < kNear; ++k) u[j][k] = lds_get(lds, rl(dc, dl + 4 * j + k));
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int k = 0; k < kNear; ++k) need[c][j] |= u[j][k];
+    decide<kTop>(need[c], s[c], rl(dc, dl + 16), 4 * c, nodes, R);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) lds_put(blk, (uint32_t)(4 * c + j) * kSlotBytes, R[j]);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      __builtin_amdgcn_raw_buffer_store_b32(R[j], b.r, (int)b.vo + kSlotBytes * j, (int)(r_off + node_off(4 * c)), 0);
+  }
+}
+// The same for any number of near users.
+template <bool kTop>
+__device__ __forceinline__ void decide_block_any(const ClosureArgs& a, const TileBufs& b, lds_char* lds, lds_char* blk,
+                                                 uint32_t r_off, uint32_t (&d)[kDescVecs], int nodes) {
+#pragma unroll 1
+  for (int c = kTile / 4 - 1; c >= 0; --c) {
+    const uint32_t dc = d[kDescVecs - 1];
+    const int dl = kDescDwords * (c & 1);
+    lds_char* ch = blk + 4 * c * kSlotBytes;
+    uint32_t need[4], s[4], R[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      need[j] = lds_get(ch, (uint32_t)(kSlotNeed + j) * kSlotBytes);
+      s[j] = lds_get(ch, (uint32_t)(kSlotS + j) * kSlotBytes);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) need[j] |= lds_get(lds, rl(dc, dl + 4 * j + k));
+      const uint32_t e0 = rl(dc, dl + 17 + 2 * j), e1 = e0 + rl(dc, dl + 18 + 2 * j);
+      for (uint32_t e = e0; e < e1; ++e) need[j] |= lds_get(lds, a.near_more[e]);
+    }
+    decide<kTop>(need, s, rl(dc, dl + 16), 4 * c, nodes, R);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) lds_put(ch, (uint32_t)j * kSlotBytes, R[j]);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      __builtin_amdgcn_raw_buffer_store_b32(R[j], b.r, (int)b.vo + kSlotBytes * j, uniform((int)(r_off + node_off(4 * c))), 0);
+    if (!(c & 1)) {
+#pragma unroll
+      for (int k = kDescVecs - 1; k > 0; --k) d[k] = d[k - 1];
+    }
+  }
+}
+template <bool kTop>
+__device__ __forceinline__ void decide_block(const ClosureArgs& a, const TileBufs& b, lds_char* lds, int nb,
+                                             uint32_t (&d)[kDescVecs]) {
+  lds_char* blk = lds + (nb & 1) * kTile * kSlotBytes;
+  const uint32_t r_off = (uint32_t)uniform((int)(a.t.rbase + node_off(kTile * nb)));
+  const int nodes = a.t.n - kTile * nb;
+  const uint32_t flags = rl(d[0], 16);
+  if (flags & kBlockMany)
+    decide_block_any<kTop>(a, b, lds, blk, r_off, d, nodes);
+  else if (flags & kBlockNear3)
+    decide_block<3, kTop>(b, lds, blk, r_off, d, nodes);
+  else
+    decide_block<2, kTop>(b, lds, blk, r_off, d, nodes);
+}
+
+// Barrier between phases. What the deciding wave wrote, to LDS and to the R
+// tile, is read by the others after it; those write LDS only, and keep their
+// loads for the next block in flight.
+__device__ __forceinline__ void phase_end_decide() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+__device__ __forceinline__ void phase_end_prep() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+__global__ void __launch_bounds__(kWave*(1 + kPrep)) ckm_closure_kernel(ClosureArgs a) {
+  __shared__ uint32_t slots[kClosureSlots * kWave];
+  const int lane = threadIdx.x & (kWave - 1), wave = uniform((int)threadIdx.x / kWave);
+  const int tile = a.t.tiles - 1 - (int)blockIdx.y;   // the longest scans start first
+  const TileBufs b(a.t, blockIdx.x, tile, lane);
+  lds_char* lds = (lds_char*)&slots[lane];
+  if (wave == 0) {
+    lds_put(lds, kRingEmpty * kSlotBytes, 0u);
+    for (int i = 0; i < kRingNodes; ++i) lds_put(lds, (uint32_t)i * kSlotBytes, 0u);
+    __builtin_amdgcn_raw_buffer_store_b32(0u, b.r, (int)b.vo, 0, 0);   // the empty word
+  }
+  if (wave > 0) {
+    // phase p prepares block tile - p; blocks tile - p + 2 and up are decided
+    const uint32_t* fars = a.far + kWave * (wave - 1) + lane;
+    int v0 = kTile * tile + kPrepNodes * (wave - 1);
+    const uint32_t* descs = a.desc + (kDescVecs / kPrep) * kWave * (wave - 1) + lane;
+    uint32_t far = fars[(size_t)tile * (kPrep * kWave)], d[kDescVecs / kPrep];
+#pragma unroll
+    for (int i = 0; i < kDescVecs / kPrep; ++i) d[i] = descs[(size_t)(tile * kDescVecs + i) * kWave];
+    PrepIn in;
+    prep_load(b, v0, in);
+    phase_end_prep();
+    for (int p = 0; p <= tile; ++p, v0 -= kTile) {
+#pragma unroll
+      for (int i = 0; i < kDescVecs / kPrep; ++i)
+        lds_put(lds, (uint32_t)(kSlotDesc + kDescVecs * ((tile - p) & 1) + kDescVecs / kPrep * (wave - 1) + i) * kSlotBytes,
+                d[i]);
+      const PrepIn now = in;
+      const uint32_t far_now = far;
+      // loads return in order: this block's before the next one's
+      uint32_t x[kPrepNodes];
+#pragma unroll
+      for (int i = 0; i < kPrepNodes; ++i) x[i] = load_r(b, rl(far, i));
+      if (p < tile) {
+        far = fars[(size_t)(tile - p - 1) * (kPrep * kWave)];
+#pragma unroll
+        for (int i = 0; i < kDescVecs / kPrep; ++i) d[i] = descs[(size_t)((tile - p - 1) * kDescVecs + i) * kWave];
+        prep_load(b, v0 - kTile, in);
+      }
+      prep_store(a, b, lds, v0, now, far_now, x);
+      phase_end_prep();
+    }
+    phase_end_prep();
+    return;
+  }
+  phase_end_decide();
+  // phase p decides block tile - p + 1
+  for (int p = 0; p <= tile + 1; ++p) {
+    if (p > 0) {
+      const int nb = tile - p + 1;
+      uint32_t d[kDescVecs];
+#pragma unroll
+      for (int i = 0; i < kDescVecs; ++i) d[i] = lds_get(lds, (uint32_t)(kSlotDesc + kDescVecs * (nb & 1) + i) * kSlotBytes);
+      if (nb == tile)
+        decide_block<true>(a, b, lds, nb, d);
+      else
+        decide_block<false>(a, b, lds, nb, d);
+    }
+    phase_end_decide();
+  }
+}
+
+// Hub words: one wave per (group, tile, hub), over the hub's users from the
+// highest down: word x of a user is the OR of R over the users above it.
+__global__ void __launch_bounds__(kWave) ckm_hub_kernel(TileArgs t, cptr<int32_t> hub_ptr, cptr<HubUser> hub) {
+  const TileBufs b(t, blockIdx.x, t.tiles - 1 - (int)blockIdx.y, threadIdx.x);
+  const int e1 = hub_ptr[blockIdx.z + 1];
+  uint32_t acc = 0;
+  for (int e = hub_ptr[blockIdx.z]; e < e1; e += 8) {
+    uint32_t x[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const uint32_t off = hub[min(e + k, e1 - 1)].r;
+      x[k] = __builtin_amdgcn_raw_buffer_load_b32(b.r, (int)b.vo, (int)(off < b.r_bytes ? off : 0u), 0);
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      if (e + k >= e1) break;
+      const uint32_t xo = hub[e + k].x;
+      if (xo) __builtin_amdgcn_raw_buffer_store_b32(acc, b.r, (int)b.vo, (int)xo, 0);
+      acc |= x[k];
+    }
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Simulate: the U recurrence (Section 4.4) and the cost (Section 4.3), one
+// wave per (group, 8 stages of a tile, part of the tile's records). Before
+// node v is computed the memory is U_{t,0} + U; computing it adds M_v (the
+// peak is taken there), then the dependencies that FREE releases after it
+// leave. All sums are binary64 integers below 2^53, exact in any order; stage
+// j of the tile counts in units of 2^(j - 1074), so that its bit of a word is
+// the unit itself (denormals are exact and run at full rate).
+struct SimArgs {
+  TileArgs t;
+  int32_t K, groups;
+  double base;                      // M_in + 2 M_param
+  cptr<u64x8> ops;                  // pairs of SimOps
+  cptr<u32x16> refs;                // pairs of SimRefs
+  cptr<SimMore> more;
+  cptr<uint32_t> more_off;
+  cptr<int32_t> tile_rec;
+  int64_t* __restrict__ peak;
+  int64_t* __restrict__ cost;
+};
+
+constexpr int kSub = 8;             // stages per wave
+constexpr int kSubs = kTile / kSub;
+
+struct SimStages {
+  double U[kSub], top[kSub], U0[kSub];   // relative to the stage's start; its peak; U_{t,0}
+};
+
+// Two stages (bits a, b) of one record: U0 += S M; U += R M, the peak, then
+// U -= F M0 + G M1. Each masked update takes its bit into the low word of a
+// binary64 whose high word is 0.
+template <int kBit>
+__device__ __forceinline__ void sim_pair(SimStages& x, int i, uint32_t R, uint32_t S, uint32_t F, uint32_t G, double M,
+                                         double M0, double M1) {
+  constexpr int a = (int)(1u << kBit), b = (int)(2u << kBit);
+  asm("v_and_b32 v8, %[a], %[S]\n\t"
+      "v_mov_b32 v9, 0\n\t"
+      "v_and_b32 v10, %[b], %[S]\n\t"
+      "v_mov_b32 v11, 0\n\t"
+      "v_fma_f64 %[z0], v[8:9], %[M], %[z0]\n\t"
+      "v_fma_f64 %[z1], v[10:11], %[M], %[z1]\n\t"
+      "v_and_b32 v8, %[a], %[R]\n\t"
+      "v_and_b32 v10, %[b], %[R]\n\t"
+      "v_fma_f64 %[u0], v[8:9], %[M], %[u0]\n\t"
+      "v_fma_f64 %[u1], v[10:11], %[M], %[u1]\n\t"
+      "v_and_b32 v8, %[a], %[F]\n\t"
+      "v_and_b32 v10, %[b], %[F]\n\t"
+      "v_max_f64 %[t0], %[t0], %[u0]\n\t"
+      "v_max_f64 %[t1], %[t1], %[u1]\n\t"
+      "v_fma_f64 %[u0], v[8:9], -%[M0], %[u0]\n\t"
+      "v_fma_f64 %[u1], v[10:11], -%[M0], %[u1]\n\t"
+      "v_and_b32 v8, %[a], %[G]\n\t"
+      "v_and_b32 v10, %[b], %[G]\n\t"
+      "v_fma_f64 %[u0], v[8:9], -%[M1], %[u0]\n\t"
+      "v_fma_f64 %[u1], v[10:11], -%[M1], %[u1]"
+      : [u0] "+v"(x.U[i]), [u1] "+v"(x.U[i + 1]), [t0] "+v"(x.top[i]), [t1] "+v"(x.top[i + 1]), [z0] "+v"(x.U0[i]),
+        [z1] "+v"(x.U0[i + 1])
+      : [R] "v"(R), [S] "v"(S), [F] "v"(F), [G] "v"(G), [M] "s"(M), [M0] "s"(M0), [M1] "s"(M1), [a] "i"(a), [b] "i"(b)
+      : "v8", "v9", "v10", "v11");
+}
+template <int kFirst, int kPair = 0>
+__device__ __forceinline__ void sim_stages(SimStages& x, uint32_t R, uint32_t S, uint32_t F, uint32_t G, double M,
+                                           double M0, double M1) {
+  if constexpr (kPair < kSub / 2) {
+    sim_pair<kFirst + 2 * kPair>(x, 2 * kPair, R, S, F, G, M, M0, M1);
+    sim_stages<kFirst, kPair + 1>(x, R, S, F, G, M, M0, M1);
+  }
+}
+
+// A record's words, requested one pair of records ahead.
+struct SimWords {
+  uint32_t R, S, s0, n0, a0, b0, s1, n1, a1, b1;
+};
+
+// Records r0 .. r1 - 1. kSubIdx: the wave's stages 8 kSubIdx .. + 7; only the
+// last 8 reach into the next tile's S words. Every fourth record's cost is this
+// wave's to count, over all 32 stages.
+template <int kSubIdx>
+__device__ __forceinline__ void sim_scan(const SimArgs& a, SimStages& x, uint64_t& cost_lo, uint64_t& cost_hi,
+                                         const TileBufs& b, int r0, int r1) {
+  constexpr bool kNext = kSubIdx == kSubs - 1;
+  const uint32_t rbase = a.t.rbase;
+  const auto load_s = [&](uint32_t off) { return (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(b.s, (int)b.vo, (int)off, 0); };
+  const auto load_n = [&](uint32_t off) {
+    return kNext ? (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(b.next, (int)b.vo_next, (int)off, 0) : 0u;
+  };
+  const auto load_r = [&](uint32_t off) {
+    return (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(b.r, (int)b.vo, (int)(off < b.r_bytes ? off : 0u), 0);
+  };
+  // pair p of records (reads clamped to the last pair, whose second record may
+  // be past the tile: its S words are then not read)
+  const auto load = [&](SimWords(&w)[2], int p) {
+    const u32x16 f = a.refs[min(p, (r1 - 1) >> 1)];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const auto g = [&](int k) {
+        const uint32_t off = f[8 * i + k];
+        return i == 0 || off < b.r_bytes - rbase ? off : 0u;
+      };
+      w[i].R = load_r(f[8 * i] + rbase);
+      w[i].S = load_s(g(0));
+      w[i].s0 = load_s(g(1));
+      w[i].n0 = load_n(g(1));
+      w[i].a0 = load_r(f[8 * i + 2]);
+      w[i].b0 = load_r(f[8 * i + 3]);
+      w[i].s1 = load_s(g(4));
+      w[i].n1 = load_n(g(4));
+      w[i].a1 = load_r(f[8 * i + 5]);
+      w[i].b1 = load_r(f[8 * i + 6]);
+    }
+  };
+  const auto pair = [&](const SimWords(&w)[2], int p) {
+    const u64x8 o = a.ops[p];
+    const u32x16 f = a.refs[p];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      if (2 * p + i < r0 || 2 * p + i >= r1) continue;
+      uint32_t x0 = s1_of(w[i].s0, w[i].n0) | w[i].a0 | w[i].b0, x1 = s1_of(w[i].s1, w[i].n1) | w[i].a1 | w[i].b1;
+      if (__builtin_expect(f[8 * i + 7] != 0u, 0)) {
+        const cptr<SimMore> m = a.more + (f[8 * i + 7] - 1);
+        const uint32_t first = m->first, c0 = m->count0, c1 = m->count1;
+        for (uint32_t e = 0; e < c0; ++e) x0 |= load_r(a.more_off[first + e]);
+        for (uint32_t e = 0; e < c1; ++e) x1 |= load_r(a.more_off[first + c0 + e]);
+      }
+      const uint32_t R = w[i].R;
+      sim_stages<kSub * kSubIdx>(x, R, w[i].S, R & ~x0, R & ~x1, __builtin_bit_cast(double, (uint64_t)o[4 * i]),
+                                 __builtin_bit_cast(double, (uint64_t)o[4 * i + 2]),
+                                 __builtin_bit_cast(double, (uint64_t)o[4 * i + 3]));
+      if (i == (kSubIdx & 1) && (p & 1) == kSubIdx >> 1) {
+        const uint32_t c = (uint32_t)__builtin_popcount(R);
+        cost_lo += (uint64_t)c * (uint32_t)o[4 * i + 1];
+        cost_hi += (uint64_t)c * (uint32_t)(o[4 * i + 1] >> 32);
+      }
+    }
+  };
+  SimWords wa[2], wb[2];
+  const int p1 = (r1 + 1) >> 1;
+  int p = r0 >> 1;
+  load(wa, p);
+  for (; p < p1; p += 2) {
+    load(wb, p + 1);
+    pair(wa, p);
+    if (p + 1 >= p1) break;
+    load(wa, p + 2);
+    pair(wb, p + 1);
+  }
+}
+
+// kSegs waves share a tile's 16 stages, each a part of the records; each
+// then counts from the memory that the parts before it leave.
+template <int kSegs>
+__global__ void __launch_bounds__(kWave* kSegs) ckm_simulate_kernel(SimArgs a) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int seg = kSegs == 1 ? 0 : uniform((int)threadIdx.x / kWave);
+  // the blocks that read one tile come 8 apart: blocks go to the 8 XCDs in
+  // turn, so these share an L2
+  const int id = blockIdx.x, sub = (id >> 3) & (kSubs - 1), item = (id / (8 * kSubs)) * 8 + (id & 7);
+  if (item >= a.t.tiles * a.groups) return;
+  const int tile = a.t.tiles - 1 - item / a.groups;   // the longest start first
+  const int group = item % a.groups;
+  const TileBufs b(a.t, group, tile, lane);
+  const int recs = a.tile_rec[tile];
+  const int r0 = (int)((int64_t)recs * seg / kSegs), r1 = (int)((int64_t)recs * (seg + 1) / kSegs);
+  SimStages x;
+#pragma unroll
+  for (int j = 0; j < kSub; ++j) {
+    x.U[j] = 0.0;
+    x.top[j] = -INFINITY;
+    x.U0[j] = 0.0;
+  }
+  uint64_t cost_lo = 0, cost_hi = 0;
+  if (r0 < r1) {
+    switch (sub) {
+      case 0: sim_scan<0>(a, x, cost_lo, cost_hi, b, r0, r1); break;
+      case 1: sim_scan<1>(a, x, cost_lo, cost_hi, b, r0, r1); break;
+      case 2: sim_scan<2>(a, x, cost_lo, cost_hi, b, r0, r1); break;
+      default: sim_scan<3>(a, x, cost_lo, cost_hi, b, r0, r1); break;
+    }
+  }
+  const int k = group * kWave + lane;
+  const uint64_t cost = cost_lo + (cost_hi << 32);
+  if (k < a.K && cost) atomicAdd(reinterpret_cast<unsigned long long*>(a.cost) + k, (unsigned long long)cost);
+  if constexpr (kSegs > 1) {
+    // a part's peak counts from the memory that the parts before it leave
+    __shared__ double part[kSegs][2 * kSub][kWave];
+#pragma unroll
+    for (int j = 0; j < kSub; ++j) {
+      part[seg][j][lane] = x.U[j];
+      part[seg][kSub + j][lane] = x.U0[j];
+    }
+    __syncthreads();
+    for (int s = 0; s < kSegs; ++s) {
+      if (s == seg) continue;
+#pragma unroll
+      for (int j = 0; j < kSub; ++j) x.U0[j] += part[s][kSub + j][lane];
+      if (s > seg) continue;
+#pragma unroll
+      for (int j = 0; j < kSub; ++j) x.top[j] += part[s][j][lane];
+    }
+  }
+  if (r0 >= r1) return;
+  int64_t peak = INT64_MIN;
+#pragma unroll
+  for (int j = 0; j < kSub; ++j) {
+    const int bit = kSub * sub + j;
+    if (kTile * tile + bit < a.t.n) {
+      const int64_t p = (int64_t)(a.base + ldexp(x.U0[j] + x.top[j], 1074 - bit));
+      peak = p > peak ? p : peak;
+    }
+  }
+  if (k < a.K) atomicMax(reinterpret_cast<long long*>(a.peak) + k, (long long)peak);
+}
+
+// ---------------------------------------------------------------------------
+// Best candidate's R rows from its R tiles: block per tile and 256 nodes, lane
+// = node.
+__global__ void __launch_bounds__(256) ckm_best_tiles_kernel(TileArgs t, int32_t words64,
+                                                             const int32_t* __restrict__ best_k,
+                                                             uint64_t* __restrict__ R_rows) {
+  const int tile = blockIdx.x, v = blockIdx.y * 256 + threadIdx.x;
+  const int bk = best_k[0];
+  if (v >= kWave * words64) return;               // whole waves
+  uint32_t w = 0;
+  if (bk >= 0 && v < min(t.n, kTile * (tile + 1)))   // nodes above compute nothing in these stages
+    w = *reinterpret_cast<const uint32_t*>(t.rtiles + (size_t)(bk / kWave) * t.r_bytes + rtile_off(t.rbase, tile) +
+                                           t.rbase + node_off(v) + 4 * (bk & (kWave - 1)));
+  for (int j = 0; j < kTile && kTile * tile + j < t.n; ++j) {
+    const uint64_t row = __ballot((w >> j) & 1u);
+    if ((threadIdx.x & (kWave - 1)) == 0) R_rows[(size_t)(kTile * tile + j) * words64 + v / kWave] = row;
+  }
+}
+
+}  // namespace
+
+// ---------------------------------------------------------------------------
+static TileArgs tile_args(const ckm_graph& g, const Layout& L, char* work) {
+  TileArgs t;
+  t.n = g.n;
+  t.tiles = (g.n + kTile - 1) / kTile;
+  t.rbase = g.tile.rbase;
+  t.s_bytes = stile_off(t.tiles);
+  t.r_bytes = rtile_off(t.rbase, t.tiles);
+  t.stiles = work + L.rows_off;
+  t.rtiles = work + L.rrows_off;
+  return t;
+}
+
+hipError_t launch_tiles(const ckm_graph& g, const Layout& L, int32_t K, char* work, hipStream_t stream) {
+  const int32_t groups = (K + kWave - 1) / kWave;
+  ClosureArgs c;
+  c.t = tile_args(g, L, work);
+  c.desc = g.tile.d_desc;
+  c.far = g.tile.d_far;
+  c.far_more = (cptr<uint32_t>)g.tile.d_far_more;
+  c.near_more = (cptr<uint32_t>)g.tile.d_near_more;
+  hipLaunchKernelGGL(ckm_closure_kernel, dim3(groups, c.t.tiles), dim3(kWave * (1 + kPrep)), 0, stream, c);
+  if (g.tile.nhub)
+    hipLaunchKernelGGL(ckm_hub_kernel, dim3(groups, c.t.tiles, g.tile.nhub), dim3(kWave), 0, stream, c.t,
+                       (cptr<int32_t>)g.tile.d_hub_ptr, (cptr<HubUser>)g.tile.d_hub);
+  SimArgs s;
+  s.t = c.t;
+  s.K = K;
+  s.groups = groups;
+  s.base = (double)g.base;
+  s.ops = (cptr<u64x8>)g.tile.d_ops;
+  s.refs = (cptr<u32x16>)g.tile.d_refs;
+  s.more = (cptr<SimMore>)g.tile.d_more;
+  s.more_off = (cptr<uint32_t>)g.tile.d_more_off;
+  s.tile_rec = (cptr<int32_t>)g.tile.d_tile_rec;
+  s.peak = reinterpret_cast<int64_t*>(work + L.part_peak_off);
+  s.cost = reinterpret_cast<int64_t*>(work + L.part_cost_off);
+  const int64_t items = (int64_t)groups * c.t.tiles;
+  const dim3 grid((unsigned)((items + 7) / 8 * 8 * kSubs));
+  if (items >= 4096)
+    hipLaunchKernelGGL(ckm_simulate_kernel<2>, grid, dim3(2 * kWave), 0, stream, s);
+  else if (items >= 1024)
+    hipLaunchKernelGGL(ckm_simulate_kernel<4>, grid, dim3(4 * kWave), 0, stream, s);
+  else
+    hipLaunchKernelGGL(ckm_simulate_kernel<8>, grid, dim3(8 * kWave), 0, stream, s);
+  return hipGetLastError();
+}
+
+hipError_t launch_best_tiles(const ckm_graph& g, const Layout& L, const int32_t* d_best_k, uint64_t* d_best_R,
+                             char* work, hipStream_t stream) {
+  const TileArgs t = tile_args(g, L, work);
+  const int32_t words64 = L.row_words / 2;
+  hipLaunchKernelGGL(ckm_best_tiles_kernel, dim3(t.tiles, (kWave * words64 + 255) / 256), dim3(256), 0, stream, t,
+                     words64, d_best_k, d_best_R);
+  return hipGetLastError();
+}
+
+}  // namespace ckm

@@ -449,7 +449,8 @@ static ckm_status graph_create(int32_t n, const int32_t* dep_ptr, const int32_t*
   const size_t off_mrec = align256(off_rec + (size_t)n * ckm::kNodeRecBytes);
   // the tile path's tables (its sums are binary64)
   ckm::TileTables tt;
-  if (!wide) ckm::build_tiles(n, bytes, cost, dp.data(), di.data(), up.data(), ui.data(), tt);
+  const bool tiles =
+      !wide && ckm::build_tiles(n, bytes, cost, dp.data(), di.data(), up.data(), ui.data(), tt);
   size_t tile_end = off_mrec;
   const auto place = [&](size_t b) {
     const size_t at = tile_end;
@@ -459,7 +460,6 @@ static ckm_status graph_create(int32_t n, const int32_t* dep_ptr, const int32_t*
   const size_t off_desc = place(tt.desc.size() * 4), off_nmore = place(tt.near_more.size() * 4),
                off_far = place(tt.far.size() * 4), off_fmore = place(tt.far_more.size() * 4), off_ops = place(tt.ops.size() * sizeof(ckm::SimOps)),
                off_refs = place(tt.refs.size() * sizeof(ckm::SimRefs)),
-               off_more = place(tt.more.size() * sizeof(ckm::SimMore)), off_moff = place(tt.more_off.size() * 4),
                off_trec = place(tt.tile_rec.size() * 4), off_hptr = place(tt.hub_ptr.size() * 4),
                off_hub = place(tt.hub.size() * sizeof(ckm::HubUser));
   const size_t total = tile_end;
@@ -473,8 +473,6 @@ static ckm_status graph_create(int32_t n, const int32_t* dep_ptr, const int32_t*
   copy(off_fmore, tt.far_more);
   copy(off_ops, tt.ops);
   copy(off_refs, tt.refs);
-  copy(off_more, tt.more);
-  copy(off_moff, tt.more_off);
   copy(off_trec, tt.tile_rec);
   copy(off_hptr, tt.hub_ptr);
   copy(off_hub, tt.hub);
@@ -527,7 +525,7 @@ static ckm_status graph_create(int32_t n, const int32_t* dep_ptr, const int32_t*
   g->d_dep_idx = reinterpret_cast<const int32_t*>(base + off_di);
   g->d_dep_upos = reinterpret_cast<const int32_t*>(base + off_uo);
   g->d_recs = base + off_rec;
-  if (!wide) {
+  if (tiles) {
     g->tile.on = true;
     g->tile.rbase = tt.rbase;
     g->tile.nhub = tt.nhub;
@@ -537,8 +535,6 @@ static ckm_status graph_create(int32_t n, const int32_t* dep_ptr, const int32_t*
     g->tile.d_far_more = reinterpret_cast<const uint32_t*>(base + off_fmore);
     g->tile.d_ops = base + off_ops;
     g->tile.d_refs = base + off_refs;
-    g->tile.d_more = base + off_more;
-    g->tile.d_more_off = reinterpret_cast<const uint32_t*>(base + off_moff);
     g->tile.d_tile_rec = reinterpret_cast<const int32_t*>(base + off_trec);
     g->tile.d_hub_ptr = reinterpret_cast<const int32_t*>(base + off_hptr);
     g->tile.d_hub = base + off_hub;

@@ -14,7 +14,7 @@ namespace ckm {
 struct SyncCache;  // buffers and stream of the synchronous entry points (ckm_host.cpp)
 
 // The tile path's tables on the device (TileTables, ckm_tiles.h); on is false
-// for the graphs that do not take it (wide ones).
+// for the graphs that do not take it (wide or very dense ones).
 struct TileGraph {
   bool on = false;
   uint32_t rbase = 0;
@@ -25,8 +25,6 @@ struct TileGraph {
   const uint32_t* d_far_more = nullptr;
   const void* d_ops = nullptr;
   const void* d_refs = nullptr;
-  const void* d_more = nullptr;
-  const uint32_t* d_more_off = nullptr;
   const int32_t* d_tile_rec = nullptr;
   const int32_t* d_hub_ptr = nullptr;
   const void* d_hub = nullptr;
@@ -186,11 +184,8 @@ hipError_t launch_max_batch(const ckm_graph& g, const Layout& L, int32_t K, int6
 hipError_t launch_evaluate(const ckm_graph& g, const Layout& L, int32_t K, uint64_t seed,
                            uint32_t flags, const Plan& plan, int src, const uint64_t* s_user, char* work,
                            hipStream_t stream);
-// Tile path (ckm_tiles.hip): the evaluate of all candidates on their S tiles,
-// and the best candidate's R rows.
+// Tile path (ckm_tiles.hip): the evaluate of all candidates on their S tiles.
 hipError_t launch_tiles(const ckm_graph& g, const Layout& L, int32_t K, char* work, hipStream_t stream);
-hipError_t launch_best_tiles(const ckm_graph& g, const Layout& L, const int32_t* d_best_k, uint64_t* d_best_R,
-                             char* work, hipStream_t stream);
 hipError_t launch_select(const ckm_graph& g, const Layout& L, int32_t K, uint64_t seed,
                          int64_t budget, uint32_t flags, int64_t* d_peak,
                          int64_t* d_cost, uint8_t* d_feasible, int32_t* d_best_k,

@@ -1387,12 +1387,34 @@ __global__ void __launch_bounds__(256) ckm_batch_argmax_kernel(int32_t nblocks, 
   }
 }
 
+// The tile path's R words (rbase and r_bytes as in its kernels).
+struct RTiles {
+  const char* rtiles;
+  uint32_t rbase;
+  size_t r_bytes;
+  uint64_t* __restrict__ R_rows;   // null: none are gathered
+};
+// Best candidate's R rows from its R tiles: block (tile, 256 nodes), lane = node.
+__device__ __forceinline__ void best_r_tiles(const RTiles& t, int n, int words64, int item, int bk) {
+  const int vblocks = (kWave * words64 + 255) / 256, tile = item / vblocks, v = item % vblocks * 256 + (int)threadIdx.x;
+  if (32 * tile >= n || v >= kWave * words64) return;   // whole waves
+  uint32_t w = 0;
+  if (bk >= 0 && v < min(n, 32 * (tile + 1)))   // nodes above compute nothing in these stages
+    w = *reinterpret_cast<const uint32_t*>(t.rtiles + (size_t)(bk / kWave) * t.r_bytes + rtile_off(t.rbase, tile) +
+                                           t.rbase + (size_t)v * 256 + 4 * (bk & (kWave - 1)));
+  for (int j = 0; j < 32 && 32 * tile + j < n; ++j) {
+    const uint64_t row = __ballot((w >> j) & 1u);
+    if ((threadIdx.x & (kWave - 1)) == 0) t.R_rows[(size_t)(32 * tile + j) * words64 + v / kWave] = row;
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Best candidate's S rows: thread per (row r, 32-bit word w). Output rows
 // have row_words words; words with no node (32w >= n) are zero. rank: the
 // threshold family (q holds keys), else randomized or deterministic rounding.
 // With R_rows, the same threads also gather the best candidate's R rows
-// from the R rows the evaluate kernel kept (words above r/32 are zero).
+// from the R rows the evaluate kernel kept (words above r/32 are zero). Block
+// rows past n gather them from the tile path's R tiles.
 __global__ void __launch_bounds__(256) ckm_best_rows_kernel(const uint32_t* __restrict__ q,
                                                             const uint32_t* __restrict__ det,
                                                             int32_t n, int32_t ldq, int32_t det_words,
@@ -1402,11 +1424,15 @@ __global__ void __launch_bounds__(256) ckm_best_rows_kernel(const uint32_t* __re
                                                             const int32_t* __restrict__ best_k,
                                                             uint32_t* __restrict__ S_rows,
                                                             const uint32_t* __restrict__ rrows, int32_t kpad,
-                                                            uint32_t* __restrict__ R_rows) {
-  const int r = blockIdx.y;
+                                                            uint32_t* __restrict__ R_rows, RTiles tiles) {
+  const int bk = best_k[0];
+  const int r = S_rows ? (int)blockIdx.y : (int)blockIdx.y + n;
+  if (r >= n) {
+    best_r_tiles(tiles, n, row_words / 2, (r - n) * (int)gridDim.x + (int)blockIdx.x, bk);
+    return;
+  }
   const int w = blockIdx.x * blockDim.x + threadIdx.x;
   if (w >= row_words) return;
-  const int bk = best_k[0];
   if (R_rows) {
     uint32_t rw = 0;
     if (bk >= 0 && w <= (r >> 5)) rw = rrows[(row_base(r) + w) * (size_t)kpad + bk];
@@ -1663,24 +1689,27 @@ __device__ __forceinline__ void philox_block(const PhiloxRow& pr, uint32_t b, ui
 
 // Randomized rounding: bit [u_{k,t,i} < q[t][i]] (the draws of round_word);
 // candidate 0 takes the deterministic bits under CKM_F_DET0. One Philox output
-// serves 8 nodes, which are a wave's; the four waves of a block share the lines
-// of the thresholds.
+// serves 8 nodes, which are a wave's, with kStages of the tile's stages; waves
+// that share the nodes join their bytes in LDS.
 constexpr int kItemWaves = 4;
-__global__ void __launch_bounds__(kWave* kItemWaves) ckm_round_tiles_kernel(
+template <int kStages>
+__global__ void __launch_bounds__(kWave* kItemWaves* 32 / kStages) ckm_round_tiles_kernel(
     const uint32_t* __restrict__ q, const uint32_t* __restrict__ det, int32_t n, int32_t ldq, int32_t det_words,
     uint32_t key0, uint32_t key1, uint32_t det0, size_t group_bytes, char* __restrict__ stiles, Totals tot) {
+  constexpr int kParts = 32 / kStages;
   const int group = blockIdx.x;
   clear_totals(tot, group);
   int T, nb;
   tile_item(blockIdx.y, T, nb);
-  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave), m = kItemWaves * nb + wave;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
+  const int m = kItemWaves * nb + wave % kItemWaves, part = wave / kItemWaves;
   const uint32_t lane = threadIdx.x & (kWave - 1), k = (uint32_t)(group * kWave) + lane;
-  const bool det_here = det0 && group == 0;
   uint32_t w[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) w[i] = 0u;
-  // stages above the block's first node, from the last one down
-  const int last = (32 * T + 31 < n ? 32 * T + 31 : n - 1), first = 8 * m + 1 > 32 * T ? 8 * m + 1 : 32 * T;
+  // the part's stages above the nodes' first, from the last one down
+  const int t0 = 32 * T + kStages * part;
+  const int last = t0 + kStages - 1 < n ? t0 + kStages - 1 : n - 1, first = 8 * m + 1 > t0 ? 8 * m + 1 : t0;
 #pragma unroll 2
   for (int t = last; t >= first; --t) {
     const cptr<uint32_t> qrow = as_const(q) + (size_t)t * ldq + 8 * m;
@@ -1689,20 +1718,34 @@ __global__ void __launch_bounds__(kWave* kItemWaves) ckm_round_tiles_kernel(
     for (int i = 0; i < 8; ++i) qv[i] = qrow[i];
     philox_block(philox_row((uint32_t)t, k, key0), (uint32_t)m, key0, key1, x);
     shift_in8(w, x, qv);
-    if (det_here) {
-      const uint32_t dw = as_const(det)[(size_t)t * det_words + nb] >> (8 * wave);
-      if (lane == 0) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) w[i] = (w[i] & ~1u) | ((dw >> i) & 1u);
-      }
-    }
   }
   // bits of the stages below the first (zeros)
   if (last >= first) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) w[i] <<= first - 32 * T;
+    for (int i = 0; i < 8; ++i) w[i] <<= first - t0;
   }
-  store_tile(stiles, group_bytes, group, T, 8 * m, w);
+  if (det0 && group == 0) {
+    // lane j has the bits of stage t0 + j: a node's word is a ballot
+    const int t = t0 + (int)lane;
+    const uint32_t dw = (int)lane < kStages && t < n ? det[(size_t)t * det_words + nb] >> (8 * (wave % kItemWaves)) : 0u;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const uint32_t bits = (uint32_t)__ballot((dw >> i) & 1u);
+      if (lane == 0) w[i] = bits;
+    }
+  }
+  if constexpr (kParts == 1) {
+    store_tile(stiles, group_bytes, group, T, 8 * m, w);
+  } else {
+    static_assert(kParts == 4, "a part is a byte");
+    __shared__ uint32_t words[32][kWave];
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      reinterpret_cast<uint8_t*>(&words[8 * (wave % kItemWaves) + i][lane])[part] = (uint8_t)w[i];
+    __syncthreads();
+    const uint32_t out[2] = {words[2 * wave][lane], words[2 * wave + 1][lane]};
+    store_tile(stiles, group_bytes, group, T, 32 * nb + 2 * wave, out);
+  }
 }
 
 // Threshold candidates: bit [rank_k < key[t][i]], the threshold test of
@@ -1849,6 +1892,8 @@ static unsigned tile_items(int32_t n) {
 
 static bool use_tiles(const ckm_graph& g, const Layout& L) { return L.rows_on && g.tile.on; }
 
+constexpr int64_t kRoundBig = 1024;
+
 hipError_t launch_round_rows(const ckm_graph& g, const Layout& L, int32_t K, uint64_t seed, uint32_t flags,
                              char* work, hipStream_t stream) {
   return launch_round_rows(g, L, K, seed, flags, false, work, stream);
@@ -1859,10 +1904,17 @@ hipError_t launch_round_rows(const ckm_graph& g, const Layout& L, int32_t K, uin
   if (!L.rows_on) return hipSuccess;
   if (use_tiles(g, L)) {
     const Totals tot{clear ? at<int64_t>(work, L.part_peak_off) : nullptr, at<int64_t>(work, L.part_cost_off), K};
-    hipLaunchKernelGGL(ckm_round_tiles_kernel, dim3(groups_of(K), tile_items(g.n)), dim3(kWave * kItemWaves), 0, stream,
-                       at<const uint32_t>(work, L.q_off), at<const uint32_t>(work, L.det_off), g.n, L.ldq,
-                       L.det_words, (uint32_t)(seed & 0xFFFFFFFFu), (uint32_t)(seed >> 32),
-                       (flags & CKM_F_DET0) ? 1u : 0u, stile_off((g.n + 31) / 32), work + L.rows_off, tot);
+    const dim3 grid(groups_of(K), tile_items(g.n));
+    const auto launch = [&](auto kernel, int waves) {
+      hipLaunchKernelGGL(kernel, grid, dim3(kWave * waves), 0, stream, at<const uint32_t>(work, L.q_off),
+                         at<const uint32_t>(work, L.det_off), g.n, L.ldq, L.det_words, (uint32_t)(seed & 0xFFFFFFFFu),
+                         (uint32_t)(seed >> 32), (flags & CKM_F_DET0) ? 1u : 0u, stile_off((g.n + 31) / 32),
+                         work + L.rows_off, tot);
+    };
+    if ((int64_t)grid.x * grid.y < kRoundBig)
+      launch(ckm_round_tiles_kernel<8>, 4 * kItemWaves);
+    else
+      launch(ckm_round_tiles_kernel<32>, kItemWaves);
     return hipGetLastError();
   }
   const int32_t kpad = ((K + kWave - 1) / kWave) * kWave;
@@ -2035,17 +2087,26 @@ hipError_t launch_select(const ckm_graph& g, const Layout& L, int32_t K, uint64_
   }
   // With the row arrays the evaluate stage kept every candidate's R rows, so
   // the best R is a gather; otherwise Algorithm 2 runs again for it.
+  RTiles tiles = {};
   if (use_tiles(g, L) && d_best_R) {
-    const hipError_t e = launch_best_tiles(g, L, d_best_k, d_best_R, work, stream);
-    if (e != hipSuccess) return e;
+    tiles.rtiles = work + L.rrows_off;
+    tiles.rbase = g.tile.rbase;
+    tiles.r_bytes = rtile_off(g.tile.rbase, (g.n + 31) / 32);
+    tiles.R_rows = d_best_R;
     d_best_R = nullptr;
   }
   const bool gather_R = d_best_R && L.rows_on;
   const int32_t kpad = (int32_t)(groups_of(K) * kWave);
   const dim3 rows_grid((L.row_words + 255) / 256, g.n);
   uint32_t* R_out = reinterpret_cast<uint32_t*>(d_best_R);
+  // block rows of the tile gather
+  const unsigned tile_blocks = (unsigned)((g.n + 31) / 32 * ((L.row_words * 32 + 255) / 256));
+  const unsigned tile_rows = tiles.R_rows ? (tile_blocks + rows_grid.x - 1) / rows_grid.x : 0u;
   if (src == kSrcUser) {
-    if (gather_R) {
+    if (tiles.R_rows) {
+      hipLaunchKernelGGL(ckm_best_rows_kernel, dim3(rows_grid.x, tile_rows), dim3(256), 0, stream, nullptr, nullptr, g.n,
+                         0, 0, L.row_words, 0u, 0u, 0u, nullptr, d_best_k, nullptr, nullptr, 0, nullptr, tiles);
+    } else if (gather_R) {
       hipLaunchKernelGGL(ckm_best_rrows_kernel, rows_grid, dim3(256), 0, stream,
                          at<const uint32_t>(work, L.rrows_off), kpad, L.row_words, d_best_k, R_out);
     } else if (d_best_R) {
@@ -2053,15 +2114,16 @@ hipError_t launch_select(const ckm_graph& g, const Layout& L, int32_t K, uint64_
                                     (size_t)g.n * L.row_words, R_out, stream);
       if (e != hipSuccess) return e;
     }
-  } else if (d_best_S || d_best_R) {
+  } else if (d_best_S || d_best_R || tiles.R_rows) {
     // the S rows: output, and the closure's input when there is no gather
-    uint32_t* srows = d_best_S ? reinterpret_cast<uint32_t*>(d_best_S) : at<uint32_t>(work, L.srows_off);
-    hipLaunchKernelGGL(ckm_best_rows_kernel, rows_grid, dim3(256), 0, stream,
+    uint32_t* srows = d_best_S ? reinterpret_cast<uint32_t*>(d_best_S)
+                      : d_best_R ? at<uint32_t>(work, L.srows_off) : nullptr;
+    hipLaunchKernelGGL(ckm_best_rows_kernel, dim3(rows_grid.x, (srows ? g.n : 0) + tile_rows), dim3(256), 0, stream,
                        at<const uint32_t>(work, L.q_off), at<const uint32_t>(work, L.det_off), g.n,
                        L.ldq, L.det_words, L.row_words, (uint32_t)(seed & 0xFFFFFFFFu),
                        (uint32_t)(seed >> 32), (flags & CKM_F_DET0) ? 1u : 0u,
                        src == kSrcThreshold ? at<const uint32_t>(work, L.thr_rank_off) : nullptr, d_best_k,
-                       srows, at<const uint32_t>(work, L.rrows_off), kpad, gather_R ? R_out : nullptr);
+                       srows, at<const uint32_t>(work, L.rrows_off), kpad, gather_R ? R_out : nullptr, tiles);
     if (d_best_R && !gather_R) {
       hipError_t e = launch_closure(g, L, d_best_k, static_cast<const uint32_t*>(srows), (size_t)0, R_out, stream);
       if (e != hipSuccess) return e;

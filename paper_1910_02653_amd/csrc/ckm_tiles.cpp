@@ -5,7 +5,7 @@
 
 namespace ckm {
 
-void build_tiles(int32_t n, const int64_t* M, const int64_t* C, const int32_t* dep_ptr, const int32_t* dep_idx,
+bool build_tiles(int32_t n, const int64_t* M, const int64_t* C, const int32_t* dep_ptr, const int32_t* dep_idx,
                  const int32_t* user_ptr, const int32_t* user_idx, TileTables& T) {
   T = TileTables();
   T.n = n;
@@ -14,11 +14,13 @@ void build_tiles(int32_t n, const int64_t* M, const int64_t* C, const int32_t* d
   // hub words: their places first (they set rbase), then their tables
   uint32_t words = 0;
   std::vector<uint32_t> first_word(n, 0);
+  if (n >= kMaxSlots) return false;
   for (int32_t i = 0; i < n; ++i) {
     const int32_t m = user_ptr[i + 1] - user_ptr[i];
     if (m <= kHubUsers) continue;
     first_word[i] = words;
     words += (uint32_t)(m - 3);
+    if (1 + (int64_t)words + kTile * (int64_t)T.tiles > kMaxSlots) return false;
   }
   T.rbase = node_off((int32_t)(1 + words));
   const auto word_off = [](uint32_t x) { return node_off((int32_t)(1 + x)); };
@@ -89,39 +91,28 @@ void build_tiles(int32_t n, const int64_t* M, const int64_t* C, const int32_t* d
   for (int32_t v = 0; v < n; ++v) {
     const int32_t nd = dep_ptr[v + 1] - dep_ptr[v];
     for (int32_t a = 0; a < std::max(nd, 1); a += 2) {
-      SimOps o{0.0, 0, 0.0, 0.0};
-      SimRefs r{node_off(v), node_off(v), {0, 0}, node_off(v), {0, 0}, 0};
+      SimOps o{};
+      SimRefs r{};
+      const auto slot = [](uint32_t off) { return (uint16_t)(off / kSlotBytes); };
+      r.v = r.s[0] = r.s[1] = (uint16_t)v;
       if (a == 0) {
         o.M = (double)M[v];
-        o.C = (uint64_t)C[v];
+        r.C = (uint64_t)C[v];
       }
-      SimMore more{(uint32_t)T.more_off.size(), 0, 0, 0};
       for (int k = 0; k < 2 && a + k < nd; ++k) {
         const int32_t i = dep_idx[dep_ptr[v] + a + k];
         (k ? o.M1 : o.M0) = (double)M[i];
-        (k ? r.s1 : r.s0) = node_off(i);
-        uint32_t* u = k ? r.u1 : r.u0;
+        r.s[k] = (uint16_t)i;
         const int32_t* b = user_idx + user_ptr[i];
         const int32_t* e = user_idx + user_ptr[i + 1];
         const int32_t* above = std::upper_bound(b, e, v);
         const int32_t na = (int32_t)(e - above);
         if (e - b > kHubUsers && na >= 3) {
-          u[0] = word_off(first_word[i] + (uint32_t)(na - 3));
-          continue;
+          r.u[k][0] = slot(word_off(first_word[i] + (uint32_t)(na - 3)));
+        } else {
+          for (int32_t x = 0; x < na; ++x) r.u[k][x] = slot(T.rbase + node_off(above[x]));   // at most kHubUsers - 1
+          if (na > 2) r.more = 1;
         }
-        for (int32_t x = 0; x < na; ++x) {
-          const uint32_t off = T.rbase + node_off(above[x]);
-          if (x < 2) {
-            u[x] = off;
-          } else {
-            T.more_off.push_back(off);
-            ++(k ? more.count1 : more.count0);
-          }
-        }
-      }
-      if (more.count0 + more.count1) {
-        T.more.push_back(more);
-        r.more = (uint32_t)T.more.size();
       }
       T.ops.push_back(o);
       T.refs.push_back(r);
@@ -130,9 +121,12 @@ void build_tiles(int32_t n, const int64_t* M, const int64_t* C, const int32_t* d
   }
   T.nrec = (int32_t)T.ops.size();
   for (int32_t k = 0; k < T.tiles; ++k) T.tile_rec.push_back(rec_end[std::min(kTile * (k + 1), n) - 1]);
-  // pairs of records are read together
-  T.ops.push_back({0.0, 0, 0.0, 0.0});
-  T.refs.push_back({0, 0, {0, 0}, 0, {0, 0}, 0});
+  // pairs of records are read together, two pairs ahead
+  for (int k = 0; k < 6; ++k) {
+    T.ops.push_back(SimOps{});
+    T.refs.push_back(SimRefs{});
+  }
+  return true;
 }
 
 }  // namespace ckm

@@ -52,24 +52,24 @@ constexpr int kFarNodes = 16, kFarDwords = 64;
 // has further records of two dependencies each right after it.
 struct SimOps {
   double M;            // M_v (0 past a node's first record)
-  uint64_t C;          // C_v (0 past a node's first record)
   double M0, M1;       // sizes of the dependencies (0 when absent)
+  double pad;
 };
+// Its words, as offsets in slots (node_off / 256): S tile slots of the node and
+// the dependencies, R tile slots of the dependencies' users above v (0 when
+// absent).
 struct SimRefs {
-  uint32_t v;          // S tile byte offset of the node
-  uint32_t s0;         // S tile byte offset of dependency 0
-  uint32_t u0[2];      // R tile byte offsets of two of its users above v (0 when absent)
-  uint32_t s1, u1[2];  // the same for dependency 1
-  uint32_t more;       // 0, or 1 + index of a SimMore
+  uint16_t v, s[2];
+  uint16_t u[2][4];
+  uint16_t more;       // u[.][2] present
+  uint64_t C;          // C_v (0 past a node's first record)
 };
-struct SimMore {       // users beyond the two: offsets at more_off[first ..], count0 of dependency 0, then count1
-  uint32_t first, count0, count1, pad;
-};
+constexpr int32_t kMaxSlots = 65536;         // of an R tile, for the tile path
 
 // Nodes with more than kHubUsers users: for each user with three or more above
 // it, the OR of those above (a hub word) is made once, after the closure, and
 // stands in for them.
-constexpr int kHubUsers = 8;
+constexpr int kHubUsers = 5;
 struct HubUser {
   uint32_t r;          // R tile byte offset of the user
   uint32_t x;          // R tile byte offset of the hub word of the users above it (0: none)
@@ -84,8 +84,6 @@ struct TileTables {
   std::vector<uint32_t> far_more;       // R tile byte offsets
   std::vector<SimOps> ops;              // nrec
   std::vector<SimRefs> refs;            // nrec
-  std::vector<SimMore> more;
-  std::vector<uint32_t> more_off;
   std::vector<int32_t> tile_rec;        // records of the nodes below each tile's end
   std::vector<int32_t> hub_ptr;         // nhub + 1
   std::vector<HubUser> hub;             // users in decreasing order
@@ -93,7 +91,9 @@ struct TileTables {
 
 // S tile byte offset of node v's words (R tiles: + rbase).
 constexpr uint32_t node_off(int32_t v) { return (uint32_t)v * (uint32_t)kSlotBytes; }
-void build_tiles(int32_t n, const int64_t* M, const int64_t* C, const int32_t* dep_ptr, const int32_t* dep_idx,
+// False when the graph does not take the tile path (an R tile with its hub words
+// has more than kMaxSlots slots).
+bool build_tiles(int32_t n, const int64_t* M, const int64_t* C, const int32_t* dep_ptr, const int32_t* dep_idx,
                  const int32_t* user_ptr, const int32_t* user_idx, TileTables& T);
 
 }  // namespace ckm

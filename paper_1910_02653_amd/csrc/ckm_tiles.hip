@@ -324,231 +324,204 @@ __global__ void __launch_bounds__(kWave) ckm_hub_kernel(TileArgs t, cptr<int32_t
 // wave per (group, 8 stages of a tile, part of the tile's records). Before
 // node v is computed the memory is U_{t,0} + U; computing it adds M_v (the
 // peak is taken there), then the dependencies that FREE releases after it
-// leave. All sums are binary64 integers below 2^53, exact in any order; stage
-// j of the tile counts in units of 2^(j - 1074), so that its bit of a word is
-// the unit itself (denormals are exact and run at full rate).
+// leave. All sums are binary64 integers below 2^53, exact in any order; a
+// wave's stage j counts U in units of 2^(j - 1074), so that its bit of a word
+// is the unit itself (denormals are exact and run at full rate).
 struct SimArgs {
   TileArgs t;
   int32_t K, groups;
   double base;                      // M_in + 2 M_param
   cptr<u64x8> ops;                  // pairs of SimOps
   cptr<u32x16> refs;                // pairs of SimRefs
-  cptr<SimMore> more;
-  cptr<uint32_t> more_off;
   cptr<int32_t> tile_rec;
   int64_t* __restrict__ peak;
   int64_t* __restrict__ cost;
 };
 
-constexpr int kSub = 8;             // stages per wave
-constexpr int kSubs = kTile / kSub;
-
-struct SimStages {
-  double U[kSub], top[kSub], U0[kSub];   // relative to the stage's start; its peak; U_{t,0}
+struct SimStages8 {
+  double U[8], top[8], U0[8];       // relative to the stage's start; its highest value; the start
 };
 
-// Two stages (bits a, b) of one record: U0 += S M; U += R M, the peak, then
-// U -= F M0 + G M1. Each masked update takes its bit into the low word of a
-// binary64 whose high word is 0.
-template <int kBit>
-__device__ __forceinline__ void sim_pair(SimStages& x, int i, uint32_t R, uint32_t S, uint32_t F, uint32_t G, double M,
-                                         double M0, double M1) {
-  constexpr int a = (int)(1u << kBit), b = (int)(2u << kBit);
-  asm("v_and_b32 v8, %[a], %[S]\n\t"
-      "v_mov_b32 v9, 0\n\t"
-      "v_and_b32 v10, %[b], %[S]\n\t"
-      "v_mov_b32 v11, 0\n\t"
-      "v_fma_f64 %[z0], v[8:9], %[M], %[z0]\n\t"
-      "v_fma_f64 %[z1], v[10:11], %[M], %[z1]\n\t"
-      "v_and_b32 v8, %[a], %[R]\n\t"
-      "v_and_b32 v10, %[b], %[R]\n\t"
-      "v_fma_f64 %[u0], v[8:9], %[M], %[u0]\n\t"
-      "v_fma_f64 %[u1], v[10:11], %[M], %[u1]\n\t"
-      "v_and_b32 v8, %[a], %[F]\n\t"
-      "v_and_b32 v10, %[b], %[F]\n\t"
-      "v_max_f64 %[t0], %[t0], %[u0]\n\t"
-      "v_max_f64 %[t1], %[t1], %[u1]\n\t"
-      "v_fma_f64 %[u0], v[8:9], -%[M0], %[u0]\n\t"
-      "v_fma_f64 %[u1], v[10:11], -%[M0], %[u1]\n\t"
-      "v_and_b32 v8, %[a], %[G]\n\t"
-      "v_and_b32 v10, %[b], %[G]\n\t"
-      "v_fma_f64 %[u0], v[8:9], -%[M1], %[u0]\n\t"
-      "v_fma_f64 %[u1], v[10:11], -%[M1], %[u1]"
-      : [u0] "+v"(x.U[i]), [u1] "+v"(x.U[i + 1]), [t0] "+v"(x.top[i]), [t1] "+v"(x.top[i + 1]), [z0] "+v"(x.U0[i]),
-        [z1] "+v"(x.U0[i + 1])
-      : [R] "v"(R), [S] "v"(S), [F] "v"(F), [G] "v"(G), [M] "s"(M), [M0] "s"(M0), [M1] "s"(M1), [a] "i"(a), [b] "i"(b)
-      : "v8", "v9", "v10", "v11");
-}
-template <int kFirst, int kPair = 0>
-__device__ __forceinline__ void sim_stages(SimStages& x, uint32_t R, uint32_t S, uint32_t F, uint32_t G, double M,
-                                           double M0, double M1) {
-  if constexpr (kPair < kSub / 2) {
-    sim_pair<kFirst + 2 * kPair>(x, 2 * kPair, R, S, F, G, M, M0, M1);
-    sim_stages<kFirst, kPair + 1>(x, R, S, F, G, M, M0, M1);
-  }
+// One record's masked updates of eight stages, whose bits are b0 .. b7 of the
+// words: U0 += S M, U += R M, the peak, U -= F M0, U -= G M1. Each takes its bit
+// into the low word of a binary64 whose high word is 0. Zero sizes (absent
+// dependencies, records past a node's first) change nothing and are passed by.
+#define CKM_SIM_FMA(acc, i0, i1, b0, b1, W, Msz)                                     \
+  "v_and_b32 v8, " b0 ", %[" W "]\n\tv_and_b32 v10, " b1 ", %[" W "]\n\t"            \
+  "v_fma_f64 %[" acc i0 "], v[8:9], " Msz ", %[" acc i0 "]\n\t"                      \
+  "v_fma_f64 %[" acc i1 "], v[10:11], " Msz ", %[" acc i1 "]\n\t"
+#define CKM_SIM_ADD(i0, i1, b0, b1)                  \
+  CKM_SIM_FMA("z", i0, i1, b0, b1, "S", "%[M]")      \
+  CKM_SIM_FMA("u", i0, i1, b0, b1, "R", "%[M]")      \
+  "v_max_f64 %[t" i0 "], %[t" i0 "], %[u" i0 "]\n\t" \
+  "v_max_f64 %[t" i1 "], %[t" i1 "], %[u" i1 "]\n\t"
+#define CKM_SIM_FREE0(i0, i1, b0, b1) CKM_SIM_FMA("u", i0, i1, b0, b1, "F", "-%[M0]")
+#define CKM_SIM_FREE1(i0, i1, b0, b1) CKM_SIM_FMA("u", i0, i1, b0, b1, "G", "-%[M1]")
+#define CKM_SIM_LOW(X) X("0", "1", "1", "2") X("2", "3", "4", "8") X("4", "5", "16", "32") X("6", "7", "64", "0x80")
+#define CKM_SIM_HIGH(X) \
+  X("0", "1", "0x100", "0x200") X("2", "3", "0x400", "0x800") X("4", "5", "0x1000", "0x2000") X("6", "7", "0x4000", "0x8000")
+#define CKM_SIM_RECORD(EACH, x)                                                                                \
+  asm("v_mov_b32 v9, 0\n\tv_mov_b32 v11, 0\n\t"                                                               \
+      "s_cmp_eq_u64 %[M], 0\n\ts_cbranch_scc1 .Lsim_free%=\n\t" EACH(CKM_SIM_ADD)                            \
+      ".Lsim_free%=:\n\t" EACH(CKM_SIM_FREE0)                                                                 \
+      "s_cmp_eq_u64 %[M1], 0\n\ts_cbranch_scc1 .Lsim_done%=\n\t" EACH(CKM_SIM_FREE1) ".Lsim_done%=:"         \
+      : [u0] "+v"(x.U[0]), [u1] "+v"(x.U[1]), [u2] "+v"(x.U[2]), [u3] "+v"(x.U[3]), [u4] "+v"(x.U[4]),         \
+        [u5] "+v"(x.U[5]), [u6] "+v"(x.U[6]), [u7] "+v"(x.U[7]), [t0] "+v"(x.top[0]), [t1] "+v"(x.top[1]),     \
+        [t2] "+v"(x.top[2]), [t3] "+v"(x.top[3]), [t4] "+v"(x.top[4]), [t5] "+v"(x.top[5]),                    \
+        [t6] "+v"(x.top[6]), [t7] "+v"(x.top[7]), [z0] "+v"(x.U0[0]), [z1] "+v"(x.U0[1]), [z2] "+v"(x.U0[2]),  \
+        [z3] "+v"(x.U0[3]), [z4] "+v"(x.U0[4]), [z5] "+v"(x.U0[5]), [z6] "+v"(x.U0[6]), [z7] "+v"(x.U0[7])     \
+      : [R] "v"(R), [S] "v"(S), [F] "v"(F), [G] "v"(G), [M] "s"(M), [M0] "s"(M0), [M1] "s"(M1)                 \
+      : "v8", "v9", "v10", "v11", "scc")
+
+template <int kSub>
+__device__ __forceinline__ void sim_record(SimStages8 (&x)[kSub / 8], uint32_t R, uint32_t S, uint32_t F, uint32_t G,
+                                           double M, double M0, double M1) {
+  CKM_SIM_RECORD(CKM_SIM_LOW, x[0]);
+  if constexpr (kSub > 8) CKM_SIM_RECORD(CKM_SIM_HIGH, x[1]);
 }
 
-// A record's words, requested one pair of records ahead.
+// A wave's stages' part of a record's words.
 struct SimWords {
-  uint32_t R, S, s0, n0, a0, b0, s1, n1, a1, b1;
+  uint32_t R, S, F, G;
+};
+// What they are made from: requested a pair of records ahead.
+struct SimIn {
+  uint32_t R, S, s0, n0, s1, n1, u[8];
 };
 
-// Records r0 .. r1 - 1. kSubIdx: the wave's stages 8 kSubIdx .. + 7; only the
-// last 8 reach into the next tile's S words. Every fourth record's cost is this
-// wave's to count, over all 32 stages.
-template <int kSubIdx>
-__device__ __forceinline__ void sim_scan(const SimArgs& a, SimStages& x, uint64_t& cost_lo, uint64_t& cost_hi,
-                                         const TileBufs& b, int r0, int r1) {
-  constexpr bool kNext = kSubIdx == kSubs - 1;
-  const uint32_t rbase = a.t.rbase;
-  const auto load_s = [&](uint32_t off) { return (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(b.s, (int)b.vo, (int)off, 0); };
-  const auto load_n = [&](uint32_t off) {
-    return kNext ? (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(b.next, (int)b.vo_next, (int)off, 0) : 0u;
-  };
-  const auto load_r = [&](uint32_t off) {
-    return (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(b.r, (int)b.vo, (int)(off < b.r_bytes ? off : 0u), 0);
-  };
-  // pair p of records (reads clamped to the last pair, whose second record may
-  // be past the tile: its S words are then not read)
-  const auto load = [&](SimWords(&w)[2], int p) {
-    const u32x16 f = a.refs[min(p, (r1 - 1) >> 1)];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const auto g = [&](int k) {
-        const uint32_t off = f[8 * i + k];
-        return i == 0 || off < b.r_bytes - rbase ? off : 0u;
-      };
-      w[i].R = load_r(f[8 * i] + rbase);
-      w[i].S = load_s(g(0));
-      w[i].s0 = load_s(g(1));
-      w[i].n0 = load_n(g(1));
-      w[i].a0 = load_r(f[8 * i + 2]);
-      w[i].b0 = load_r(f[8 * i + 3]);
-      w[i].s1 = load_s(g(4));
-      w[i].n1 = load_n(g(4));
-      w[i].a1 = load_r(f[8 * i + 5]);
-      w[i].b1 = load_r(f[8 * i + 6]);
-    }
-  };
-  const auto pair = [&](const SimWords(&w)[2], int p) {
-    const u64x8 o = a.ops[p];
-    const u32x16 f = a.refs[p];
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      if (2 * p + i < r0 || 2 * p + i >= r1) continue;
-      uint32_t x0 = s1_of(w[i].s0, w[i].n0) | w[i].a0 | w[i].b0, x1 = s1_of(w[i].s1, w[i].n1) | w[i].a1 | w[i].b1;
-      if (__builtin_expect(f[8 * i + 7] != 0u, 0)) {
-        const cptr<SimMore> m = a.more + (f[8 * i + 7] - 1);
-        const uint32_t first = m->first, c0 = m->count0, c1 = m->count1;
-        for (uint32_t e = 0; e < c0; ++e) x0 |= load_r(a.more_off[first + e]);
-        for (uint32_t e = 0; e < c1; ++e) x1 |= load_r(a.more_off[first + c0 + e]);
-      }
-      const uint32_t R = w[i].R;
-      sim_stages<kSub * kSubIdx>(x, R, w[i].S, R & ~x0, R & ~x1, __builtin_bit_cast(double, (uint64_t)o[4 * i]),
-                                 __builtin_bit_cast(double, (uint64_t)o[4 * i + 2]),
-                                 __builtin_bit_cast(double, (uint64_t)o[4 * i + 3]));
-      if (i == (kSubIdx & 1) && (p & 1) == kSubIdx >> 1) {
-        const uint32_t c = (uint32_t)__builtin_popcount(R);
-        cost_lo += (uint64_t)c * (uint32_t)o[4 * i + 1];
-        cost_hi += (uint64_t)c * (uint32_t)(o[4 * i + 1] >> 32);
-      }
-    }
-  };
-  SimWords wa[2], wb[2];
-  const int p1 = (r1 + 1) >> 1;
-  int p = r0 >> 1;
-  load(wa, p);
-  for (; p < p1; p += 2) {
-    load(wb, p + 1);
-    pair(wa, p);
-    if (p + 1 >= p1) break;
-    load(wa, p + 2);
-    pair(wb, p + 1);
-  }
-}
-
-// kSegs waves share a tile's 16 stages, each a part of the records; each
+// kSub stages per wave; kSegs waves share the tile's records, and each part
 // then counts from the memory that the parts before it leave.
-template <int kSegs>
+template <int kSub, int kSegs>
 __global__ void __launch_bounds__(kWave* kSegs) ckm_simulate_kernel(SimArgs a) {
+  constexpr int kSubs = kTile / kSub;
+  constexpr int kJoin = 8;   // stages joined at a time
   const int lane = threadIdx.x & (kWave - 1);
   const int seg = kSegs == 1 ? 0 : uniform((int)threadIdx.x / kWave);
-  // the blocks that read one tile come 8 apart: blocks go to the 8 XCDs in
-  // turn, so these share an L2
-  const int id = blockIdx.x, sub = (id >> 3) & (kSubs - 1), item = (id / (8 * kSubs)) * 8 + (id & 7);
+  // blocks go to the 8 XCDs in turn; those that read one tile come 8 apart and
+  // share an L2
+  const int id = blockIdx.x, sub = (id >> 3) % kSubs, item = (id / (8 * kSubs)) * 8 + (id & 7);
   if (item >= a.t.tiles * a.groups) return;
   const int tile = a.t.tiles - 1 - item / a.groups;   // the longest start first
   const int group = item % a.groups;
-  const TileBufs b(a.t, group, tile, lane);
-  const int recs = a.tile_rec[tile];
-  const int r0 = (int)((int64_t)recs * seg / kSegs), r1 = (int)((int64_t)recs * (seg + 1) / kSegs);
-  SimStages x;
+  TileBufs b(a.t, group, tile, lane);
+  if (sub != kSubs - 1) b.vo_next = kPastEnd;   // only the last stages reach into the next tile
+  const int recs = a.tile_rec[tile], pairs = (recs + 1) >> 1;
+  const int p0 = (int)((int64_t)pairs * seg / kSegs), p1 = (int)((int64_t)pairs * (seg + 1) / kSegs);
+  const uint32_t s_bytes = b.r_bytes - a.t.rbase;
+  const uint32_t sh = (uint32_t)(kSub * sub);
+  // whole words: loads of a byte or half per lane take the cache as many cycles
+  // as eight words
+  const auto word_s = [&](uint32_t off) { return (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(b.s, (int)b.vo, (int)off, 0); };
+  const auto word_n = [&](uint32_t off) { return (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(b.next, (int)b.vo_next, (int)off, 0); };
+
+  SimStages8 x[kSub / 8];
 #pragma unroll
-  for (int j = 0; j < kSub; ++j) {
-    x.U[j] = 0.0;
-    x.top[j] = -INFINITY;
-    x.U0[j] = 0.0;
-  }
+  for (int h = 0; h < kSub / 8; ++h)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      x[h].U[j] = 0.0;
+      x[h].top[j] = 0.0;   // no stage's peak is below its start
+      x[h].U0[j] = 0.0;
+    }
   uint64_t cost_lo = 0, cost_hi = 0;
-  if (r0 < r1) {
-    switch (sub) {
-      case 0: sim_scan<0>(a, x, cost_lo, cost_hi, b, r0, r1); break;
-      case 1: sim_scan<1>(a, x, cost_lo, cost_hi, b, r0, r1); break;
-      case 2: sim_scan<2>(a, x, cost_lo, cost_hi, b, r0, r1); break;
-      default: sim_scan<3>(a, x, cost_lo, cost_hi, b, r0, r1); break;
+  SimIn in[2];
+  const auto load_words = [&](const u32x16& f) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      SimIn& w = in[i];
+      const auto slot = [&](int k) { return k % 2 ? f[8 * i + k / 2] >> 16 : f[8 * i + k / 2] & 0xFFFFu; };
+      const auto word_r = [&](int k) { return load_r(b, slot(k) * kSlotBytes); };
+      // records past the tile's last are not used
+      const auto at = [&](int k) { return slot(k) * kSlotBytes < s_bytes ? slot(k) * kSlotBytes : 0u; };
+      w.R = load_r(b, slot(0) * kSlotBytes + a.t.rbase);
+      w.S = word_s(at(0));
+      w.s0 = word_s(at(1));
+      w.n0 = word_n(at(1));
+      w.s1 = word_s(at(2));
+      w.n1 = word_n(at(2));
+#pragma unroll
+      for (int k = 0; k < 8; ++k) w.u[k] = 0u;
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        if ((k & 2) == 0) w.u[k] = word_r(3 + k);   // the first two of either
+      if (slot(11)) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+          if (k & 2) w.u[k] = word_r(3 + k);
+      }
+    }
+  };
+  if (p0 < p1) {
+    u32x16 f = a.refs[p0];
+    load_words(f);
+    uint64_t C0 = (uint64_t)f[6] | (uint64_t)f[7] << 32, C1 = (uint64_t)f[14] | (uint64_t)f[15] << 32;
+    f = a.refs[p0 + 1];
+    for (int p = p0; p < p1; ++p) {
+      const u32x16 ahead = a.refs[p + 2];
+      const u64x8 now = a.ops[p];
+      SimWords w[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const SimIn& q = in[i];
+        w[i].R = q.R >> sh;
+        w[i].S = q.S >> sh;
+        w[i].F = (q.R & ~(s1_of(q.s0, q.n0) | q.u[0] | q.u[1] | q.u[2] | q.u[3])) >> sh;
+        w[i].G = (q.R & ~(s1_of(q.s1, q.n1) | q.u[4] | q.u[5] | q.u[6] | q.u[7])) >> sh;
+        asm volatile("" : "+v"(w[i].R), "+v"(w[i].S), "+v"(w[i].F), "+v"(w[i].G));   // before the next loads
+      }
+      const bool both = 2 * p + 1 < recs;
+      const uint32_t mine = (1u << kSub) - 1u;
+      const uint32_t c0 = (uint32_t)__builtin_popcount(w[0].R & mine),
+                     c1 = both ? (uint32_t)__builtin_popcount(w[1].R & mine) : 0u;
+      cost_lo += (uint64_t)c0 * (uint32_t)C0 + (uint64_t)c1 * (uint32_t)C1;
+      cost_hi += (uint64_t)c0 * (uint32_t)(C0 >> 32) + (uint64_t)c1 * (uint32_t)(C1 >> 32);
+      // past the part's end these are loaded and not used
+      load_words(f);
+      C0 = (uint64_t)f[6] | (uint64_t)f[7] << 32;
+      C1 = (uint64_t)f[14] | (uint64_t)f[15] << 32;
+      f = ahead;
+      sim_record<kSub>(x, w[0].R, w[0].S, w[0].F, w[0].G, __builtin_bit_cast(double, (uint64_t)now[0]),
+                       __builtin_bit_cast(double, (uint64_t)now[1]), __builtin_bit_cast(double, (uint64_t)now[2]));
+      if (both)
+        sim_record<kSub>(x, w[1].R, w[1].S, w[1].F, w[1].G, __builtin_bit_cast(double, (uint64_t)now[4]),
+                         __builtin_bit_cast(double, (uint64_t)now[5]), __builtin_bit_cast(double, (uint64_t)now[6]));
+    }
+  }
+  if constexpr (kSegs > 1) {
+    __shared__ double cell[kSegs][2 * kJoin][kWave];
+#pragma unroll
+    for (int h = 0; h < kSub; h += kJoin) {
+      SimStages8& y = x[h / 8];
+      if (h) __syncthreads();
+#pragma unroll
+      for (int j = 0; j < kJoin; ++j) {
+        cell[seg][j][lane] = y.U[h % 8 + j];
+        cell[seg][kJoin + j][lane] = y.U0[h % 8 + j];
+      }
+      __syncthreads();
+      for (int s = 0; s < kSegs; ++s) {
+        if (s == seg) continue;
+#pragma unroll
+        for (int j = 0; j < kJoin; ++j) y.U0[h % 8 + j] += cell[s][kJoin + j][lane];
+        if (s > seg) continue;
+#pragma unroll
+        for (int j = 0; j < kJoin; ++j) y.top[h % 8 + j] += cell[s][j][lane];
+      }
     }
   }
   const int k = group * kWave + lane;
+  if (k >= a.K) return;
   const uint64_t cost = cost_lo + (cost_hi << 32);
-  if (k < a.K && cost) atomicAdd(reinterpret_cast<unsigned long long*>(a.cost) + k, (unsigned long long)cost);
-  if constexpr (kSegs > 1) {
-    // a part's peak counts from the memory that the parts before it leave
-    __shared__ double part[kSegs][2 * kSub][kWave];
+  if (cost) atomicAdd(reinterpret_cast<unsigned long long*>(a.cost) + k, (unsigned long long)cost);
+  double peak = 0.0;   // above the base
 #pragma unroll
-    for (int j = 0; j < kSub; ++j) {
-      part[seg][j][lane] = x.U[j];
-      part[seg][kSub + j][lane] = x.U0[j];
+  for (int h = 0; h < kSub / 8; ++h)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int bit = 8 * h + j;
+      if (kTile * tile + kSub * sub + bit < a.t.n) peak = fmax(peak, ldexp(x[h].U0[j] + x[h].top[j], 1074 - bit));
     }
-    __syncthreads();
-    for (int s = 0; s < kSegs; ++s) {
-      if (s == seg) continue;
-#pragma unroll
-      for (int j = 0; j < kSub; ++j) x.U0[j] += part[s][kSub + j][lane];
-      if (s > seg) continue;
-#pragma unroll
-      for (int j = 0; j < kSub; ++j) x.top[j] += part[s][j][lane];
-    }
-  }
-  if (r0 >= r1) return;
-  int64_t peak = INT64_MIN;
-#pragma unroll
-  for (int j = 0; j < kSub; ++j) {
-    const int bit = kSub * sub + j;
-    if (kTile * tile + bit < a.t.n) {
-      const int64_t p = (int64_t)(a.base + ldexp(x.U0[j] + x.top[j], 1074 - bit));
-      peak = p > peak ? p : peak;
-    }
-  }
-  if (k < a.K) atomicMax(reinterpret_cast<long long*>(a.peak) + k, (long long)peak);
-}
-
-// ---------------------------------------------------------------------------
-// Best candidate's R rows from its R tiles: block per tile and 256 nodes, lane
-// = node.
-__global__ void __launch_bounds__(256) ckm_best_tiles_kernel(TileArgs t, int32_t words64,
-                                                             const int32_t* __restrict__ best_k,
-                                                             uint64_t* __restrict__ R_rows) {
-  const int tile = blockIdx.x, v = blockIdx.y * 256 + threadIdx.x;
-  const int bk = best_k[0];
-  if (v >= kWave * words64) return;               // whole waves
-  uint32_t w = 0;
-  if (bk >= 0 && v < min(t.n, kTile * (tile + 1)))   // nodes above compute nothing in these stages
-    w = *reinterpret_cast<const uint32_t*>(t.rtiles + (size_t)(bk / kWave) * t.r_bytes + rtile_off(t.rbase, tile) +
-                                           t.rbase + node_off(v) + 4 * (bk & (kWave - 1)));
-  for (int j = 0; j < kTile && kTile * tile + j < t.n; ++j) {
-    const uint64_t row = __ballot((w >> j) & 1u);
-    if ((threadIdx.x & (kWave - 1)) == 0) R_rows[(size_t)(kTile * tile + j) * words64 + v / kWave] = row;
-  }
+  atomicMax(reinterpret_cast<long long*>(a.peak) + k, (long long)(a.base + peak));
 }
 
 }  // namespace
@@ -565,6 +538,15 @@ static TileArgs tile_args(const ckm_graph& g, const Layout& L, char* work) {
   t.rtiles = work + L.rrows_off;
   return t;
 }
+
+template <int kSub, int kSegs>
+static void launch_simulate(const SimArgs& s, hipStream_t stream) {
+  const int64_t items = ((int64_t)s.groups * s.t.tiles + 7) / 8 * 8;
+  hipLaunchKernelGGL((ckm_simulate_kernel<kSub, kSegs>), dim3((unsigned)(items * (kTile / kSub))), dim3(kWave * kSegs),
+                     0, stream, s);
+}
+
+constexpr int64_t kSimBig = 512;
 
 hipError_t launch_tiles(const ckm_graph& g, const Layout& L, int32_t K, char* work, hipStream_t stream) {
   const int32_t groups = (K + kWave - 1) / kWave;
@@ -585,28 +567,14 @@ hipError_t launch_tiles(const ckm_graph& g, const Layout& L, int32_t K, char* wo
   s.base = (double)g.base;
   s.ops = (cptr<u64x8>)g.tile.d_ops;
   s.refs = (cptr<u32x16>)g.tile.d_refs;
-  s.more = (cptr<SimMore>)g.tile.d_more;
-  s.more_off = (cptr<uint32_t>)g.tile.d_more_off;
   s.tile_rec = (cptr<int32_t>)g.tile.d_tile_rec;
   s.peak = reinterpret_cast<int64_t*>(work + L.part_peak_off);
   s.cost = reinterpret_cast<int64_t*>(work + L.part_cost_off);
   const int64_t items = (int64_t)groups * c.t.tiles;
-  const dim3 grid((unsigned)((items + 7) / 8 * 8 * kSubs));
-  if (items >= 4096)
-    hipLaunchKernelGGL(ckm_simulate_kernel<2>, grid, dim3(2 * kWave), 0, stream, s);
-  else if (items >= 1024)
-    hipLaunchKernelGGL(ckm_simulate_kernel<4>, grid, dim3(4 * kWave), 0, stream, s);
+  if (items >= kSimBig)
+    launch_simulate<16, 4>(s, stream);
   else
-    hipLaunchKernelGGL(ckm_simulate_kernel<8>, grid, dim3(8 * kWave), 0, stream, s);
-  return hipGetLastError();
-}
-
-hipError_t launch_best_tiles(const ckm_graph& g, const Layout& L, const int32_t* d_best_k, uint64_t* d_best_R,
-                             char* work, hipStream_t stream) {
-  const TileArgs t = tile_args(g, L, work);
-  const int32_t words64 = L.row_words / 2;
-  hipLaunchKernelGGL(ckm_best_tiles_kernel, dim3(t.tiles, (kWave * words64 + 255) / 256), dim3(256), 0, stream, t,
-                     words64, d_best_k, d_best_R);
+    launch_simulate<8, 8>(s, stream);
   return hipGetLastError();
 }
 

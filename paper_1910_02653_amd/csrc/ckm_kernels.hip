@@ -1084,9 +1084,9 @@ struct Totals {
   int64_t* __restrict__ cost;
   int32_t K;
 };
-__device__ __forceinline__ void clear_totals(const Totals& tot, int group) {
+__device__ __forceinline__ void clear_totals(const Totals& tot, int group, bool first) {
   const int k = group * kWave + (int)threadIdx.x;
-  if (tot.peak && blockIdx.y == 0 && threadIdx.x < kWave && k < tot.K) {
+  if (tot.peak && first && threadIdx.x < kWave && k < tot.K) {
     tot.peak[k] = INT64_MIN;
     tot.cost[k] = 0;
   }
@@ -1219,6 +1219,30 @@ __device__ __forceinline__ bool better(const Best& x, const Best& y) {
   return x.k < y.k;
 }
 
+// The best over a block's threads (blockDim.x a multiple of 64, at most 1024),
+// in its first thread: shuffles within each wave, then one barrier and the
+// waves' bests.
+__device__ __forceinline__ Best wave_best(Best b, int width) {
+#pragma unroll 1
+  for (int off = width / 2; off > 0; off >>= 1) {
+    const Best o{__shfl_down(b.cost, off), __shfl_down(b.peak, off), __shfl_down(b.k, off), 0};
+    if (better(o, b)) b = o;
+  }
+  return b;
+}
+__device__ __forceinline__ Best block_best(Best b) {
+  __shared__ Best waves[16];
+  b = wave_best(b, kWave);
+  if ((threadIdx.x & (kWave - 1)) == 0) waves[threadIdx.x / kWave] = b;
+  __syncthreads();
+  if (threadIdx.x < kWave) {
+    b = Best{0, 0, -1, 0};
+    if (threadIdx.x < blockDim.x / kWave) b = waves[threadIdx.x];
+    b = wave_best(b, 16);
+  }
+  return b;
+}
+
 // One thread per candidate: copy out its totals, test the budget, then the
 // block's minimum.
 __global__ void __launch_bounds__(256) ckm_reduce_kernel(int32_t K, const int64_t* __restrict__ tot_peak,
@@ -1278,41 +1302,46 @@ __global__ void __launch_bounds__(256) ckm_argmin_kernel(int32_t nblocks, const 
 // thread walks candidates tid, tid + 1024, ... (in increasing k, so among
 // equal (cost, peak) it keeps the smallest k), then the block's minimum.
 constexpr int kSelectOneBlock = 1 << 16;
-__global__ void __launch_bounds__(1024) ckm_select_kernel(int32_t K, const int64_t* __restrict__ tot_peak,
-                                                          const int64_t* __restrict__ tot_cost, int64_t budget,
-                                                          int64_t* __restrict__ peak, int64_t* __restrict__ cost,
-                                                          uint8_t* __restrict__ feasible, int32_t n,
-                                                          const int32_t* __restrict__ nan_row,
-                                                          int32_t* __restrict__ best_k,
-                                                          int32_t* __restrict__ status) {
-  __shared__ Best sb[1024];
-  __shared__ int any_nan;
-  if (threadIdx.x == 0) any_nan = 0;
+struct SelectArgs {
+  int32_t K, nan_rows;
+  const int64_t* __restrict__ tot_peak;
+  const int64_t* __restrict__ tot_cost;
+  int64_t budget;
+  int64_t* __restrict__ peak;
+  int64_t* __restrict__ cost;
+  uint8_t* __restrict__ feasible;
+  const int32_t* __restrict__ nan_row;
+  int32_t* __restrict__ best_k;
+  int32_t* __restrict__ status;
+};
+// The best candidate, in the block's first thread; write: the block also copies
+// the results out.
+__device__ __forceinline__ int select_best(const SelectArgs& a, bool write) {
   Best b{0, 0, -1, 0};
-  for (int k = threadIdx.x; k < K; k += blockDim.x) {
-    const int64_t p = tot_peak[k], c = tot_cost[k];
-    peak[k] = p;
-    cost[k] = c;
-    const bool f = p <= budget;
-    feasible[k] = f ? 1 : 0;
+  for (int k = threadIdx.x; k < a.K; k += blockDim.x) {
+    const int64_t p = a.tot_peak[k], c = a.tot_cost[k];
+    const bool f = p <= a.budget;
+    if (write) {
+      a.peak[k] = p;
+      a.cost[k] = c;
+      a.feasible[k] = f ? 1 : 0;
+    }
     const Best x{c, p, k, 0};
     if (f && better(x, b)) b = x;
   }
-  int nan = 0;
-  for (int r = threadIdx.x; r < n; r += blockDim.x) nan |= nan_row[r];
-  sb[threadIdx.x] = b;
-  __syncthreads();
-  if (nan) atomicOr(&any_nan, 1);
-  for (int off = blockDim.x / 2; off > 0; off >>= 1) {
-    if ((int)threadIdx.x < off && better(sb[threadIdx.x + off], sb[threadIdx.x]))
-      sb[threadIdx.x] = sb[threadIdx.x + off];
-    __syncthreads();
+  b = block_best(b);
+  if (write) {
+    int nan = 0;
+    for (int r = threadIdx.x; r < a.nan_rows; r += blockDim.x) nan |= a.nan_row[r];
+    const int any_nan = __syncthreads_or(nan);
+    if (threadIdx.x == 0) {
+      a.best_k[0] = b.k;
+      if (a.status) a.status[0] = any_nan ? (int32_t)CKM_E_INVALID_ARG : (int32_t)CKM_OK;
+    }
   }
-  if (threadIdx.x == 0) {
-    best_k[0] = sb[0].k;
-    if (status) status[0] = any_nan ? (int32_t)CKM_E_INVALID_ARG : (int32_t)CKM_OK;
-  }
+  return b.k;
 }
+__global__ void __launch_bounds__(1024) ckm_select_kernel(SelectArgs a) { select_best(a, true); }
 
 // ---------------------------------------------------------------------------
 // Largest batch multiplier per candidate (the maximum-batch experiment of
@@ -1413,8 +1442,9 @@ __device__ __forceinline__ void best_r_tiles(const RTiles& t, int n, int words64
 // have row_words words; words with no node (32w >= n) are zero. rank: the
 // threshold family (q holds keys), else randomized or deterministic rounding.
 // With R_rows, the same threads also gather the best candidate's R rows
-// from the R rows the evaluate kernel kept (words above r/32 are zero). Block
-// rows past n gather them from the tile path's R tiles.
+// from the R rows the evaluate kernel kept (words above r/32 are zero). Blocks
+// past the S rows' gather them from the tile path's R tiles. With sel, every block
+// selects the best candidate itself, and the first one writes the results out.
 __global__ void __launch_bounds__(256) ckm_best_rows_kernel(const uint32_t* __restrict__ q,
                                                             const uint32_t* __restrict__ det,
                                                             int32_t n, int32_t ldq, int32_t det_words,
@@ -1424,14 +1454,24 @@ __global__ void __launch_bounds__(256) ckm_best_rows_kernel(const uint32_t* __re
                                                             const int32_t* __restrict__ best_k,
                                                             uint32_t* __restrict__ S_rows,
                                                             const uint32_t* __restrict__ rrows, int32_t kpad,
-                                                            uint32_t* __restrict__ R_rows, RTiles tiles) {
-  const int bk = best_k[0];
-  const int r = S_rows ? (int)blockIdx.y : (int)blockIdx.y + n;
-  if (r >= n) {
-    best_r_tiles(tiles, n, row_words / 2, (r - n) * (int)gridDim.x + (int)blockIdx.x, bk);
+                                                            uint32_t* __restrict__ R_rows, RTiles tiles,
+                                                            SelectArgs sel) {
+  int bk;
+  if (sel.K) {
+    __shared__ int best;
+    const int found = select_best(sel, blockIdx.x == 0);
+    if (threadIdx.x == 0) best = found;
+    __syncthreads();
+    bk = best;
+  } else {
+    bk = best_k[0];
+  }
+  const int row_blocks = (row_words + 255) / 256, s_blocks = S_rows ? n * row_blocks : 0;
+  if ((int)blockIdx.x >= s_blocks) {
+    best_r_tiles(tiles, n, row_words / 2, (int)blockIdx.x - s_blocks, bk);
     return;
   }
-  const int w = blockIdx.x * blockDim.x + threadIdx.x;
+  const int r = (int)blockIdx.x / row_blocks, w = ((int)blockIdx.x - r * row_blocks) * 256 + (int)threadIdx.x;
   if (w >= row_words) return;
   if (R_rows) {
     uint32_t rw = 0;
@@ -1689,20 +1729,20 @@ __device__ __forceinline__ void philox_block(const PhiloxRow& pr, uint32_t b, ui
 
 // Randomized rounding: bit [u_{k,t,i} < q[t][i]] (the draws of round_word);
 // candidate 0 takes the deterministic bits under CKM_F_DET0. One Philox output
-// serves 8 nodes, which are a wave's, with kStages of the tile's stages; waves
-// that share the nodes join their bytes in LDS.
+// serves 8 nodes, which are a wave's, with all the tile's stages or (kBytes) a
+// quarter of them in its byte of the words.
 constexpr int kItemWaves = 4;
-template <int kStages>
-__global__ void __launch_bounds__(kWave* kItemWaves* 32 / kStages) ckm_round_tiles_kernel(
+template <bool kBytes>
+__global__ void __launch_bounds__(kWave* kItemWaves) ckm_round_tiles_kernel(
     const uint32_t* __restrict__ q, const uint32_t* __restrict__ det, int32_t n, int32_t ldq, int32_t det_words,
-    uint32_t key0, uint32_t key1, uint32_t det0, size_t group_bytes, char* __restrict__ stiles, Totals tot) {
-  constexpr int kParts = 32 / kStages;
-  const int group = blockIdx.x;
-  clear_totals(tot, group);
+    uint32_t key0, uint32_t key1, uint32_t det0, size_t group_bytes, char* __restrict__ stiles, int32_t groups, Totals tot) {
+  constexpr int kStages = kBytes ? 8 : 32;
+  const int at = (int)blockIdx.x / groups, group = (int)blockIdx.x - at * groups;
+  clear_totals(tot, group, at == 0);
   int T, nb;
-  tile_item(blockIdx.y, T, nb);
-  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
-  const int m = kItemWaves * nb + wave % kItemWaves, part = wave / kItemWaves;
+  tile_item(kBytes ? at / 4 : at, T, nb);
+  const int part = kBytes ? at % 4 : 0;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave), m = kItemWaves * nb + wave;
   const uint32_t lane = threadIdx.x & (kWave - 1), k = (uint32_t)(group * kWave) + lane;
   uint32_t w[8];
 #pragma unroll
@@ -1710,15 +1750,20 @@ __global__ void __launch_bounds__(kWave* kItemWaves* 32 / kStages) ckm_round_til
   // the part's stages above the nodes' first, from the last one down
   const int t0 = 32 * T + kStages * part;
   const int last = t0 + kStages - 1 < n ? t0 + kStages - 1 : n - 1, first = 8 * m + 1 > t0 ? 8 * m + 1 : t0;
-#pragma unroll 2
-  for (int t = last; t >= first; --t) {
+  const auto stage = [&](int t) {
     const cptr<uint32_t> qrow = as_const(q) + (size_t)t * ldq + 8 * m;
     uint32_t qv[8], x[4];
 #pragma unroll
     for (int i = 0; i < 8; ++i) qv[i] = qrow[i];
     philox_block(philox_row((uint32_t)t, k, key0), (uint32_t)m, key0, key1, x);
     shift_in8(w, x, qv);
+  };
+  int t = last;
+  for (; t > first; t -= 2) {
+    stage(t);
+    stage(t - 1);
   }
+  if (t == first) stage(t);
   // bits of the stages below the first (zeros)
   if (last >= first) {
 #pragma unroll
@@ -1726,25 +1771,21 @@ __global__ void __launch_bounds__(kWave* kItemWaves* 32 / kStages) ckm_round_til
   }
   if (det0 && group == 0) {
     // lane j has the bits of stage t0 + j: a node's word is a ballot
-    const int t = t0 + (int)lane;
-    const uint32_t dw = (int)lane < kStages && t < n ? det[(size_t)t * det_words + nb] >> (8 * (wave % kItemWaves)) : 0u;
+    const int td = t0 + (int)lane;
+    const uint32_t dw = (int)lane < kStages && td < n ? det[(size_t)td * det_words + nb] >> (8 * wave) : 0u;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const uint32_t bits = (uint32_t)__ballot((dw >> i) & 1u);
       if (lane == 0) w[i] = bits;
     }
   }
-  if constexpr (kParts == 1) {
-    store_tile(stiles, group_bytes, group, T, 8 * m, w);
-  } else {
-    static_assert(kParts == 4, "a part is a byte");
-    __shared__ uint32_t words[32][kWave];
+  if constexpr (kBytes) {
+    uint8_t* dst = reinterpret_cast<uint8_t*>(stiles) + (size_t)group * group_bytes + stile_off(T) +
+                   ((size_t)8 * m * kWave + lane) * 4 + part;
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-      reinterpret_cast<uint8_t*>(&words[8 * (wave % kItemWaves) + i][lane])[part] = (uint8_t)w[i];
-    __syncthreads();
-    const uint32_t out[2] = {words[2 * wave][lane], words[2 * wave + 1][lane]};
-    store_tile(stiles, group_bytes, group, T, 32 * nb + 2 * wave, out);
+    for (int i = 0; i < 8; ++i) dst[i * kWave * 4] = (uint8_t)w[i];
+  } else {
+    store_tile(stiles, group_bytes, group, T, 8 * m, w);
   }
 }
 
@@ -1752,11 +1793,11 @@ __global__ void __launch_bounds__(kWave* kItemWaves* 32 / kStages) ckm_round_til
 // threshold_word (keys on and above the diagonal are 0). A wave has 8 nodes.
 __global__ void __launch_bounds__(kWave* kItemWaves) ckm_threshold_tiles_kernel(
     const uint32_t* __restrict__ key, int32_t ldq, const uint32_t* __restrict__ rank, int32_t K, int32_t n,
-    size_t group_bytes, char* __restrict__ stiles, Totals tot) {
-  const int group = blockIdx.x;
-  clear_totals(tot, group);
+    size_t group_bytes, char* __restrict__ stiles, int32_t groups, Totals tot) {
+  const int item = (int)blockIdx.x / groups, group = (int)blockIdx.x - item * groups;
+  clear_totals(tot, group, item == 0);
   int T, nb;
-  tile_item(blockIdx.y, T, nb);
+  tile_item(item, T, nb);
   const int m = kItemWaves * nb + __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
   const uint32_t k = (uint32_t)(group * kWave) + (threadIdx.x & (kWave - 1));
   const uint32_t rk = rank[k < (uint32_t)K ? k : (uint32_t)K - 1u];
@@ -1789,11 +1830,11 @@ __device__ __forceinline__ void transpose_step(uint32_t (&a)[32], uint32_t m) {
 }
 __global__ void __launch_bounds__(kWave) ckm_user_tiles_kernel(const uint32_t* __restrict__ s_user, int32_t n,
                                                                int32_t K, int32_t s_words, size_t group_bytes,
-                                                               char* __restrict__ stiles, Totals tot) {
-  const int group = blockIdx.x;
-  clear_totals(tot, group);
+                                                               char* __restrict__ stiles, int32_t groups, Totals tot) {
+  const int item = (int)blockIdx.x / groups, group = (int)blockIdx.x - item * groups;
+  clear_totals(tot, group, item == 0);
   int T, nb;
-  tile_item(blockIdx.y, T, nb);
+  tile_item(item, T, nb);
   const uint32_t k = (uint32_t)(group * kWave) + threadIdx.x;
   const uint32_t kk = k < (uint32_t)K ? k : (uint32_t)K - 1u;
   const uint32_t* src = s_user + (size_t)kk * n * s_words + nb;
@@ -1904,17 +1945,17 @@ hipError_t launch_round_rows(const ckm_graph& g, const Layout& L, int32_t K, uin
   if (!L.rows_on) return hipSuccess;
   if (use_tiles(g, L)) {
     const Totals tot{clear ? at<int64_t>(work, L.part_peak_off) : nullptr, at<int64_t>(work, L.part_cost_off), K};
-    const dim3 grid(groups_of(K), tile_items(g.n));
-    const auto launch = [&](auto kernel, int waves) {
-      hipLaunchKernelGGL(kernel, grid, dim3(kWave * waves), 0, stream, at<const uint32_t>(work, L.q_off),
-                         at<const uint32_t>(work, L.det_off), g.n, L.ldq, L.det_words, (uint32_t)(seed & 0xFFFFFFFFu),
-                         (uint32_t)(seed >> 32), (flags & CKM_F_DET0) ? 1u : 0u, stile_off((g.n + 31) / 32),
-                         work + L.rows_off, tot);
+    const unsigned groups = groups_of(K), items = tile_items(g.n);
+    const auto launch = [&](auto kernel, unsigned parts) {
+      hipLaunchKernelGGL(kernel, dim3(groups * items * parts), dim3(kWave * kItemWaves), 0, stream,
+                         at<const uint32_t>(work, L.q_off), at<const uint32_t>(work, L.det_off), g.n, L.ldq, L.det_words,
+                         (uint32_t)(seed & 0xFFFFFFFFu), (uint32_t)(seed >> 32), (flags & CKM_F_DET0) ? 1u : 0u,
+                         stile_off((g.n + 31) / 32), work + L.rows_off, (int32_t)groups, tot);
     };
-    if ((int64_t)grid.x * grid.y < kRoundBig)
-      launch(ckm_round_tiles_kernel<8>, 4 * kItemWaves);
+    if ((int64_t)groups * items < kRoundBig)
+      launch(ckm_round_tiles_kernel<true>, 4);
     else
-      launch(ckm_round_tiles_kernel<32>, kItemWaves);
+      launch(ckm_round_tiles_kernel<false>, 1);
     return hipGetLastError();
   }
   const int32_t kpad = ((K + kWave - 1) / kWave) * kWave;
@@ -1931,15 +1972,15 @@ hipError_t launch_round_rows(const ckm_graph& g, const Layout& L, int32_t K, uin
 static hipError_t launch_tile_producer(const ckm_graph& g, const Layout& L, int32_t K, uint64_t seed, uint32_t flags,
                                        int src, const uint64_t* s_user, char* work, hipStream_t stream) {
   const Totals tot{at<int64_t>(work, L.part_peak_off), at<int64_t>(work, L.part_cost_off), K};
-  const dim3 grid(groups_of(K), tile_items(g.n));
+  const int32_t groups = (int32_t)groups_of(K);
+  const dim3 grid((unsigned)groups * tile_items(g.n));
   if (src == kSrcThreshold) {
     hipLaunchKernelGGL(ckm_threshold_tiles_kernel, grid, dim3(kWave * kItemWaves), 0, stream, at<const uint32_t>(work, L.q_off),
-                       L.ldq, at<const uint32_t>(work, L.thr_rank_off), K, g.n, stile_off((g.n + 31) / 32), work + L.rows_off,
-                       tot);
+                       L.ldq, at<const uint32_t>(work, L.thr_rank_off), K, g.n, stile_off((g.n + 31) / 32), work + L.rows_off, groups, tot);
   } else if (src == kSrcUser) {
     hipLaunchKernelGGL(ckm_user_tiles_kernel, grid, dim3(kWave), 0, stream,
                        reinterpret_cast<const uint32_t*>(s_user), g.n, K, L.row_words, stile_off((g.n + 31) / 32),
-                       work + L.rows_off, tot);
+                       work + L.rows_off, groups, tot);
   } else {
     return launch_round_rows(g, L, K, seed, flags, true, work, stream);
   }
@@ -2065,6 +2106,10 @@ hipError_t launch_max_batch(const ckm_graph& g, const Layout& L, int32_t K, int6
   return hipGetLastError();
 }
 
+// Totals read by all blocks together up to which every block of the best rows
+// selects for itself.
+constexpr int64_t kSelectTotals = 2 << 20;
+
 hipError_t launch_select(const ckm_graph& g, const Layout& L, int32_t K, uint64_t seed,
                          int64_t budget, uint32_t flags, int64_t* d_peak, int64_t* d_cost,
                          uint8_t* d_feasible, int32_t* d_best_k, uint64_t* d_best_S,
@@ -2072,19 +2117,6 @@ hipError_t launch_select(const ckm_graph& g, const Layout& L, int32_t K, uint64_
                          char* work, hipStream_t stream) {
   // rounded candidates: NaN flags from the quantize or key stage; supplied S: none
   const int32_t nan_rows = src == kSrcUser ? 0 : g.n;
-  if (K <= kSelectOneBlock) {
-    hipLaunchKernelGGL(ckm_select_kernel, dim3(1), dim3(1024), 0, stream, K,
-                       at<const int64_t>(work, L.part_peak_off), at<const int64_t>(work, L.part_cost_off), budget,
-                       d_peak, d_cost, d_feasible, nan_rows, at<const int32_t>(work, L.nan_off), d_best_k, d_status);
-  } else {
-    const int rb = L.reduce_blocks;
-    hipLaunchKernelGGL(ckm_reduce_kernel, dim3(rb), dim3(256), 0, stream, K,
-                       at<const int64_t>(work, L.part_peak_off), at<const int64_t>(work, L.part_cost_off),
-                       budget, d_peak, d_cost, d_feasible, at<Best>(work, L.best_off));
-    hipLaunchKernelGGL(ckm_argmin_kernel, dim3(1), dim3(256), 0, stream, rb,
-                       at<const Best>(work, L.best_off), nan_rows, at<const int32_t>(work, L.nan_off), d_best_k,
-                       d_status);
-  }
   // With the row arrays the evaluate stage kept every candidate's R rows, so
   // the best R is a gather; otherwise Algorithm 2 runs again for it.
   RTiles tiles = {};
@@ -2099,13 +2131,31 @@ hipError_t launch_select(const ckm_graph& g, const Layout& L, int32_t K, uint64_
   const int32_t kpad = (int32_t)(groups_of(K) * kWave);
   const dim3 rows_grid((L.row_words + 255) / 256, g.n);
   uint32_t* R_out = reinterpret_cast<uint32_t*>(d_best_R);
-  // block rows of the tile gather
-  const unsigned tile_blocks = (unsigned)((g.n + 31) / 32 * ((L.row_words * 32 + 255) / 256));
-  const unsigned tile_rows = tiles.R_rows ? (tile_blocks + rows_grid.x - 1) / rows_grid.x : 0u;
+  // blocks of the S rows and of the tile gather
+  const unsigned blocks = (src != kSrcUser && (d_best_S || d_best_R) ? (unsigned)g.n * rows_grid.x : 0u) +
+                          (tiles.R_rows ? (unsigned)((g.n + 31) / 32 * ((L.row_words * 32 + 255) / 256)) : 0u);
+  SelectArgs sel = {K, nan_rows, at<const int64_t>(work, L.part_peak_off), at<const int64_t>(work, L.part_cost_off),
+                    budget, d_peak, d_cost, d_feasible, at<const int32_t>(work, L.nan_off), d_best_k, d_status};
+  if (blocks && (int64_t)blocks * K <= kSelectTotals) {
+    // in the launch that writes the best rows
+  } else if (K <= kSelectOneBlock) {
+    hipLaunchKernelGGL(ckm_select_kernel, dim3(1), dim3(1024), 0, stream, sel);
+    sel.K = 0;
+  } else {
+    const int rb = L.reduce_blocks;
+    hipLaunchKernelGGL(ckm_reduce_kernel, dim3(rb), dim3(256), 0, stream, K,
+                       at<const int64_t>(work, L.part_peak_off), at<const int64_t>(work, L.part_cost_off),
+                       budget, d_peak, d_cost, d_feasible, at<Best>(work, L.best_off));
+    hipLaunchKernelGGL(ckm_argmin_kernel, dim3(1), dim3(256), 0, stream, rb,
+                       at<const Best>(work, L.best_off), nan_rows, at<const int32_t>(work, L.nan_off), d_best_k,
+                       d_status);
+    sel.K = 0;
+  }
   if (src == kSrcUser) {
     if (tiles.R_rows) {
-      hipLaunchKernelGGL(ckm_best_rows_kernel, dim3(rows_grid.x, tile_rows), dim3(256), 0, stream, nullptr, nullptr, g.n,
-                         0, 0, L.row_words, 0u, 0u, 0u, nullptr, d_best_k, nullptr, nullptr, 0, nullptr, tiles);
+      hipLaunchKernelGGL(ckm_best_rows_kernel, dim3(blocks), dim3(256), 0, stream, nullptr, nullptr, g.n,
+                         0, 0, L.row_words, 0u, 0u, 0u, nullptr, d_best_k, nullptr, nullptr, 0, nullptr, tiles,
+                         sel);
     } else if (gather_R) {
       hipLaunchKernelGGL(ckm_best_rrows_kernel, rows_grid, dim3(256), 0, stream,
                          at<const uint32_t>(work, L.rrows_off), kpad, L.row_words, d_best_k, R_out);
@@ -2118,12 +2168,13 @@ hipError_t launch_select(const ckm_graph& g, const Layout& L, int32_t K, uint64_
     // the S rows: output, and the closure's input when there is no gather
     uint32_t* srows = d_best_S ? reinterpret_cast<uint32_t*>(d_best_S)
                       : d_best_R ? at<uint32_t>(work, L.srows_off) : nullptr;
-    hipLaunchKernelGGL(ckm_best_rows_kernel, dim3(rows_grid.x, (srows ? g.n : 0) + tile_rows), dim3(256), 0, stream,
+    hipLaunchKernelGGL(ckm_best_rows_kernel, dim3(blocks), dim3(256), 0, stream,
                        at<const uint32_t>(work, L.q_off), at<const uint32_t>(work, L.det_off), g.n,
                        L.ldq, L.det_words, L.row_words, (uint32_t)(seed & 0xFFFFFFFFu),
                        (uint32_t)(seed >> 32), (flags & CKM_F_DET0) ? 1u : 0u,
                        src == kSrcThreshold ? at<const uint32_t>(work, L.thr_rank_off) : nullptr, d_best_k,
-                       srows, at<const uint32_t>(work, L.rrows_off), kpad, gather_R ? R_out : nullptr, tiles);
+                       srows, at<const uint32_t>(work, L.rrows_off), kpad, gather_R ? R_out : nullptr, tiles,
+                       sel);
     if (d_best_R && !gather_R) {
       hipError_t e = launch_closure(g, L, d_best_k, static_cast<const uint32_t*>(srows), (size_t)0, R_out, stream);
       if (e != hipSuccess) return e;

@@ -394,7 +394,6 @@ struct SimIn {
 template <int kSub, int kSegs>
 __global__ void __launch_bounds__(kWave* kSegs) ckm_simulate_kernel(SimArgs a) {
   constexpr int kSubs = kTile / kSub;
-  constexpr int kJoin = 8;   // stages joined at a time
   const int lane = threadIdx.x & (kWave - 1);
   const int seg = kSegs == 1 ? 0 : uniform((int)threadIdx.x / kWave);
   // blocks go to the 8 XCDs in turn; those that read one tile come 8 apart and
@@ -407,7 +406,6 @@ __global__ void __launch_bounds__(kWave* kSegs) ckm_simulate_kernel(SimArgs a) {
   if (sub != kSubs - 1) b.vo_next = kPastEnd;   // only the last stages reach into the next tile
   const int recs = a.tile_rec[tile], pairs = (recs + 1) >> 1;
   const int p0 = (int)((int64_t)pairs * seg / kSegs), p1 = (int)((int64_t)pairs * (seg + 1) / kSegs);
-  const uint32_t s_bytes = b.r_bytes - a.t.rbase;
   const uint32_t sh = (uint32_t)(kSub * sub);
   // whole words: loads of a byte or half per lane take the cache as many cycles
   // as eight words
@@ -431,14 +429,14 @@ __global__ void __launch_bounds__(kWave* kSegs) ckm_simulate_kernel(SimArgs a) {
       SimIn& w = in[i];
       const auto slot = [&](int k) { return k % 2 ? f[8 * i + k / 2] >> 16 : f[8 * i + k / 2] & 0xFFFFu; };
       const auto word_r = [&](int k) { return load_r(b, slot(k) * kSlotBytes); };
-      // records past the tile's last are not used
-      const auto at = [&](int k) { return slot(k) * kSlotBytes < s_bytes ? slot(k) * kSlotBytes : 0u; };
-      w.R = load_r(b, slot(0) * kSlotBytes + a.t.rbase);
-      w.S = word_s(at(0));
-      w.s0 = word_s(at(1));
-      w.n0 = word_n(at(1));
-      w.s1 = word_s(at(2));
-      w.n1 = word_n(at(2));
+      // the few records read past a tile's last belong to the next tile's first
+      // nodes: their words are in the memory after the tile's, and are not used
+      w.R = __builtin_amdgcn_raw_buffer_load_b32(b.r, (int)b.vo, (int)(slot(0) * kSlotBytes + a.t.rbase), 0);
+      w.S = word_s(slot(0) * kSlotBytes);
+      w.s0 = word_s(slot(1) * kSlotBytes);
+      w.n0 = word_n(slot(1) * kSlotBytes);
+      w.s1 = word_s(slot(2) * kSlotBytes);
+      w.n1 = word_n(slot(2) * kSlotBytes);
 #pragma unroll
       for (int k = 0; k < 8; ++k) w.u[k] = 0u;
 #pragma unroll
@@ -487,41 +485,49 @@ __global__ void __launch_bounds__(kWave* kSegs) ckm_simulate_kernel(SimArgs a) {
                          __builtin_bit_cast(double, (uint64_t)now[5]), __builtin_bit_cast(double, (uint64_t)now[6]));
     }
   }
-  if constexpr (kSegs > 1) {
-    __shared__ double cell[kSegs][2 * kJoin][kWave];
-#pragma unroll
-    for (int h = 0; h < kSub; h += kJoin) {
-      SimStages8& y = x[h / 8];
-      if (h) __syncthreads();
-#pragma unroll
-      for (int j = 0; j < kJoin; ++j) {
-        cell[seg][j][lane] = y.U[h % 8 + j];
-        cell[seg][kJoin + j][lane] = y.U0[h % 8 + j];
-      }
-      __syncthreads();
-      for (int s = 0; s < kSegs; ++s) {
-        if (s == seg) continue;
-#pragma unroll
-        for (int j = 0; j < kJoin; ++j) y.U0[h % 8 + j] += cell[s][kJoin + j][lane];
-        if (s > seg) continue;
-#pragma unroll
-        for (int j = 0; j < kJoin; ++j) y.top[h % 8 + j] += cell[s][j][lane];
-      }
-    }
-  }
   const int k = group * kWave + lane;
-  if (k >= a.K) return;
   const uint64_t cost = cost_lo + (cost_hi << 32);
-  if (cost) atomicAdd(reinterpret_cast<unsigned long long*>(a.cost) + k, (unsigned long long)cost);
+  if (k < a.K && cost) atomicAdd(reinterpret_cast<unsigned long long*>(a.cost) + k, (unsigned long long)cost);
+  // the parts' sums meet in LDS, eight stages at a time; each wave joins some
+  // of the stages
+  __shared__ double cell[kSegs][16][kWave];
+  constexpr int kMine = 8 / kSegs;
   double peak = 0.0;   // above the base
 #pragma unroll
-  for (int h = 0; h < kSub / 8; ++h)
+  for (int h = 0; h < kSub / 8; ++h) {
+    if (h) __syncthreads();
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-      const int bit = 8 * h + j;
-      if (kTile * tile + kSub * sub + bit < a.t.n) peak = fmax(peak, ldexp(x[h].U0[j] + x[h].top[j], 1074 - bit));
+      cell[seg][j][lane] = x[h].U[j];
+      cell[seg][8 + j][lane] = x[h].top[j];
     }
-  atomicMax(reinterpret_cast<long long*>(a.peak) + k, (long long)(a.base + peak));
+    __syncthreads();
+    double top[kMine], U0[kMine];
+#pragma unroll
+    for (int i = 0; i < kMine; ++i) {
+      const int j = kMine * seg + i;
+      double before = 0.0;
+      top[i] = 0.0;
+#pragma unroll
+      for (int s = 0; s < kSegs; ++s) {
+        top[i] = fmax(top[i], before + cell[s][8 + j][lane]);
+        before += cell[s][j][lane];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 8; ++j) cell[seg][j][lane] = x[h].U0[j];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < kMine; ++i) {
+      const int j = kMine * seg + i, bit = 8 * h + j;
+      U0[i] = 0.0;
+#pragma unroll
+      for (int s = 0; s < kSegs; ++s) U0[i] += cell[s][j][lane];
+      if (kTile * tile + kSub * sub + bit < a.t.n) peak = fmax(peak, ldexp(U0[i] + top[i], 1074 - bit));
+    }
+  }
+  if (k < a.K) atomicMax(reinterpret_cast<long long*>(a.peak) + k, (long long)(a.base + peak));
 }
 
 }  // namespace

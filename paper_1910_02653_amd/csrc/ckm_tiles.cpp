@@ -77,7 +77,8 @@ bool build_tiles(int32_t n, const int64_t* M, const int64_t* C, const int32_t* d
       far[48] = (uint32_t)T.far_more.size() - far[32];
       d[18 + 2 * j] = (uint32_t)T.near_more.size() - d[17 + 2 * j];
       if (nn > 2) block |= kBlockNear3;
-      if (nn > 3) block |= kBlockMany;
+      if (nn > 3) block |= kBlockNear4;
+      if (nn > 4) block |= kBlockMany;
     }
     d[16] |= flags;
     if (c % kChunks == kChunks - 1) {
@@ -121,8 +122,8 @@ bool build_tiles(int32_t n, const int64_t* M, const int64_t* C, const int32_t* d
   }
   T.nrec = (int32_t)T.ops.size();
   for (int32_t k = 0; k < T.tiles; ++k) T.tile_rec.push_back(rec_end[std::min(kTile * (k + 1), n) - 1]);
-  // pairs of records are read together, two pairs ahead
-  for (int k = 0; k < 6; ++k) {
+  // records are read up to two past a tile's last
+  for (int k = 0; k < 2; ++k) {
     T.ops.push_back(SimOps{});
     T.refs.push_back(SimRefs{});
   }

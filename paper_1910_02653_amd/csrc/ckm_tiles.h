@@ -41,7 +41,8 @@ constexpr int kClosureSlots = kSlotDesc + 8;
 //   17 + 2 j, +1  first and count of node 4c + j's near users beyond the four
 constexpr int kDescDwords = 32;
 constexpr uint32_t kBlockNear3 = 1u << 8;    // some node of the block has a third near user
-constexpr uint32_t kBlockMany = 1u << 9;     // ... a fourth
+constexpr uint32_t kBlockNear4 = 1u << 9;    // ... a fourth
+constexpr uint32_t kBlockMany = 1u << 10;    // ... a fifth
 
 // Far users of half a block (16 nodes), 64 dwords: node i's first two users' R
 // tile byte offsets at i and 16 + i (0, the tile's empty word, when absent),

@@ -22,8 +22,8 @@ namespace {
 
 template <typename T>
 using cptr = const __attribute__((address_space(4))) T*;
-typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
-typedef uint64_t u64x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
+typedef uint64_t u64x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) char lds_char;
 typedef __attribute__((address_space(3))) uint32_t lds_u32;
 
@@ -222,6 +222,8 @@ __device__ __forceinline__ void decide_block(const ClosureArgs& a, const TileBuf
   const uint32_t flags = rl(d[0], 16);
   if (flags & kBlockMany)
     decide_block_any<kTop>(a, b, lds, blk, r_off, d, nodes);
+  else if (flags & kBlockNear4)
+    decide_block<4, kTop>(b, lds, blk, r_off, d, nodes);
   else if (flags & kBlockNear3)
     decide_block<3, kTop>(b, lds, blk, r_off, d, nodes);
   else
@@ -331,8 +333,8 @@ struct SimArgs {
   TileArgs t;
   int32_t K, groups;
   double base;                      // M_in + 2 M_param
-  cptr<u64x8> ops;                  // pairs of SimOps
-  cptr<u32x16> refs;                // pairs of SimRefs
+  cptr<u64x4> ops;                  // SimOps
+  cptr<u32x8> refs;                 // SimRefs
   cptr<int32_t> tile_rec;
   int64_t* __restrict__ peak;
   int64_t* __restrict__ cost;
@@ -380,11 +382,7 @@ __device__ __forceinline__ void sim_record(SimStages8 (&x)[kSub / 8], uint32_t R
   if constexpr (kSub > 8) CKM_SIM_RECORD(CKM_SIM_HIGH, x[1]);
 }
 
-// A wave's stages' part of a record's words.
-struct SimWords {
-  uint32_t R, S, F, G;
-};
-// What they are made from: requested a pair of records ahead.
+// The words of a record: requested a record ahead.
 struct SimIn {
   uint32_t R, S, s0, n0, s1, n1, u[8];
 };
@@ -404,8 +402,8 @@ __global__ void __launch_bounds__(kWave* kSegs) ckm_simulate_kernel(SimArgs a) {
   const int group = item % a.groups;
   TileBufs b(a.t, group, tile, lane);
   if (sub != kSubs - 1) b.vo_next = kPastEnd;   // only the last stages reach into the next tile
-  const int recs = a.tile_rec[tile], pairs = (recs + 1) >> 1;
-  const int p0 = (int)((int64_t)pairs * seg / kSegs), p1 = (int)((int64_t)pairs * (seg + 1) / kSegs);
+  const int recs = a.tile_rec[tile];
+  const int r0 = (int)((int64_t)recs * seg / kSegs), r1 = (int)((int64_t)recs * (seg + 1) / kSegs);
   const uint32_t sh = (uint32_t)(kSub * sub);
   // whole words: loads of a byte or half per lane take the cache as many cycles
   // as eight words
@@ -422,67 +420,45 @@ __global__ void __launch_bounds__(kWave* kSegs) ckm_simulate_kernel(SimArgs a) {
       x[h].U0[j] = 0.0;
     }
   uint64_t cost_lo = 0, cost_hi = 0;
-  SimIn in[2];
-  const auto load_words = [&](const u32x16& f) {
+  SimIn in;
+  uint64_t C;
+  const auto load_words = [&](const u32x8& f) {
+    C = (uint64_t)f[6] | (uint64_t)f[7] << 32;
+    const auto slot = [&](int k) { return (k % 2 ? f[k / 2] >> 16 : f[k / 2] & 0xFFFFu) * (uint32_t)kSlotBytes; };
+    // the record read past a tile's last belongs to the next tile's first node:
+    // its words are in the memory after the tile's, and are not used
+    in.R = __builtin_amdgcn_raw_buffer_load_b32(b.r, (int)b.vo, (int)(slot(0) + a.t.rbase), 0);
+    in.S = word_s(slot(0));
+    in.s0 = word_s(slot(1));
+    in.n0 = word_n(slot(1));
+    in.s1 = word_s(slot(2));
+    in.n1 = word_n(slot(2));
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      SimIn& w = in[i];
-      const auto slot = [&](int k) { return k % 2 ? f[8 * i + k / 2] >> 16 : f[8 * i + k / 2] & 0xFFFFu; };
-      const auto word_r = [&](int k) { return load_r(b, slot(k) * kSlotBytes); };
-      // the few records read past a tile's last belong to the next tile's first
-      // nodes: their words are in the memory after the tile's, and are not used
-      w.R = __builtin_amdgcn_raw_buffer_load_b32(b.r, (int)b.vo, (int)(slot(0) * kSlotBytes + a.t.rbase), 0);
-      w.S = word_s(slot(0) * kSlotBytes);
-      w.s0 = word_s(slot(1) * kSlotBytes);
-      w.n0 = word_n(slot(1) * kSlotBytes);
-      w.s1 = word_s(slot(2) * kSlotBytes);
-      w.n1 = word_n(slot(2) * kSlotBytes);
-#pragma unroll
-      for (int k = 0; k < 8; ++k) w.u[k] = 0u;
+    for (int k = 0; k < 8; ++k) in.u[k] = (k & 2) == 0 ? load_r(b, slot(3 + k)) : 0u;   // the first two of either
+    if (f[5] >> 16) {
 #pragma unroll
       for (int k = 0; k < 8; ++k)
-        if ((k & 2) == 0) w.u[k] = word_r(3 + k);   // the first two of either
-      if (slot(11)) {
-#pragma unroll
-        for (int k = 0; k < 8; ++k)
-          if (k & 2) w.u[k] = word_r(3 + k);
-      }
+        if (k & 2) in.u[k] = load_r(b, slot(3 + k));
     }
   };
-  if (p0 < p1) {
-    u32x16 f = a.refs[p0];
+  if (r0 < r1) {
+    u32x8 f = a.refs[r0];
     load_words(f);
-    uint64_t C0 = (uint64_t)f[6] | (uint64_t)f[7] << 32, C1 = (uint64_t)f[14] | (uint64_t)f[15] << 32;
-    f = a.refs[p0 + 1];
-    for (int p = p0; p < p1; ++p) {
-      const u32x16 ahead = a.refs[p + 2];
-      const u64x8 now = a.ops[p];
-      SimWords w[2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-        const SimIn& q = in[i];
-        w[i].R = q.R >> sh;
-        w[i].S = q.S >> sh;
-        w[i].F = (q.R & ~(s1_of(q.s0, q.n0) | q.u[0] | q.u[1] | q.u[2] | q.u[3])) >> sh;
-        w[i].G = (q.R & ~(s1_of(q.s1, q.n1) | q.u[4] | q.u[5] | q.u[6] | q.u[7])) >> sh;
-        asm volatile("" : "+v"(w[i].R), "+v"(w[i].S), "+v"(w[i].F), "+v"(w[i].G));   // before the next loads
-      }
-      const bool both = 2 * p + 1 < recs;
-      const uint32_t mine = (1u << kSub) - 1u;
-      const uint32_t c0 = (uint32_t)__builtin_popcount(w[0].R & mine),
-                     c1 = both ? (uint32_t)__builtin_popcount(w[1].R & mine) : 0u;
-      cost_lo += (uint64_t)c0 * (uint32_t)C0 + (uint64_t)c1 * (uint32_t)C1;
-      cost_hi += (uint64_t)c0 * (uint32_t)(C0 >> 32) + (uint64_t)c1 * (uint32_t)(C1 >> 32);
-      // past the part's end these are loaded and not used
-      load_words(f);
-      C0 = (uint64_t)f[6] | (uint64_t)f[7] << 32;
-      C1 = (uint64_t)f[14] | (uint64_t)f[15] << 32;
+    f = a.refs[r0 + 1];
+    for (int r = r0; r < r1; ++r) {
+      const u32x8 ahead = a.refs[r + 2];
+      const u64x4 now = a.ops[r];
+      uint32_t R = in.R >> sh, S = in.S >> sh,
+               F = (in.R & ~(s1_of(in.s0, in.n0) | in.u[0] | in.u[1] | in.u[2] | in.u[3])) >> sh,
+               G = (in.R & ~(s1_of(in.s1, in.n1) | in.u[4] | in.u[5] | in.u[6] | in.u[7])) >> sh;
+      asm volatile("" : "+v"(R), "+v"(S), "+v"(F), "+v"(G));   // before the next loads
+      const uint32_t c = (uint32_t)__builtin_popcount(R & ((1u << kSub) - 1u));
+      cost_lo += (uint64_t)c * (uint32_t)C;
+      cost_hi += (uint64_t)c * (uint32_t)(C >> 32);
+      load_words(f);   // past the part's end they are not used
       f = ahead;
-      sim_record<kSub>(x, w[0].R, w[0].S, w[0].F, w[0].G, __builtin_bit_cast(double, (uint64_t)now[0]),
+      sim_record<kSub>(x, R, S, F, G, __builtin_bit_cast(double, (uint64_t)now[0]),
                        __builtin_bit_cast(double, (uint64_t)now[1]), __builtin_bit_cast(double, (uint64_t)now[2]));
-      if (both)
-        sim_record<kSub>(x, w[1].R, w[1].S, w[1].F, w[1].G, __builtin_bit_cast(double, (uint64_t)now[4]),
-                         __builtin_bit_cast(double, (uint64_t)now[5]), __builtin_bit_cast(double, (uint64_t)now[6]));
     }
   }
   const int k = group * kWave + lane;
@@ -552,7 +528,7 @@ static void launch_simulate(const SimArgs& s, hipStream_t stream) {
                      0, stream, s);
 }
 
-constexpr int64_t kSimBig = 512;
+constexpr int64_t kSimItems = 512;
 
 hipError_t launch_tiles(const ckm_graph& g, const Layout& L, int32_t K, char* work, hipStream_t stream) {
   const int32_t groups = (K + kWave - 1) / kWave;
@@ -571,14 +547,16 @@ hipError_t launch_tiles(const ckm_graph& g, const Layout& L, int32_t K, char* wo
   s.K = K;
   s.groups = groups;
   s.base = (double)g.base;
-  s.ops = (cptr<u64x8>)g.tile.d_ops;
-  s.refs = (cptr<u32x16>)g.tile.d_refs;
+  s.ops = (cptr<u64x4>)g.tile.d_ops;
+  s.refs = (cptr<u32x8>)g.tile.d_refs;
   s.tile_rec = (cptr<int32_t>)g.tile.d_tile_rec;
   s.peak = reinterpret_cast<int64_t*>(work + L.part_peak_off);
   s.cost = reinterpret_cast<int64_t*>(work + L.part_cost_off);
   const int64_t items = (int64_t)groups * c.t.tiles;
-  if (items >= kSimBig)
+  if (items >= 2 * kSimItems)
     launch_simulate<16, 4>(s, stream);
+  else if (items >= kSimItems)
+    launch_simulate<16, 8>(s, stream);
   else
     launch_simulate<8, 8>(s, stream);
   return hipGetLastError();

@@ -66,12 +66,15 @@ HBM_PEAK_GBS = 8000.0
 # int32 VALU lane-operations per second: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz
 ALU_PEAK_TOPS = 256 * 4 * 16 * 2.4e9 / 1e12
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic_eval_transformer_n1009_K1024.json")
-KERNEL_SRC = os.path.join(ROOT, "paper_1910_02653_amd", "csrc", "ckm_kernels.hip")
+KERNEL_SRCS = [os.path.join(ROOT, "paper_1910_02653_amd", "csrc", f) for f in ("ckm_kernels.hip", "ckm_tiles.hip")]
 
 
 def kernel_hash() -> str:
-    with open(KERNEL_SRC, "rb") as f:
-        return hashlib.sha256(f.read()).hexdigest()[:16]
+    h = hashlib.sha256()
+    for path in KERNEL_SRCS:
+        with open(path, "rb") as f:
+            h.update(f.read())
+    return h.hexdigest()[:16]
 
 
 def measured_counters():
@@ -527,9 +530,7 @@ def main():
     stream = torch.cuda.current_stream()
 
     def step(ev=None):
-        # quantize, round + evaluate (one call: the library overlaps the
-        # rounding of later candidate groups with the evaluate of earlier
-        # ones), select
+        # quantize, round + evaluate (one call), select
         if ev is not None:
             ev[0].record(stream)
         g.quantize_async(d_s, work, stream)

@@ -145,17 +145,12 @@ ckm_status ckm_round_eval(const ckm_graph* g, const double* s_frac, int64_t ld, 
  * The calls enqueue kernel launches only (no allocation, memset, copy or
  * synchronization), so a sequence of them can be captured into a HIP graph
  * on `stream` and replayed; scalar arguments (K, seed, budget, flags) are
- * fixed at capture. On a graph whose evaluate LDS holds to a few waves per
- * CU (the seen path of large graphs), an evaluate with 8 or more groups of
- * 64 candidates runs the later groups on the graph's second stream, forked
- * from `stream` and joined back to it by events before the call's work on
- * `stream` ends; a capture takes that fork and join in as dependencies. */
+ * fixed at capture. Every launch goes on `stream`. */
 
 /* Bytes of work buffer for K candidates on graph g. This includes, when the
  * S rows of all K candidates fit in 8 GiB, room for them and for their R
- * rows (the row arrays, twice the S rows' size; 8.3 GB at n = 4001,
- * K = 4096):
- * the evaluate stage then streams each row from there instead of making it
+ * rows (the row arrays, about twice the S rows' size; 8.5 GB at n = 4001,
+ * K = 4096): the evaluate stage then streams each row from there instead of making it
  * twice (randomized rounding, threshold rounding) or reading it from each
  * candidate's own matrix (supplied schedules). A smaller buffer of at least
  * ckm_workspace_size_min bytes is accepted, and the rows are then made

@@ -312,7 +312,7 @@ Layout make_layout(const ckm_graph& g, int32_t K) {
     const size_t full = (size_t)(n >> 5), rem = (size_t)(n & 31);
     s_bytes = r_bytes = kpad * (32 * full * (full + 1) / 2 + rem * (full + 1)) * sizeof(uint32_t);
   }
-  L.rows_on = s_bytes <= ckm::kRowsMaxBytes;
+  L.rows_on = s_bytes <= ckm::kRowsMaxBytes && r_bytes <= ckm::kRRowsMaxBytes;
   L.rrows_off = align256(off + s_bytes);
   L.total_rows = L.rows_on ? align256(L.rrows_off + r_bytes) : off;
   return L;

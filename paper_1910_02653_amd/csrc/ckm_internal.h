@@ -76,7 +76,10 @@ enum : int {
 // each; 4.1 GB at n = 4001, K = 4096); larger problems, or work buffers sized
 // without them, make the S rows in the evaluate kernel and recompute the best
 // candidate's R.
+// R tiles also hold the hub words, which a dense graph has many more of than
+// nodes: their bound is four times that of the S rows.
 constexpr size_t kRowsMaxBytes = (size_t)8 << 30;
+constexpr size_t kRRowsMaxBytes = (size_t)32 << 30;
 
 // Host-side builder of the per-node records the evaluate kernel reads
 // (layout documented with NodeRec in ckm_kernels.hip). Writes n records.

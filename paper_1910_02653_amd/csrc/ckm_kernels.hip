@@ -29,7 +29,6 @@
 
 #include "ckm_internal.h"
 
-
 namespace ckm {
 namespace {
 
@@ -1077,8 +1076,8 @@ __global__ void __launch_bounds__(256) ckm_eval_init_kernel(int32_t K, int64_t* 
   }
 }
 
-// The same for the 64 candidates of one group, done by the mask producers'
-// blocks of y = 0 in place of a launch of its own (peak NULL: nothing).
+// The same for the 64 candidates of one group, done by the tile producers'
+// first item in place of a launch of its own (peak NULL: nothing).
 struct Totals {
   int64_t* __restrict__ peak;
   int64_t* __restrict__ cost;
@@ -1221,22 +1220,28 @@ __device__ __forceinline__ bool better(const Best& x, const Best& y) {
 
 // The best over a block's threads (blockDim.x a multiple of 64, at most 1024),
 // in its first thread: shuffles within each wave, then one barrier and the
-// waves' bests.
-__device__ __forceinline__ Best wave_best(Best b, int width) {
+// waves' bests. A value-initialized T with k = -1 is no candidate.
+__device__ __forceinline__ Best from_lane(const Best& b, int off) {
+  return Best{__shfl_down(b.cost, off), __shfl_down(b.peak, off), __shfl_down(b.k, off), 0};
+}
+template <typename T>
+__device__ __forceinline__ T wave_best(T b, int width) {
 #pragma unroll 1
   for (int off = width / 2; off > 0; off >>= 1) {
-    const Best o{__shfl_down(b.cost, off), __shfl_down(b.peak, off), __shfl_down(b.k, off), 0};
+    const T o = from_lane(b, off);
     if (better(o, b)) b = o;
   }
   return b;
 }
-__device__ __forceinline__ Best block_best(Best b) {
-  __shared__ Best waves[16];
+template <typename T>
+__device__ __forceinline__ T block_best(T b) {
+  __shared__ T waves[16];
   b = wave_best(b, kWave);
   if ((threadIdx.x & (kWave - 1)) == 0) waves[threadIdx.x / kWave] = b;
   __syncthreads();
   if (threadIdx.x < kWave) {
-    b = Best{0, 0, -1, 0};
+    b = T{};
+    b.k = -1;
     if (threadIdx.x < blockDim.x / kWave) b = waves[threadIdx.x];
     b = wave_best(b, 16);
   }
@@ -1357,7 +1362,7 @@ struct BestB {
   int32_t k, pad;
 };
 
-__device__ __forceinline__ bool better_b(const BestB& x, const BestB& y) {
+__device__ __forceinline__ bool better(const BestB& x, const BestB& y) {
   if (x.k < 0) return false;
   if (y.k < 0) return true;
   if (x.B != y.B) return x.B > y.B;
@@ -1366,54 +1371,62 @@ __device__ __forceinline__ bool better_b(const BestB& x, const BestB& y) {
   return x.k < y.k;
 }
 
-__global__ void __launch_bounds__(256) ckm_batch_kernel(int32_t K, const int64_t* __restrict__ tot_peak,
-                                                        const int64_t* __restrict__ tot_cost, int64_t base,
-                                                        int64_t budget, int64_t cost_cap,
-                                                        int64_t* __restrict__ batch, BestB* __restrict__ block_best) {
-  __shared__ BestB sb[256];
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  BestB b{0, 0, 0, -1, 0};
-  if (k < K) {
-    const int64_t p = tot_peak[k], c = tot_cost[k];
-    int64_t B = 0;
-    if (c <= cost_cap && p <= budget) B = p > base ? (budget - base) / (p - base) : INT64_MAX;
-    batch[k] = B;
-    if (B > 0) b = BestB{B, c, p, k, 0};
-  }
-  sb[threadIdx.x] = b;
-  __syncthreads();
-  for (int off = blockDim.x / 2; off > 0; off >>= 1) {
-    if ((int)threadIdx.x < off && better_b(sb[threadIdx.x + off], sb[threadIdx.x])) sb[threadIdx.x] = sb[threadIdx.x + off];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) block_best[blockIdx.x] = sb[0];
+__device__ __forceinline__ BestB from_lane(const BestB& b, int off) {
+  return BestB{__shfl_down(b.B, off), __shfl_down(b.cost, off), __shfl_down(b.peak, off), __shfl_down(b.k, off), 0};
 }
 
-__global__ void __launch_bounds__(256) ckm_batch_argmax_kernel(int32_t nblocks, const BestB* __restrict__ block_best,
-                                                               int32_t n, const int32_t* __restrict__ nan_row,
-                                                               int32_t* __restrict__ best_k,
-                                                               int64_t* __restrict__ best_batch,
-                                                               int32_t* __restrict__ status) {
-  __shared__ BestB sb[256];
-  __shared__ int any_nan;
-  if (threadIdx.x == 0) any_nan = 0;
+struct BatchArgs {
+  int32_t K, n;
+  const int64_t* __restrict__ tot_peak;
+  const int64_t* __restrict__ tot_cost;
+  int64_t base, budget, cost_cap;
+  int64_t* __restrict__ batch;
+  const int32_t* __restrict__ nan_row;
+  int32_t* __restrict__ best_k;
+  int64_t* __restrict__ best_batch;
+  int32_t* __restrict__ status;
+};
+// Candidate k's multiplier, written out, as an entry of the maximum.
+__device__ __forceinline__ BestB batch_of(const BatchArgs& a, int k) {
+  const int64_t p = a.tot_peak[k], c = a.tot_cost[k];
+  int64_t B = 0;
+  if (c <= a.cost_cap && p <= a.budget) B = p > a.base ? (a.budget - a.base) / (p - a.base) : INT64_MAX;
+  a.batch[k] = B;
+  return B > 0 ? BestB{B, c, p, k, 0} : BestB{0, 0, 0, -1, 0};
+}
+// The block's best of its threads' b, and the status, written out.
+__device__ __forceinline__ void batch_result(const BatchArgs& a, BestB b) {
+  int nan = 0;
+  for (int r = threadIdx.x; r < a.n; r += blockDim.x) nan |= a.nan_row[r];
+  const int any_nan = __syncthreads_or(nan);
+  b = block_best(b);
+  if (threadIdx.x == 0) {
+    a.best_k[0] = b.k;
+    if (a.best_batch) a.best_batch[0] = b.k >= 0 ? b.B : 0;
+    if (a.status) a.status[0] = any_nan ? (int32_t)CKM_E_INVALID_ARG : (int32_t)CKM_OK;
+  }
+}
+// Everything in one block, for K up to kBatchOneBlock.
+__global__ void __launch_bounds__(1024) ckm_batch_one_kernel(BatchArgs a) {
+  BestB b{0, 0, 0, -1, 0};
+  for (int k = threadIdx.x; k < a.K; k += blockDim.x) {
+    const BestB x = batch_of(a, k);
+    if (better(x, b)) b = x;
+  }
+  batch_result(a, b);
+}
+// More candidates: a block's best each, then the best of those.
+__global__ void __launch_bounds__(256) ckm_batch_kernel(BatchArgs a, BestB* __restrict__ block_bests) {
+  const int k = blockIdx.x * blockDim.x + threadIdx.x;
+  const BestB b = block_best(k < a.K ? batch_of(a, k) : BestB{0, 0, 0, -1, 0});
+  if (threadIdx.x == 0) block_bests[blockIdx.x] = b;
+}
+__global__ void __launch_bounds__(256) ckm_batch_argmax_kernel(BatchArgs a, int32_t nblocks,
+                                                               const BestB* __restrict__ block_bests) {
   BestB b{0, 0, 0, -1, 0};
   for (int i = threadIdx.x; i < nblocks; i += blockDim.x)
-    if (better_b(block_best[i], b)) b = block_best[i];
-  int nan = 0;
-  for (int r = threadIdx.x; r < n; r += blockDim.x) nan |= nan_row[r];
-  sb[threadIdx.x] = b;
-  __syncthreads();
-  if (nan) atomicOr(&any_nan, 1);
-  for (int off = blockDim.x / 2; off > 0; off >>= 1) {
-    if ((int)threadIdx.x < off && better_b(sb[threadIdx.x + off], sb[threadIdx.x])) sb[threadIdx.x] = sb[threadIdx.x + off];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    best_k[0] = sb[0].k;
-    if (best_batch) best_batch[0] = sb[0].k >= 0 ? sb[0].B : 0;
-    if (status) status[0] = any_nan ? (int32_t)CKM_E_INVALID_ARG : (int32_t)CKM_OK;
-  }
+    if (better(block_bests[i], b)) b = block_bests[i];
+  batch_result(a, b);
 }
 
 // The tile path's R words (rbase and r_bytes as in its kernels).
@@ -1933,6 +1946,12 @@ static unsigned tile_items(int32_t n) {
 
 static bool use_tiles(const ckm_graph& g, const Layout& L) { return L.rows_on && g.tile.on; }
 
+// Rounding blocks (group, tile, 32 nodes) from which whole words beat bytes: a
+// byte's wave runs a quarter of the stages, so that small calls end sooner, but
+// stores bytes of a word from four blocks.
+// Measured, bytes / words: 60 blocks (n = 129, K = 256) 4.9 / 10.4 us;
+// 528 (n = 337, K = 501) 12.3 / 12.1; 680 (n = 505) 16.5 / 18.1;
+// 1056 (n = 337, K = 1024) 18.3 / 18.8; 8448 (n = 1009, K = 1024) 117 / 104.
 constexpr int64_t kRoundBig = 1024;
 
 hipError_t launch_round_rows(const ckm_graph& g, const Layout& L, int32_t K, uint64_t seed, uint32_t flags,
@@ -2094,20 +2113,33 @@ static hipError_t launch_closure(const ckm_graph& g, const Layout& L, const int3
   return hipGetLastError();
 }
 
+// Candidates up to which one block takes them all: K = 1024 6.4 us in one launch,
+// 4.7 + 4.2 us in two; a block walks 1024 candidates in well under a microsecond.
+constexpr int32_t kBatchOneBlock = 8192;
+
 hipError_t launch_max_batch(const ckm_graph& g, const Layout& L, int32_t K, int64_t budget, int64_t cost_cap,
                             int64_t* d_batch, int32_t* d_best_k, int64_t* d_best_batch, int32_t* d_status,
                             char* work, hipStream_t stream) {
+  const BatchArgs a = {K, g.n, at<const int64_t>(work, L.part_peak_off), at<const int64_t>(work, L.part_cost_off),
+                       g.base, budget, cost_cap, d_batch, at<const int32_t>(work, L.nan_off), d_best_k, d_best_batch,
+                       d_status};
+  if (K <= kBatchOneBlock) {
+    hipLaunchKernelGGL(ckm_batch_one_kernel, dim3(1), dim3(1024), 0, stream, a);
+    return hipGetLastError();
+  }
   const int rb = L.reduce_blocks;
-  hipLaunchKernelGGL(ckm_batch_kernel, dim3(rb), dim3(256), 0, stream, K, at<const int64_t>(work, L.part_peak_off),
-                     at<const int64_t>(work, L.part_cost_off), g.base, budget, cost_cap, d_batch,
-                     at<BestB>(work, L.bbest_off));
-  hipLaunchKernelGGL(ckm_batch_argmax_kernel, dim3(1), dim3(256), 0, stream, rb, at<const BestB>(work, L.bbest_off),
-                     g.n, at<const int32_t>(work, L.nan_off), d_best_k, d_best_batch, d_status);
+  BestB* bests = at<BestB>(work, L.bbest_off);
+  hipLaunchKernelGGL(ckm_batch_kernel, dim3(rb), dim3(256), 0, stream, a, bests);
+  hipLaunchKernelGGL(ckm_batch_argmax_kernel, dim3(1), dim3(256), 0, stream, a, rb, bests);
   return hipGetLastError();
 }
 
 // Totals read by all blocks together up to which every block of the best rows
-// selects for itself.
+// selects for itself: that saves a launch while the reads, from L2, take less.
+// Measured, together / the two kernels' sum:
+// n = 337, K = 501: 6.9 / 9.3 us; n = 1009, K = 1024 (1137 blocks, 1.2 M totals)
+// 7.6 / 9.6; n = 747, K = 3000 (819 blocks, 2.5 M totals) 12.3 / 10.0; n = 4001,
+// K = 4096 52 / 32.
 constexpr int64_t kSelectTotals = 2 << 20;
 
 hipError_t launch_select(const ckm_graph& g, const Layout& L, int32_t K, uint64_t seed,

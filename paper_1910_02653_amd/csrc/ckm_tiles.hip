@@ -65,7 +65,12 @@ struct TileBufs {
 
 // ---------------------------------------------------------------------------
 // Closure: one block per (group, tile): a wave that decides, and kPrep waves
-// that prepare the block of nodes below.
+// that prepare the block of nodes below. The bound is the deciding wave's chain:
+// per chunk of four nodes an LDS round trip (near users) and a few dependent
+// bit operations, 8 (T + 1) chunks in a row for tile T. So all else is taken
+// off that wave, and a launch hides the chain only by its number of blocks.
+// Measured: n = 1009: 64 us with 3 or 8 groups, 69 us with 16 (its 256 chunks at
+// 0.25 us); n = 4001, K = 4096 (8064 blocks): 2.82 ms.
 constexpr int kPrep = 2;
 constexpr int kPrepNodes = kTile / kPrep;
 
@@ -328,7 +333,12 @@ __global__ void __launch_bounds__(kWave) ckm_hub_kernel(TileArgs t, cptr<int32_t
 // peak is taken there), then the dependencies that FREE releases after it
 // leave. All sums are binary64 integers below 2^53, exact in any order; a
 // wave's stage j counts U in units of 2^(j - 1074), so that its bit of a word
-// is the unit itself (denormals are exact and run at full rate).
+// is the unit itself (denormals are exact and run at full rate). The bound is
+// vector issue (per record and stage four ANDs, four FMAs and a maximum), then
+// the latency of a record's words, hidden by four waves per SIMD.
+// Measured: n = 1009, K = 1024: 164 us (the instructions alone 119 us); n = 4001,
+// K = 4096: 10.1 ms (7.5 ms). One kernel for closure and simulation, a stage to a
+// wave: 440 us and 75 ms.
 struct SimArgs {
   TileArgs t;
   int32_t K, groups;
@@ -528,6 +538,13 @@ static void launch_simulate(const SimArgs& s, hipStream_t stream) {
                      0, stream, s);
 }
 
+// (group, tile) pairs from which the chip is full with fewer waves per pair:
+// with few, eight stages a wave and eight parts a tile shorten each wave's run
+// over the records; sixteen stages read each word once for twice the stages;
+// four parts leave half the sums to join.
+// Measured, with 8 stages and 8 parts / 16 and 8 / 16 and 4: 256 pairs (n = 1009,
+// K = 512) 112 us / - / 166; 512 pairs (K = 1024) 200 / 164 / 184; 1128 pairs
+// (n = 747, K = 3000) 457 / - / 313; 8064 pairs (n = 4001) 15.2 ms / - / 10.1.
 constexpr int64_t kSimItems = 512;
 
 hipError_t launch_tiles(const ckm_graph& g, const Layout& L, int32_t K, char* work, hipStream_t stream) {

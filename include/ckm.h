@@ -149,12 +149,14 @@ ckm_status ckm_round_eval(const ckm_graph* g, const double* s_frac, int64_t ld, 
 
 /* Bytes of work buffer for K candidates on graph g. This includes, when the
  * S rows of all K candidates fit in 8 GiB, room for them and for their R
- * rows (the row arrays, about twice the S rows' size; 8.5 GB at n = 4001,
- * K = 4096): the evaluate stage then streams each row from there instead of making it
- * twice (randomized rounding, threshold rounding) or reading it from each
- * candidate's own matrix (supplied schedules). A smaller buffer of at least
- * ckm_workspace_size_min bytes is accepted, and the rows are then made
- * inside the evaluate stage (same results). */
+ * rows (the row arrays, about twice the S rows' size), and on a graph with
+ * nodes of more than five users room for what is read of these users together
+ * (1 GiB at most, and at most a few times the S rows' size except where nodes
+ * have tens of users): 9.5 GB at n = 4001, K = 4096. The evaluate stage then
+ * makes each row once. With less of that last part (16 MiB are always enough)
+ * it runs in more launches. A smaller buffer of at least ckm_workspace_size_min
+ * bytes is accepted, and the rows are then made inside the evaluate stage, by
+ * another and much slower kernel (same results). */
 ckm_status ckm_workspace_size(const ckm_graph* g, int32_t K, size_t* bytes);
 
 /* The smallest work buffer accepted for K candidates: without the row array. */
@@ -333,8 +335,8 @@ ckm_status ckm_plan_async(const ckm_graph* g, const uint64_t* d_S, const uint64_
  * graph is created on the device. The call allocates nothing (no hipMalloc,
  * hipFree or other allocating routine) and only enqueues work on `stream`.
  * A problem whose smallest work buffer (ckm_workspace_size_min) exceeds the
- * area gives CKM_E_UNSUPPORTED; the row arrays are used when the full work
- * buffer (ckm_workspace_size) fits in it. Every call on one device shares
+ * area gives CKM_E_UNSUPPORTED; the row arrays are used when they fit in it
+ * (see ckm_workspace_size). Every call on one device shares
  * that device's area and the area keeps the last call's contents: calls
  * that may overlap on one device (other streams, other threads) race, and
  * the caller must serialize them. */

@@ -300,21 +300,23 @@ Layout make_layout(const ckm_graph& g, int32_t K) {
   L.total = off;
   // The row arrays: last, and optional (without them the evaluate stage
   // makes its S rows itself and select recomputes the best R).
-  const size_t kpad = (size_t)((K + kWave - 1) / kWave) * kWave;
+  const size_t kpad = (size_t)((K + kWave - 1) / kWave) * kWave, groups = kpad / kWave;
   L.rows_off = off;
+  const int32_t tiles = (n + ckm::kTile - 1) / ckm::kTile;
   size_t s_bytes, r_bytes;
   if (g.tile.on) {
-    const int32_t tiles = (n + ckm::kTile - 1) / ckm::kTile;
-    s_bytes = kpad / kWave * stile_off(tiles);
-    r_bytes = kpad / kWave * rtile_off(g.tile.rbase, tiles);
+    s_bytes = groups * stile_off(tiles);
+    r_bytes = groups * rtile_off(tiles);
+    if (g.tile.nhub) L.hub_bytes = std::min(groups * 256 * g.tile.hub_at[0], ckm::kHubMaxBytes);
   } else {
     // word w of row t at (base(t) + w) * kpad + k
     const size_t full = (size_t)(n >> 5), rem = (size_t)(n & 31);
     s_bytes = r_bytes = kpad * (32 * full * (full + 1) / 2 + rem * (full + 1)) * sizeof(uint32_t);
   }
-  L.rows_on = s_bytes <= ckm::kRowsMaxBytes && r_bytes <= ckm::kRRowsMaxBytes;
+  L.rows_on = s_bytes <= ckm::kRowsMaxBytes;
   L.rrows_off = align256(off + s_bytes);
-  L.total_rows = L.rows_on ? align256(L.rrows_off + r_bytes) : off;
+  L.hub_off = align256(L.rrows_off + r_bytes);
+  L.total_rows = L.rows_on ? L.hub_off + L.hub_bytes : off;
   return L;
 }
 
@@ -446,12 +448,10 @@ static ckm_status graph_create(int32_t n, const int32_t* dep_ptr, const int32_t*
   const size_t off_di = align256(off_dp + (n + 1) * sizeof(int32_t));
   const size_t off_uo = align256(off_di + Ea * sizeof(int32_t));
   const size_t off_rec = align256(off_uo + Ea * sizeof(int32_t));
-  const size_t off_mrec = align256(off_rec + (size_t)n * ckm::kNodeRecBytes);
   // the tile path's tables (its sums are binary64)
   ckm::TileTables tt;
-  const bool tiles =
-      !wide && ckm::build_tiles(n, bytes, cost, dp.data(), di.data(), up.data(), ui.data(), tt);
-  size_t tile_end = off_mrec;
+  if (!wide) ckm::build_tiles(n, bytes, cost, dp.data(), di.data(), up.data(), ui.data(), tt);
+  size_t tile_end = align256(off_rec + (size_t)n * ckm::kNodeRecBytes);
   const auto place = [&](size_t b) {
     const size_t at = tile_end;
     tile_end = align256(tile_end + b);
@@ -461,7 +461,7 @@ static ckm_status graph_create(int32_t n, const int32_t* dep_ptr, const int32_t*
                off_far = place(tt.far.size() * 4), off_fmore = place(tt.far_more.size() * 4), off_ops = place(tt.ops.size() * sizeof(ckm::SimOps)),
                off_refs = place(tt.refs.size() * sizeof(ckm::SimRefs)),
                off_trec = place(tt.tile_rec.size() * 4), off_hptr = place(tt.hub_ptr.size() * 4),
-               off_hub = place(tt.hub.size() * sizeof(ckm::HubUser));
+               off_hub = place(tt.hub.size() * sizeof(ckm::HubUser)), off_hat = place(tt.hub_at.size() * 4);
   const size_t total = tile_end;
   std::vector<char> host(total, 0);
   const auto copy = [&](size_t off, const auto& v) {
@@ -476,6 +476,7 @@ static ckm_status graph_create(int32_t n, const int32_t* dep_ptr, const int32_t*
   copy(off_trec, tt.tile_rec);
   copy(off_hptr, tt.hub_ptr);
   copy(off_hub, tt.hub);
+  copy(off_hat, tt.hub_at);
   memcpy(host.data() + off_M, bytes, n * sizeof(int64_t));
   memcpy(host.data() + off_C, cost, n * sizeof(int64_t));
   memcpy(host.data() + off_up, up.data(), (n + 1) * sizeof(int32_t));
@@ -525,9 +526,8 @@ static ckm_status graph_create(int32_t n, const int32_t* dep_ptr, const int32_t*
   g->d_dep_idx = reinterpret_cast<const int32_t*>(base + off_di);
   g->d_dep_upos = reinterpret_cast<const int32_t*>(base + off_uo);
   g->d_recs = base + off_rec;
-  if (tiles) {
+  if (!wide) {
     g->tile.on = true;
-    g->tile.rbase = tt.rbase;
     g->tile.nhub = tt.nhub;
     g->tile.d_desc = reinterpret_cast<const uint32_t*>(base + off_desc);
     g->tile.d_near_more = reinterpret_cast<const uint32_t*>(base + off_nmore);
@@ -538,6 +538,8 @@ static ckm_status graph_create(int32_t n, const int32_t* dep_ptr, const int32_t*
     g->tile.d_tile_rec = reinterpret_cast<const int32_t*>(base + off_trec);
     g->tile.d_hub_ptr = reinterpret_cast<const int32_t*>(base + off_hptr);
     g->tile.d_hub = base + off_hub;
+    g->tile.d_hub_at = reinterpret_cast<const uint32_t*>(base + off_hat);
+    g->tile.hub_at = std::move(tt.hub_at);
   }
   g->sync = new (std::nothrow) ckm::SyncCache;
   if (!g->sync) {
@@ -585,7 +587,12 @@ static ckm_status check_work(const ckm_graph* g, int32_t K, void* d_work, size_t
   *L = ckm::make_layout(*g, K);
   if (work_bytes < L->total)
     return fail(CKM_E_INVALID_ARG, "work buffer of %zu bytes, %zu needed", work_bytes, L->total);
-  L->rows_on = L->rows_on && work_bytes >= L->total_rows;
+  if (L->rows_on && work_bytes < L->total_rows) {
+    // less room than asked for: hub words of fewer pairs at a time, or no row arrays
+    const size_t most = g->tile.nhub ? ckm::hub_pair_bytes(g->tile, (g->n - 1) / ckm::kTile) : 0;
+    L->rows_on = most && work_bytes >= L->hub_off + most;
+    if (L->rows_on) L->hub_bytes = work_bytes - L->hub_off;
+  }
   return CKM_OK;
 }
 

@@ -14,11 +14,11 @@ namespace ckm {
 struct SyncCache;  // buffers and stream of the synchronous entry points (ckm_host.cpp)
 
 // The tile path's tables on the device (TileTables, ckm_tiles.h); on is false
-// for the graphs that do not take it (wide or very dense ones).
+// for wide graphs, which do not take it.
 struct TileGraph {
   bool on = false;
-  uint32_t rbase = 0;
   int32_t nhub = 0;
+  std::vector<uint32_t> hub_at;  // slots of hub words of a group in the tiles above each (TileTables)
   const uint32_t* d_desc = nullptr;
   const uint32_t* d_near_more = nullptr;
   const uint32_t* d_far = nullptr;
@@ -28,6 +28,7 @@ struct TileGraph {
   const int32_t* d_tile_rec = nullptr;
   const int32_t* d_hub_ptr = nullptr;
   const void* d_hub = nullptr;
+  const uint32_t* d_hub_at = nullptr;
 };
 }
 
@@ -71,15 +72,18 @@ enum : int {
   kSrcRows = 3,       // randomized rounding done beforehand into the work buffer's row array
 };
 
-// The row arrays (S rows streamed by the evaluate kernel, R rows it keeps)
-// are used when the S rows fit in this many bytes (about K * n^2 / 16 bytes
-// each; 4.1 GB at n = 4001, K = 4096); larger problems, or work buffers sized
-// without them, make the S rows in the evaluate kernel and recompute the best
-// candidate's R.
-// R tiles also hold the hub words, which a dense graph has many more of than
-// nodes: their bound is four times that of the S rows.
+// The row arrays (S rows streamed by the evaluate kernel, R rows it keeps; S and
+// R tiles on the tile path) are used when the S rows fit in this many bytes
+// (about K * n^2 / 16 bytes each; 4.1 GB at n = 4001, K = 4096); larger
+// problems, or work buffers sized without them, make the S rows in the evaluate
+// kernel and recompute the best candidate's R.
 constexpr size_t kRowsMaxBytes = (size_t)8 << 30;
-constexpr size_t kRRowsMaxBytes = (size_t)32 << 30;
+// Room asked for hub words, at most: when all (group, tile) pairs have more, hub
+// words and simulation run in several launches, each over the pairs that fit (64
+// at least). Measured, in the launches that the room leads to:
+// n = 2049, 65,568 edges, K = 512 (520 pairs): 17.2 ms in eight, 8.2 in one;
+// n = 801, 40,008 edges, K = 512 (208 pairs): 4.0 ms in two, 3.5 in one.
+constexpr size_t kHubMaxBytes = (size_t)1 << 30;
 
 // Host-side builder of the per-node records the evaluate kernel reads
 // (layout documented with NodeRec in ckm_kernels.hip). Writes n records.
@@ -89,10 +93,13 @@ void build_node_records(int32_t n, const int64_t* M, const int64_t* C, bool wide
                         void* out);
 
 // The tile path's S and R words (ckm_tiles.h): for one candidate group, tile T
-// of 32 stages holds a word per lane of 32 (T + 1) nodes, one tile after another. An R tile has rbase bytes before them.
+// of 32 stages holds a word per lane of 32 (T + 1) nodes, one tile after another. An R tile has a word before them.
 __host__ __device__ __forceinline__ uint32_t stile_bytes(int T) { return 8192u * (uint32_t)(T + 1); }
 __host__ __device__ __forceinline__ size_t stile_off(int T) { return (size_t)4096 * T * (T + 1); }
-__host__ __device__ __forceinline__ size_t rtile_off(uint32_t rbase, int T) { return stile_off(T) + (size_t)rbase * T; }
+__host__ __device__ __forceinline__ size_t rtile_off(int T) { return stile_off(T) + (size_t)256 * T; }
+
+// Hub words of a (group, tile) pair: a word of zeros and the tile's.
+inline size_t hub_pair_bytes(const TileGraph& t, int T) { return (size_t)256 * (t.hub_at[T] - t.hub_at[T + 1]); }
 
 // Work-buffer layout for (n, K). Offsets are bytes from the buffer start,
 // each 256-byte aligned.
@@ -116,7 +123,9 @@ struct Layout {
          total = 0,        // bytes every call needs
          rows_off = 0,     // S rows of every candidate (kSrcRows, or S tiles), past `total`
          rrows_off = 0,    // R rows (or R tiles) of every candidate, written by the evaluate stage
-         total_rows = 0;   // total plus the two row arrays when they are used
+         hub_off = 0,      // the tile path's hub words, of as many (group, tile) pairs as hub_bytes hold
+         hub_bytes = 0,
+         total_rows = 0;   // total plus the row arrays (and the hub words) when they are used
   bool rows_on = false;    // the S rows fit kRowsMaxBytes (and, after
                            // check_work, the caller's buffer holds both)
 };

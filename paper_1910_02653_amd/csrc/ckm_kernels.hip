@@ -1429,10 +1429,9 @@ __global__ void __launch_bounds__(256) ckm_batch_argmax_kernel(BatchArgs a, int3
   batch_result(a, b);
 }
 
-// The tile path's R words (rbase and r_bytes as in its kernels).
+// The tile path's R words (r_bytes as in its kernels).
 struct RTiles {
   const char* rtiles;
-  uint32_t rbase;
   size_t r_bytes;
   uint64_t* __restrict__ R_rows;   // null: none are gathered
 };
@@ -1442,8 +1441,8 @@ __device__ __forceinline__ void best_r_tiles(const RTiles& t, int n, int words64
   if (32 * tile >= n || v >= kWave * words64) return;   // whole waves
   uint32_t w = 0;
   if (bk >= 0 && v < min(n, 32 * (tile + 1)))   // nodes above compute nothing in these stages
-    w = *reinterpret_cast<const uint32_t*>(t.rtiles + (size_t)(bk / kWave) * t.r_bytes + rtile_off(t.rbase, tile) +
-                                           t.rbase + (size_t)v * 256 + 4 * (bk & (kWave - 1)));
+    w = *reinterpret_cast<const uint32_t*>(t.rtiles + (size_t)(bk / kWave) * t.r_bytes + rtile_off(tile) +
+                                           (size_t)(v + 1) * 256 + 4 * (bk & (kWave - 1)));
   for (int j = 0; j < 32 && 32 * tile + j < n; ++j) {
     const uint64_t row = __ballot((w >> j) & 1u);
     if ((threadIdx.x & (kWave - 1)) == 0) t.R_rows[(size_t)(32 * tile + j) * words64 + v / kWave] = row;
@@ -1915,8 +1914,7 @@ static void (*eval_kernel_for(int32_t words, int src, bool wide))(EvalArgs) {
     if (src == kSrcThreshold) return ckm_eval_kernel<0, kSrcThreshold, true>;
     return ckm_eval_kernel<0, kSrcRound, true>;
   }
-  const int w = reg_row_width(words);
-  if (src == kSrcRows) return eval_kernel_w<kSrcRows>(w);
+  const int w = reg_row_width(words);   // no row arrays: with them a graph that is not wide takes the tile path
   if (src == kSrcUser) return eval_kernel_w<kSrcUser>(w);
   if (src == kSrcThreshold) return eval_kernel_w<kSrcThreshold>(w);
   return eval_kernel_w<kSrcRound>(w);
@@ -2154,8 +2152,7 @@ hipError_t launch_select(const ckm_graph& g, const Layout& L, int32_t K, uint64_
   RTiles tiles = {};
   if (use_tiles(g, L) && d_best_R) {
     tiles.rtiles = work + L.rrows_off;
-    tiles.rbase = g.tile.rbase;
-    tiles.r_bytes = rtile_off(g.tile.rbase, (g.n + 31) / 32);
+    tiles.r_bytes = rtile_off((g.n + 31) / 32);
     tiles.R_rows = d_best_R;
     d_best_R = nullptr;
   }

@@ -5,32 +5,49 @@
 
 namespace ckm {
 
-bool build_tiles(int32_t n, const int64_t* M, const int64_t* C, const int32_t* dep_ptr, const int32_t* dep_idx,
-                 const int32_t* user_ptr, const int32_t* user_idx, TileTables& T) {
+void build_tiles(int32_t n, const int64_t* M, const int64_t* C, const int32_t* dep_ptr, const int32_t* dep_idx,
+                 const int32_t* user_ptr, const int32_t* user_idx, TileTables& T, int64_t max_hub_words) {
   T = TileTables();
   T.n = n;
   T.tiles = (n + kTile - 1) / kTile;
 
-  // hub words: their places first (they set rbase), then their tables
-  uint32_t words = 0;
-  std::vector<uint32_t> first_word(n, 0);
-  if (n >= kMaxSlots) return false;
-  for (int32_t i = 0; i < n; ++i) {
+  // hub words: word w of a node with m users covers its highest w step, which are
+  // three at least (or step) and below m (no dependency has all m above it)
+  const auto first_of = [](int32_t step) { return step == 1 ? 3 : 1; };
+  const auto words_at = [&](int32_t i, int32_t step) {
     const int32_t m = user_ptr[i + 1] - user_ptr[i];
-    if (m <= kHubUsers) continue;
-    first_word[i] = words;
-    words += (uint32_t)(m - 3);
-    if (1 + (int64_t)words + kTile * (int64_t)T.tiles > kMaxSlots) return false;
+    return m > kHubUsers ? (m - 1) / step + 1 - first_of(step) : 0;
+  };
+  for (;; ++T.step) {
+    int64_t words = 0;
+    for (int32_t i = 0; i < n; ++i) words += words_at(i, T.step);
+    if (words <= (T.step < kHubStep ? std::min(max_hub_words, (int64_t)kHubWordsPerNode * n) : max_hub_words)) break;
   }
-  T.rbase = node_off((int32_t)(1 + words));
-  const auto word_off = [](uint32_t x) { return node_off((int32_t)(1 + x)); };
+  const int32_t w0 = first_of(T.step);
+  std::vector<int32_t> first_word(n + 1, 0);
+  for (int32_t i = 0; i < n; ++i) first_word[i + 1] = first_word[i] + words_at(i, T.step);
+  std::vector<int32_t> lowest(first_word[n]), order(first_word[n]), slot_of(first_word[n]);
+  for (int32_t i = 0; i < n; ++i)
+    for (int32_t w = first_word[i]; w < first_word[i + 1]; ++w)
+      lowest[w] = user_idx[user_ptr[i + 1] - T.step * (w - first_word[i] + w0)];
+  for (size_t w = 0; w < order.size(); ++w) order[w] = (int32_t)w;
+  std::stable_sort(order.begin(), order.end(), [&](int32_t a, int32_t b) { return lowest[a] < lowest[b]; });
+  for (size_t k = 0; k < order.size(); ++k) slot_of[order[k]] = (int32_t)k + 1;
+  if (!order.empty()) {
+    T.hub_at.assign(T.tiles + 1, 0);
+    for (int32_t k = T.tiles - 1, w = (int32_t)order.size(); k >= 0; --k) {
+      while (w > 0 && lowest[order[w - 1]] >= kTile * (k + 1)) --w;
+      T.hub_at[k] = T.hub_at[k + 1] + 1 + (uint32_t)w;
+    }
+  }
   T.hub_ptr.push_back(0);
   for (int32_t i = 0; i < n; ++i) {
-    const int32_t m = user_ptr[i + 1] - user_ptr[i];
-    if (m <= kHubUsers) continue;
-    for (int32_t k = 0; k < m; ++k) {   // k users above
+    if (first_word[i] == first_word[i + 1]) continue;
+    const int32_t used = T.step * (first_word[i + 1] - first_word[i] + w0 - 1);   // the users that some word covers
+    for (int32_t k = 0; k < used; ++k) {
       const int32_t u = user_idx[user_ptr[i + 1] - 1 - k];
-      T.hub.push_back({T.rbase + node_off(u), k >= 3 ? word_off(first_word[i] + (uint32_t)(k - 3)) : 0u});
+      const int32_t w = (k + 1) / T.step;
+      T.hub.push_back({kRBase + node_off(u), (k + 1) % T.step || w < w0 ? 0u : node_off(slot_of[first_word[i] + w - w0])});
     }
     T.hub_ptr.push_back((int32_t)T.hub.size());
     ++T.nhub;
@@ -68,9 +85,9 @@ bool build_tiles(int32_t n, const int64_t* M, const int64_t* C, const int32_t* d
           ++nn;
         } else {
           if (nf < 2)
-            far[16 * nf] = T.rbase + node_off(u);
+            far[16 * nf] = kRBase + node_off(u);
           else
-            T.far_more.push_back(T.rbase + node_off(u));
+            T.far_more.push_back(kRBase + node_off(u));
           ++nf;
         }
       }
@@ -94,25 +111,35 @@ bool build_tiles(int32_t n, const int64_t* M, const int64_t* C, const int32_t* d
     for (int32_t a = 0; a < std::max(nd, 1); a += 2) {
       SimOps o{};
       SimRefs r{};
-      const auto slot = [](uint32_t off) { return (uint16_t)(off / kSlotBytes); };
       r.v = r.s[0] = r.s[1] = (uint16_t)v;
       if (a == 0) {
         o.M = (double)M[v];
-        r.C = (uint64_t)C[v];
+        o.C = (uint64_t)C[v];
       }
       for (int k = 0; k < 2 && a + k < nd; ++k) {
         const int32_t i = dep_idx[dep_ptr[v] + a + k];
         (k ? o.M1 : o.M0) = (double)M[i];
         r.s[k] = (uint16_t)i;
-        const int32_t* b = user_idx + user_ptr[i];
-        const int32_t* e = user_idx + user_ptr[i + 1];
-        const int32_t* above = std::upper_bound(b, e, v);
-        const int32_t na = (int32_t)(e - above);
-        if (e - b > kHubUsers && na >= 3) {
-          r.u[k][0] = slot(word_off(first_word[i] + (uint32_t)(na - 3)));
-        } else {
-          for (int32_t x = 0; x < na; ++x) r.u[k][x] = slot(T.rbase + node_off(above[x]));   // at most kHubUsers - 1
-          if (na > 2) r.more = 1;
+        const int32_t* above = std::upper_bound(user_idx + user_ptr[i], user_idx + user_ptr[i + 1], v);
+        const int32_t na = (int32_t)(user_idx + user_ptr[i + 1] - above);
+        const bool hub = na > 2 && first_word[i] < first_word[i + 1] && na >= T.step;
+        const int32_t left = hub ? na % T.step : na;
+        if (hub) {
+          r.u[k][3] = (uint16_t)slot_of[first_word[i] + na / T.step - w0];
+          r.more |= kMoreHub << k;
+        }
+        for (int32_t x = 0; x < left && x < 2; ++x) r.u[k][x] = (uint16_t)(above[x] + 1);
+        if (left > 2 && T.step > kHubStep) {
+          r.list[k] = (uint32_t)(above - user_idx) + 2;
+          r.u[k][2] = (uint16_t)(left - 2);
+          r.more |= kMoreList << k;
+        } else if (left > 2) {
+          r.u[k][2] = (uint16_t)(above[2] + 1);
+          r.more |= kMoreThird << k;
+          if (left > 3) {
+            r.u[k][3] = (uint16_t)(above[3] + 1);
+            r.more |= kMoreFourth << k;
+          }
         }
       }
       T.ops.push_back(o);
@@ -127,7 +154,6 @@ bool build_tiles(int32_t n, const int64_t* M, const int64_t* C, const int32_t* d
     T.ops.push_back(SimOps{});
     T.refs.push_back(SimRefs{});
   }
-  return true;
 }
 
 }  // namespace ckm

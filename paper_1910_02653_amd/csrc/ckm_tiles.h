@@ -54,31 +54,41 @@ constexpr int kFarNodes = 16, kFarDwords = 64;
 struct SimOps {
   double M;            // M_v (0 past a node's first record)
   double M0, M1;       // sizes of the dependencies (0 when absent)
-  double pad;
-};
-// Its words, as offsets in slots (node_off / 256): S tile slots of the node and
-// the dependencies, R tile slots of the dependencies' users above v (0 when
-// absent).
-struct SimRefs {
-  uint16_t v, s[2];
-  uint16_t u[2][4];
-  uint16_t more;       // u[.][2] present
   uint64_t C;          // C_v (0 past a node's first record)
 };
-constexpr int32_t kMaxSlots = 65536;         // of an R tile, for the tile path
+// Its words, as slots of kSlotBytes: of the S tile for the node and the
+// dependencies, of the R tile for the dependencies' users above v (0, the empty
+// word, when absent), of the tile's hub words for the rest of them.
+struct SimRefs {
+  uint16_t v, s[2];
+  uint16_t more;       // kMore* << dependency
+  uint16_t u[2][4];    // three users, or two and the count of the list; the hub word or a fourth user
+  uint32_t list[2];    // kMoreList: where the users past the second are in the graph's users
+};
+constexpr uint32_t kMoreThird = 1, kMoreHub = 4, kMoreList = 16, kMoreFourth = 64;
 
-// Nodes with more than kHubUsers users: for each user with three or more above
-// it, the OR of those above (a hub word) is made once, after the closure, and
-// stands in for them.
+// Hub words. A node with more than kHubUsers users has a word for its highest
+// `step` users, one for its highest 2 step, and so on: the OR of their R, made
+// after the closure. A dependency with three or more users above v takes one of
+// them and the less than `step` users below those that it covers; with two or
+// less it takes these (so that step 1 needs no word of one or two users).
+// step is the smallest with at most kHubWordsPerNode words per node, or 4, the
+// largest whose users fit in a record; if a tile would have more than kMaxHubWords
+// then, it is as large as that needs, and the users past the second come in a
+// list. So a tile's hub words are a few per node, or at most a quarter of the
+// edges, and never above 16 MB, whatever the graph. (A word per user, without
+// these bounds, took 75 times the S rows at n = 300 and all edges.)
 constexpr int kHubUsers = 5;
+constexpr int kHubWordsPerNode = 4;
+constexpr int kHubStep = 4;
+constexpr int64_t kMaxHubWords = 65535;      // slot 0 is a word of zeros
 struct HubUser {
   uint32_t r;          // R tile byte offset of the user
-  uint32_t x;          // R tile byte offset of the hub word of the users above it (0: none)
+  uint32_t x;          // byte offset among the hub words of the word that it completes (0: none)
 };
 
 struct TileTables {
-  int32_t n = 0, tiles = 0, nrec = 0, nhub = 0;
-  uint32_t rbase = 0;                   // R tile byte offset of node 0: after the empty word and the hub words
+  int32_t n = 0, tiles = 0, nrec = 0, nhub = 0, step = 1;
   std::vector<uint32_t> desc;           // tiles * 8 chunks * kDescDwords
   std::vector<uint32_t> near_more;      // LDS byte offsets
   std::vector<uint32_t> far;            // tiles * 2 * kFarDwords
@@ -88,13 +98,18 @@ struct TileTables {
   std::vector<int32_t> tile_rec;        // records of the nodes below each tile's end
   std::vector<int32_t> hub_ptr;         // nhub + 1
   std::vector<HubUser> hub;             // users in decreasing order
+  // Hub words are numbered from 1 in the order of the lowest user that each
+  // covers, and a tile makes those that cover a node of it. hub_at[T]: slots
+  // of a group's tiles T and up (each with a word of zeros, slot 0); empty
+  // without hub words.
+  std::vector<uint32_t> hub_at;         // tiles + 1
 };
 
-// S tile byte offset of node v's words (R tiles: + rbase).
+// S tile byte offset of node v's words; R tiles have an empty word before them.
 constexpr uint32_t node_off(int32_t v) { return (uint32_t)v * (uint32_t)kSlotBytes; }
-// False when the graph does not take the tile path (an R tile with its hub words
-// has more than kMaxSlots slots).
-bool build_tiles(int32_t n, const int64_t* M, const int64_t* C, const int32_t* dep_ptr, const int32_t* dep_idx,
-                 const int32_t* user_ptr, const int32_t* user_idx, TileTables& T);
+constexpr uint32_t kRBase = kSlotBytes;
+void build_tiles(int32_t n, const int64_t* M, const int64_t* C, const int32_t* dep_ptr, const int32_t* dep_idx,
+                 const int32_t* user_ptr, const int32_t* user_idx, TileTables& T,
+                 int64_t max_hub_words = kMaxHubWords);
 
 }  // namespace ckm

@@ -39,8 +39,7 @@ __device__ __forceinline__ uint32_t rl(uint32_t w, int lane) { return __builtin_
 __device__ __forceinline__ uint32_t s1_of(uint32_t s, uint32_t next) { return __builtin_amdgcn_alignbit(next, s, 1); }
 
 struct TileArgs {
-  int32_t n, tiles;
-  uint32_t rbase;
+  int32_t n, tiles, groups;
   size_t s_bytes, r_bytes;          // S and R tiles of one group
   const char* stiles;
   char* rtiles;
@@ -58,8 +57,8 @@ struct TileBufs {
     next = buffer(last ? st : st + bytes, bytes);   // as many nodes of it are read
     vo = 4u * (uint32_t)lane;
     vo_next = last ? kPastEnd : vo;
-    r_bytes = a.rbase + bytes;
-    r = buffer(a.rtiles + (size_t)group * a.r_bytes + rtile_off(a.rbase, tile), r_bytes);
+    r_bytes = kRBase + bytes;
+    r = buffer(a.rtiles + (size_t)group * a.r_bytes + rtile_off(tile), r_bytes);
   }
 };
 
@@ -222,7 +221,7 @@ template <bool kTop>
 __device__ __forceinline__ void decide_block(const ClosureArgs& a, const TileBufs& b, lds_char* lds, int nb,
                                              uint32_t (&d)[kDescVecs]) {
   lds_char* blk = lds + (nb & 1) * kTile * kSlotBytes;
-  const uint32_t r_off = (uint32_t)uniform((int)(a.t.rbase + node_off(kTile * nb)));
+  const uint32_t r_off = (uint32_t)uniform((int)(kRBase + node_off(kTile * nb)));
   const int nodes = a.t.n - kTile * nb;
   const uint32_t flags = rl(d[0], 16);
   if (flags & kBlockMany)
@@ -303,25 +302,59 @@ __global__ void __launch_bounds__(kWave*(1 + kPrep)) ckm_closure_kernel(ClosureA
   }
 }
 
-// Hub words: one wave per (group, tile, hub), over the hub's users from the
-// highest down: word x of a user is the OR of R over the users above it.
-__global__ void __launch_bounds__(kWave) ckm_hub_kernel(TileArgs t, cptr<int32_t> hub_ptr, cptr<HubUser> hub) {
-  const TileBufs b(t, blockIdx.x, t.tiles - 1 - (int)blockIdx.y, threadIdx.x);
-  const int e1 = hub_ptr[blockIdx.z + 1];
+// Hub words of the (group, tile) pairs from item0 on: one wave per pair and hub,
+// over the hub's users below the tile's end from the highest down. The bound is
+// memory: a word read per user, a quarter as many written.
+struct HubArgs {
+  cptr<int32_t> ptr;
+  cptr<HubUser> users;
+  cptr<uint32_t> at;                // TileTables::hub_at (null: no hub words)
+  char* buf;                        // the words of the launch's pairs, one pair after another
+  int32_t item0, items;
+};
+__device__ __forceinline__ void tile_of(const TileArgs& t, int item, int& tile, int& group) {
+  tile = t.tiles - 1 - item / t.groups;   // the longest start first
+  group = item % t.groups;
+}
+// A pair's hub words: a word of zeros, then `words` words.
+struct HubBuf {
+  __amdgpu_buffer_rsrc_t buf;
+  uint32_t words;
+  __device__ __forceinline__ HubBuf(const TileArgs& t, const HubArgs& h, int tile, int group) {
+    const auto before = [&](int T, int g) { return (uint64_t)t.groups * h.at[T + 1] + (uint64_t)g * (h.at[T] - h.at[T + 1]); };
+    int tile0, group0;
+    tile_of(t, h.item0, tile0, group0);
+    words = h.at[tile] - h.at[tile + 1] - 1;
+    buf = buffer(h.buf + (before(tile, group) - before(tile0, group0)) * kSlotBytes, node_off(1 + (int)words));
+  }
+};
+__global__ void __launch_bounds__(kWave) ckm_hub_kernel(TileArgs t, HubArgs h) {
+  int tile, group;
+  tile_of(t, h.item0 + (int)blockIdx.x, tile, group);
+  const TileBufs b(t, group, tile, threadIdx.x);
+  const auto out = HubBuf(t, h, tile, group).buf;
+  if (blockIdx.y == 0) __builtin_amdgcn_raw_buffer_store_b32(0u, out, (int)b.vo, 0, 0);
+  const int e1 = h.ptr[blockIdx.y + 1];
+  int e0 = h.ptr[blockIdx.y];
+  for (int end = e1; e0 < end;) {   // users at or above the tile's end compute nothing in its stages
+    const int mid = (e0 + end) / 2;
+    if (h.users[mid].r < b.r_bytes)
+      end = mid;
+    else
+      e0 = mid + 1;
+  }
   uint32_t acc = 0;
-  for (int e = hub_ptr[blockIdx.z]; e < e1; e += 8) {
+  for (int e = e0; e < e1; e += 8) {
     uint32_t x[8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const uint32_t off = hub[min(e + k, e1 - 1)].r;
-      x[k] = __builtin_amdgcn_raw_buffer_load_b32(b.r, (int)b.vo, (int)(off < b.r_bytes ? off : 0u), 0);
-    }
+    for (int k = 0; k < 8; ++k)
+      x[k] = __builtin_amdgcn_raw_buffer_load_b32(b.r, (int)b.vo, (int)h.users[min(e + k, e1 - 1)].r, 0);
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
       if (e + k >= e1) break;
-      const uint32_t xo = hub[e + k].x;
-      if (xo) __builtin_amdgcn_raw_buffer_store_b32(acc, b.r, (int)b.vo, (int)xo, 0);
       acc |= x[k];
+      const uint32_t xo = h.users[e + k].x;
+      if (xo) __builtin_amdgcn_raw_buffer_store_b32(acc, out, (int)b.vo, (int)xo, 0);
     }
   }
 }
@@ -341,11 +374,13 @@ __global__ void __launch_bounds__(kWave) ckm_hub_kernel(TileArgs t, cptr<int32_t
 // wave: 440 us and 75 ms.
 struct SimArgs {
   TileArgs t;
-  int32_t K, groups;
+  HubArgs h;                        // and the pairs of the launch
+  int32_t K;
   double base;                      // M_in + 2 M_param
   cptr<u64x4> ops;                  // SimOps
   cptr<u32x8> refs;                 // SimRefs
   cptr<int32_t> tile_rec;
+  cptr<int32_t> users;              // the graph's users lists
   int64_t* __restrict__ peak;
   int64_t* __restrict__ cost;
 };
@@ -394,7 +429,7 @@ __device__ __forceinline__ void sim_record(SimStages8 (&x)[kSub / 8], uint32_t R
 
 // The words of a record: requested a record ahead.
 struct SimIn {
-  uint32_t R, S, s0, n0, s1, n1, u[8];
+  uint32_t R, S, s0, n0, s1, n1, u[2][4];
 };
 
 // kSub stages per wave; kSegs waves share the tile's records, and each part
@@ -407,10 +442,17 @@ __global__ void __launch_bounds__(kWave* kSegs) ckm_simulate_kernel(SimArgs a) {
   // blocks go to the 8 XCDs in turn; those that read one tile come 8 apart and
   // share an L2
   const int id = blockIdx.x, sub = (id >> 3) % kSubs, item = (id / (8 * kSubs)) * 8 + (id & 7);
-  if (item >= a.t.tiles * a.groups) return;
-  const int tile = a.t.tiles - 1 - item / a.groups;   // the longest start first
-  const int group = item % a.groups;
+  if (item >= a.h.items) return;
+  int tile, group;
+  tile_of(a.t, a.h.item0 + item, tile, group);
   TileBufs b(a.t, group, tile, lane);
+  __amdgpu_buffer_rsrc_t hubs = b.r;
+  uint32_t hub_words = 0;
+  if (a.h.at) {
+    const HubBuf h(a.t, a.h, tile, group);
+    hubs = h.buf;
+    hub_words = h.words;
+  }
   if (sub != kSubs - 1) b.vo_next = kPastEnd;   // only the last stages reach into the next tile
   const int recs = a.tile_rec[tile];
   const int r0 = (int)((int64_t)recs * seg / kSegs), r1 = (int)((int64_t)recs * (seg + 1) / kSegs);
@@ -431,24 +473,42 @@ __global__ void __launch_bounds__(kWave* kSegs) ckm_simulate_kernel(SimArgs a) {
     }
   uint64_t cost_lo = 0, cost_hi = 0;
   SimIn in;
-  uint64_t C;
   const auto load_words = [&](const u32x8& f) {
-    C = (uint64_t)f[6] | (uint64_t)f[7] << 32;
-    const auto slot = [&](int k) { return (k % 2 ? f[k / 2] >> 16 : f[k / 2] & 0xFFFFu) * (uint32_t)kSlotBytes; };
+    const auto half = [&](int k) { return k % 2 ? f[k / 2] >> 16 : f[k / 2] & 0xFFFFu; };
+    const auto slot = [&](int k) { return half(k) * (uint32_t)kSlotBytes; };
     // the record read past a tile's last belongs to the next tile's first node:
     // its words are in the memory after the tile's, and are not used
-    in.R = __builtin_amdgcn_raw_buffer_load_b32(b.r, (int)b.vo, (int)(slot(0) + a.t.rbase), 0);
+    in.R = __builtin_amdgcn_raw_buffer_load_b32(b.r, (int)b.vo, (int)(slot(0) + kRBase), 0);
     in.S = word_s(slot(0));
     in.s0 = word_s(slot(1));
     in.n0 = word_n(slot(1));
     in.s1 = word_s(slot(2));
     in.n1 = word_n(slot(2));
 #pragma unroll
-    for (int k = 0; k < 8; ++k) in.u[k] = (k & 2) == 0 ? load_r(b, slot(3 + k)) : 0u;   // the first two of either
-    if (f[5] >> 16) {
+    for (int d = 0; d < 2; ++d)
 #pragma unroll
-      for (int k = 0; k < 8; ++k)
-        if (k & 2) in.u[k] = load_r(b, slot(3 + k));
+      for (int k = 0; k < 4; ++k) in.u[d][k] = k < 2 ? load_r(b, slot(4 + 4 * d + k)) : 0u;
+    const uint32_t more = f[1] >> 16;
+    if (more) {
+#pragma unroll
+      for (int d = 0; d < 2; ++d) {
+        if (more & kMoreThird << d) in.u[d][2] = load_r(b, slot(6 + 4 * d));
+        if (more & kMoreFourth << d) in.u[d][3] = load_r(b, slot(7 + 4 * d));
+        if (more & kMoreHub << d) {
+          const uint32_t h = half(7 + 4 * d);   // a word that the tile does not make covers nothing in it
+          in.u[d][3] = __builtin_amdgcn_raw_buffer_load_b32(hubs, (int)b.vo, (int)(h <= hub_words ? h * kSlotBytes : 0u), 0);
+        }
+        if (more & kMoreList << d) {
+          const uint32_t e1 = f[6 + d] + half(6 + 4 * d);
+          for (uint32_t e = f[6 + d]; e < e1; e += 4) {
+            uint32_t y[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) y[k] = load_r(b, kRBase + node_off(a.users[min(e + k, e1 - 1)]));
+#pragma unroll
+            for (int k = 0; k < 4; ++k) in.u[d][2] |= y[k];
+          }
+        }
+      }
     }
   };
   if (r0 < r1) {
@@ -459,14 +519,14 @@ __global__ void __launch_bounds__(kWave* kSegs) ckm_simulate_kernel(SimArgs a) {
       const u32x8 ahead = a.refs[r + 2];
       const u64x4 now = a.ops[r];
       uint32_t R = in.R >> sh, S = in.S >> sh,
-               F = (in.R & ~(s1_of(in.s0, in.n0) | in.u[0] | in.u[1] | in.u[2] | in.u[3])) >> sh,
-               G = (in.R & ~(s1_of(in.s1, in.n1) | in.u[4] | in.u[5] | in.u[6] | in.u[7])) >> sh;
+               F = (in.R & ~(s1_of(in.s0, in.n0) | in.u[0][0] | in.u[0][1] | in.u[0][2] | in.u[0][3])) >> sh,
+               G = (in.R & ~(s1_of(in.s1, in.n1) | in.u[1][0] | in.u[1][1] | in.u[1][2] | in.u[1][3])) >> sh;
       asm volatile("" : "+v"(R), "+v"(S), "+v"(F), "+v"(G));   // before the next loads
-      const uint32_t c = (uint32_t)__builtin_popcount(R & ((1u << kSub) - 1u));
-      cost_lo += (uint64_t)c * (uint32_t)C;
-      cost_hi += (uint64_t)c * (uint32_t)(C >> 32);
       load_words(f);   // past the part's end they are not used
       f = ahead;
+      const uint32_t c = (uint32_t)__builtin_popcount(R & ((1u << kSub) - 1u));
+      cost_lo += (uint64_t)c * (uint32_t)now[3];
+      cost_hi += (uint64_t)c * (uint32_t)(now[3] >> 32);
       sim_record<kSub>(x, R, S, F, G, __builtin_bit_cast(double, (uint64_t)now[0]),
                        __builtin_bit_cast(double, (uint64_t)now[1]), __builtin_bit_cast(double, (uint64_t)now[2]));
     }
@@ -519,21 +579,9 @@ __global__ void __launch_bounds__(kWave* kSegs) ckm_simulate_kernel(SimArgs a) {
 }  // namespace
 
 // ---------------------------------------------------------------------------
-static TileArgs tile_args(const ckm_graph& g, const Layout& L, char* work) {
-  TileArgs t;
-  t.n = g.n;
-  t.tiles = (g.n + kTile - 1) / kTile;
-  t.rbase = g.tile.rbase;
-  t.s_bytes = stile_off(t.tiles);
-  t.r_bytes = rtile_off(t.rbase, t.tiles);
-  t.stiles = work + L.rows_off;
-  t.rtiles = work + L.rrows_off;
-  return t;
-}
-
 template <int kSub, int kSegs>
 static void launch_simulate(const SimArgs& s, hipStream_t stream) {
-  const int64_t items = ((int64_t)s.groups * s.t.tiles + 7) / 8 * 8;
+  const int64_t items = ((int64_t)s.h.items + 7) / 8 * 8;
   hipLaunchKernelGGL((ckm_simulate_kernel<kSub, kSegs>), dim3((unsigned)(items * (kTile / kSub))), dim3(kWave * kSegs),
                      0, stream, s);
 }
@@ -550,32 +598,55 @@ constexpr int64_t kSimItems = 512;
 hipError_t launch_tiles(const ckm_graph& g, const Layout& L, int32_t K, char* work, hipStream_t stream) {
   const int32_t groups = (K + kWave - 1) / kWave;
   ClosureArgs c;
-  c.t = tile_args(g, L, work);
+  c.t.n = g.n;
+  c.t.tiles = (g.n + kTile - 1) / kTile;
+  c.t.groups = groups;
+  c.t.s_bytes = stile_off(c.t.tiles);
+  c.t.r_bytes = rtile_off(c.t.tiles);
+  c.t.stiles = work + L.rows_off;
+  c.t.rtiles = work + L.rrows_off;
   c.desc = g.tile.d_desc;
   c.far = g.tile.d_far;
   c.far_more = (cptr<uint32_t>)g.tile.d_far_more;
   c.near_more = (cptr<uint32_t>)g.tile.d_near_more;
   hipLaunchKernelGGL(ckm_closure_kernel, dim3(groups, c.t.tiles), dim3(kWave * (1 + kPrep)), 0, stream, c);
-  if (g.tile.nhub)
-    hipLaunchKernelGGL(ckm_hub_kernel, dim3(groups, c.t.tiles, g.tile.nhub), dim3(kWave), 0, stream, c.t,
-                       (cptr<int32_t>)g.tile.d_hub_ptr, (cptr<HubUser>)g.tile.d_hub);
   SimArgs s;
   s.t = c.t;
   s.K = K;
-  s.groups = groups;
   s.base = (double)g.base;
   s.ops = (cptr<u64x4>)g.tile.d_ops;
   s.refs = (cptr<u32x8>)g.tile.d_refs;
   s.tile_rec = (cptr<int32_t>)g.tile.d_tile_rec;
+  s.users = (cptr<int32_t>)g.d_user_idx;
   s.peak = reinterpret_cast<int64_t*>(work + L.part_peak_off);
   s.cost = reinterpret_cast<int64_t*>(work + L.part_cost_off);
-  const int64_t items = (int64_t)groups * c.t.tiles;
-  if (items >= 2 * kSimItems)
-    launch_simulate<16, 4>(s, stream);
-  else if (items >= kSimItems)
-    launch_simulate<16, 8>(s, stream);
-  else
-    launch_simulate<8, 8>(s, stream);
+  s.h.ptr = (cptr<int32_t>)g.tile.d_hub_ptr;
+  s.h.users = (cptr<HubUser>)g.tile.d_hub;
+  s.h.at = g.tile.nhub ? (cptr<uint32_t>)g.tile.d_hub_at : nullptr;
+  s.h.buf = work + L.hub_off;
+  // one launch, or as many as the room for hub words asks for
+  const int32_t pairs = groups * c.t.tiles;
+  s.h.item0 = 0;
+  for (; s.h.item0 < pairs; s.h.item0 += s.h.items) {
+    s.h.items = pairs - s.h.item0;
+    if (g.tile.nhub) {
+      size_t room = L.hub_bytes;   // holds the largest pair at least
+      int32_t i = s.h.item0, fit = 1;
+      for (; i < pairs && fit; i += fit) {
+        const size_t bytes = hub_pair_bytes(g.tile, c.t.tiles - 1 - i / groups);
+        fit = (int32_t)std::min<size_t>(groups - i % groups, room / bytes);
+        room -= fit * bytes;
+      }
+      s.h.items = i - s.h.item0;
+      hipLaunchKernelGGL(ckm_hub_kernel, dim3(s.h.items, g.tile.nhub), dim3(kWave), 0, stream, s.t, s.h);
+    }
+    if (s.h.items >= 2 * kSimItems)
+      launch_simulate<16, 4>(s, stream);
+    else if (s.h.items >= kSimItems)
+      launch_simulate<16, 8>(s, stream);
+    else
+      launch_simulate<8, 8>(s, stream);
+  }
   return hipGetLastError();
 }
 

@@ -9,6 +9,7 @@ import numpy as np
 import pytest
 import torch
 
+from oracle import ref
 from paper_1910_02653_amd import ckm
 from paper_1910_02653_amd import workloads as wl
 from test_gpu_parity import check_full, gpu_round_eval, log, oracle_candidates
@@ -102,3 +103,93 @@ def test_largest_batch_launches(K):
     g.close()
     assert np.array_equal(got["batch"], B)
     assert (got["best_k"], got["best_batch"]) == (best[3], -best[0])
+
+
+def complete(n, K):
+    return graph(n, range(1, n), n, K)
+
+
+def by_definition(w, S):
+    """R, peak and cost of a schedule of a graph with many edges, where the
+    oracle's scan of all users takes minutes: a value is freed right after the
+    last node computed that uses it (or itself), unless the next stage keeps it."""
+    n = w.n
+    use = np.zeros((n, n), bool)   # [i, u]: u uses i
+    for u in range(n):
+        use[w.deps(u), u] = True
+    S = np.vstack([np.asarray(S, bool)[:, :n], np.zeros((1, n), bool)])
+    R, peak, cost = np.zeros((n, n), bool), 0, 0
+    for t in range(n):
+        r = R[t]
+        r[t] = True
+        for v in range(t - 1, -1, -1):
+            r[v] = (S[t + 1, v] or (use[v] & r).any()) and not S[t, v]
+        last = np.where(use & r, np.arange(n), -1).max(1)
+        last = np.maximum(last, np.where(r, np.arange(n), -1))
+        gone = np.bincount(last[(last >= 0) & ~S[t + 1]], w.size[(last >= 0) & ~S[t + 1]], n).astype(np.int64)
+        mem = w.m_input + 2 * w.m_param + int(w.size[S[t]].sum())
+        # before a node's own allocation its predecessors' releases are done
+        peak = max(peak, int((mem + np.cumsum(w.size * r) - np.concatenate([[0], np.cumsum(gone)[:-1]]))[r].max()))
+        cost += int(w.cost[r].sum())
+    return R, peak, cost
+
+
+def test_dense_graphs():
+    """Graphs of many users per node: rounding, thresholds and supplied
+    schedules. Hub words four users apart (n = 370) and five apart with the
+    users between in lists (n = 740); the reference against the oracle first."""
+    for n, K in ((60, 3), (370, 5), (740, 2)):
+        w = complete(n, K)
+        log("dense: n=%d" % n)
+        q = ref.quantize(w.s_frac)
+        S = [ref.round_random(q, w.seed, k) for k in range(K)]
+        want = [by_definition(w, x) for x in S]
+        if n == 60:
+            for k in range(K):
+                peak, cost, _, R = ref.eval_candidate(w, k, want_rows=True)
+                assert (int(peak), int(cost)) == want[k][1:] and np.array_equal(np.asarray(R, bool)[:, :n], want[k][0])
+        p = np.linspace(0.1, 0.5, 3)
+        T = [ref.round_threshold(w.s_frac, x) for x in p]
+        mats = wl.random_schedules(n, K, seed=3, density=0.3, kind="intervals")
+        U = np.tril(wl.unpack_schedules(mats, n), -1)
+        g = ckm.Graph.from_workload(w)
+        top = 1 << 60
+        for name, got, mine in (("rounding", g.round_eval(w.s_frac, K, w.seed, top), want),
+                                ("thresholds", g.threshold_eval(w.s_frac, p, top), [by_definition(w, x) for x in T]),
+                                ("schedules", g.eval_schedules(mats, top), [by_definition(w, x) for x in U])):
+            assert [(int(a), int(b)) for a, b in zip(got["peak"], got["cost"])] == [x[1:] for x in mine], (n, name)
+            assert np.array_equal(got["best_R"], ref.pack_rows(mine[got["best_k"]][0])), (n, name)
+        g.close()
+
+
+def test_room_for_hub_words():
+    """A work buffer asks for a bounded room for hub words, and one with less
+    room (down to the largest pair of a group and a tile, and less) gives the
+    same results in more launches; so does the area that allocates nothing."""
+    w = complete(150, 128)
+    g, chain = ckm.Graph.from_workload(w), ckm.Graph.from_workload(graph(150, (1,), 1, 1))
+    for K in (1, 128, 4096, 65536):
+        assert g.workspace_size(K) <= chain.workspace_size(K) + (1 << 30) + 256
+    full = g.workspace_size(w.K)
+    room = full - chain.workspace_size(w.K)
+    most = 256 * (1 + sum((m - 1) // 4 for m in range(6, w.n)))   # the last tile's
+    assert most < 64 * w.num_edges and 2 * most < room < 10 * most
+    s = torch.from_numpy(w.s_frac).cuda()
+    want = None
+    for less in (0, 256, room // 2, room - 2 * most, room - most - 256, room - most, room - most + 256, None):
+        log("hub words: room for %s bytes" % (less and room - less))
+        out = g.alloc_outputs(w.K)
+        if less is None:
+            g.round_eval_noalloc(s, w.K, w.seed, w.budget, 0, out)
+        else:
+            work = torch.full((full - less,), 0xA5, dtype=torch.uint8, device="cuda")
+            g.round_eval_async(s, w.K, w.seed, w.budget, 0, out, work)
+        torch.cuda.synchronize()
+        res = {k: v.cpu() for k, v in out.items()}
+        want = want or res
+        for k in want:
+            assert torch.equal(res[k], want[k]), (less, k)
+    got = {k: ckm.rows_to_numpy(v) if k in ("best_S", "best_R") else v.numpy() for k, v in want.items()}
+    check_full(w, dict(got, best_k=int(got["best_k"][0])))
+    g.close()
+    chain.close()

@@ -154,9 +154,11 @@ ckm_status ckm_round_eval(const ckm_graph* g, const double* s_frac, int64_t ld, 
  * (1 GiB at most, and at most a few times the S rows' size except where nodes
  * have tens of users): 9.5 GB at n = 4001, K = 4096. The evaluate stage then
  * makes each row once. With less of that last part (16 MiB are always enough)
- * it runs in more launches. A smaller buffer of at least ckm_workspace_size_min
- * bytes is accepted, and the rows are then made inside the evaluate stage, by
- * another and much slower kernel (same results). */
+ * it runs in more launches, and on graphs of more than 64 nodes a buffer with
+ * room for some thousands of candidates' rows is used in passes over the
+ * candidates. A smaller buffer of at least ckm_workspace_size_min bytes is
+ * accepted, and the rows are then made inside the evaluate stage, by another
+ * and on large graphs slower kernel (same results). */
 ckm_status ckm_workspace_size(const ckm_graph* g, int32_t K, size_t* bytes);
 
 /* The smallest work buffer accepted for K candidates: without the row array. */
@@ -171,7 +173,7 @@ ckm_status ckm_quantize_async(const ckm_graph* g, const double* d_s_frac, int64_
 
 /* Stage a2 on its own: rounds every candidate's S rows (Section 5.1) once
  * into the work buffer's row array, after ckm_quantize_async. It does
- * nothing when the buffer or the problem has no room for them (see
+ * nothing when the buffer or the problem has no room for all of them (see
  * ckm_workspace_size); ckm_evaluate_async then rounds inside. flags: 0 or
  * CKM_F_DET0. Call ckm_evaluate_async with CKM_F_ROUNDED and the same K,
  * seed and CKM_F_DET0 to use the rows; without CKM_F_ROUNDED it rounds them

@@ -303,17 +303,16 @@ Layout make_layout(const ckm_graph& g, int32_t K) {
   const size_t kpad = (size_t)((K + kWave - 1) / kWave) * kWave, groups = kpad / kWave;
   L.rows_off = off;
   const int32_t tiles = (n + ckm::kTile - 1) / ckm::kTile;
-  size_t s_bytes, r_bytes;
-  if (g.tile.on) {
+  // word w of row t at (base(t) + w) * kpad + k
+  const size_t full = (size_t)(n >> 5), rem = (size_t)(n & 31);
+  size_t s_bytes = kpad * (32 * full * (full + 1) / 2 + rem * (full + 1)) * sizeof(uint32_t), r_bytes = s_bytes;
+  L.rows_on = s_bytes <= ckm::kRowsMaxBytes;
+  if (g.tile.on) {   // the tiles' words, of whole blocks of nodes and stages
     s_bytes = groups * stile_off(tiles);
     r_bytes = groups * rtile_off(tiles);
     if (g.tile.nhub) L.hub_bytes = std::min(groups * 256 * g.tile.hub_at[0], ckm::kHubMaxBytes);
-  } else {
-    // word w of row t at (base(t) + w) * kpad + k
-    const size_t full = (size_t)(n >> 5), rem = (size_t)(n & 31);
-    s_bytes = r_bytes = kpad * (32 * full * (full + 1) / 2 + rem * (full + 1)) * sizeof(uint32_t);
+    if (L.rows_on) L.pass_groups = (int32_t)groups;
   }
-  L.rows_on = s_bytes <= ckm::kRowsMaxBytes;
   L.rrows_off = align256(off + s_bytes);
   L.hub_off = align256(L.rrows_off + r_bytes);
   L.total_rows = L.rows_on ? L.hub_off + L.hub_bytes : off;
@@ -588,10 +587,28 @@ static ckm_status check_work(const ckm_graph* g, int32_t K, void* d_work, size_t
   if (work_bytes < L->total)
     return fail(CKM_E_INVALID_ARG, "work buffer of %zu bytes, %zu needed", work_bytes, L->total);
   if (L->rows_on && work_bytes < L->total_rows) {
-    // less room than asked for: hub words of fewer pairs at a time, or no row arrays
-    const size_t most = g->tile.nhub ? ckm::hub_pair_bytes(g->tile, (g->n - 1) / ckm::kTile) : 0;
-    L->rows_on = most && work_bytes >= L->hub_off + most;
-    if (L->rows_on) L->hub_bytes = work_bytes - L->hub_off;
+    // less room than asked for: hub words of fewer pairs at a time, fewer groups
+    // at a time, or none
+    L->rows_on = false;
+    L->pass_groups = 0;
+    if (!g->tile.on) return CKM_OK;
+    const int32_t tiles = (g->n + ckm::kTile - 1) / ckm::kTile, groups = (K + ckm::kWave - 1) / ckm::kWave;
+    const size_t most = g->tile.nhub ? ckm::hub_pair_bytes(g->tile, tiles - 1) : 0;
+    const size_t room = work_bytes - L->total, s = ckm::stile_off(tiles), rs = s + ckm::rtile_off(tiles);
+    if (room >= groups * rs + most) {
+      L->rows_on = true;
+      L->pass_groups = groups;
+    } else {
+      // a quarter of the room for hub words
+      const size_t hub = most ? std::max(most, std::min(groups * 256 * (size_t)g->tile.hub_at[0], room / 4)) : 0;
+      const int32_t fit = room < hub ? 0 : (int32_t)std::min<size_t>((room - hub) / rs, groups);
+      if (tiles < ckm::kPassTiles || (int64_t)fit * tiles < ckm::kPassPairs) return CKM_OK;
+      const int32_t passes = (groups + fit - 1) / fit;
+      L->pass_groups = (groups + passes - 1) / passes;
+    }
+    L->rrows_off = L->rows_off + L->pass_groups * s;
+    L->hub_off = L->rows_off + L->pass_groups * rs;
+    L->hub_bytes = work_bytes - L->hub_off;
   }
   return CKM_OK;
 }

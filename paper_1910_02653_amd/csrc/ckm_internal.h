@@ -78,6 +78,13 @@ enum : int {
 // problems, or work buffers sized without them, make the S rows in the evaluate
 // kernel and recompute the best candidate's R.
 constexpr size_t kRowsMaxBytes = (size_t)8 << 30;
+// A buffer that does not hold the tiles of all groups is used in passes over them
+// on graphs of at least kPassTiles tiles when a pass has kPassPairs (group, tile)
+// pairs, which fill the chip. Measured, passes / the scan without row arrays:
+// n = 129, K = 65,536 in 2 passes 494 / 787 us, in 8 (640 pairs each) 626; K = 4096
+// in 2 (160 pairs) 86 / 74; n = 1009, K = 4096 in 4 (512 pairs) 1249 / 2773;
+// n = 33, K = 65,536 in 2 (1024 pairs) 129 / 105.
+constexpr int32_t kPassTiles = 3, kPassPairs = 512;
 // Room asked for hub words, at most: when all (group, tile) pairs have more, hub
 // words and simulation run in several launches, each over the pairs that fit (64
 // at least). Measured, in the launches that the room leads to:
@@ -128,6 +135,8 @@ struct Layout {
          total_rows = 0;   // total plus the row arrays (and the hub words) when they are used
   bool rows_on = false;    // the S rows fit kRowsMaxBytes (and, after
                            // check_work, the caller's buffer holds both)
+  int32_t pass_groups = 0; // tile path: candidate groups evaluated at a time, all with
+                           // rows_on; fewer where the buffer holds no more (0: none)
 };
 
 Layout make_layout(const ckm_graph& g, int32_t K);
@@ -172,9 +181,6 @@ hipError_t launch_quantize(const ckm_graph& g, const Layout& L, const double* d_
 // buffer's row array (nothing when L.rows_on is false).
 hipError_t launch_round_rows(const ckm_graph& g, const Layout& L, int32_t K, uint64_t seed, uint32_t flags,
                              char* work, hipStream_t stream);
-// clear: on the tile path, also reset the candidates' evaluate totals.
-hipError_t launch_round_rows(const ckm_graph& g, const Layout& L, int32_t K, uint64_t seed, uint32_t flags,
-                             bool clear, char* work, hipStream_t stream);
 // Threshold family: ranks of the K thresholds, their sorted copy, and the
 // keys of S* in place of the quantized thresholds q.
 hipError_t launch_threshold_keys(const ckm_graph& g, const Layout& L, const double* d_s, int64_t ld,
@@ -196,8 +202,10 @@ hipError_t launch_max_batch(const ckm_graph& g, const Layout& L, int32_t K, int6
 hipError_t launch_evaluate(const ckm_graph& g, const Layout& L, int32_t K, uint64_t seed,
                            uint32_t flags, const Plan& plan, int src, const uint64_t* s_user, char* work,
                            hipStream_t stream);
-// Tile path (ckm_tiles.hip): the evaluate of all candidates on their S tiles.
-hipError_t launch_tiles(const ckm_graph& g, const Layout& L, int32_t K, char* work, hipStream_t stream);
+// Tile path (ckm_tiles.hip): the evaluate of candidate groups g0 .. g0 + groups - 1
+// on their S tiles.
+hipError_t launch_tiles(const ckm_graph& g, const Layout& L, int32_t K, int32_t g0, int32_t groups, char* work,
+                        hipStream_t stream);
 hipError_t launch_select(const ckm_graph& g, const Layout& L, int32_t K, uint64_t seed,
                          int64_t budget, uint32_t flags, int64_t* d_peak,
                          int64_t* d_cost, uint8_t* d_feasible, int32_t* d_best_k,

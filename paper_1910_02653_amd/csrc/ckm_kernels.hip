@@ -1077,14 +1077,15 @@ __global__ void __launch_bounds__(256) ckm_eval_init_kernel(int32_t K, int64_t* 
 }
 
 // The same for the 64 candidates of one group, done by the tile producers'
-// first item in place of a launch of its own (peak NULL: nothing).
+// first item in place of a launch of its own (peak NULL: nothing). A producer
+// makes the S tiles of `groups` groups, from group g0 on.
 struct Totals {
   int64_t* __restrict__ peak;
   int64_t* __restrict__ cost;
-  int32_t K;
+  int32_t K, g0, groups;
 };
 __device__ __forceinline__ void clear_totals(const Totals& tot, int group, bool first) {
-  const int k = group * kWave + (int)threadIdx.x;
+  const int k = (tot.g0 + group) * kWave + (int)threadIdx.x;
   if (tot.peak && first && threadIdx.x < kWave && k < tot.K) {
     tot.peak[k] = INT64_MIN;
     tot.cost[k] = 0;
@@ -1747,15 +1748,15 @@ constexpr int kItemWaves = 4;
 template <bool kBytes>
 __global__ void __launch_bounds__(kWave* kItemWaves) ckm_round_tiles_kernel(
     const uint32_t* __restrict__ q, const uint32_t* __restrict__ det, int32_t n, int32_t ldq, int32_t det_words,
-    uint32_t key0, uint32_t key1, uint32_t det0, size_t group_bytes, char* __restrict__ stiles, int32_t groups, Totals tot) {
+    uint32_t key0, uint32_t key1, uint32_t det0, size_t group_bytes, char* __restrict__ stiles, Totals tot) {
   constexpr int kStages = kBytes ? 8 : 32;
-  const int at = (int)blockIdx.x / groups, group = (int)blockIdx.x - at * groups;
+  const int at = (int)blockIdx.x / tot.groups, group = (int)blockIdx.x - at * tot.groups;
   clear_totals(tot, group, at == 0);
   int T, nb;
   tile_item(kBytes ? at / 4 : at, T, nb);
   const int part = kBytes ? at % 4 : 0;
   const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave), m = kItemWaves * nb + wave;
-  const uint32_t lane = threadIdx.x & (kWave - 1), k = (uint32_t)(group * kWave) + lane;
+  const uint32_t lane = threadIdx.x & (kWave - 1), k = (uint32_t)((tot.g0 + group) * kWave) + lane;
   uint32_t w[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) w[i] = 0u;
@@ -1781,7 +1782,7 @@ __global__ void __launch_bounds__(kWave* kItemWaves) ckm_round_tiles_kernel(
 #pragma unroll
     for (int i = 0; i < 8; ++i) w[i] <<= first - t0;
   }
-  if (det0 && group == 0) {
+  if (det0 && tot.g0 + group == 0) {
     // lane j has the bits of stage t0 + j: a node's word is a ballot
     const int td = t0 + (int)lane;
     const uint32_t dw = (int)lane < kStages && td < n ? det[(size_t)td * det_words + nb] >> (8 * wave) : 0u;
@@ -1805,13 +1806,13 @@ __global__ void __launch_bounds__(kWave* kItemWaves) ckm_round_tiles_kernel(
 // threshold_word (keys on and above the diagonal are 0). A wave has 8 nodes.
 __global__ void __launch_bounds__(kWave* kItemWaves) ckm_threshold_tiles_kernel(
     const uint32_t* __restrict__ key, int32_t ldq, const uint32_t* __restrict__ rank, int32_t K, int32_t n,
-    size_t group_bytes, char* __restrict__ stiles, int32_t groups, Totals tot) {
-  const int item = (int)blockIdx.x / groups, group = (int)blockIdx.x - item * groups;
+    size_t group_bytes, char* __restrict__ stiles, Totals tot) {
+  const int item = (int)blockIdx.x / tot.groups, group = (int)blockIdx.x - item * tot.groups;
   clear_totals(tot, group, item == 0);
   int T, nb;
   tile_item(item, T, nb);
   const int m = kItemWaves * nb + __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave);
-  const uint32_t k = (uint32_t)(group * kWave) + (threadIdx.x & (kWave - 1));
+  const uint32_t k = (uint32_t)((tot.g0 + group) * kWave) + (threadIdx.x & (kWave - 1));
   const uint32_t rk = rank[k < (uint32_t)K ? k : (uint32_t)K - 1u];
   uint32_t w[8];
 #pragma unroll
@@ -1842,12 +1843,12 @@ __device__ __forceinline__ void transpose_step(uint32_t (&a)[32], uint32_t m) {
 }
 __global__ void __launch_bounds__(kWave) ckm_user_tiles_kernel(const uint32_t* __restrict__ s_user, int32_t n,
                                                                int32_t K, int32_t s_words, size_t group_bytes,
-                                                               char* __restrict__ stiles, int32_t groups, Totals tot) {
-  const int item = (int)blockIdx.x / groups, group = (int)blockIdx.x - item * groups;
+                                                               char* __restrict__ stiles, Totals tot) {
+  const int item = (int)blockIdx.x / tot.groups, group = (int)blockIdx.x - item * tot.groups;
   clear_totals(tot, group, item == 0);
   int T, nb;
   tile_item(item, T, nb);
-  const uint32_t k = (uint32_t)(group * kWave) + threadIdx.x;
+  const uint32_t k = (uint32_t)((tot.g0 + group) * kWave) + threadIdx.x;
   const uint32_t kk = k < (uint32_t)K ? k : (uint32_t)K - 1u;
   const uint32_t* src = s_user + (size_t)kk * n * s_words + nb;
   uint32_t w[32];
@@ -1942,8 +1943,6 @@ static unsigned tile_items(int32_t n) {
   return tiles * (tiles + 1) / 2;
 }
 
-static bool use_tiles(const ckm_graph& g, const Layout& L) { return L.rows_on && g.tile.on; }
-
 // Rounding blocks (group, tile, 32 nodes) from which whole words beat bytes: a
 // byte's wave runs a quarter of the stages, so that small calls end sooner, but
 // stores bytes of a word from four blocks.
@@ -1952,29 +1951,40 @@ static bool use_tiles(const ckm_graph& g, const Layout& L) { return L.rows_on &&
 // 1056 (n = 337, K = 1024) 18.3 / 18.8; 8448 (n = 1009, K = 1024) 117 / 104.
 constexpr int64_t kRoundBig = 1024;
 
-hipError_t launch_round_rows(const ckm_graph& g, const Layout& L, int32_t K, uint64_t seed, uint32_t flags,
-                             char* work, hipStream_t stream) {
-  return launch_round_rows(g, L, K, seed, flags, false, work, stream);
-}
-
-hipError_t launch_round_rows(const ckm_graph& g, const Layout& L, int32_t K, uint64_t seed, uint32_t flags,
-                             bool clear, char* work, hipStream_t stream) {
-  if (!L.rows_on) return hipSuccess;
-  if (use_tiles(g, L)) {
-    const Totals tot{clear ? at<int64_t>(work, L.part_peak_off) : nullptr, at<int64_t>(work, L.part_cost_off), K};
-    const unsigned groups = groups_of(K), items = tile_items(g.n);
+// The S tiles of tot's groups from source src (kSrcRound, kSrcThreshold or kSrcUser).
+static hipError_t launch_tile_producer(const ckm_graph& g, const Layout& L, uint64_t seed, uint32_t flags, int src,
+                                       const uint64_t* s_user, const Totals& tot, char* work, hipStream_t stream) {
+  const unsigned blocks = (unsigned)tot.groups * tile_items(g.n);
+  const size_t group_bytes = stile_off((g.n + 31) / 32);
+  if (src == kSrcThreshold) {
+    hipLaunchKernelGGL(ckm_threshold_tiles_kernel, dim3(blocks), dim3(kWave * kItemWaves), 0, stream,
+                       at<const uint32_t>(work, L.q_off), L.ldq, at<const uint32_t>(work, L.thr_rank_off), tot.K, g.n,
+                       group_bytes, work + L.rows_off, tot);
+  } else if (src == kSrcUser) {
+    hipLaunchKernelGGL(ckm_user_tiles_kernel, dim3(blocks), dim3(kWave), 0, stream,
+                       reinterpret_cast<const uint32_t*>(s_user), g.n, tot.K, L.row_words, group_bytes, work + L.rows_off,
+                       tot);
+  } else {
     const auto launch = [&](auto kernel, unsigned parts) {
-      hipLaunchKernelGGL(kernel, dim3(groups * items * parts), dim3(kWave * kItemWaves), 0, stream,
+      hipLaunchKernelGGL(kernel, dim3(blocks * parts), dim3(kWave * kItemWaves), 0, stream,
                          at<const uint32_t>(work, L.q_off), at<const uint32_t>(work, L.det_off), g.n, L.ldq, L.det_words,
                          (uint32_t)(seed & 0xFFFFFFFFu), (uint32_t)(seed >> 32), (flags & CKM_F_DET0) ? 1u : 0u,
-                         stile_off((g.n + 31) / 32), work + L.rows_off, (int32_t)groups, tot);
+                         group_bytes, work + L.rows_off, tot);
     };
-    if ((int64_t)groups * items < kRoundBig)
+    if ((int64_t)blocks < kRoundBig)
       launch(ckm_round_tiles_kernel<true>, 4);
     else
       launch(ckm_round_tiles_kernel<false>, 1);
-    return hipGetLastError();
   }
+  return hipGetLastError();
+}
+
+hipError_t launch_round_rows(const ckm_graph& g, const Layout& L, int32_t K, uint64_t seed, uint32_t flags,
+                             char* work, hipStream_t stream) {
+  if (!L.rows_on) return hipSuccess;
+  if (g.tile.on)
+    return launch_tile_producer(g, L, seed, flags, kSrcRound, nullptr, Totals{nullptr, nullptr, K, 0, (int32_t)groups_of(K)},
+                                work, stream);
   const int32_t kpad = ((K + kWave - 1) / kWave) * kWave;
   hipLaunchKernelGGL(ckm_round_rows_kernel, dim3((K + kWave - 1) / kWave, g.n), dim3(kWave), 0, stream,
                      at<const uint32_t>(work, L.q_off), at<const uint32_t>(work, L.det_off), L.ldq, L.det_words,
@@ -1983,43 +1993,24 @@ hipError_t launch_round_rows(const ckm_graph& g, const Layout& L, int32_t K, uin
   return hipGetLastError();
 }
 
-// The S tiles from source src (kSrcRound, kSrcThreshold or kSrcUser); the
-// candidates' totals are cleared on the way (the evaluate that follows
-// accumulates into them).
-static hipError_t launch_tile_producer(const ckm_graph& g, const Layout& L, int32_t K, uint64_t seed, uint32_t flags,
-                                       int src, const uint64_t* s_user, char* work, hipStream_t stream) {
-  const Totals tot{at<int64_t>(work, L.part_peak_off), at<int64_t>(work, L.part_cost_off), K};
-  const int32_t groups = (int32_t)groups_of(K);
-  const dim3 grid((unsigned)groups * tile_items(g.n));
-  if (src == kSrcThreshold) {
-    hipLaunchKernelGGL(ckm_threshold_tiles_kernel, grid, dim3(kWave * kItemWaves), 0, stream, at<const uint32_t>(work, L.q_off),
-                       L.ldq, at<const uint32_t>(work, L.thr_rank_off), K, g.n, stile_off((g.n + 31) / 32), work + L.rows_off, groups, tot);
-  } else if (src == kSrcUser) {
-    hipLaunchKernelGGL(ckm_user_tiles_kernel, grid, dim3(kWave), 0, stream,
-                       reinterpret_cast<const uint32_t*>(s_user), g.n, K, L.row_words, stile_off((g.n + 31) / 32),
-                       work + L.rows_off, groups, tot);
-  } else {
-    return launch_round_rows(g, L, K, seed, flags, true, work, stream);
-  }
-  return hipGetLastError();
-}
-
 hipError_t launch_evaluate(const ckm_graph& g, const Layout& L, int32_t K, uint64_t seed,
                            uint32_t flags, const Plan& plan, int src, const uint64_t* s_user, char* work,
                            hipStream_t stream) {
-  if (use_tiles(g, L)) {
-    // S tiles made by a producer (none when the caller rounded them
-    // beforehand), then the tile path
-    hipError_t e = hipSuccess;
-    if (!(src == kSrcRound && (flags & CKM_F_ROUNDED))) {
-      e = launch_tile_producer(g, L, K, seed, flags, src, s_user, work, stream);
-    } else {
-      // no producer to clear the totals on the way
-      hipLaunchKernelGGL(ckm_eval_init_kernel, dim3((K + 255) / 256), dim3(256), 0, stream, K,
-                         at<int64_t>(work, L.part_peak_off), at<int64_t>(work, L.part_cost_off));
-      e = hipGetLastError();
+  if (L.pass_groups) {
+    // S tiles made by a producer, which clears the candidates' totals on the
+    // way (the evaluate accumulates into them), then the tile path
+    Totals tot{at<int64_t>(work, L.part_peak_off), at<int64_t>(work, L.part_cost_off), K, 0, 0};
+    const bool rounded = src == kSrcRound && (flags & CKM_F_ROUNDED) && L.rows_on;   // by the caller, beforehand
+    if (rounded)
+      hipLaunchKernelGGL(ckm_eval_init_kernel, dim3((K + 255) / 256), dim3(256), 0, stream, K, tot.peak, tot.cost);
+    const int32_t groups = (int32_t)groups_of(K);
+    for (; tot.g0 < groups; tot.g0 += tot.groups) {
+      tot.groups = std::min(groups - tot.g0, L.pass_groups);
+      hipError_t e = rounded ? hipGetLastError() : launch_tile_producer(g, L, seed, flags, src, s_user, tot, work, stream);
+      if (e == hipSuccess) e = launch_tiles(g, L, K, tot.g0, tot.groups, work, stream);
+      if (e != hipSuccess) return e;
     }
-    return e == hipSuccess ? launch_tiles(g, L, K, work, stream) : e;
+    return hipSuccess;
   }
   EvalArgs a;
   a.n = g.n;
@@ -2150,7 +2141,7 @@ hipError_t launch_select(const ckm_graph& g, const Layout& L, int32_t K, uint64_
   // With the row arrays the evaluate stage kept every candidate's R rows, so
   // the best R is a gather; otherwise Algorithm 2 runs again for it.
   RTiles tiles = {};
-  if (use_tiles(g, L) && d_best_R) {
+  if (g.tile.on && L.rows_on && d_best_R) {
     tiles.rtiles = work + L.rrows_off;
     tiles.r_bytes = rtile_off((g.n + 31) / 32);
     tiles.R_rows = d_best_R;

@@ -375,7 +375,7 @@ __global__ void __launch_bounds__(kWave) ckm_hub_kernel(TileArgs t, HubArgs h) {
 struct SimArgs {
   TileArgs t;
   HubArgs h;                        // and the pairs of the launch
-  int32_t K;
+  int32_t K, g0;                    // g0: the first group of the pass
   double base;                      // M_in + 2 M_param
   cptr<u64x4> ops;                  // SimOps
   cptr<u32x8> refs;                 // SimRefs
@@ -531,7 +531,7 @@ __global__ void __launch_bounds__(kWave* kSegs) ckm_simulate_kernel(SimArgs a) {
                        __builtin_bit_cast(double, (uint64_t)now[1]), __builtin_bit_cast(double, (uint64_t)now[2]));
     }
   }
-  const int k = group * kWave + lane;
+  const int k = (a.g0 + group) * kWave + lane;
   const uint64_t cost = cost_lo + (cost_hi << 32);
   if (k < a.K && cost) atomicAdd(reinterpret_cast<unsigned long long*>(a.cost) + k, (unsigned long long)cost);
   // the parts' sums meet in LDS, eight stages at a time; each wave joins some
@@ -595,8 +595,8 @@ static void launch_simulate(const SimArgs& s, hipStream_t stream) {
 // (n = 747, K = 3000) 457 / - / 313; 8064 pairs (n = 4001) 15.2 ms / - / 10.1.
 constexpr int64_t kSimItems = 512;
 
-hipError_t launch_tiles(const ckm_graph& g, const Layout& L, int32_t K, char* work, hipStream_t stream) {
-  const int32_t groups = (K + kWave - 1) / kWave;
+hipError_t launch_tiles(const ckm_graph& g, const Layout& L, int32_t K, int32_t g0, int32_t groups, char* work,
+                        hipStream_t stream) {
   ClosureArgs c;
   c.t.n = g.n;
   c.t.tiles = (g.n + kTile - 1) / kTile;
@@ -613,6 +613,7 @@ hipError_t launch_tiles(const ckm_graph& g, const Layout& L, int32_t K, char* wo
   SimArgs s;
   s.t = c.t;
   s.K = K;
+  s.g0 = g0;
   s.base = (double)g.base;
   s.ops = (cptr<u64x4>)g.tile.d_ops;
   s.refs = (cptr<u32x8>)g.tile.d_refs;

@@ -193,3 +193,46 @@ def test_room_for_hub_words():
     check_full(w, dict(got, best_k=int(got["best_k"][0])))
     g.close()
     chain.close()
+
+
+@pytest.mark.parametrize("hubs", [(), [(0, 20, 9), (5, 6, 1)]], ids=["no hubs", "hubs"])
+def test_room_for_groups(hubs):
+    """A buffer with room for the tiles of fewer groups than the call has: the
+    groups are evaluated in passes of at least 512 pairs of a group and a tile
+    (five tiles: 103 of the 401 groups), with the same results as in one; with
+    less room the per-lane scan."""
+    n, K = 129, 400 * 64 + 5
+    w = graph(n, (1, 33), 3, K, hubs=hubs)
+    g = ckm.Graph.from_workload(w)
+    s = torch.from_numpy(w.s_frac).cuda()
+    p = torch.from_numpy(np.random.default_rng(1).random(K)).cuda()
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    S = torch.randint(-2 ** 63, 2 ** 63 - 1, (K, n, 3), generator=gen, device="cuda")   # above the diagonal too
+    budget = int(np.median(g.round_eval(w.s_frac, K, w.seed, 1 << 60, ckm.F_DET0)["peak"]))
+    low, full = g.workspace_size(K, rows=False), g.workspace_size(K)
+
+    def calls(work):
+        out = [g.alloc_outputs(K) for _ in range(4)]
+        g.round_eval_async(s, K, w.seed, budget, ckm.F_DET0, out[0], work)
+        g.threshold_eval_async(s, p, budget, out[1], work)
+        g.eval_schedules_async(S, K, 1 << 60, out[2], work)
+        g.quantize_async(s, work)
+        g.round_async(K, w.seed + 1, 0, work)
+        g.evaluate_async(K, w.seed + 1, ckm.F_ROUNDED, work)
+        g.select_async(K, w.seed + 1, budget, 0, out[3], work)
+        batch = torch.empty(K, dtype=torch.int64, device="cuda")
+        best = torch.empty(1, dtype=torch.int32, device="cuda")
+        g.max_batch_async(K, 2 * budget, 1 << 60, batch, best, None, None, work)
+        torch.cuda.synchronize()
+        return [{k: v.cpu() for k, v in o.items() if not (i == 2 and k == "best_S")} for i, o in enumerate(out)] + [
+            {"batch": batch.cpu(), "best": best.cpu()}]
+
+    want = calls(torch.empty(full, dtype=torch.uint8, device="cuda"))
+    assert all(int(o["best_k"]) >= 0 for o in want[:4])
+    for part in (1.0, 0.99, 0.7, 0.4, 0.28, 0.25, 0.0):
+        log("passes: %d of %d bytes" % (part * (full - low), full - low))
+        work = torch.full((low + int(part * (full - low)),), 0xA5, dtype=torch.uint8, device="cuda")
+        for a, b in zip(want, calls(work)):
+            for k in a:
+                assert torch.equal(a[k], b[k]), (part, k)
+    g.close()

@@ -528,6 +528,7 @@ static ckm_status graph_create(int32_t n, const int32_t* dep_ptr, const int32_t*
   if (!wide) {
     g->tile.on = true;
     g->tile.nhub = tt.nhub;
+    for (int32_t h = 0; h < tt.nhub; ++h) g->tile.hub_rounds += (tt.hub_ptr[h + 1] - tt.hub_ptr[h] + 7) / 8;
     g->tile.d_desc = reinterpret_cast<const uint32_t*>(base + off_desc);
     g->tile.d_near_more = reinterpret_cast<const uint32_t*>(base + off_nmore);
     g->tile.d_far = reinterpret_cast<const uint32_t*>(base + off_far);

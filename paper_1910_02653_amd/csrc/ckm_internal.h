@@ -17,7 +17,7 @@ struct SyncCache;  // buffers and stream of the synchronous entry points (ckm_ho
 // for wide graphs, which do not take it.
 struct TileGraph {
   bool on = false;
-  int32_t nhub = 0;
+  int32_t nhub = 0, hub_rounds = 0;   // hub_rounds: users of all hubs, in rounds of eight
   std::vector<uint32_t> hub_at;  // slots of hub words of a group in the tiles above each (TileTables)
   const uint32_t* d_desc = nullptr;
   const uint32_t* d_near_more = nullptr;

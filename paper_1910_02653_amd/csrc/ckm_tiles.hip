@@ -63,6 +63,66 @@ struct TileBufs {
 };
 
 // ---------------------------------------------------------------------------
+// Hub words, in the closure's blocks or in a launch of their own.
+struct HubArgs {
+  cptr<int32_t> ptr;
+  cptr<HubUser> users;
+  cptr<uint32_t> at;                // TileTables::hub_at (null: no hub words)
+  char* buf;                        // the words of a launch's pairs, one pair after another
+  int32_t item0, items;             // the pairs
+  int32_t nhub;
+};
+__device__ __forceinline__ void tile_of(const TileArgs& t, int item, int& tile, int& group) {
+  tile = t.tiles - 1 - item / t.groups;   // the longest start first
+  group = item % t.groups;
+}
+// A pair's hub words: a word of zeros, then `words` words.
+struct HubBuf {
+  __amdgpu_buffer_rsrc_t buf;
+  uint32_t words;
+  __device__ __forceinline__ HubBuf(const TileArgs& t, const HubArgs& h, int tile, int group) {
+    const auto before = [&](int T, int g) { return (uint64_t)t.groups * h.at[T + 1] + (uint64_t)g * (h.at[T] - h.at[T + 1]); };
+    int tile0, group0;
+    tile_of(t, h.item0, tile0, group0);
+    words = h.at[tile] - h.at[tile + 1] - 1;
+    buf = buffer(h.buf + (before(tile, group) - before(tile0, group0)) * kSlotBytes, node_off(1 + (int)words));
+  }
+};
+// One wave's hub, over its users below the tile's end from the highest down. The
+// bound is memory: a word read per user, and one written per step of them.
+__device__ __forceinline__ void hub_words(const TileBufs& b, const HubArgs& h, __amdgpu_buffer_rsrc_t out, int hub) {
+  if (hub == 0) __builtin_amdgcn_raw_buffer_store_b32(0u, out, (int)b.vo, 0, 0);
+  const int e1 = h.ptr[hub + 1];
+  int e0 = h.ptr[hub];
+  for (int end = e1; e0 < end;) {   // users at or above the tile's end compute nothing in its stages
+    const int mid = (e0 + end) / 2;
+    if (h.users[mid].r < b.r_bytes)
+      end = mid;
+    else
+      e0 = mid + 1;
+  }
+  uint32_t acc = 0;
+  for (int e = e0; e < e1; e += 8) {
+    uint32_t x[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+      x[k] = __builtin_amdgcn_raw_buffer_load_b32(b.r, (int)b.vo, (int)h.users[min(e + k, e1 - 1)].r, 0);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      if (e + k >= e1) break;
+      acc |= x[k];
+      const uint32_t xo = h.users[e + k].x;
+      if (xo) __builtin_amdgcn_raw_buffer_store_b32(acc, out, (int)b.vo, (int)xo, 0);
+    }
+  }
+}
+__global__ void __launch_bounds__(kWave) ckm_hub_kernel(TileArgs t, HubArgs h) {
+  int tile, group;
+  tile_of(t, h.item0 + (int)blockIdx.x, tile, group);
+  hub_words(TileBufs(t, group, tile, threadIdx.x), h, HubBuf(t, h, tile, group).buf, blockIdx.y);
+}
+
+// ---------------------------------------------------------------------------
 // Closure: one block per (group, tile): a wave that decides, and kPrep waves
 // that prepare the block of nodes below. The bound is the deciding wave's chain:
 // per chunk of four nodes an LDS round trip (near users) and a few dependent
@@ -80,6 +140,7 @@ struct ClosureArgs {
   const uint32_t* desc;
   const uint32_t* far;
   cptr<uint32_t> far_more, near_more;
+  HubArgs h;                        // nhub 0: the hub words, if any, are made in another launch
 };
 
 __device__ __forceinline__ uint32_t lds_get(lds_char* p, uint32_t off) { return *(const lds_u32*)(p + off); }
@@ -283,79 +344,26 @@ __global__ void __launch_bounds__(kWave*(1 + kPrep)) ckm_closure_kernel(ClosureA
       phase_end_prep();
     }
     phase_end_prep();
-    return;
-  }
-  phase_end_decide();
-  // phase p decides block tile - p + 1
-  for (int p = 0; p <= tile + 1; ++p) {
-    if (p > 0) {
-      const int nb = tile - p + 1;
-      uint32_t d[kDescVecs];
-#pragma unroll
-      for (int i = 0; i < kDescVecs; ++i) d[i] = lds_get(lds, (uint32_t)(kSlotDesc + kDescVecs * (nb & 1) + i) * kSlotBytes);
-      if (nb == tile)
-        decide_block<true>(a, b, lds, nb, d);
-      else
-        decide_block<false>(a, b, lds, nb, d);
-    }
+  } else {
     phase_end_decide();
-  }
-}
-
-// Hub words of the (group, tile) pairs from item0 on: one wave per pair and hub,
-// over the hub's users below the tile's end from the highest down. The bound is
-// memory: a word read per user, a quarter as many written.
-struct HubArgs {
-  cptr<int32_t> ptr;
-  cptr<HubUser> users;
-  cptr<uint32_t> at;                // TileTables::hub_at (null: no hub words)
-  char* buf;                        // the words of the launch's pairs, one pair after another
-  int32_t item0, items;
-};
-__device__ __forceinline__ void tile_of(const TileArgs& t, int item, int& tile, int& group) {
-  tile = t.tiles - 1 - item / t.groups;   // the longest start first
-  group = item % t.groups;
-}
-// A pair's hub words: a word of zeros, then `words` words.
-struct HubBuf {
-  __amdgpu_buffer_rsrc_t buf;
-  uint32_t words;
-  __device__ __forceinline__ HubBuf(const TileArgs& t, const HubArgs& h, int tile, int group) {
-    const auto before = [&](int T, int g) { return (uint64_t)t.groups * h.at[T + 1] + (uint64_t)g * (h.at[T] - h.at[T + 1]); };
-    int tile0, group0;
-    tile_of(t, h.item0, tile0, group0);
-    words = h.at[tile] - h.at[tile + 1] - 1;
-    buf = buffer(h.buf + (before(tile, group) - before(tile0, group0)) * kSlotBytes, node_off(1 + (int)words));
-  }
-};
-__global__ void __launch_bounds__(kWave) ckm_hub_kernel(TileArgs t, HubArgs h) {
-  int tile, group;
-  tile_of(t, h.item0 + (int)blockIdx.x, tile, group);
-  const TileBufs b(t, group, tile, threadIdx.x);
-  const auto out = HubBuf(t, h, tile, group).buf;
-  if (blockIdx.y == 0) __builtin_amdgcn_raw_buffer_store_b32(0u, out, (int)b.vo, 0, 0);
-  const int e1 = h.ptr[blockIdx.y + 1];
-  int e0 = h.ptr[blockIdx.y];
-  for (int end = e1; e0 < end;) {   // users at or above the tile's end compute nothing in its stages
-    const int mid = (e0 + end) / 2;
-    if (h.users[mid].r < b.r_bytes)
-      end = mid;
-    else
-      e0 = mid + 1;
-  }
-  uint32_t acc = 0;
-  for (int e = e0; e < e1; e += 8) {
-    uint32_t x[8];
+    // phase p decides block tile - p + 1
+    for (int p = 0; p <= tile + 1; ++p) {
+      if (p > 0) {
+        const int nb = tile - p + 1;
+        uint32_t d[kDescVecs];
 #pragma unroll
-    for (int k = 0; k < 8; ++k)
-      x[k] = __builtin_amdgcn_raw_buffer_load_b32(b.r, (int)b.vo, (int)h.users[min(e + k, e1 - 1)].r, 0);
-#pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      if (e + k >= e1) break;
-      acc |= x[k];
-      const uint32_t xo = h.users[e + k].x;
-      if (xo) __builtin_amdgcn_raw_buffer_store_b32(acc, out, (int)b.vo, (int)xo, 0);
+        for (int i = 0; i < kDescVecs; ++i) d[i] = lds_get(lds, (uint32_t)(kSlotDesc + kDescVecs * (nb & 1) + i) * kSlotBytes);
+        if (nb == tile)
+          decide_block<true>(a, b, lds, nb, d);
+        else
+          decide_block<false>(a, b, lds, nb, d);
+      }
+      phase_end_decide();
     }
+  }
+  if (a.h.nhub) {
+    const auto out = HubBuf(a.t, a.h, tile, blockIdx.x).buf;
+    for (int hub = wave; hub < a.h.nhub; hub += 1 + kPrep) hub_words(b, a.h, out, hub);
   }
 }
 
@@ -595,6 +603,10 @@ static void launch_simulate(const SimArgs& s, hipStream_t stream) {
 // (n = 747, K = 3000) 457 / - / 313; 8064 pairs (n = 4001) 15.2 ms / - / 10.1.
 constexpr int64_t kSimItems = 512;
 
+// Rounds of eight users (all hubs together) up to which the closure's waves make
+// the hub words after their last block: a launch costs more than a few rounds.
+constexpr int32_t kHubInline = 24;
+
 hipError_t launch_tiles(const ckm_graph& g, const Layout& L, int32_t K, int32_t g0, int32_t groups, char* work,
                         hipStream_t stream) {
   ClosureArgs c;
@@ -609,7 +621,6 @@ hipError_t launch_tiles(const ckm_graph& g, const Layout& L, int32_t K, int32_t 
   c.far = g.tile.d_far;
   c.far_more = (cptr<uint32_t>)g.tile.d_far_more;
   c.near_more = (cptr<uint32_t>)g.tile.d_near_more;
-  hipLaunchKernelGGL(ckm_closure_kernel, dim3(groups, c.t.tiles), dim3(kWave * (1 + kPrep)), 0, stream, c);
   SimArgs s;
   s.t = c.t;
   s.K = K;
@@ -621,16 +632,23 @@ hipError_t launch_tiles(const ckm_graph& g, const Layout& L, int32_t K, int32_t 
   s.users = (cptr<int32_t>)g.d_user_idx;
   s.peak = reinterpret_cast<int64_t*>(work + L.part_peak_off);
   s.cost = reinterpret_cast<int64_t*>(work + L.part_cost_off);
-  s.h.ptr = (cptr<int32_t>)g.tile.d_hub_ptr;
-  s.h.users = (cptr<HubUser>)g.tile.d_hub;
-  s.h.at = g.tile.nhub ? (cptr<uint32_t>)g.tile.d_hub_at : nullptr;
-  s.h.buf = work + L.hub_off;
-  // one launch, or as many as the room for hub words asks for
   const int32_t pairs = groups * c.t.tiles;
-  s.h.item0 = 0;
+  HubArgs h = {};
+  if (g.tile.nhub) {
+    h.ptr = (cptr<int32_t>)g.tile.d_hub_ptr;
+    h.users = (cptr<HubUser>)g.tile.d_hub;
+    h.at = (cptr<uint32_t>)g.tile.d_hub_at;
+    h.buf = work + L.hub_off;
+    h.nhub = g.tile.nhub;
+  }
+  s.h = c.h = h;
+  const bool inlined = g.tile.hub_rounds <= kHubInline && (size_t)groups * 256 * (h.nhub ? g.tile.hub_at[0] : 0) <= L.hub_bytes;
+  if (!inlined) c.h.nhub = 0;
+  hipLaunchKernelGGL(ckm_closure_kernel, dim3(groups, c.t.tiles), dim3(kWave * (1 + kPrep)), 0, stream, c);
+  // the simulation in one launch, or as many as the room for hub words asks for
   for (; s.h.item0 < pairs; s.h.item0 += s.h.items) {
     s.h.items = pairs - s.h.item0;
-    if (g.tile.nhub) {
+    if (!inlined) {
       size_t room = L.hub_bytes;   // holds the largest pair at least
       int32_t i = s.h.item0, fit = 1;
       for (; i < pairs && fit; i += fit) {
@@ -639,7 +657,7 @@ hipError_t launch_tiles(const ckm_graph& g, const Layout& L, int32_t K, int32_t 
         room -= fit * bytes;
       }
       s.h.items = i - s.h.item0;
-      hipLaunchKernelGGL(ckm_hub_kernel, dim3(s.h.items, g.tile.nhub), dim3(kWave), 0, stream, s.t, s.h);
+      hipLaunchKernelGGL(ckm_hub_kernel, dim3(s.h.items, h.nhub), dim3(kWave), 0, stream, s.t, s.h);
     }
     if (s.h.items >= 2 * kSimItems)
       launch_simulate<16, 4>(s, stream);

@@ -1324,16 +1324,30 @@ struct SelectArgs {
 // the results out.
 __device__ __forceinline__ int select_best(const SelectArgs& a, bool write) {
   Best b{0, 0, -1, 0};
-  for (int k = threadIdx.x; k < a.K; k += blockDim.x) {
-    const int64_t p = a.tot_peak[k], c = a.tot_cost[k];
-    const bool f = p <= a.budget;
-    if (write) {
-      a.peak[k] = p;
-      a.cost[k] = c;
-      a.feasible[k] = f ? 1 : 0;
+  // four candidates' totals at a time: their loads are in flight together
+  constexpr int kAtOnce = 4;
+  const int step = (int)blockDim.x;
+  for (int k0 = (int)threadIdx.x; k0 < a.K; k0 += kAtOnce * step) {
+    int64_t p[kAtOnce], c[kAtOnce];
+#pragma unroll
+    for (int i = 0; i < kAtOnce; ++i) {
+      const int k = min(k0 + i * step, a.K - 1);
+      p[i] = a.tot_peak[k];
+      c[i] = a.tot_cost[k];
     }
-    const Best x{c, p, k, 0};
-    if (f && better(x, b)) b = x;
+#pragma unroll
+    for (int i = 0; i < kAtOnce; ++i) {
+      const int k = k0 + i * step;
+      if (k >= a.K) break;
+      const bool f = p[i] <= a.budget;
+      if (write) {
+        a.peak[k] = p[i];
+        a.cost[k] = c[i];
+        a.feasible[k] = f ? 1 : 0;
+      }
+      const Best x{c[i], p[i], k, 0};
+      if (f && better(x, b)) b = x;
+    }
   }
   b = block_best(b);
   if (write) {

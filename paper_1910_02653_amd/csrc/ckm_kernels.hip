@@ -1969,10 +1969,10 @@ static unsigned tile_items(int32_t n) {
 // Rounding blocks (group, tile, 32 nodes) from which whole words beat bytes: a
 // byte's wave runs a quarter of the stages, so that small calls end sooner, but
 // stores bytes of a word from four blocks.
-// Measured, bytes / words: 60 blocks (n = 129, K = 256) 4.9 / 10.4 us;
-// 528 (n = 337, K = 501) 12.3 / 12.1; 680 (n = 505) 16.5 / 18.1;
-// 1056 (n = 337, K = 1024) 18.3 / 18.8; 8448 (n = 1009, K = 1024) 117 / 104.
-constexpr int64_t kRoundBig = 1024;
+// Measured, bytes / words: 60 blocks (n = 129, K = 256) 4.9 / 10.4 us; 504 (n = 169)
+// 8.5 / 9.6; 544 (n = 505) 10.8 / 11.3; 600 (n = 747) 12.5 / 12.5; 693 (n = 169) 12.8 / 9.7;
+// 726 (n = 337) 14.6 / 12.8; 1584 (n = 1009) 25.4 / 22.2; 6000 (n = 747) 75 / 67.
+constexpr int64_t kRoundBig = 600;
 
 // The S tiles of tot's groups from source src (kSrcRound, kSrcThreshold or kSrcUser).
 static hipError_t launch_tile_producer(const ckm_graph& g, const Layout& L, uint64_t seed, uint32_t flags, int src,
@@ -2125,9 +2125,10 @@ static hipError_t launch_closure(const ckm_graph& g, const Layout& L, const int3
   return hipGetLastError();
 }
 
-// Candidates up to which one block takes them all: K = 1024 6.4 us in one launch,
-// 4.7 + 4.2 us in two; a block walks 1024 candidates in well under a microsecond.
-constexpr int32_t kBatchOneBlock = 8192;
+// Candidates up to which one block takes them all. Measured, one launch / two, at a
+// launch rate that hides what is below 9.3: K = 4096 9.3 to 9.6 / 12.0 us; 6144 9.4 to
+// 11.6 / 12.0; 8192 9.8 to 13.8 / 12.0; 16,384 14.4 to 22.1 / 12.2.
+constexpr int32_t kBatchOneBlock = 6144;
 
 hipError_t launch_max_batch(const ckm_graph& g, const Layout& L, int32_t K, int64_t budget, int64_t cost_cap,
                             int64_t* d_batch, int32_t* d_best_k, int64_t* d_best_batch, int32_t* d_status,
@@ -2148,11 +2149,11 @@ hipError_t launch_max_batch(const ckm_graph& g, const Layout& L, int32_t K, int6
 
 // Totals read by all blocks together up to which every block of the best rows
 // selects for itself: that saves a launch while the reads, from L2, take less.
-// Measured, together / the two kernels' sum:
-// n = 337, K = 501: 6.9 / 9.3 us; n = 1009, K = 1024 (1137 blocks, 1.2 M totals)
-// 7.6 / 9.6; n = 747, K = 3000 (819 blocks, 2.5 M totals) 12.3 / 10.0; n = 4001,
-// K = 4096 52 / 32.
-constexpr int64_t kSelectTotals = 2 << 20;
+// Measured, together / apart, at a launch rate that hides what is below 11:
+// n = 1009 (1137 blocks): K = 4096 (4.7 M totals) 11.0 / 13.8 us; 6144 (7.0 M) 13.1 / 13.9;
+// 8192 (9.3 M) 15.9 / 13.7; n = 747 (819 blocks): 6144 (5.0 M) 11.9 / 13.8; 8192 (6.7 M)
+// 14.1 / 13.7. From the slope the two launches themselves are as fast at 4 to 5 M.
+constexpr int64_t kSelectTotals = 4 << 20;
 
 hipError_t launch_select(const ckm_graph& g, const Layout& L, int32_t K, uint64_t seed,
                          int64_t budget, uint32_t flags, int64_t* d_peak, int64_t* d_cost,

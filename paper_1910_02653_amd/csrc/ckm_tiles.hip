@@ -453,6 +453,7 @@ __global__ void __launch_bounds__(kWave* kSegs) ckm_simulate_kernel(SimArgs a) {
   if (item >= a.h.items) return;
   int tile, group;
   tile_of(a.t, a.h.item0 + item, tile, group);
+  if (kTile * tile + kSub * sub >= a.t.n) return;   // no stages
   TileBufs b(a.t, group, tile, lane);
   __amdgpu_buffer_rsrc_t hubs = b.r;
   uint32_t hub_words = 0;
@@ -596,12 +597,14 @@ static void launch_simulate(const SimArgs& s, hipStream_t stream) {
 
 // (group, tile) pairs from which the chip is full with fewer waves per pair:
 // with few, eight stages a wave and eight parts a tile shorten each wave's run
-// over the records; sixteen stages read each word once for twice the stages;
-// four parts leave half the sums to join.
-// Measured, with 8 stages and 8 parts / 16 and 8 / 16 and 4: 256 pairs (n = 1009,
-// K = 512) 112 us / - / 166; 512 pairs (K = 1024) 200 / 164 / 184; 1128 pairs
-// (n = 747, K = 3000) 457 / - / 313; 8064 pairs (n = 4001) 15.2 ms / - / 10.1.
-constexpr int64_t kSimItems = 512;
+// over the records; from kSimWide on sixteen stages read each word once for
+// twice the stages; from kSimFull on four parts leave half the sums to join.
+// Measured, whole call, 8 stages and 8 parts / 16 and 8 / 16 and 4:
+// n = 1009: 256 pairs (K = 512) 227 / 236 / 267 us; 288 242 / 249; 320 260 / 261;
+// 352 275 / 271; 512 357 / 323 / 345; 704 - / 418 / 424; 768 - / 447 / 445; 1024 - / 562 / 547.
+// n = 747: 264 pairs 242 / 244 / 280; 288 250 / 251; 312 263 / 258; 384 296 / 274 / 295;
+// 672 - / 381 / 383; 768 - / 415 / 409. n = 337: 264 pairs 95 / 96; 308 104 / 103; 352 112 / 106.
+constexpr int64_t kSimWide = 304, kSimFull = 736;
 
 // Rounds of eight users (all hubs together) up to which the closure's waves make
 // the hub words after their last block: a launch costs more than a few rounds.
@@ -659,9 +662,9 @@ hipError_t launch_tiles(const ckm_graph& g, const Layout& L, int32_t K, int32_t 
       s.h.items = i - s.h.item0;
       hipLaunchKernelGGL(ckm_hub_kernel, dim3(s.h.items, h.nhub), dim3(kWave), 0, stream, s.t, s.h);
     }
-    if (s.h.items >= 2 * kSimItems)
+    if (s.h.items >= kSimFull)
       launch_simulate<16, 4>(s, stream);
-    else if (s.h.items >= kSimItems)
+    else if (s.h.items >= kSimWide)
       launch_simulate<16, 8>(s, stream);
     else
       launch_simulate<8, 8>(s, stream);

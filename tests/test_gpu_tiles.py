@@ -74,10 +74,10 @@ def test_hubs(hubs):
     both_paths(w, budget=int(np.median(peak)))
 
 
-@pytest.mark.parametrize("K", [6528, 6529, 8128, 8129, 16320, 16321])
+@pytest.mark.parametrize("K", [3776, 3777, 4800, 4801, 6528, 6529, 8128, 8129, 11712, 11713, 16320, 16321])
 def test_launch_rules(K):
-    """n = 97 (4 tiles, 10 rounding items): 102 and 103 groups are either side
-    of the byte rounding, 127 and 128 of eight stages a wave, 255 and 256 of
+    """n = 97 (4 tiles, 10 rounding items): 59 and 60 groups are either side
+    of the byte rounding, 75 and 76 of eight stages a wave, 183 and 184 of
     eight parts a tile."""
     w = graph(97, (1, 3, 40), K, K, hubs=[(2, 50, 4)])
     log("tiles: K=%d" % K)
@@ -87,9 +87,9 @@ def test_launch_rules(K):
         assert (int(got["peak"][k]), int(got["cost"][k])) == r, k
 
 
-@pytest.mark.parametrize("K", [1, 1025, 8192, 8193])
+@pytest.mark.parametrize("K", [1, 1025, 6144, 6145, 8192, 8193])
 def test_largest_batch_launches(K):
-    """One block up to 8192 candidates, block maxima beyond: the multipliers and
+    """One block up to 6144 candidates, block maxima beyond: the multipliers and
     the best one from the evaluation's peaks and costs."""
     w = graph(33, (1, 3), K, K)
     log("largest batch: K=%d" % K)

@@ -264,6 +264,29 @@ Plan plan_auto(int32_t n, int32_t K, int32_t max_items, int32_t waves_per_cu) {
   return p;
 }
 
+Plan plan_stages(int32_t n, int32_t max_items) {
+  // One stage per item from T0 = n/16 up, the longest first, then the first
+  // T0 stages in T0 items: the mask kernel reads each stage's rows from the
+  // row array, so an item costs no more than its stages, and the finest items
+  // balance best.
+  if (n < 8) return plan_splits(n, max_items);
+  Plan p;
+  p.kind = 1;
+  p.T0 = std::max(1, n / 16);
+  p.P = 1;
+  p.R1 = n - p.T0;
+  p.R2 = std::max(1, std::min(p.T0, p.R1));
+  p.items = p.R1 + p.R2;
+  if (p.items > max_items) return plan_splits(n, max_items);
+  return p;
+}
+
+// The automatic plan of a graph's evaluate (the tile path has none).
+static Plan plan_for(const ckm_graph& g, const Layout& L, int32_t K) {
+  if (L.masks) return plan_stages(g.n, L.max_splits);
+  return L.pass_groups ? Plan() : plan_auto(g.n, K, L.max_splits, g.eval_waves);
+}
+
 Layout make_layout(const ckm_graph& g, int32_t K) {
   const int32_t n = g.n;
   Layout L;
@@ -307,7 +330,10 @@ Layout make_layout(const ckm_graph& g, int32_t K) {
   const size_t full = (size_t)(n >> 5), rem = (size_t)(n & 31);
   size_t s_bytes = kpad * (32 * full * (full + 1) / 2 + rem * (full + 1)) * sizeof(uint32_t), r_bytes = s_bytes;
   L.rows_on = s_bytes <= ckm::kRowsMaxBytes;
-  if (g.tile.on) {   // the tiles' words, of whole blocks of nodes and stages
+  L.masks = L.rows_on && use_masks(g, K);
+  if (L.masks) {
+    s_bytes = std::max(s_bytes, groups * mask_rows_words(n) * sizeof(uint64_t));
+  } else if (g.tile.on) {   // the tiles' words, of whole blocks of nodes and stages
     s_bytes = groups * stile_off(tiles);
     r_bytes = groups * rtile_off(tiles);
     if (g.tile.nhub) L.hub_bytes = std::min(groups * 256 * g.tile.hub_at[0], ckm::kHubMaxBytes);
@@ -447,7 +473,12 @@ static ckm_status graph_create(int32_t n, const int32_t* dep_ptr, const int32_t*
   const size_t off_di = align256(off_dp + (n + 1) * sizeof(int32_t));
   const size_t off_uo = align256(off_di + Ea * sizeof(int32_t));
   const size_t off_rec = align256(off_uo + Ea * sizeof(int32_t));
-  // the tile path's tables (its sums are binary64)
+  // the mask path's node data and the tile path's tables (their sums are binary64)
+  std::vector<char> mrecs;
+  if (!wide) {
+    mrecs.resize((size_t)ckm::mask_records_bytes(n));
+    if (!ckm::build_mask_records(n, bytes, cost, dp.data(), di.data(), up.data(), ui.data(), mrecs.data())) mrecs.clear();
+  }
   ckm::TileTables tt;
   if (!wide) ckm::build_tiles(n, bytes, cost, dp.data(), di.data(), up.data(), ui.data(), tt);
   size_t tile_end = align256(off_rec + (size_t)n * ckm::kNodeRecBytes);
@@ -460,7 +491,8 @@ static ckm_status graph_create(int32_t n, const int32_t* dep_ptr, const int32_t*
                off_far = place(tt.far.size() * 4), off_fmore = place(tt.far_more.size() * 4), off_ops = place(tt.ops.size() * sizeof(ckm::SimOps)),
                off_refs = place(tt.refs.size() * sizeof(ckm::SimRefs)),
                off_trec = place(tt.tile_rec.size() * 4), off_hptr = place(tt.hub_ptr.size() * 4),
-               off_hub = place(tt.hub.size() * sizeof(ckm::HubUser)), off_hat = place(tt.hub_at.size() * 4);
+               off_hub = place(tt.hub.size() * sizeof(ckm::HubUser)), off_hat = place(tt.hub_at.size() * 4),
+               off_mrec = place(mrecs.size());
   const size_t total = tile_end;
   std::vector<char> host(total, 0);
   const auto copy = [&](size_t off, const auto& v) {
@@ -475,6 +507,7 @@ static ckm_status graph_create(int32_t n, const int32_t* dep_ptr, const int32_t*
   copy(off_trec, tt.tile_rec);
   copy(off_hptr, tt.hub_ptr);
   copy(off_hub, tt.hub);
+  copy(off_mrec, mrecs);
   copy(off_hat, tt.hub_at);
   memcpy(host.data() + off_M, bytes, n * sizeof(int64_t));
   memcpy(host.data() + off_C, cost, n * sizeof(int64_t));
@@ -525,6 +558,7 @@ static ckm_status graph_create(int32_t n, const int32_t* dep_ptr, const int32_t*
   g->d_dep_idx = reinterpret_cast<const int32_t*>(base + off_di);
   g->d_dep_upos = reinterpret_cast<const int32_t*>(base + off_uo);
   g->d_recs = base + off_rec;
+  if (!mrecs.empty()) g->d_mrecs = base + off_mrec;
   if (!wide) {
     g->tile.on = true;
     g->tile.nhub = tt.nhub;
@@ -590,7 +624,7 @@ static ckm_status check_work(const ckm_graph* g, int32_t K, void* d_work, size_t
   if (L->rows_on && work_bytes < L->total_rows) {
     // less room than asked for: hub words of fewer pairs at a time, fewer groups
     // at a time, or none
-    L->rows_on = false;
+    L->rows_on = L->masks = false;
     L->pass_groups = 0;
     if (!g->tile.on) return CKM_OK;
     const int32_t tiles = (g->n + ckm::kTile - 1) / ckm::kTile, groups = (K + ckm::kWave - 1) / ckm::kWave;
@@ -652,7 +686,7 @@ static ckm_status evaluate_impl(const ckm_graph* g, int32_t K, uint64_t seed, ui
     return fail(CKM_E_INVALID_ARG, "unknown flags 0x%x", flags);
   if (stage_splits < 0) return fail(CKM_E_INVALID_ARG, "stage_splits = %d < 0", stage_splits);
   const ckm::Plan plan = stage_splits ? ckm::plan_splits(g->n, std::min(stage_splits, L.max_splits))
-                                      : ckm::plan_auto(g->n, K, L.max_splits, g->eval_waves);
+                                      : ckm::plan_for(*g, L, K);
   DeviceGuard dg(g->device);
   if (!dg.ok) return fail(CKM_E_DEVICE, "cannot select the graph's device %d", g->device);
   hipError_t e = ckm::launch_evaluate(*g, L, K, seed, flags, plan, ckm::kSrcRound, nullptr,
@@ -728,7 +762,7 @@ ckm_status ckm_eval_schedules_async(const ckm_graph* g, const uint64_t* d_S, int
   if (budget < 0) return fail(CKM_E_INVALID_ARG, "budget = %lld < 0", (long long)budget);
   if (!d_peak || !d_cost || !d_feasible || !d_best_k)
     return fail(CKM_E_INVALID_ARG, "NULL peak, cost, feasible or best_k");
-  const ckm::Plan plan = ckm::plan_auto(g->n, K, L.max_splits, g->eval_waves);
+  const ckm::Plan plan = ckm::plan_for(*g, L, K);
   DeviceGuard dg(g->device);
   if (!dg.ok) return fail(CKM_E_DEVICE, "cannot select the graph's device %d", g->device);
   hipError_t e = ckm::launch_evaluate(*g, L, K, 0, 0, plan, ckm::kSrcUser, d_S, static_cast<char*>(d_work),
@@ -796,7 +830,7 @@ ckm_status ckm_threshold_eval_async(const ckm_graph* g, const double* d_s_frac, 
   if (budget < 0) return fail(CKM_E_INVALID_ARG, "budget = %lld < 0", (long long)budget);
   if (!d_peak || !d_cost || !d_feasible || !d_best_k)
     return fail(CKM_E_INVALID_ARG, "NULL peak, cost, feasible or best_k");
-  const ckm::Plan plan = ckm::plan_auto(g->n, K, L.max_splits, g->eval_waves);
+  const ckm::Plan plan = ckm::plan_for(*g, L, K);
   DeviceGuard dg(g->device);
   if (!dg.ok) return fail(CKM_E_DEVICE, "cannot select the graph's device %d", g->device);
   hipStream_t s = static_cast<hipStream_t>(stream);

@@ -55,6 +55,7 @@ struct ckm_graph {
   const int32_t* d_dep_upos = nullptr;
   const void* d_recs = nullptr;  // n node records of ckm::kNodeRecBytes (see ckm_kernels.hip)
   ckm::TileGraph tile;           // the tile path's tables
+  const void* d_mrecs = nullptr; // mask-path node data when the graph fits it, else NULL
   ckm::SyncCache* sync = nullptr;  // reused by the synchronous calls; freed with the graph
 };
 
@@ -99,6 +100,14 @@ void build_node_records(int32_t n, const int64_t* M, const int64_t* C, bool wide
                         const int32_t* dep_idx, const int32_t* user_ptr, const int32_t* user_idx,
                         void* out);
 
+// Mask path (ckm_kernels.hip): bytes and builder of a graph's node data (false
+// when it does not fit), 64-bit words of a group's mask rows, and when it is used.
+int32_t mask_records_bytes(int32_t n);
+bool build_mask_records(int32_t n, const int64_t* M, const int64_t* C, const int32_t* dep_ptr,
+                        const int32_t* dep_idx, const int32_t* user_ptr, const int32_t* user_idx, void* out);
+size_t mask_rows_words(int32_t n);
+bool use_masks(const ckm_graph& g, int32_t K);
+
 // The tile path's S and R words (ckm_tiles.h): for one candidate group, tile T
 // of 32 stages holds a word per lane of 32 (T + 1) nodes, one tile after another. An R tile has a word before them.
 __host__ __device__ __forceinline__ uint32_t stile_bytes(int T) { return 8192u * (uint32_t)(T + 1); }
@@ -135,6 +144,7 @@ struct Layout {
          total_rows = 0;   // total plus the row arrays (and the hub words) when they are used
   bool rows_on = false;    // the S rows fit kRowsMaxBytes (and, after
                            // check_work, the caller's buffer holds both)
+  bool masks = false;      // the mask path: S rows as masks, R rows as the row arrays
   int32_t pass_groups = 0; // tile path: candidate groups evaluated at a time, all with
                            // rows_on; fewer where the buffer holds no more (0: none)
 };
@@ -162,6 +172,7 @@ struct Plan {
   int32_t items = 1, kind = 0, P = 0, T0 = 0, R1 = 0, R2 = 0;
 };
 Plan plan_auto(int32_t n, int32_t K, int32_t max_items, int32_t waves_per_cu);
+Plan plan_stages(int32_t n, int32_t max_items);
 Plan plan_splits(int32_t n, int32_t splits);
 
 // Resident evaluate waves per CU for a graph of n nodes (the runtime's

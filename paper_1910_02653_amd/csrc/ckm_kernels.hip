@@ -4,10 +4,12 @@
 // Work decomposition: one wave of 64 lanes owns 64 candidates (lane =
 // candidate) and one work item of stages. All lanes walk the same nodes in
 // the same order, so graph data and loop bounds are wave-uniform and only the
-// candidates' bits and running sums differ per lane. Most graphs take the
-// tile path (ckm_tiles.hip); this file makes its S rows, and evaluates what
-// that path does not: ckm_eval_kernel (wide graphs, work
-// buffers without the row arrays). Each of its lanes keeps its own bit rows
+// candidates' bits and running sums differ per lane. Three paths evaluate:
+// - the tile path (ckm_tiles.hip; its S tiles are made here): most calls;
+// - ckm_mask_eval_kernel: small graphs, up to a size of the call (use_masks);
+// - ckm_eval_kernel, the per-lane scan: wide graphs, and work buffers without
+//   room for the row arrays.
+// Each lane of the per-lane scan keeps its own bit rows
 // (32-bit words, bit i%32 of word i/32): S_t, which becomes R_t as the scan
 // passes, in LDS laid out [word][lane] so that a wave-uniform word index
 // touches 64 consecutive dwords, and S_{t+1} in vector registers (in LDS too
@@ -1889,6 +1891,539 @@ __global__ void __launch_bounds__(kWave) ckm_user_tiles_kernel(const uint32_t* _
   store_tile(stiles, group_bytes, group, T, 32 * nb, w);
 }
 
+// ---------------------------------------------------------------------------
+// Mask path. A group's 64 candidates share one 64-bit word per (stage row,
+// node): bit j is candidate 64g + j. With the rows in that form, the repair
+// of Algorithm 2 and the FREE tests of eq. collectable become scalar-unit
+// operations on whole words (one instruction decides a node for all 64
+// candidates), and the vector unit keeps only the sums, each a masked
+// binary64 update selected by such a word. A node's record and its S words
+// come through the scalar cache; the R bits of the nodes above it stay in
+// each lane's window register and register row, as in ckm_eval_kernel. One
+// wave runs a stage (or a few of the first ones), closure and simulation in one
+// scan: no padding to tiles, one launch for both, and no chain that all waves
+// wait for, which on small graphs outweighs what the tiles save (see use_masks).
+//
+// Mask rows of a group: row t holds 8 (t/8 + 1) words (nodes 0 .. t rounded
+// up to whole blocks of 8; words for nodes >= t are zero); row n, after the
+// last stage, is all zero.
+__host__ __device__ __forceinline__ size_t mrow_off(int t) {
+  const size_t q = (size_t)(t >> 3), r = (size_t)(t & 7);
+  return 8 * ((size_t)t + 4 * q * (q ? q - 1 : 0) + q * r);
+}
+
+// Node v's data, 128 bytes at 128 v:
+//   [0, 64)   record, 16 dwords (one scalar load)
+//   [64, 96)  slots 2-3 (nodes with three or four dependencies): lm, ref of
+//             slot 2, of slot 3, dependency count, byte offsets in a mask
+//             row of the S_{t+1} words of the slot 2 and 3 dependencies
+//   [96, 112) binary64 M of slots 2 and 3
+// A far reference names a node u more than 32 above v as u << 16 | (u & 31)
+// (none: 0xFFFF << 16). Its R bit matters only when u <= t, i.e. when the
+// field is below (t + 1) << 16: a node above t computes nothing in stage t.
+// Record words:
+//   0: users u of v with u <= v + 32 (bit u - v - 1)
+//   1: ctrl: far reference to the user of v more than 32 above it | slots
+//      2-3 present << 8
+//   slot s (words 2 + 2s, 3 + 2s):
+//      lm: users u of the dependency with v < u <= v + 32 (bit u - v - 1)
+//      ref: far reference to the dependency's later user
+//      An absent slot has lm = 0 and no far reference: it frees nothing, its
+//      size being 0.
+//   6: for node v-1, the byte offset in a mask row of the S_{t+1} word of
+//      its slot 0 dependency (0 for an absent slot), fetched one node ahead
+//   7: high half: the gate, the high half of the least of the node's three
+//      far references (words 1, 3 and 5), or 0 when the node has more than
+//      two dependencies: when the word is at or above the stage's limit
+//      (t + 1) << 16, the node is decided in a form without far lookups or
+//      rare slots (the limit's low half is 0, so the low half of the word
+//      never decides). Low half: for node v-1, the byte offset of its slot 1
+//      dependency's S_{t+1} word, as word 6. (Both offsets in word 6 cost a
+//      shift and a mask per node.)
+//   8-15: binary64 M_v, C_v, M of slots 0 and 1, used from scalar registers
+//      (the vector registers they would take are worth a wave per SIMD)
+// Pairs of nodes are aligned (nodes 2c, 2c+1). A stage's scan starts at the
+// top of its node's pair; a node above t there (or past n - 1, whose data is
+// padded with empty nodes up to np = round_up(n, 4) + 4) computes nothing
+// and holds nothing, so it leaves every sum unchanged.
+constexpr uint32_t kMNoFar = 0xFFFFu << 16, kMRare = 1u << 8;
+constexpr int kMNodeBytes = 128;
+__host__ __device__ __forceinline__ int mask_padded_nodes(int n) { return ((n + 3) & ~3) + 4; }
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
+
+struct MaskArgs {
+  int32_t n, K, items, kind, P, T0, R1, R2;   // work plan (see Plan)
+  int32_t np;                                 // padded node count of the node data
+  double base;                                // M_in + 2 M_param
+  size_t mgroup;                              // words of one group's mask rows
+  cptr<uint64_t> mrows;                       // S masks, group-major
+  cptr<u32x16> mnodes;                        // np x 128 bytes of node data
+  uint32_t* __restrict__ rrows;               // R rows out (row array layout), or NULL
+  int32_t kpad;
+  int64_t* __restrict__ part_peak;
+  int64_t* __restrict__ part_cost;
+};
+
+__device__ __forceinline__ bool lane_of(uint64_t m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
+__device__ __forceinline__ uint64_t mask_of(bool b) { return __builtin_amdgcn_ballot_w64(b); }
+// acc + [lane's bit of m] * x, one masked binary64 update
+__device__ __forceinline__ double madd_m(double acc, uint64_t m, double x) {
+  return fma(lane_of(m) ? 1.0 : 0.0, x, acc);
+}
+// A scalar load at a 32-bit byte offset from a base (one instruction, the
+// offset in a register).
+template <typename T, typename B>
+__device__ __forceinline__ T sload(cptr<B> base, uint32_t off) {
+  return *(const __attribute__((address_space(4))) T*)((const __attribute__((address_space(4))) char*)base + off);
+}
+// 16 bytes at byte offset off + kOff of the node data, in every lane
+template <int kOff>
+__device__ __forceinline__ uint4 load_mval(__amdgpu_buffer_rsrc_t rs, uint32_t off) {
+  const auto x = __builtin_amdgcn_raw_buffer_load_b128(rs, kOff, (int)off, 0);
+  return make_uint4(x[0], x[1], x[2], x[3]);
+}
+
+struct MScan {
+  double U0, Y, maxv, cost;
+  uint32_t Rwin;   // R bits of nodes v+1 .. v+32 (bit d <-> node v + 1 + d)
+};
+
+// The R bit of the far node that field f names (more than 32 above the node
+// being decided: its word of the register row is complete). A shift uses the
+// low five bits of its count by itself. Only for u <= t; the empty asm keeps
+// the compiler from hoisting the indexed register read out of that branch
+// (the word index is clamped to the row all the same).
+__device__ __forceinline__ uint32_t far_bit(const u32x32& Rrow, uint32_t f) {
+  asm volatile("");
+  return (Rrow[(f >> 21) & 31u] >> (f & 31u)) & 1u;
+}
+
+// One dependency slot of node v: the dependency's value is released after
+// v (FREE(t,i,v) = 1) on the candidates that compute v, do not keep the
+// value into stage t+1 and compute none of its later users in stage t.
+template <bool kFar>
+__device__ __forceinline__ double mask_slot(double val, uint64_t R, uint32_t lm, uint32_t ref, double Mi,
+                                            uint64_t s1i, uint32_t Rwin, const u32x32& Rrow, uint32_t tlim) {
+  uint32_t y = Rwin & lm;
+  if (kFar && __builtin_expect(ref < tlim, 0)) y |= far_bit(Rrow, ref);
+  const uint64_t later = mask_of(y != 0u);
+  const uint64_t fr = R & ~(s1i | later);
+  return madd_m(val, fr, Mi);
+}
+
+// What node v needs besides its block: its record, the S_{t+1} words of its
+// slot 0 and 1 dependencies and its binary64 operands (M_v, C_v | M of slots
+// 0, 1), all requested one node ahead.
+struct MNode {
+  u32x16 rec;
+  uint64_t d0, d1;
+};
+
+// Node v of stage t for the 64 candidates of a group: S0, S1 are the words
+// of S_t[v] and S_{t+1}[v]. Algorithm 2: v is computed if it is node t
+// (constraint 4a), or it is not held and is kept into t+1 (1c) or used by a
+// computed node (1b). kTop: v is in the block of node t, and may be t; below
+// that block, v < t and the scan has passed at least one node. Released
+// right after its own compute (eq. collectable with i = v): a computed node
+// that is neither kept nor used, which only node t can be.
+// kSlow: the general form, for a node whose gate (record word 7: the least
+// of its three far references, 0 with more than two dependencies) is below
+// the stage's limit; the fast form has no far lookup and no rare slots.
+template <bool kTop, bool kSlow, bool kSkip>
+__device__ __forceinline__ void mask_node_as(const MaskArgs& a, int t, int v, const MNode& nd, uint64_t S0,
+                                             uint64_t S1, cptr<uint64_t> s1row, MScan& sc, u32x32& Rrow,
+                                             uint32_t tlim) {
+  const u32x16& rec = nd.rec;
+  const uint32_t ctrl = rec[1];
+  const double Mv = dbl(rec[8], rec[9]), Cv = dbl(rec[10], rec[11]);
+  uint32_t x = sc.Rwin & rec[0];
+  if (kSlow && __builtin_expect(ctrl < tlim, 0)) x |= far_bit(Rrow, ctrl);
+  const uint64_t x1 = S1 | mask_of(x != 0u);
+  uint64_t R = x1 & ~S0;
+  sc.U0 = madd_m(sc.U0, S0, Mv);
+  // A lane that does not compute v frees nothing after it, and its val = Y
+  // changes neither maxv (which already covers Y: the running value has only
+  // fallen since the last computed node) nor Y. kSkip: a node that no
+  // candidate of the group computes returns here. Without it such nodes take
+  // the general path, which is a little faster for randomized rounding, while
+  // the threshold family, whose groups hold neighbouring thresholds, has many
+  // more of them and gains from the skip (n = 1009: 0.455 against 0.458 ms
+  // and 0.557 against 0.570 ms, without and with the other form).
+  if (kSkip && !kTop && R == 0ull) {
+    sc.Rwin = sc.Rwin + sc.Rwin;
+    return;
+  }
+  double val = sc.Y;
+  if (kTop && v == t) {
+    R = ~0ull;
+    val = madd_m(val, ~x1, Mv);
+  }
+  val = mask_slot<kSlow>(val, R, rec[2], rec[3], dbl(rec[12], rec[13]), nd.d0, sc.Rwin, Rrow, tlim);
+  val = mask_slot<kSlow>(val, R, rec[4], rec[5], dbl(rec[14], rec[15]), nd.d1, sc.Rwin, Rrow, tlim);
+  if (kSlow && __builtin_expect((ctrl & kMRare) != 0u, 0)) {
+    const uint32_t off = (uint32_t)v * kMNodeBytes;
+    const u32x8 r2 = sload<u32x8>(a.mnodes, off + 64);
+    const u32x4 m23 = sload<u32x4>(a.mnodes, off + 96);
+    val = mask_slot<true>(val, R, r2[0], r2[1], dbl(m23[0], m23[1]), sload<uint64_t>(s1row, r2[5]), sc.Rwin, Rrow,
+                          tlim);
+    if (r2[4] >= 4)
+      val = mask_slot<true>(val, R, r2[2], r2[3], dbl(m23[2], m23[3]), sload<uint64_t>(s1row, r2[6]), sc.Rwin,
+                            Rrow, tlim);
+  }
+  // suffix form of the U recurrence (see scan_node): val = Y + freed_v
+  sc.maxv = max_f64(sc.maxv, val);
+  const bool rb = lane_of(R);
+  const double sel = rb ? 1.0 : 0.0;
+  sc.Y = fma(-sel, Mv, val);
+  sc.cost = fma(sel, Cv, sc.cost);
+  sc.Rwin = sc.Rwin + sc.Rwin + (rb ? 1u : 0u);
+}
+
+template <bool kTop, bool kSkip>
+__device__ __forceinline__ void mask_node(const MaskArgs& a, int t, int v, const MNode& nd, uint64_t S0, uint64_t S1,
+                                          cptr<uint64_t> s1row, MScan& sc, u32x32& Rrow) {
+  const uint32_t tlim = (uint32_t)(t + 1) << 16;
+  if (__builtin_expect(nd.rec[7] < tlim, 0))
+    mask_node_as<kTop, true, kSkip>(a, t, v, nd, S0, S1, s1row, sc, Rrow, tlim);
+  else
+    mask_node_as<kTop, false, kSkip>(a, t, v, nd, S0, S1, s1row, sc, Rrow, tlim);
+}
+
+// x, made to depend on a word of a record that a wait delivers, so that the
+// loads it addresses are issued after that wait: scalar loads complete out
+// of order, and a wait for the record would wait for them as well.
+__device__ __forceinline__ uint32_t after_record(uint32_t x, uint32_t word) {
+  asm("" : "+s"(x) : "s"(word));
+  return x;
+}
+
+// The loads node v-1 needs, issued while node v is decided: its record (with
+// its operands) at byte off, and the dependency words node v's record lists
+// for it.
+__device__ __forceinline__ MNode mask_fetch(const MaskArgs& a, const u32x16& rec_v, cptr<uint64_t> s1row,
+                                            uint32_t off) {
+  MNode nx;
+  nx.rec = sload<u32x16>(a.mnodes, off);
+  nx.d0 = sload<uint64_t>(s1row, rec_v[6]);
+  nx.d1 = sload<uint64_t>(s1row, rec_v[7] & 0xFFFFu);
+  return nx;
+}
+
+// Node v at position P of its pair (P = v & 1), with the next node's loads
+// issued first; at P = 0 they include the next pair's words, into Bn0 and
+// Bn1 (the current pair is in B0, B1). The loads alternate between two
+// buffers by position (node v's in buf[P], node v-1's into the other), so
+// nothing moves from one to the other.
+template <int P, bool kTop, bool kSkip>
+__device__ __forceinline__ void mask_step(const MaskArgs& a, int t, int v, MNode (&buf)[2], const u32x4& B0,
+                                          const u32x4& B1, u32x4& Bn0, u32x4& Bn1, cptr<uint64_t> s0row,
+                                          cptr<uint64_t> s1row, MScan& sc, u32x32& Rrow, uint32_t* rrow_t) {
+  constexpr int kCur = P, kNext = P ^ 1;
+  const uint64_t S0 = (uint64_t)B0[2 * P] | (uint64_t)B0[2 * P + 1] << 32;
+  const uint64_t S1 = (uint64_t)B1[2 * P] | (uint64_t)B1[2 * P + 1] << 32;
+  const u32x16& rec = buf[kCur].rec;
+  // node v-1's data (node 0 fetches its own again: nothing is left to load)
+  buf[kNext] = mask_fetch(a, rec, s1row, after_record(v >= 1 ? (uint32_t)(v - 1) * kMNodeBytes : 0u, rec[6]));
+  if (P == 0) {
+    // pair c-1 (v = 2c) starts 16 (c - 1) bytes into a row (0 for c = 0)
+    const uint32_t boff = after_record(v >= 2 ? 8u * (uint32_t)v - 16u : 0u, rec[6]);
+    Bn0 = sload<u32x4>(s0row, boff);
+    Bn1 = sload<u32x4>(s1row, boff);
+  }
+  // The loads stay ahead of the node's gate branch. Placed after it, in a
+  // block that both forms of the node share, they made the compiler route
+  // the fast form through a flag, a test and a taken jump per node pair (one
+  // per cent).
+  asm volatile("" ::: "memory");
+  mask_node<kTop, kSkip>(a, t, v, buf[kCur], S0, S1, s1row, sc, Rrow);
+  if (P == 0 && (v & 31) == 0) {
+    // the R bits of nodes v .. v+31 are complete: one word of R_t, kept in
+    // the register row (and stored for the output)
+    Rrow[v >> 5] = sc.Rwin;
+    if (rrow_t) rrow_t[(size_t)(v >> 5) * a.kpad] = sc.Rwin;
+  }
+}
+
+// Pair c (nodes 2c+1, 2c) from B0, B1; pair c-1 loaded into Bn0, Bn1.
+template <bool kTop, bool kSkip>
+__device__ __forceinline__ void mask_block(const MaskArgs& a, int t, int c, MNode (&buf)[2], const u32x4& B0,
+                                           const u32x4& B1, u32x4& Bn0, u32x4& Bn1, cptr<uint64_t> s0row,
+                                           cptr<uint64_t> s1row, MScan& sc, u32x32& Rrow, uint32_t* rrow_t) {
+  mask_step<1, kTop, kSkip>(a, t, 2 * c + 1, buf, B0, B1, Bn0, Bn1, s0row, s1row, sc, Rrow, rrow_t);
+  mask_step<0, kTop, kSkip>(a, t, 2 * c, buf, B0, B1, Bn0, Bn1, s0row, s1row, sc, Rrow, rrow_t);
+}
+
+// One wave per work item: the 64 candidates of group blockIdx.x over the
+// stages of item blockIdx.y. The R row is in 32 registers: eight would do, but are
+// indexed by selects and cost a tenth (n = 129, K = 64: 39.2 against 36.5 us a call).
+// None of the graph's nodes exceeds the record (at most four dependencies, one
+// user more than 32 nodes above the node, one such later user per dependency).
+// Each node's loads are issued one node ahead, in one batch, so that a node
+// waits once, for loads that had a whole node's work to arrive.
+template <bool kSkip>
+__global__ void __launch_bounds__(kWave) ckm_mask_eval_kernel(MaskArgs a) {
+  const int lane = threadIdx.x;
+  const int group = blockIdx.x;
+  const int item = blockIdx.y;
+  const uint32_t k = (uint32_t)(group * kWave + lane);
+  int t0, t1;
+  item_range(a, item, t0, t1);
+  const cptr<uint64_t> rows = a.mrows + (size_t)group * a.mgroup;
+  u32x32 Rrow = (u32x32)0u;
+  double seg_peak = -INFINITY;
+  int64_t seg_cost = 0;
+  for (int t = t0; t < t1; ++t) {
+    const cptr<uint64_t> s0row = rows + mrow_off(t);
+    const cptr<uint64_t> s1row = rows + mrow_off(t + 1);
+    uint32_t* rrow_t = a.rrows ? a.rrows + row_base(t) * (size_t)a.kpad + k : nullptr;
+    MScan sc;
+    sc.U0 = (double)a.base;
+    sc.Y = 0.0;
+    sc.maxv = -INFINITY;
+    sc.cost = 0.0;
+    sc.Rwin = 0u;
+    // the scan starts at the top of t's pair: node 2c + 1, whose loads node
+    // 2c + 2's record names
+    const int c = t >> 1;
+    MNode buf[2];
+    const u32x16 top = a.mnodes[(size_t)(2 * c + 2) * (kMNodeBytes / 64)];
+    buf[1] = mask_fetch(a, top, s1row, (uint32_t)(2 * c + 1) * kMNodeBytes);
+    const u32x4 T0 = sload<u32x4>(s0row, 16u * c), T1 = sload<u32x4>(s1row, 16u * c);
+    u32x4 A0, A1, B0, B1;
+    mask_block<true, kSkip>(a, t, c, buf, T0, T1, B0, B1, s0row, s1row, sc, Rrow, rrow_t);
+    int cc = c - 1;
+    for (; cc >= 1; cc -= 2) {
+      mask_block<false, kSkip>(a, t, cc, buf, B0, B1, A0, A1, s0row, s1row, sc, Rrow, rrow_t);
+      mask_block<false, kSkip>(a, t, cc - 1, buf, A0, A1, B0, B1, s0row, s1row, sc, Rrow, rrow_t);
+    }
+    if (cc == 0) mask_block<false, kSkip>(a, t, 0, buf, B0, B1, A0, A1, s0row, s1row, sc, Rrow, rrow_t);
+    seg_peak = fmax(seg_peak, sc.U0 - sc.Y + sc.maxv);
+    seg_cost += (int64_t)sc.cost;
+  }
+  if ((int)k < a.K && t0 < t1) {
+    atomicMax(reinterpret_cast<long long*>(a.part_peak) + k, (long long)seg_peak);
+    atomicAdd(reinterpret_cast<unsigned long long*>(a.part_cost) + k, (unsigned long long)seg_cost);
+  }
+}
+
+}  // namespace
+// v_writelane_b32 through its compiler intrinsic, so that the compiler sees
+// the instruction and its hazards (this compiler has no builtin for it). The
+// declaration binds a name to the intrinsic, so it stays outside the unnamed
+// namespace: there it would name an internal function that is never defined.
+__device__ int amdgcn_writelane(int x, int lane, int v) __asm("llvm.amdgcn.writelane.i32");
+namespace {
+// Lane L of v takes the wave-uniform x.
+template <int L>
+__device__ __forceinline__ uint32_t write_lane(uint32_t v, uint32_t x) {
+  return (uint32_t)amdgcn_writelane((int)x, L, (int)v);
+}
+// Lanes 2j and 2j+1 take the low and high halves of m[j], j >= J.
+template <int J>
+__device__ __forceinline__ uint32_t put_masks(uint32_t v, const uint64_t (&m)[8]) {
+  v = write_lane<2 * J>(v, (uint32_t)m[J]);
+  v = write_lane<2 * J + 1>(v, (uint32_t)(m[J] >> 32));
+  if constexpr (J + 1 < 8) v = put_masks<J + 1>(v, m);
+  return v;
+}
+
+// The 8 entries of block b of a row of thresholds (q or keys), read into
+// every lane by vector loads: they complete in order, so the next block's
+// can be requested while this one is in use (scalar loads complete out of
+// order, and waiting for one waits for all).
+struct Q8 {
+  uint4 lo, hi;
+  __device__ uint32_t operator[](int j) const {
+    const uint4& h = j < 4 ? lo : hi;
+    const int i = j & 3;
+    return i == 0 ? h.x : i == 1 ? h.y : i == 2 ? h.z : h.w;
+  }
+};
+__device__ __forceinline__ Q8 load_q8(__amdgpu_buffer_rsrc_t rs, uint32_t row_bytes, int b) {
+  // the offset is wave-uniform; stating it keeps it a scalar operand where
+  // the compiler cannot prove it (else it loops over the lanes' values)
+  const uint32_t off = __builtin_amdgcn_readfirstlane(row_bytes + 32u * (uint32_t)b);
+  Q8 x;
+  x.lo = load_mval<0>(rs, off);
+  x.hi = load_mval<16>(rs, off);
+  return x;
+}
+
+// Randomized rounding into mask row r of a group, lane = candidate. Word i
+// of the row is the group's 64 decisions [u_{k,r,i} < q[r][i]] (the same
+// draws as round_word); candidate 0 takes the deterministic bits under
+// CKM_F_DET0. A block of 8 nodes shares one Philox output per lane.
+// Block b of row r (8 nodes) for the 64 candidates of a group, thresholds
+// qb: one Philox output per lane, 8 compares whose lane masks are the words,
+// one 64-byte store.
+__device__ __forceinline__ void round_mask_block(const PhiloxRow& pr, const Q8& qb, int b, int r, uint32_t k,
+                                                 uint32_t key0, uint32_t key1, bool det_here,
+                                                 cptr<uint32_t> drow, uint32_t* dst) {
+  uint64_t m[8];
+  if (8 * b >= r) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) m[j] = 0ull;
+  } else {
+    uint32_t x[4];
+    philox_block(pr, (uint32_t)b, key0, key1, x);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const uint32_t u = (x[j >> 1] >> (16 * (j & 1))) & 0xFFFFu;
+      m[j] = mask_of(u < qb[j]);
+    }
+    if (det_here) {
+      const uint32_t dw = drow[b >> 2] >> (8 * (b & 3));
+#pragma unroll
+      for (int j = 0; j < 8; ++j) m[j] = (m[j] & ~1ull) | ((dw >> j) & 1u);
+    }
+  }
+  // lanes 16-63 of out are never stored, so out starts from any value
+  const uint32_t out = put_masks<0>(k, m);
+  if (threadIdx.x < 16) dst[16 * b + threadIdx.x] = out;   // words 8b .. 8b+7 of the row
+}
+
+__device__ __forceinline__ void round_mask_row(const uint32_t* __restrict__ q, const uint32_t* __restrict__ det,
+                                               int32_t n, int32_t ldq, int32_t det_words, uint32_t key0,
+                                               uint32_t key1, uint32_t det0, int group, int r, uint64_t* row) {
+  const int lane = threadIdx.x;
+  const uint32_t k = (uint32_t)(group * kWave + lane);
+  uint32_t* dst = reinterpret_cast<uint32_t*>(row);
+  const int nblk = (r >> 3) + 1;
+  const auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(q), 0, n * ldq * 4, kBufWord3);
+  const uint32_t row_bytes = (uint32_t)(r < n ? r : 0) * (uint32_t)ldq * 4u;
+  const cptr<uint32_t> drow = as_const(det + (size_t)(r < n ? r : 0) * det_words);
+  const PhiloxRow pr = philox_row((uint32_t)r, k, key0);
+  const bool det_here = det0 && group == 0;
+  // two threshold buffers by block parity, each block's requested one block
+  // ahead (vector loads complete in order)
+  Q8 qa = load_q8(rs, row_bytes, 0), qb;
+  for (int b = 0; b < nblk; b += 2) {
+    if (b + 1 < nblk) qb = load_q8(rs, row_bytes, b + 1);
+    round_mask_block(pr, qa, b, r, k, key0, key1, det_here, drow, dst);
+    if (b + 1 >= nblk) break;
+    if (b + 2 < nblk) qa = load_q8(rs, row_bytes, b + 2);
+    round_mask_block(pr, qb, b + 1, r, k, key0, key1, det_here, drow, dst);
+  }
+}
+
+// Block (group, y) makes row n - y of the group (rows 0 .. n; row n is
+// zero). Blocks start in order of y, so the longest rows start first and the
+// last to start are the shortest: the launch ends with little left on any
+// SIMD. (Equal pairs of rows y and n - y per block ended with most SIMDs
+// running one wave, the youngest, which the issue order serves last.)
+__global__ void __launch_bounds__(kWave) ckm_round_masks_kernel(const uint32_t* __restrict__ q,
+                                                                const uint32_t* __restrict__ det, int32_t n,
+                                                                int32_t ldq, int32_t det_words, uint32_t key0,
+                                                                uint32_t key1, uint32_t det0, size_t mgroup,
+                                                                uint64_t* __restrict__ mrows, Totals tot) {
+  const int group = blockIdx.x;
+  const int y = blockIdx.y;
+  clear_totals(tot, group, blockIdx.y == 0);
+  uint64_t* rows = mrows + (size_t)group * mgroup;
+  round_mask_row(q, det, n, ldq, det_words, key0, key1, det0, group, n - y, rows + mrow_off(n - y));
+}
+
+// Threshold candidates into mask rows (block (group, y): row n - y):
+// word i of row r is the group's 64 decisions [rank_k < key[r][i]], the
+// threshold test of threshold_word. Keys on and above the diagonal are 0, so
+// are their words (row n reads row 0, all of whose keys are 0).
+// Block b (8 nodes) of a threshold row: word i is the lane mask of
+// [rank_k < key_i] (keys at and above the diagonal are 0).
+__device__ __forceinline__ void threshold_mask_block(const Q8& kb, uint32_t rk, uint32_t k, int b, uint32_t* dst) {
+  uint64_t m[8];
+#pragma unroll
+  for (int j = 0; j < 8; ++j) m[j] = mask_of(rk < kb[j]);
+  // lanes 16-63 of out are never stored, so out starts from any value
+  const uint32_t out = put_masks<0>(k, m);
+  if (threadIdx.x < 16) dst[16 * b + threadIdx.x] = out;
+}
+
+__global__ void __launch_bounds__(kWave) ckm_threshold_masks_kernel(const uint32_t* __restrict__ key, int32_t ldq,
+                                                                    const uint32_t* __restrict__ rank, int32_t K,
+                                                                    int32_t n, size_t mgroup,
+                                                                    uint64_t* __restrict__ mrows, Totals tot) {
+  const int lane = threadIdx.x;
+  const int group = blockIdx.x;
+  clear_totals(tot, group, blockIdx.y == 0);
+  const uint32_t k = (uint32_t)(group * kWave + lane);
+  const uint32_t rk = rank[k < (uint32_t)K ? k : (uint32_t)K - 1u];
+  uint64_t* rows = mrows + (size_t)group * mgroup;
+  const auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(key), 0, n * ldq * 4, kBufWord3);
+  // row n - y (longest first, as in ckm_round_masks_kernel); the row is
+  // wave-uniform, and stating it keeps the block loop scalar
+  const int r = __builtin_amdgcn_readfirstlane(n - (int)blockIdx.y);
+  uint32_t* dst = reinterpret_cast<uint32_t*>(rows + mrow_off(r));
+  const int lim = r < n ? r : 0;   // row n (after the last stage) is empty
+  const uint32_t rb = (uint32_t)lim * (uint32_t)ldq * 4u;
+  const int nblk = (r >> 3) + 1;
+  // two key buffers by block parity, each block's requested one block ahead
+  Q8 ka = load_q8(rs, rb, 0), kb;
+  for (int b = 0; b < nblk; b += 2) {
+    if (b + 1 < nblk) kb = load_q8(rs, rb, b + 1);
+    threshold_mask_block(ka, rk, k, b, dst);
+    if (b + 1 >= nblk) break;
+    if (b + 2 < nblk) ka = load_q8(rs, rb, b + 2);
+    threshold_mask_block(kb, rk, k, b + 1, dst);
+  }
+}
+
+// Caller-supplied checkpoint matrices into mask rows (block (group, y): row
+// n - y): word i of row r is bit i of row r of each of the group's 64
+// matrices ([K][n][s_words] 32-bit words), for i < r only (bits on and above
+// the diagonal are not part of S). Lanes past K repeat candidate K-1. Each
+// lane reads its matrix row 16 bytes (128 nodes) at a time, the next chunk
+// requested before the current one is turned into masks.
+__device__ __forceinline__ uint4 user_chunk(const uint32_t* row, int c, int lim) {
+  // chunk c: words 4c .. 4c+3; only words with a node below lim are read
+  uint4 x = make_uint4(0u, 0u, 0u, 0u);
+  if (128 * c < lim) x.x = row[4 * c];
+  if (128 * c + 32 < lim) x.y = row[4 * c + 1];
+  if (128 * c + 64 < lim) x.z = row[4 * c + 2];
+  if (128 * c + 96 < lim) x.w = row[4 * c + 3];
+  return x;
+}
+
+__global__ void __launch_bounds__(kWave) ckm_user_masks_kernel(const uint32_t* __restrict__ s_user, int32_t n,
+                                                               int32_t K, int32_t s_words, size_t mgroup,
+                                                               uint64_t* __restrict__ mrows, Totals tot) {
+  const int lane = threadIdx.x;
+  const int group = blockIdx.x;
+  clear_totals(tot, group, blockIdx.y == 0);
+  const uint32_t k = (uint32_t)(group * kWave + lane);
+  const uint32_t kk = k < (uint32_t)K ? k : (uint32_t)K - 1u;
+  uint64_t* rows = mrows + (size_t)group * mgroup;
+  // row n - y (longest first, as in ckm_round_masks_kernel); the row is
+  // wave-uniform, and stating it keeps the block loop scalar
+  const int r = __builtin_amdgcn_readfirstlane(n - (int)blockIdx.y);
+  uint32_t* dst = reinterpret_cast<uint32_t*>(rows + mrow_off(r));
+  const int lim = r < n ? r : 0;   // row n (after the last stage) is empty
+  const uint32_t* src = s_user + ((size_t)kk * n + lim) * s_words;
+  const int nblk = (r >> 3) + 1;
+  uint4 cur = user_chunk(src, 0, lim);
+  for (int c = 0; 16 * c < nblk; ++c) {
+    const uint4 nxt = user_chunk(src, c + 1, lim);
+    const uint32_t w4[4] = {cur.x, cur.y, cur.z, cur.w};
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+      const int b = 16 * c + q;
+      if (b >= nblk) break;
+      // the block's bits of nodes below lim only
+      const int below = lim - 8 * b;
+      const uint32_t keep = below >= 8 ? 0xFFu : below <= 0 ? 0u : (1u << below) - 1u;
+      const uint32_t byte = (w4[q >> 2] >> (8 * (q & 3))) & keep;
+      uint64_t m[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) m[j] = mask_of(((byte >> j) & 1u) != 0u);
+      const uint32_t out = put_masks<0>(k, m);   // lanes 16-63 are not stored
+      if (lane < 16) dst[16 * b + lane] = out;
+    }
+    cur = nxt;
+  }
+}
+
 template <typename T>
 T* at(char* work, size_t off) { return reinterpret_cast<T*>(work + off); }
 
@@ -2002,12 +2537,83 @@ static hipError_t launch_tile_producer(const ckm_graph& g, const Layout& L, uint
   return hipGetLastError();
 }
 
+// Masks or tiles: the same results from other kernels. The tiles decide 32 stages
+// in one instruction but pad to 32 stages and nodes, and their closure is a chain
+// that a launch of few blocks waits for; so on small graphs masks are faster up
+// to a size of the call, on those above kMaskSmall nodes from some thousand
+// candidates on only, and above kMaskLargest nowhere.
+// Measured, masks / tiles: n = 17, K = 64 24.0 / 24.5 us (alone 35 / 40), K = 65,536 63 / 80;
+// n = 33, K = 8192 22.9 / 34.7; n = 43, K = 65,536 (121 M) 110 / 133; n = 57, K = 16,384 (53 M node pairs) 47 / 55, 65,536
+// (213 M) 159 / 149; n = 85, K = 4096 30 / 39, 16,384 (118 M) 74.0 / 73.6;
+// n = 101, K = 64 28.2 / 30.4, 4096 34.6 / 47.2, 8192 (84 M) 54 / 62, 16,384 (167 M) 94.4 / 93.9;
+// n = 129, K = 64 36.5 / 35.2, 1024 37.9 / 37.3, 2048 39 / 44, 8192 (136 M) 78 / 84;
+// n = 169, K = 64 41 / 38, 1024 42.9 / 42.9, 2048 45 / 53, 4096 (117 M) 66 / 69, 8192 119 / 102;
+// n = 253, K = 64 59 / 48, 2048 75 / 77, 4096 136 / 105.
+constexpr int32_t kMaskSmall = 112, kMaskLargest = 176, kMaskManyCandidates = 1024;
+constexpr int64_t kMaskWork = 140 << 20;   // K n^2
+bool use_masks(const ckm_graph& g, int32_t K) {
+  return g.d_mrecs && (int64_t)K * g.n * g.n <= kMaskWork && (g.n <= kMaskSmall || K >= kMaskManyCandidates);
+}
+
+size_t mask_rows_words(int32_t n) { return mrow_off(n + 1); }
+
+// The mask rows of all groups from source src, as launch_tile_producer.
+static hipError_t launch_mask_producer(const ckm_graph& g, const Layout& L, uint64_t seed, uint32_t flags, int src,
+                                       const uint64_t* s_user, const Totals& tot, char* work, hipStream_t stream) {
+  const dim3 grid(groups_of(tot.K), g.n + 1);
+  if (src == kSrcThreshold) {
+    hipLaunchKernelGGL(ckm_threshold_masks_kernel, grid, dim3(kWave), 0, stream, at<const uint32_t>(work, L.q_off), L.ldq,
+                       at<const uint32_t>(work, L.thr_rank_off), tot.K, g.n, mask_rows_words(g.n),
+                       at<uint64_t>(work, L.rows_off), tot);
+  } else if (src == kSrcUser) {
+    hipLaunchKernelGGL(ckm_user_masks_kernel, grid, dim3(kWave), 0, stream, reinterpret_cast<const uint32_t*>(s_user), g.n,
+                       tot.K, L.row_words, mask_rows_words(g.n), at<uint64_t>(work, L.rows_off), tot);
+  } else {
+    hipLaunchKernelGGL(ckm_round_masks_kernel, grid, dim3(kWave), 0, stream, at<const uint32_t>(work, L.q_off),
+                       at<const uint32_t>(work, L.det_off), g.n, L.ldq, L.det_words, (uint32_t)(seed & 0xFFFFFFFFu),
+                       (uint32_t)(seed >> 32), (flags & CKM_F_DET0) ? 1u : 0u, mask_rows_words(g.n),
+                       at<uint64_t>(work, L.rows_off), tot);
+  }
+  return hipGetLastError();
+}
+
+// The evaluate on the mask rows. Rows of the threshold family or of supplied
+// schedules take the kernel that skips a node no candidate of the group
+// computes (see mask_node_as).
+static hipError_t launch_masks(const ckm_graph& g, const Layout& L, int32_t K, const Plan& plan, int src, char* work,
+                               hipStream_t stream) {
+  MaskArgs m;
+  m.n = g.n;
+  m.K = K;
+  m.items = plan.items;
+  m.kind = plan.kind;
+  m.P = plan.P;
+  m.T0 = plan.T0;
+  m.R1 = plan.R1;
+  m.R2 = plan.R2;
+  m.np = mask_padded_nodes(g.n);
+  m.base = (double)g.base;
+  m.mgroup = mask_rows_words(g.n);
+  m.mrows = as_const(at<const uint64_t>(work, L.rows_off));
+  m.mnodes = (cptr<u32x16>)(g.d_mrecs);
+  m.rrows = at<uint32_t>(work, L.rrows_off);
+  m.kpad = (int32_t)groups_of(K) * kWave;
+  m.part_peak = at<int64_t>(work, L.part_peak_off);
+  m.part_cost = at<int64_t>(work, L.part_cost_off);
+  const dim3 grid(groups_of(K), plan.items);
+  if (src == kSrcRound)
+    hipLaunchKernelGGL(ckm_mask_eval_kernel<false>, grid, dim3(kWave), 0, stream, m);
+  else
+    hipLaunchKernelGGL(ckm_mask_eval_kernel<true>, grid, dim3(kWave), 0, stream, m);
+  return hipGetLastError();
+}
+
 hipError_t launch_round_rows(const ckm_graph& g, const Layout& L, int32_t K, uint64_t seed, uint32_t flags,
                              char* work, hipStream_t stream) {
   if (!L.rows_on) return hipSuccess;
-  if (g.tile.on)
-    return launch_tile_producer(g, L, seed, flags, kSrcRound, nullptr, Totals{nullptr, nullptr, K, 0, (int32_t)groups_of(K)},
-                                work, stream);
+  const Totals kept{nullptr, nullptr, K, 0, (int32_t)groups_of(K)};
+  if (L.masks) return launch_mask_producer(g, L, seed, flags, kSrcRound, nullptr, kept, work, stream);
+  if (g.tile.on) return launch_tile_producer(g, L, seed, flags, kSrcRound, nullptr, kept, work, stream);
   const int32_t kpad = ((K + kWave - 1) / kWave) * kWave;
   hipLaunchKernelGGL(ckm_round_rows_kernel, dim3((K + kWave - 1) / kWave, g.n), dim3(kWave), 0, stream,
                      at<const uint32_t>(work, L.q_off), at<const uint32_t>(work, L.det_off), L.ldq, L.det_words,
@@ -2019,13 +2625,17 @@ hipError_t launch_round_rows(const ckm_graph& g, const Layout& L, int32_t K, uin
 hipError_t launch_evaluate(const ckm_graph& g, const Layout& L, int32_t K, uint64_t seed,
                            uint32_t flags, const Plan& plan, int src, const uint64_t* s_user, char* work,
                            hipStream_t stream) {
-  if (L.pass_groups) {
-    // S tiles made by a producer, which clears the candidates' totals on the
-    // way (the evaluate accumulates into them), then the tile path
+  if (L.masks || L.pass_groups) {
+    // mask rows or S tiles made by a producer, which clears the candidates'
+    // totals on the way (the evaluate accumulates into them), then the evaluate
     Totals tot{at<int64_t>(work, L.part_peak_off), at<int64_t>(work, L.part_cost_off), K, 0, 0};
     const bool rounded = src == kSrcRound && (flags & CKM_F_ROUNDED) && L.rows_on;   // by the caller, beforehand
     if (rounded)
       hipLaunchKernelGGL(ckm_eval_init_kernel, dim3((K + 255) / 256), dim3(256), 0, stream, K, tot.peak, tot.cost);
+    if (L.masks) {
+      const hipError_t e = rounded ? hipGetLastError() : launch_mask_producer(g, L, seed, flags, src, s_user, tot, work, stream);
+      return e == hipSuccess ? launch_masks(g, L, K, plan, src, work, stream) : e;
+    }
     const int32_t groups = (int32_t)groups_of(K);
     for (; tot.g0 < groups; tot.g0 += tot.groups) {
       tot.groups = std::min(groups - tot.g0, L.pass_groups);
@@ -2153,7 +2763,10 @@ hipError_t launch_max_batch(const ckm_graph& g, const Layout& L, int32_t K, int6
 // n = 1009 (1137 blocks): K = 4096 (4.7 M totals) 11.0 / 13.8 us; 6144 (7.0 M) 13.1 / 13.9;
 // 8192 (9.3 M) 15.9 / 13.7; n = 747 (819 blocks): 6144 (5.0 M) 11.9 / 13.8; 8192 (6.7 M)
 // 14.1 / 13.7. From the slope the two launches themselves are as fast at 4 to 5 M.
+// A block of 256 threads walks the candidates, so these are bounded too: n = 17,
+// K = 16,384 27.6 us a call together, 25.4 apart; K = 65,536 71.8 / 63.4.
 constexpr int64_t kSelectTotals = 4 << 20;
+constexpr int32_t kSelectCandidates = 8192;
 
 hipError_t launch_select(const ckm_graph& g, const Layout& L, int32_t K, uint64_t seed,
                          int64_t budget, uint32_t flags, int64_t* d_peak, int64_t* d_cost,
@@ -2165,7 +2778,7 @@ hipError_t launch_select(const ckm_graph& g, const Layout& L, int32_t K, uint64_
   // With the row arrays the evaluate stage kept every candidate's R rows, so
   // the best R is a gather; otherwise Algorithm 2 runs again for it.
   RTiles tiles = {};
-  if (g.tile.on && L.rows_on && d_best_R) {
+  if (L.pass_groups && L.rows_on && d_best_R) {
     tiles.rtiles = work + L.rrows_off;
     tiles.r_bytes = rtile_off((g.n + 31) / 32);
     tiles.R_rows = d_best_R;
@@ -2180,7 +2793,7 @@ hipError_t launch_select(const ckm_graph& g, const Layout& L, int32_t K, uint64_
                           (tiles.R_rows ? (unsigned)((g.n + 31) / 32 * ((L.row_words * 32 + 255) / 256)) : 0u);
   SelectArgs sel = {K, nan_rows, at<const int64_t>(work, L.part_peak_off), at<const int64_t>(work, L.part_cost_off),
                     budget, d_peak, d_cost, d_feasible, at<const int32_t>(work, L.nan_off), d_best_k, d_status};
-  if (blocks && (int64_t)blocks * K <= kSelectTotals) {
+  if (blocks && K <= kSelectCandidates && (int64_t)blocks * K <= kSelectTotals) {
     // in the launch that writes the best rows
   } else if (K <= kSelectOneBlock) {
     hipLaunchKernelGGL(ckm_select_kernel, dim3(1), dim3(1024), 0, stream, sel);
@@ -2337,6 +2950,86 @@ void build_node_records(int32_t n, const int64_t* M, const int64_t* C, bool wide
     }
     recs[v] = r;
   }
+}
+
+// Node data of the mask path, or false when the graph does not fit it.
+int32_t mask_records_bytes(int32_t n) { return mask_padded_nodes(n) * kMNodeBytes; }
+
+bool build_mask_records(int32_t n, const int64_t* M, const int64_t* C, const int32_t* dep_ptr,
+                        const int32_t* dep_idx, const int32_t* user_ptr, const int32_t* user_idx, void* out) {
+  if (n > kMaskLargest) return false;
+  const int32_t np = mask_padded_nodes(n);
+  char* base = static_cast<char*>(out);
+  memset(out, 0, (size_t)mask_records_bytes(n));
+  auto far = [](int u) { return (uint32_t)u << 16 | (uint32_t)(u & 31); };
+  auto put = [](uint32_t* w, double x) { memcpy(w, &x, sizeof(x)); };
+  for (int32_t v = 0; v < np; ++v) {   // no far references, padded nodes included
+    uint32_t* r = reinterpret_cast<uint32_t*>(base + (size_t)v * kMNodeBytes);
+    r[1] = r[3] = r[5] = r[7] = r[16 + 1] = r[16 + 3] = kMNoFar;
+  }
+  for (int32_t v = 0; v < n; ++v) {
+    char* node = base + (size_t)v * kMNodeBytes;
+    uint32_t* r = reinterpret_cast<uint32_t*>(node);
+    uint32_t* r2 = reinterpret_cast<uint32_t*>(node + 64);
+    uint32_t* m23 = reinterpret_cast<uint32_t*>(node + 96);
+    uint32_t ctrl = kMNoFar;   // stays, or names the one far user
+    int nfar = 0;
+    for (int32_t e = user_ptr[v]; e < user_ptr[v + 1]; ++e) {
+      const int u = user_idx[e];
+      if (u - v - 1 < 32) {
+        r[0] |= 1u << (u - v - 1);
+      } else {
+        if (nfar++) return false;
+        ctrl = far(u);
+      }
+    }
+    const int nd = dep_ptr[v + 1] - dep_ptr[v];
+    if (nd > 4) return false;
+    if (nd > 2) {
+      ctrl |= kMRare;
+      r2[4] = (uint32_t)nd;
+    }
+    put(r + 8, (double)M[v]);
+    put(r + 10, (double)C[v]);
+    for (int sl = 0; sl < nd; ++sl) {
+      const int i = dep_idx[dep_ptr[v] + sl];
+      uint32_t* w = sl < 2 ? r + 2 + 2 * sl : r2 + 2 * (sl - 2);
+      if (sl >= 2) r2[5 + (sl - 2)] = (uint32_t)i * 8u;
+      uint32_t ref = kMNoFar;
+      int nlate = 0;
+      for (int32_t e = user_ptr[i]; e < user_ptr[i + 1]; ++e) {
+        const int u = user_idx[e];
+        if (u <= v) continue;
+        if (u - v - 1 < 32) {
+          w[0] |= 1u << (u - v - 1);
+        } else {
+          if (nlate++) return false;
+          ref = far(u);
+        }
+      }
+      w[1] = ref;
+      put(sl < 2 ? r + 12 + 2 * sl : m23 + 2 * (sl - 2), (double)M[i]);
+    }
+    r[1] = ctrl;
+    // the gate: below the stage's limit when a far reference may apply (the
+    // low half takes node v-1's slot 1 offset below)
+    r[7] = (ctrl & kMRare) ? 0u : std::min(ctrl, std::min(r[3], r[5])) & 0xFFFF0000u;
+  }
+  // fetch lists: record v (padded ones included) names the S_{t+1} words of
+  // node v-1's slots 0 (word 6) and 1 (low half of word 7)
+  for (int32_t v = 1; v < np; ++v) {
+    const int32_t u = v - 1;
+    uint32_t f0 = 0, f1 = 0;
+    if (u < n) {
+      const int nd = dep_ptr[u + 1] - dep_ptr[u];
+      if (nd >= 1) f0 = (uint32_t)dep_idx[dep_ptr[u]] * 8u;
+      if (nd >= 2) f1 = (uint32_t)dep_idx[dep_ptr[u] + 1] * 8u;
+    }
+    uint32_t* r = reinterpret_cast<uint32_t*>(base + (size_t)v * kMNodeBytes);
+    r[6] = f0;
+    r[7] = (r[7] & 0xFFFF0000u) | f1;
+  }
+  return true;   // node 0 keeps fetch list 0
 }
 
 }  // namespace ckm

@@ -54,6 +54,16 @@ def test_sizes(n):
     both_paths(w, budget=int(np.median(peak)))
 
 
+@pytest.mark.parametrize("n", [1, 2, 31, 32, 33, 63, 64, 65, 96, 97, 112, 113])
+def test_sizes_two_far_users(n):
+    """The same sizes where nodes have two users more than 32 above them, which
+    the mask path of small graphs does not take (from 42 nodes on)."""
+    w = graph(n, (1, 33, 41), n, 65)
+    log("tiles: n=%d, two far users" % n)
+    peak, _ = check_full(w, gpu_round_eval(w, flags=ckm.F_DET0), flags=ckm.F_DET0)
+    both_paths(w, budget=int(np.median(peak)))
+
+
 @pytest.mark.parametrize("offsets", [
     (), (1, 2, 3), (4, 9), (4, 9, 31), (5, 8, 30, 31), (4, 5, 6, 7, 31), (4, 5, 6, 7, 8, 30), (64, 65), (64, 65, 96),
     (64, 65, 66, 67, 68, 69, 70, 71, 72, 73, 74, 75), (1, 40, 63, 64, 100)], ids=str)
@@ -167,11 +177,11 @@ def test_room_for_hub_words():
     room (down to the largest pair of a group and a tile, and less) gives the
     same results in more launches; so does the area that allocates nothing."""
     w = complete(150, 128)
-    g, chain = ckm.Graph.from_workload(w), ckm.Graph.from_workload(graph(150, (1,), 1, 1))
+    g, plain = ckm.Graph.from_workload(w), ckm.Graph.from_workload(graph(150, (1, 40, 64), 1, 1))   # tiles, no hubs
     for K in (1, 128, 4096, 65536):
-        assert g.workspace_size(K) <= chain.workspace_size(K) + (1 << 30) + 256
+        assert g.workspace_size(K) <= plain.workspace_size(K) + (1 << 30) + 256
     full = g.workspace_size(w.K)
-    room = full - chain.workspace_size(w.K)
+    room = full - plain.workspace_size(w.K)
     most = 256 * (1 + sum((m - 1) // 4 for m in range(6, w.n)))   # the last tile's
     assert most < 64 * w.num_edges and 2 * most < room < 10 * most
     s = torch.from_numpy(w.s_frac).cuda()
@@ -192,7 +202,7 @@ def test_room_for_hub_words():
     got = {k: ckm.rows_to_numpy(v) if k in ("best_S", "best_R") else v.numpy() for k, v in want.items()}
     check_full(w, dict(got, best_k=int(got["best_k"][0])))
     g.close()
-    chain.close()
+    plain.close()
 
 
 @pytest.mark.parametrize("hubs", [(), [(0, 20, 9), (5, 6, 1)]], ids=["no hubs", "hubs"])

@@ -2540,19 +2540,21 @@ static hipError_t launch_tile_producer(const ckm_graph& g, const Layout& L, uint
 // Masks or tiles: the same results from other kernels. The tiles decide 32 stages
 // in one instruction but pad to 32 stages and nodes, and their closure is a chain
 // that a launch of few blocks waits for; so on small graphs masks are faster up
-// to a size of the call, on those above kMaskSmall nodes from some thousand
-// candidates on only, and above kMaskLargest nowhere.
+// to a size of the call, on those above kMaskSmall nodes from kMaskCandidates on only,
+// and above kMaskLargest nowhere.
 // Measured, masks / tiles: n = 17, K = 64 24.0 / 24.5 us (alone 35 / 40), K = 65,536 63 / 80;
 // n = 33, K = 8192 22.9 / 34.7; n = 43, K = 65,536 (121 M) 110 / 133; n = 57, K = 16,384 (53 M node pairs) 47 / 55, 65,536
 // (213 M) 159 / 149; n = 85, K = 4096 30 / 39, 16,384 (118 M) 74.0 / 73.6;
 // n = 101, K = 64 28.2 / 30.4, 4096 34.6 / 47.2, 8192 (84 M) 54 / 62, 16,384 (167 M) 94.4 / 93.9;
 // n = 129, K = 64 36.5 / 35.2, 1024 37.9 / 37.3, 2048 39 / 44, 8192 (136 M) 78 / 84;
 // n = 169, K = 64 41 / 38, 1024 42.9 / 42.9, 2048 45 / 53, 4096 (117 M) 66 / 69, 8192 119 / 102;
+// n = 201, K = 1024 54 / 49, 1536 55 / 57, 2048 58 / 64, 4096 (165 M) 88 / 86; n = 221,
+// K = 1024 50 / 49, 1536 52 / 57;
 // n = 253, K = 64 59 / 48, 2048 75 / 77, 4096 136 / 105.
-constexpr int32_t kMaskSmall = 112, kMaskLargest = 176, kMaskManyCandidates = 1024;
+constexpr int32_t kMaskSmall = 112, kMaskLargest = 224, kMaskCandidates = 1152;
 constexpr int64_t kMaskWork = 140 << 20;   // K n^2
 bool use_masks(const ckm_graph& g, int32_t K) {
-  return g.d_mrecs && (int64_t)K * g.n * g.n <= kMaskWork && (g.n <= kMaskSmall || K >= kMaskManyCandidates);
+  return g.d_mrecs && (int64_t)K * g.n * g.n <= kMaskWork && (g.n <= kMaskSmall || K >= kMaskCandidates);
 }
 
 size_t mask_rows_words(int32_t n) { return mrow_off(n + 1); }

@@ -604,7 +604,13 @@ static void launch_simulate(const SimArgs& s, hipStream_t stream) {
 // 352 275 / 271; 512 357 / 323 / 345; 704 - / 418 / 424; 768 - / 447 / 445; 1024 - / 562 / 547.
 // n = 747: 264 pairs 242 / 244 / 280; 288 250 / 251; 312 263 / 258; 384 296 / 274 / 295;
 // 672 - / 381 / 383; 768 - / 415 / 409. n = 337: 264 pairs 95 / 96; 308 104 / 103; 352 112 / 106.
-constexpr int64_t kSimWide = 304, kSimFull = 736;
+// On graphs of up to kSimFewTiles tiles, whose waves have few records, four parts are
+// enough from kSimFew pairs on. Measured, 8 and 8 / 8 and 4 / 16 and 8: n = 101: 128 pairs
+// 35.8 / 37.1 us; 192 44.9 / 43.6; 256 48.8 / 45.9 / 46.9; n = 169: 192 pairs 55.0 / 55.0; 288
+// 68.5 / 65.9 / 67.1; 384 78 / 74 / 72;
+// n = 337: 176 pairs 78.3 / 81.4.
+constexpr int64_t kSimWide = 304, kSimFull = 736, kSimFew = 176;
+constexpr int32_t kSimFewTiles = 6;
 
 // Rounds of eight users (all hubs together) up to which the closure's waves make
 // the hub words after their last block: a launch costs more than a few rounds.
@@ -666,6 +672,8 @@ hipError_t launch_tiles(const ckm_graph& g, const Layout& L, int32_t K, int32_t 
       launch_simulate<16, 4>(s, stream);
     else if (s.h.items >= kSimWide)
       launch_simulate<16, 8>(s, stream);
+    else if (s.h.items >= kSimFew && c.t.tiles <= kSimFewTiles)
+      launch_simulate<8, 4>(s, stream);
     else
       launch_simulate<8, 8>(s, stream);
   }

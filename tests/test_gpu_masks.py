@@ -18,9 +18,9 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("n,K,offsets", [
     (1, 70, ()), (2, 1, (1,)), (7, 65, (1, 2)), (8, 64, (1, 3)), (33, 130, (1, 2, 3, 32)), (64, 200, (1, 33)),
     # the first size past the small ones, with few candidates and with many
-    (112, 300, (1, 2, 5, 40)), (113, 300, (1, 2, 5, 40)), (113, 1023, (1, 40)), (113, 1024, (1, 40)),
+    (112, 300, (1, 2, 5, 40)), (113, 300, (1, 2, 5, 40)), (113, 1151, (1, 40)), (113, 1152, (1, 40)),
     # the largest size, and the first past it
-    (176, 1536, (2, 7, 50)), (177, 1536, (2, 7, 50)),
+    (224, 1152, (2, 7, 50)), (225, 1152, (2, 7, 50)),
     # K n^2 on either side of 140 Mi: 35,840 candidates of 64 nodes
     (64, 35840, (1, 40)), (64, 35841, (1, 40)),
     # what the path's records do not hold: five dependencies, two far users, two later far users

@@ -84,11 +84,11 @@ def test_hubs(hubs):
     both_paths(w, budget=int(np.median(peak)))
 
 
-@pytest.mark.parametrize("K", [3776, 3777, 4800, 4801, 6528, 6529, 8128, 8129, 11712, 11713, 16320, 16321])
+@pytest.mark.parametrize("K", [2752, 2753, 3776, 3777, 4800, 4801, 6528, 6529, 8128, 8129, 11712, 11713, 16320, 16321])
 def test_launch_rules(K):
     """n = 97 (4 tiles, 10 rounding items): 59 and 60 groups are either side
-    of the byte rounding, 75 and 76 of eight stages a wave, 183 and 184 of
-    eight parts a tile."""
+    of the byte rounding, 43 and 44 of eight parts of few tiles, 75 and 76 of
+    eight stages a wave, 183 and 184 of eight parts a tile."""
     w = graph(97, (1, 3, 40), K, K, hubs=[(2, 50, 4)])
     log("tiles: K=%d" % K)
     got = both_paths(w, flags=ckm.F_DET0)

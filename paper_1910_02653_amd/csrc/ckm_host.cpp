@@ -298,7 +298,6 @@ Layout make_layout(const ckm_graph& g, int32_t K) {
   L.max_splits = max_splits_for(n, K);
   L.reduce_blocks = (K + 255) / 256;
   size_t off = 0;
-  L.hdr_off = off;       off = align256(off + 256);
   L.q_off = off;         off = align256(off + (size_t)n * L.ldq * sizeof(uint32_t));
   L.det_off = off;       off = align256(off + (size_t)n * L.det_words * sizeof(uint32_t));
   L.nan_off = off;       off = align256(off + (size_t)n * sizeof(int32_t));

@@ -126,8 +126,7 @@ struct Layout {
   int32_t row_words = 0;  // 32-bit words per output bit row: 2 * ceil(n / 64)
   int32_t max_splits = 0; // most work items per group of 64 candidates
   int32_t reduce_blocks = 0;
-  // hdr: int32 number of work items (rows of the partial arrays) of the last evaluate
-  size_t hdr_off = 0, q_off = 0, det_off = 0, nan_off = 0, part_peak_off = 0, part_cost_off = 0,
+  size_t q_off = 0, det_off = 0, nan_off = 0, part_peak_off = 0, part_cost_off = 0,
          best_off = 0, srows_off = 0, thr_sorted_off = 0, thr_rank_off = 0,
          // execution plans: per-stage statement and compute counts, check
          // flags, first statement and first register, and the go flag

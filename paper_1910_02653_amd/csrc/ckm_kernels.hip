@@ -383,7 +383,6 @@ struct EvalArgs {
   int32_t kpad;                         // row arrays: candidates per row word (64 * groups)
   int64_t* __restrict__ part_peak;   // [K] running max over work items
   int64_t* __restrict__ part_cost;   // [K] running sum over work items
-  int32_t* __restrict__ hdr;
 };
 
 // First stage of range s of `parts` ranges over stages 0 .. m-1 with about
@@ -1065,7 +1064,6 @@ ckm_eval_kernel(EvalArgs a) {
     atomicMax(reinterpret_cast<long long*>(a.part_peak) + k, (long long)AR::i64(seg_peak));
     atomicAdd(reinterpret_cast<unsigned long long*>(a.part_cost) + k, (unsigned long long)seg_cost);
   }
-  if (group == 0 && item == 0 && lane == 0) a.hdr[0] = a.items;
 }
 
 // Empty totals before an evaluate launch: peak = INT64_MIN, cost = 0.
@@ -2701,7 +2699,6 @@ hipError_t launch_evaluate(const ckm_graph& g, const Layout& L, int32_t K, uint6
   a.recs = reinterpret_cast<const uint4*>(g.d_recs);
   a.part_peak = at<int64_t>(work, L.part_peak_off);
   a.part_cost = at<int64_t>(work, L.part_cost_off);
-  a.hdr = at<int32_t>(work, L.hdr_off);
   const int groups = (K + kWave - 1) / kWave;
   void (*fn)(EvalArgs) = eval_kernel_for(a.row_words, src, g.wide);
   const size_t lds_bytes = eval_lds_bytes(a.row_words, g.wide);

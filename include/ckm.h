@@ -185,8 +185,10 @@ ckm_status ckm_round_async(const ckm_graph* g, int32_t K, uint64_t seed, uint32_
  * memory simulation and cost. Leaves each candidate's peak and cost in the
  * work buffer (reset at the start of every call). stage_splits = number of
  * stage ranges each group of 64 candidates is split into, 1..n (0 =
- * automatic: ranges cut and ordered for load balance); results do not depend
- * on it. flags: CKM_F_DET0, and CKM_F_ROUNDED when ckm_round_async has
+ * automatic: ranges cut and ordered for load balance) by the kernels that run
+ * a stage per wave: those of small graphs, wide graphs and buffers without the
+ * row arrays. The kernels of most calls have their own division and ignore
+ * it; results never depend on it. flags: CKM_F_DET0, and CKM_F_ROUNDED when ckm_round_async has
  * rounded the rows (with the same K, seed and CKM_F_DET0) since the last
  * ckm_quantize_async on this buffer; the rows are then not rounded again. */
 ckm_status ckm_evaluate_async(const ckm_graph* g, int32_t K, uint64_t seed, uint32_t flags,

@@ -1,9 +1,8 @@
 """The asynchronous entry points under HIP graph capture.
 
 ckm_round_eval_async (quantize, rounding, Algorithm 2 repair and simulation,
-select) enqueues kernel launches only, plus, on seen-path graphs with eight
-or more candidate groups, an event fork to the graph's second stream and a
-join back. A graph captured from one call is replayed several times, with
+select) enqueues kernel launches only, all on the caller's stream. A graph
+captured from one call is replayed several times, with
 the program's own eager work (the same call on other buffers, outputs
 overwritten) and synchronizations between the replays, and every replay must
 equal the eager call bit for bit, which the oracle checks in turn.
@@ -99,13 +98,22 @@ def test_capture_transformer_sampled():
         assert (int(got["peak"][k]), int(got["cost"][k])) == orc[k], k
 
 
-def test_capture_seen_path_overlapped():
-    """A seen-path graph whose seen bits hold the evaluate to 14 waves per
-    CU, K = 520 (nine groups): the captured call forks to the graph's second
-    stream and joins back; every candidate."""
-    from test_gpu_seen import lds_bound_graph
-    w = lds_bound_graph(520)
+def test_capture_far_users():
+    """A graph whose every node has a far user, K = 520 (nine groups): every
+    candidate."""
+    from test_gpu_seen import far_users_graph
+    w = far_users_graph(520)
     w = w.replace(budget=int(np.median(replay_peaks(w))))
-    log("graph capture: seen path n=%d K=%d" % (w.n, w.K))
+    log("graph capture: far users n=%d K=%d" % (w.n, w.K))
+    got = replay_matches_eager(w, w.budget)
+    check_full(w, got)
+
+
+def test_capture_hub_words():
+    """A complete graph: hub words in launches of their own."""
+    from test_gpu_tiles import complete
+    w = complete(100, 130)
+    w = w.replace(budget=int(np.median(replay_peaks(w))))
+    log("graph capture: hub words n=%d K=%d" % (w.n, w.K))
     got = replay_matches_eager(w, w.budget)
     check_full(w, got)

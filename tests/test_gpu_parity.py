@@ -353,19 +353,26 @@ def test_in_kernel_rows_without_row_arrays(n):
         assert (int(direct[0][k]), int(direct[1][k])) == orc[k], k
 
 
-def test_async_stages_and_split_invariance():
-    """The staged async calls give the same bits for any stage split (a race
-    or a split-boundary error would change them)."""
+@pytest.mark.parametrize("path", ["tiles", "scan", "masks", "wide"])
+def test_async_stages_and_split_invariance(path):
+    """The staged async calls give the same bits for any stage split: on the
+    per-lane scan with rows made inside and (wide graph) read from the row
+    array, and on the mask path, whose launches the split cuts (a race or a
+    split-boundary error would change them), and on the tile path, which has
+    no use for it."""
     import torch
-    w = wl.config(3)
-    w = w.replace(K=200)
+    w = wl.config(2 if path == "masks" else 3)
+    w = w.replace(K=1200 if path == "masks" else 200)   # n = 129: masks from 1152 candidates on
+    if path == "wide":
+        from test_gpu_wide import widen
+        w = widen(w.replace(K=70), 20, 26, seed=3)[0]
     g = ckm.Graph.from_workload(w)
     d_s = torch.from_numpy(w.s_frac).cuda()
-    work = g.alloc_work(w.K)
+    work = g.alloc_work(w.K, rows=path != "scan")
     ref_out = None
     budget = w.budget * 3
     for splits in (1, 2, 7, 64, 10 ** 6, 0):
-        log("splits %d" % splits)
+        log("%s: splits %d" % (path, splits))
         out = g.alloc_outputs(w.K)
         g.quantize_async(d_s, work)
         g.evaluate_async(w.K, w.seed, 0, work, stage_splits=splits)

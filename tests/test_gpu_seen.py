@@ -1,17 +1,10 @@
-"""Parity of the seen path with the oracle: graphs the mask records cannot
-hold (more than 1023 nodes, more than four dependencies of a node, more than
-one user more than 32 nodes above a node or a dependency), so their rounding
-path evaluates with far relations kept as per-lane seen bits in LDS.
-
-Hand-built and seeded graphs put the path's limits to work: a node with 120
-far users, a dependency with dozens of far later users, a node with 60
-dependencies (the overflow list), slots 2-3, and seen rows of 1 to 127 words.
-Small graphs are compared over every candidate; large ones on sampled
-candidates, the argmin and the best rows. With eight or more candidate groups
-on a graph whose seen bits hold the evaluate to a few waves per CU, the
-library overlaps the producer of the later groups' mask rows with the
-evaluate of the first quarter (a second stream); the K = 520 cases on such a
-graph run that launch for all three sources.
+"""Parity with the oracle on graphs with many relations between far nodes: a
+node with 120 users more than 32 nodes above it, a dependency with dozens of
+far later users, a node with 60 dependencies, and graphs up to the largest
+size whose every node has a far user. None of them fits the node data of the
+mask path, so they take the tile path, the first ones with hub words. Small
+graphs are compared over every candidate; large ones on sampled candidates,
+the argmin and the best rows.
 """
 import numpy as np
 import pytest
@@ -51,7 +44,7 @@ def hub_graph():
 
 def test_hub_graph_all_candidates():
     w = hub_graph()
-    log("seen path: hub graph n=%d K=%d" % (w.n, w.K))
+    log("far users: hub graph n=%d K=%d" % (w.n, w.K))
     peak, _ = check_full(w, gpu_round_eval(w))
     med = int(np.median(peak))
     check_full(w, gpu_round_eval(w, budget=med), budget=med)
@@ -61,7 +54,7 @@ def test_fan_in_fan_out_all_candidates():
     """A random DAG with up to 12 dependencies per node and users anywhere above."""
     w = wl.random_dag(200, seed=17, K=96, max_deg=12, window=200, max_size=1000, max_cost=1000,
                       s_kind="uniform", budget_pct=60.0)
-    log("seen path: fan-in/out n=%d K=%d" % (w.n, w.K))
+    log("far users: fan-in/out n=%d K=%d" % (w.n, w.K))
     peak, _ = check_full(w, gpu_round_eval(w))
     med = int(np.median(peak))
     check_full(w, gpu_round_eval(w, budget=med), budget=med)
@@ -93,26 +86,23 @@ def test_mirrored_training_graph():
     n = len(deps)
     w = wl.Workload("mirror1501", n, ptr, idx, np.asarray(cost, np.int64), np.asarray(size, np.int64), 1 << 20,
                     1 << 19, wl.s_frac_uniform(n, 5), 70, 5, 1 << 40)
-    log("seen path: mirrored n=%d" % n)
+    log("far users: mirrored n=%d" % n)
     sampled(w)
 
 
-def test_seen_row_of_127_words():
-    """n = 4096 (the largest graph), every node used 40 nodes above it: 4056
-    seen bits, 127 words per lane."""
+def test_far_users_of_the_largest_graph():
+    """n = 4096, every node used 40 nodes above it."""
     n = 4096
     deps = [set() if v == 0 else {v - 1} for v in range(n)]
     for v in range(40, n):
         deps[v].add(v - 40)
     w = workload("skip40", deps, seed=4096, K=70)
-    log("seen path: n=%d, 127 seen words" % n)
+    log("far users: n=%d" % n)
     sampled(w, ks=(0, 63, 69))
 
 
-def lds_bound_graph(K):
-    """n = 1400, every node used by the next and by the node 40 above it:
-    1360 seen bits, 43 words per lane (11 KiB of LDS per wave, 14 waves per
-    CU), so the evaluate takes the overlapped launch."""
+def far_users_graph(K):
+    """n = 1400, every node used by the next and by the node 40 above it."""
     n = 1400
     deps = [set() if v == 0 else {v - 1} for v in range(n)]
     for v in range(40, n):
@@ -120,29 +110,28 @@ def lds_bound_graph(K):
     return workload("skip40_1400", deps, seed=1400, K=K)
 
 
-def test_overlapped_rounding_all_candidates():
-    """K = 520 (9 groups: the first two rounded and evaluated on the caller's
-    stream, the other 7 on the side stream): every candidate at two budgets."""
-    w = lds_bound_graph(520)
-    log("seen path, overlapped: rounding n=%d K=%d" % (w.n, w.K))
+def test_far_users_rounding_all_candidates():
+    """K = 520 (9 groups, the last ragged): every candidate at two budgets."""
+    w = far_users_graph(520)
+    log("far users: rounding n=%d K=%d" % (w.n, w.K))
     peak, _ = check_full(w, gpu_round_eval(w))
     med = int(np.median(peak))
     check_full(w, gpu_round_eval(w, budget=med), budget=med)
 
 
-def test_overlapped_thresholds_all_candidates():
-    w = lds_bound_graph(520)
+def test_far_users_thresholds_all_candidates():
+    w = far_users_graph(520)
     p = thr.grid(520, 9)
-    log("seen path, overlapped: thresholds n=%d K=520" % w.n)
+    log("far users: thresholds n=%d K=520" % w.n)
     peak, _ = thr.check(w, p, thr.gpu_eval(w, p, w.budget), w.budget)
     med = int(np.median(peak))
     thr.check(w, p, thr.gpu_eval(w, p, med), med)
 
 
-def test_overlapped_schedules_all_candidates():
-    w = lds_bound_graph(520)
+def test_far_users_schedules_all_candidates():
+    w = far_users_graph(520)
     rows = wl.random_schedules(w.n, 520, seed=520, density=0.3, kind="intervals")
-    log("seen path, overlapped: supplied schedules n=%d K=520" % w.n)
+    log("far users: supplied schedules n=%d K=520" % w.n)
     peak, _ = sched.check(w, rows, sched.gpu_eval(w, rows, w.budget), w.budget)
     med = int(np.median(peak))
     sched.check(w, rows, sched.gpu_eval(w, rows, med), med)

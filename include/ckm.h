@@ -151,8 +151,7 @@ ckm_status ckm_round_eval(const ckm_graph* g, const double* s_frac, int64_t ld, 
  * S rows of all K candidates fit in 8 GiB, room for them and for their R
  * rows (the row arrays, about twice the S rows' size), and on a graph with
  * nodes of more than five users room for what is read of these users together
- * (1 GiB at most, and at most a few times the S rows' size except where nodes
- * have tens of users): 9.5 GB at n = 4001, K = 4096. The evaluate stage then
+ * (1 GiB at most): 9.0 GB at n = 4001, K = 4096. The evaluate stage then
  * makes each row once. With less of that last part (16 MiB are always enough)
  * it runs in more launches, and on graphs of more than 64 nodes a buffer with
  * room for some thousands of candidates' rows is used in passes over the
@@ -188,8 +187,8 @@ ckm_status ckm_round_async(const ckm_graph* g, int32_t K, uint64_t seed, uint32_
  * automatic: ranges cut and ordered for load balance) by the kernels that run
  * a stage per wave: those of small graphs, wide graphs and buffers without the
  * row arrays. The kernels of most calls have their own division and ignore
- * it; results never depend on it. flags: CKM_F_DET0, and CKM_F_ROUNDED when ckm_round_async has
- * rounded the rows (with the same K, seed and CKM_F_DET0) since the last
+ * it; results never depend on it. flags: CKM_F_DET0, and CKM_F_ROUNDED when
+ * ckm_round_async has rounded the rows (with the same K, seed and CKM_F_DET0) since the last
  * ckm_quantize_async on this buffer; the rows are then not rounded again. */
 ckm_status ckm_evaluate_async(const ckm_graph* g, int32_t K, uint64_t seed, uint32_t flags,
                               int32_t stage_splits, void* d_work, size_t work_bytes, void* stream);

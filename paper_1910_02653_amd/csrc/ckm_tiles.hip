@@ -614,7 +614,10 @@ constexpr int32_t kSimFewTiles = 6;
 
 // Rounds of eight users (all hubs together) up to which the closure's waves make
 // the hub words after their last block: a launch costs more than a few rounds.
-constexpr int32_t kHubInline = 24;
+// Measured, whole call, in the closure / in a launch: 3 rounds (n = 61, K = 64) 30.6 /
+// 32.4 us; 9 (n = 401) 95.4 / 96.3, K = 3000 208 / 210; 20 (n = 747) 161.8 / 160.3, K = 3000
+// 545 / 552; 42 (n = 1601) 359 / 356; 97 (n = 150, six users per node) 93 / 78.
+constexpr int32_t kHubInline = 12;
 
 hipError_t launch_tiles(const ckm_graph& g, const Layout& L, int32_t K, int32_t g0, int32_t groups, char* work,
                         hipStream_t stream) {

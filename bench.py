@@ -3,22 +3,22 @@
 A step is one pass of the whole path over the transformer-stack workload
 (n = 1009 nodes, K = 1024 candidates, 25 % budget): thresholds from S*,
 rounding of every candidate's S rows, Algorithm 2 repair + memory/cost
-simulation of every candidate (both in one ckm_evaluate_async call; the
-evaluate kernel is the dominant one, and split steps, with the rounding
-launched on its own by ckm_round_async, time it alone with HIP events on its
-stream), per-candidate reduction, argmin, and the best candidate's S and R
-rows.
+simulation of every candidate (all in one ckm_evaluate_async call; split
+steps, with the rounding launched on its own by ckm_round_async, time the
+evaluation's two kernels, closure and simulation, alone with HIP events on
+their stream), per-candidate reduction, argmin, and the best candidate's S
+and R rows.
 The graph and S* are resident in HBM before timing starts.
 
 Prints one JSON line. `value` is candidate schedules evaluated per second.
-`roofline` prices the dominant kernel (the evaluate kernel) against HBM
+`roofline` prices the evaluation (both kernels) against HBM
 bandwidth with the algorithmic bytes of bit-packed S and R rows, each
 written once and read once: 4 * n * ceil(n/64) * 8 bytes per candidate.
-`roofline_alu` prices the same launch against the vector ALU issue rate:
-VALU instructions per launch (committed rocprofv3 counters of the current
-kernel source, else null) x 64 lanes / the launch time, against 256 CUs x 4
-SIMDs x 16 lanes x 2.4 GHz. (The kernel's own limit is its scalar issue and
-the round trip of each node's loads; the vector unit is about 70 % busy.)
+`roofline_alu` prices it against the vector ALU issue rate: VALU
+instructions of the two launches (committed rocprofv3 counters of the current
+kernel source, else null) x 64 lanes / their time, against 256 CUs x 4
+SIMDs x 16 lanes x 2.4 GHz. (The simulation, two thirds of the time, is bound
+by vector issue; the closure is a serial chain.)
 `roofline_step` prices the whole timed step with the same bytes.
 `cpu_baseline` times the CPU oracle on a bounded sample of the same
 workload (about 15 s of wall time, whole passes over the candidates), on the host threads a one-GPU job is
@@ -78,9 +78,9 @@ def kernel_hash() -> str:
 
 
 def measured_counters():
-    """Counters of one evaluate launch from committed rocprofv3 runs (HBM
-    bytes, VALU instructions), if they were taken on the current kernel
-    source; else {}."""
+    """Counters of one evaluation (closure and simulation) from committed
+    rocprofv3 runs (HBM bytes, VALU instructions), if they were taken on the
+    current kernel source; else {}."""
     try:
         with open(TRAFFIC_FILE) as f:
             d = json.load(f)
@@ -487,7 +487,8 @@ def main():
     ap.add_argument("--steps", type=int, default=100)
     ap.add_argument("--warmup", type=int, default=20)
     ap.add_argument("--config", type=int, default=4, help="workload 1..5 (4 = transformer stack)")
-    ap.add_argument("--splits", type=int, default=0, help="stage splits per 64 candidates (0 = auto)")
+    ap.add_argument("--splits", type=int, default=0, help="stage splits per 64 candidates (0 = auto; the tile kernels of most "
+                    "calls, the default workload's among them, ignore it)")
     ap.add_argument("--cpu-sample", type=int, default=1024,
                     help="oracle candidates to time on all host threads (0 = skip)")
     ap.add_argument("--cpu-single", type=int, default=128, help="oracle candidates to time on one thread")

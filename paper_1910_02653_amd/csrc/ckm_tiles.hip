@@ -377,9 +377,9 @@ __global__ void __launch_bounds__(kWave*(1 + kPrep)) ckm_closure_kernel(ClosureA
 // is the unit itself (denormals are exact and run at full rate). The bound is
 // vector issue (per record and stage four ANDs, four FMAs and a maximum), then
 // the latency of a record's words, hidden by four waves per SIMD.
-// Measured: n = 1009, K = 1024: 164 us (the instructions alone 119 us); n = 4001,
-// K = 4096: 10.1 ms (7.5 ms). One kernel for closure and simulation, a stage to a
-// wave: 440 us and 75 ms.
+// Measured: n = 1009, K = 1024: 158 us (its VALU instructions at 39.3 T lane
+// operations/s 138 us), K = 512 105 us, one group 73 us; n = 4001, K = 4096: 10.2 ms.
+// One kernel for closure and simulation, a stage to a wave: 440 us and 75 ms.
 struct SimArgs {
   TileArgs t;
   HubArgs h;                        // and the pairs of the launch
